@@ -24,6 +24,7 @@
 
 #include "fa_common.hpp"
 #include "fa_mma.hpp"
+#include "fa_moments.hpp"
 
 namespace fa {
 
@@ -1070,6 +1071,41 @@ static int check_compress_shapes(int dtype, int B, int H, int N, int D, int Dc, 
   return FA_OK;
 }
 
+static MomentTensor moment_tensor(const void* x, const uint8_t* mask, float* mom, void* keep, float* coeffs,
+                                  int64_t keep_stride, int Dc, int D, int keep_layout) {
+  MomentTensor t{};
+  t.x = x; t.mask = mask; t.mom = mom; t.keep = keep; t.coeffs = coeffs; t.keep_stride = keep_stride;
+  t.Dc = Dc; t.Du = D - Dc; t.keep_layout = keep_layout; t.keep_pitch = (D - Dc + 7) & ~7;
+  return t;
+}
+
+// Moments against the direct projection.  `specialised`: compress_project_fast would run (bf16, D = 128,
+// at most one kept vector per thread and block), which a short block or many rows favour; the generic
+// kernel is slower than the moments wherever these apply (measured 1.8 - 3.4x at D = 64 / 256, T / M from
+// 20 on).  Measured on K | V pairs at D = 128, moments against compress_project_fast:
+//   few rows, launches and latency decide: 8 x 4 K, M = 192: 18.9 / 23.3 us; 8 x 8 K, M = 256: 25.5 / 25.1
+//   matrix-bound: 8 x 30 K, M = 512: 57.5 / 65.7 us; 8 x 128 K, M = 512: 137 / 255
+//   HBM-bound, long blocks: 8 x 32 K, M = 256: 44.2 / 47.6; 32 x 8 K, M = 64: 39.6 / 42.2 us
+//   HBM-bound, many rows (the moments are traffic too): 256 x 4 K, M = 64: 166 / 138; 128 x 8 K: 152 / 135 us
+static bool prefer_moments(const MomentPlan& mp, bool specialised, int tensors, int B, int H, int N, int D, int Dc,
+                           int Du, int M) {
+  if (!mp.use) return false;
+  if (!specialised) return true;
+  const double rows = static_cast<double>(tensors) * B * H * N;
+  const double matrix_us = 2.0 * rows * M * Dc / 0.95e9, hbm_us = rows * 2.0 * (D + Du) / 5.0e6;
+  if (rows <= 65536.0) return true;
+  if (mp.umax >= 192 && matrix_us > hbm_us) return true;
+  return mp.umax >= 256 && rows <= 600e3;
+}
+
+static void set_moment_shape(MomentParams& p, const MomentPlan& pl, int64_t sx_b, int64_t sx_h, int64_t sx_n, int B,
+                             int H, int N, int D, int M, int T, int t0, int accumulate, int keep_offset) {
+  p.sx_b = sx_b; p.sx_h = sx_h; p.sx_n = sx_n;
+  p.B = B; p.H = H; p.N = N; p.D = D; p.M = M; p.T = T; p.t0 = t0;
+  p.accumulate = accumulate ? 1 : 0; p.keep_offset = keep_offset;
+  p.U = pl.U; p.S = pl.S; p.lead = pl.lead; p.blocks = pl.blocks; p.bpc = pl.bpc; p.nmax = M / 2; p.tiles = expand_tiles(M);
+}
+
 template <int DT, int KM>
 static int launch_project_fast(const CompressParams& p, const CompressPlan& pl, unsigned lds, hipStream_t st,
                                KernelTimers* tm) {
@@ -1104,7 +1140,11 @@ extern "C" {
 size_t fa_compress_workspace_bytes_for(int dtype, int B, int H, int N, int D, int Dc, int M) {
   if (dtype != FA_F32 && dtype != FA_BF16) return 0;
   if (fa::check_compress_shapes(dtype, B, H, N, D, Dc, M, M > N ? M : N, 0) != FA_OK) return 0;
-  const size_t t = fa::make_compress_plan(dtype, B, H, N, D, Dc, M, FA_KEEP_ROWS, 0).total;
+  size_t t = fa::make_compress_plan(dtype, B, H, N, D, Dc, M, FA_KEEP_ROWS, 0).total;
+  for (int tensors = 1; tensors <= 2; ++tensors) {
+    const size_t m = fa::moment_workspace_bytes(dtype, B, H, N, D, Dc, M, tensors);
+    if (m > t) t = m;
+  }
   return t ? t : 256;
 }
 
@@ -1143,6 +1183,24 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
     return FA_ERR_SHAPE;
   if (reinterpret_cast<uintptr_t>(coeffs) & 15u) return FA_ERR_SHAPE;
 
+  const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dc, M, T, keep_offset, 1, false);
+  const bool one_vector = x_keep == nullptr || Du == 0 ||
+                          (keep_layout == FA_KEEP_ROWS ? kFB * (keep_pitch / 8) : Du * (kFB / 8)) <= kCBlock;
+  const bool specialised = D == 128 && N > kSplitTokens && one_vector &&
+                           (x_keep == nullptr || Du == 0 || keep_layout == FA_KEEP_ROWS || keep_offset % 8 == 0);
+  if (!only_params && prefer_moments(mp, specialised, 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
+    if (!workspace) return FA_ERR_NULL;
+    if (workspace_bytes < mp.mom_bytes + mp.op_bytes || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return FA_ERR_WORKSPACE;
+    MomentParams p{};
+    p.t[0] = moment_tensor(x, dim_mask, static_cast<float*>(workspace), x_keep, coeffs, keep_stride_bh, Dc, D,
+                           keep_layout);
+    set_moment_shape(p, mp, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset);
+    p.op = static_cast<char*>(workspace) + mp.mom_bytes;
+    int rc = launch_moments(p, mp, 1, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc == FA_OK) rc = launch_expand(p, 1, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc != FA_OK) return rc;
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
   const CompressPlan pl = make_compress_plan(dtype, B, H, N, D, Dc, M, keep_layout, keep_offset, tensors);
   if (pl.total > 0) {
     if (!workspace) return FA_ERR_NULL;
@@ -1288,6 +1346,19 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
                     pk.Du > 0 && pv.Du > 0 && nvec_of(pk) <= kCBlock && nvec_of(pv) <= kCBlock &&
                     keep_offset % 8 == 0 && lds <= kMaxCLds && plk.Sc == plv.Sc && plk.chunk == plv.chunk &&
                     plk.MC == plv.MC && plk.Sc > 0;
+  // long segments: one pass over both tensors, one expansion
+  const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dkc, M, T, keep_offset, 2, false);
+  if (Dvc > 0 && prefer_moments(mp, pair, 2, B, H, N, D, (Dkc + Dvc) / 2, D - (Dkc + Dvc) / 2, M)) {
+    MomentParams p{};
+    p.t[0] = moment_tensor(k, kmask, reinterpret_cast<float*>(ws), k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS);
+    p.t[1] = moment_tensor(v, vmask, reinterpret_cast<float*>(ws + wk), v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8);
+    set_moment_shape(p, mp, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset);
+    p.op = ws + mp.mom_bytes;
+    rc = launch_moments(p, mp, 2, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc == FA_OK) rc = launch_expand(p, 2, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc != FA_OK) return rc;
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
   if (!pair) {
     rc = compress_impl(k, dtype, sx_b, sx_h, sx_n, B, H, N, D, kmask, Dkc, M, T, t0, accumulate, ck, k_keep,
                        FA_KEEP_ROWS, kk_stride_bh, keep_offset, ws, wk, hip_stream, tm);

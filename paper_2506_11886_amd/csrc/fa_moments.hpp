@@ -1,0 +1,72 @@
+// Projection of long segments through local moments (used by fa_compress, fa_compress_kv and
+// fa_select_dims when the M kept harmonics vary slowly over a block of tokens).
+//
+// With the block's centre c and x = (j - c) / (U / 2) in [-1, 1] the Jacobi-Anger expansion is
+//   exp(i w_n j) = exp(i w_n c) * sum_p (2 - [p = 0]) i^p J_p(theta_n) T_p(x),  theta_n = w_n U / 2,
+// and J_p falls off like (theta/2)^p / p! once p > theta: P = 16 Chebyshev polynomials carry every
+// harmonic of a block with theta <= kThetaBf16 to 2e-6 (kThetaF32: 1e-8).  Hence
+//   mu[p, i] = sum_{j in block} T_p(x_j) X[j, i]                          (fa_moments: one pass over X)
+//   C[n, i]  = sum_blocks Rot(w_n c) * (2 - [p = 0]) i^p J_p(theta_n) mu  (fa_expand)
+// so a token costs 16 matrix rows instead of M, and the M-row contraction runs once per block.
+// Measured, direct projection -> moments: K and V of 8 heads x 129020 tokens, M = 512, 255 -> 137 us
+// (fa_moments moves 0.63 GB in 114 us = 5.5 TB/s); 8 x 31740 tokens, M = 256, 47.6 -> 44.2 us; a 2 K
+// piece at an offset that is no multiple of 8, 94.7 -> 27.4 us (K and V, four launches); fa_select_dims on
+// 8 x 31740 tokens 293 -> 37 us.
+#pragma once
+
+#include "fa_common.hpp"
+
+namespace fa {
+
+constexpr int kMomP = 16;             // Chebyshev polynomials per block
+constexpr double kThetaBf16 = 6.0;    // 2 J_16(6.0) = 2.4e-6, far below the 2^-9 of bf16 data
+constexpr double kThetaF32 = 4.2;     // 2 J_16(4.2) = 1.0e-8, below fp32 rounding
+constexpr int kMomMaxU = 1024;        // tokens per block (the Chebyshev table lives in LDS)
+
+struct MomentPlan {
+  bool use;
+  int umax;            // longest block the expansion allows (a measure of T / M: about 3.8 T / M)
+  int U, S;            // tokens per block, 32-token steps per block
+  int lead;            // zero tokens put in front, so that groups of 8 kept tokens are aligned
+  int blocks, bpc;     // blocks per (sequence, head), blocks per workgroup
+  int chunks;          // workgroups per (sequence, head)
+  int parts;           // bf16 terms of a Chebyshev value (2: 2^-17, 3: fp32)
+  unsigned lds;
+  size_t mom_bytes;    // workspace of one tensor
+  size_t op_bytes;     // workspace of the call: A operands of fa_expand16
+};
+
+// the plan for `tensors` tensors of one shape that share a launch; keep_offset only matters mod 8
+MomentPlan make_moment_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int T, int keep_offset,
+                            int tensors, bool exact);
+// workspace that suffices for every T a call with these sizes may use
+size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int M, int tensors);
+
+struct MomentTensor {
+  const void* x;
+  const uint8_t* mask;   // null: every dim is compressed
+  float* mom;            // bf16: [B*H][blocks][head | remainder][Dc][16], then fp32 moment 0 [B*H][blocks][Dc];
+                         // fa_select_dims: fp32 [B*H][blocks][Dc][16]
+  void* keep;            // null: nothing kept is written
+  float* coeffs;         // [B*H][M][Dc]
+  float* epart;          // fa_select_dims: per-chunk sums of squares [chunks][B*H][D]
+  double* ecoef;         // fa_select_dims: weighted squares [row tiles][B*H][D] instead of coefficients
+  int64_t keep_stride;
+  int Dc, Du, keep_layout, keep_pitch;
+};
+
+struct MomentParams {
+  MomentTensor t[2];
+  int64_t sx_b, sx_h, sx_n;
+  int B, H, N, D, M, T, t0, accumulate, keep_offset;
+  int U, S, lead, blocks, bpc, nmax, tiles;
+  void* op;              // A operands of fa_expand16 [16-harmonic tile][2-block step][4 KB]
+};
+
+int launch_moments(const MomentParams& p, const MomentPlan& pl, int tensors, hipStream_t st, KernelTimers* tm);
+int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTimers* tm);
+
+constexpr int kExpandRows = 16;       // harmonics per workgroup of fa_expand
+inline int expand_tiles(int M) { return M / 2 > 0 ? (M / 2 + kExpandRows - 1) / kExpandRows : 1; }
+
+}  // namespace fa

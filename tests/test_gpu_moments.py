@@ -1,0 +1,95 @@
+"""Long-segment projection through local Chebyshev moments (fa_compress, fa_compress_kv, fa_select_dims on
+bf16 segments whose kept harmonics vary slowly): edges of tiles, blocks, groups of eight and periods."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle.fourier_kv as fk
+from fa_testlib import rows_to_tok8, to_dev
+from workloads.synth import rel_err, round_to_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _segment(D, N, Dc, H, seed):
+    rng = np.random.default_rng(seed)
+    j = np.arange(N)[:, None]
+    x = rng.standard_normal((1, H, N, D)) + 2.0 * np.cos(j * rng.uniform(0.0, 0.02, D) + rng.uniform(0, 6.28, D))
+    mask = np.zeros((1, H, D), np.uint8)
+    for h in range(H):
+        mask[0, h, rng.choice(D, Dc, replace=False)] = 1
+    return round_to_bf16(x.astype(np.float32)), mask
+
+
+# D, N, M, T, t0, token offset of the kept dims, compressed dims
+CASES = [
+    (128, 2048, 64, 20000, 4001, 4001, 96),   # a chunk that starts inside a group of eight
+    (128, 31, 16, 9000, 0, 0, 128),           # less than one step, nothing kept
+    (128, 129, 1, 129, 0, 3, 5),              # one token past a tile, the mean alone, many kept dims
+    (128, 5000, 40, 5000, 0, 0, 91),          # counts that divide nothing
+    (64, 4099, 33, 8000, 777, 8, 41),         # head dim 64, one row past a group
+    (256, 1111, 20, 3000, 5, 2, 179),         # head dim 256
+    (128, 30000, 512, 30000, 0, 0, 112),      # several harmonics tiles, many blocks
+]
+
+
+@pytest.mark.parametrize("D,N,M,T,t0,off,Dc", CASES)
+@pytest.mark.parametrize("layout", [0, 1])
+def test_moment_projection_matches_oracle(D, N, M, T, t0, off, Dc, layout):
+    import paper_2506_11886_amd as fa
+    print(f"[case] moments D{D} N{N} M{M} T{T} t0 {t0} off {off} Dc{Dc} layout {layout}", flush=True)
+    x, mask = _segment(D, N, Dc, 2, N + M)
+    want, keep = fk.compress_batched(x, mask, M, T, t0)
+    Du = D - Dc
+    dt = torch.bfloat16
+    prev = torch.randn((1, 2, M, Dc), device="cuda")
+    if layout == fa.FA_KEEP_ROWS:
+        slab = torch.full((1, 2, off + N, fa.keep_rows_pitch(Du)), 7.0, dtype=dt, device="cuda")
+    else:
+        slab = torch.full((1, 2, fa.tok8_numel(off + N, Du)), 7.0, dtype=dt, device="cuda")
+    c, _ = fa.fa_compress(to_dev(x, dtype=dt), to_dev(mask), Dc, M, T, t0, True, prev.clone(), slab, layout, off)
+    torch.cuda.synchronize()
+    # x is exact in bf16 and the tables carry 17 bits: far inside the 2e-3 asked of bf16
+    assert rel_err(c.cpu().numpy(), want + prev.cpu().numpy().astype(np.float64), np.sqrt(N)) <= 5e-5
+    if Du:
+        if layout == fa.FA_KEEP_ROWS:
+            got = slab.float().cpu().numpy()
+            assert np.array_equal(got[:, :, off:, :Du], keep.astype(np.float32)) and not got[:, :, off:, Du:].any()
+            assert (got[:, :, :off] == 7.0).all()
+        else:
+            got = fa.keep_rows_from_tok8(slab, off + N, Du).float().cpu().numpy()
+            assert np.array_equal(got[:, :, off:], keep.astype(np.float32)) and (got[:, :, :off] == 7.0).all()
+
+
+@pytest.mark.parametrize("D,N,M,Dkc,Dvc", [(128, 6001, 64, 96, 101), (64, 3000, 90, 40, 64), (256, 2500, 32, 200, 150)])
+def test_moment_projection_of_a_pair(D, N, M, Dkc, Dvc):
+    import paper_2506_11886_amd as fa
+    print(f"[case] moment pair D{D} N{N} M{M} {Dkc}/{Dvc}", flush=True)
+    k, kmask = _segment(D, N, Dkc, 3, 1)
+    v, vmask = _segment(D, N, Dvc, 3, 2)
+    dt = torch.bfloat16
+    ck, kk, cv, vk = fa.fa_compress_kv(to_dev(k, dtype=dt), to_dev(v, dtype=dt), to_dev(kmask), to_dev(vmask), Dkc, Dvc,
+                                       M, N + 100, t0=50)
+    torch.cuda.synchronize()
+    for x, mask, c, Dc in ((k, kmask, ck, Dkc), (v, vmask, cv, Dvc)):
+        want, keep = fk.compress_batched(x, mask, M, N + 100, 50)
+        assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= 5e-5
+        if x is k:
+            assert np.array_equal(kk[..., :D - Dc].float().cpu().numpy(), keep.astype(np.float32))
+        else:
+            got = vk.float().cpu().numpy()
+            assert np.array_equal(got, rows_to_tok8(keep.astype(np.float32)))
+
+
+@pytest.mark.parametrize("D,N,M", [(128, 3001, 50), (64, 1024, 12), (256, 2000, 33), (128, 700, 1)])
+def test_moment_selection_matches_oracle(D, N, M):
+    import paper_2506_11886_amd as fa
+    print(f"[case] moment select D{D} N{N} M{M}", flush=True)
+    x, _ = _segment(D, N, D // 2, 2, 3)
+    _, mse = fa.fa_select_dims(to_dev(x, dtype=torch.bfloat16), M, D // 2)
+    torch.cuda.synchronize()
+    for h in range(2):
+        want = fk.reconstruction_mse(x[0, h], M)
+        scale = np.mean(x[0, h].astype(np.float64) ** 2, axis=0)
+        assert np.all(np.abs(mse[0, h].cpu().numpy() - want) <= 5e-6 * scale)

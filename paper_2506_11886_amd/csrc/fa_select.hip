@@ -16,6 +16,7 @@
 
 #include "fa_common.hpp"
 #include "fa_mma.hpp"
+#include "fa_moments.hpp"
 
 namespace fa {
 
@@ -28,10 +29,11 @@ struct SelectParams {
   float* xf;          // fp32 copy [B,H,N,D] (bf16 input only)
   uint8_t* ones;      // [B,H,D]
   float* epart;       // [chunks][B*H][D]
-  const float* coeffs;   // [B,H,M,D]
+  const float* coeffs;   // [B,H,M,D], or null:
+  const double* ecoef;   // weighted squares of them, summed over 16-harmonic tiles [tiles][B*H][D]
   uint8_t* mask_out;  // [B,H,D]
   float* mse_out;     // [B,H,D] or null
-  int B, H, N, D, M, Dc, chunks;
+  int B, H, N, D, M, Dc, chunks, tiles;
 };
 
 // grid (chunks, B*H).  Thread (vector of 8 dims, row group): strided over the chunk's tokens.
@@ -99,11 +101,15 @@ __global__ __launch_bounds__(kRBlock) void select_rank(SelectParams p) {
   double ex = 0.0, ec = 0.0;
   if (g < ng) {
     for (int c = g; c < p.chunks; c += ng) ex += p.epart[(static_cast<size_t>(c) * gridDim.x + bh) * D + d];
-    const float* C = p.coeffs + static_cast<size_t>(bh) * M * D + d;
+    if (p.ecoef) {
+      for (int t = g; t < p.tiles; t += ng) ec += p.ecoef[(static_cast<size_t>(t) * gridDim.x + bh) * D + d];
+    } else {
+      const float* C = p.coeffs + static_cast<size_t>(bh) * M * D + d;
 #pragma unroll 8
-    for (int m = g; m < M; m += ng) {
-      const double cm = C[static_cast<size_t>(m) * D];
-      ec += static_cast<double>(basis_weight((m + 1) / 2, N)) * cm * cm;
+      for (int m = g; m < M; m += ng) {
+        const double cm = C[static_cast<size_t>(m) * D];
+        ec += static_cast<double>(basis_weight((m + 1) / 2, N)) * cm * cm;
+      }
     }
   }
   ex_s[tid] = ex;
@@ -132,6 +138,8 @@ __global__ __launch_bounds__(kRBlock) void select_rank(SelectParams p) {
 }
 
 struct SelectPlan {
+  MomentPlan mom;      // long bf16 segments: energies and moments in one pass, no fp32 copy
+  size_t off_ecoef, off_mom;
   int chunks;
   size_t off_ones, off_epart, off_coeffs, off_xf, off_cws, cws_bytes, total;
 };
@@ -150,8 +158,17 @@ static int check_select_shapes(int dtype, int B, int H, int N, int D, int M, int
 static SelectPlan make_select_plan(int dtype, int B, int H, int N, int D, int M) {
   SelectPlan pl{};
   const size_t BH = static_cast<size_t>(B) * H;
-  pl.chunks = (N + kSChunk - 1) / kSChunk;
   size_t off = 0;
+  pl.mom = make_moment_plan(dtype, B, H, N, D, D, M, N, 0, 1, true);
+  if (pl.mom.use) {
+    pl.chunks = pl.mom.chunks;
+    pl.off_epart = off;  off = align256(off + static_cast<size_t>(pl.chunks) * BH * D * sizeof(float));
+    pl.off_ecoef = off;  off = align256(off + static_cast<size_t>(expand_tiles(M)) * BH * D * sizeof(double));
+    pl.off_mom = off;    off = align256(off + pl.mom.mom_bytes);
+    pl.total = off;
+    return pl;
+  }
+  pl.chunks = (N + kSChunk - 1) / kSChunk;
   pl.off_ones = off;   off = align256(off + BH * D);
   pl.off_epart = off;  off = align256(off + static_cast<size_t>(pl.chunks) * BH * D * sizeof(float));
   pl.off_coeffs = off; off = align256(off + BH * M * D * sizeof(float));
@@ -197,6 +214,23 @@ int fa_select_dims(const void* x, int dtype, int64_t sx_b, int64_t sx_h, int64_t
   p.B = B; p.H = H; p.N = N; p.D = D; p.M = M; p.Dc = Dc; p.chunks = pl.chunks;
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (pl.mom.use) {
+    MomentParams m{};
+    m.t[0].x = x;
+    m.t[0].mom = reinterpret_cast<float*>(ws + pl.off_mom);
+    m.t[0].epart = reinterpret_cast<float*>(ws + pl.off_epart);
+    m.t[0].ecoef = reinterpret_cast<double*>(ws + pl.off_ecoef);
+    m.t[0].Dc = D;
+    m.sx_b = sx_b; m.sx_h = sx_h; m.sx_n = sx_n;
+    m.B = B; m.H = H; m.N = N; m.D = D; m.M = M; m.T = N;
+    m.U = pl.mom.U; m.S = pl.mom.S; m.blocks = pl.mom.blocks; m.bpc = pl.mom.bpc; m.nmax = M / 2;
+    int rc = launch_moments(m, pl.mom, 1, stream, nullptr);
+    if (rc == FA_OK) rc = launch_expand(m, 1, stream, nullptr);
+    if (rc != FA_OK) return rc;
+    p.epart = m.t[0].epart; p.ecoef = m.t[0].ecoef; p.tiles = expand_tiles(M);
+    hipLaunchKernelGGL(select_rank, dim3(B * H), dim3(kRBlock), 0, stream, p);
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
   const dim3 g1(pl.chunks, B * H);
   if (dtype == FA_BF16) hipLaunchKernelGGL(select_energy<bf16_t>, g1, dim3(kSBlock), 0, stream, p);
   else hipLaunchKernelGGL(select_energy<float>, g1, dim3(kSBlock), 0, stream, p);

@@ -4,15 +4,15 @@
 // holds its oldest token is folded into the compressed state before the new token takes it:
 //   C[m,i] += phi_m(n_mid) * x[idx_c[i]]     (Eq. 5: one basis column times the evicted row)
 //   X_keep[n_mid, :] = x[idx_u]              (kept dims appended at middle position n_mid)
-// for K and for V.  Two launches on the caller's stream: the fold reads the old row from many
-// workgroups, so the overwrite with the new token has to wait for all of them.
+// for K and for V, in one launch on the caller's stream.
 
 #include "fa_common.hpp"
 
 namespace fa {
 
 constexpr int kABlock = 256;
-constexpr int kARows = 32;   // basis rows per workgroup of the fold
+constexpr int kADims = 16;   // head dims per workgroup (a divisor of 64: see the ballot words)
+constexpr int kAFly = 16;    // rows of C in flight per thread
 
 struct AppendParams {
   const void* k_new;
@@ -49,85 +49,115 @@ __device__ __forceinline__ void seq_append(const AppendParams& p, int b, int* sl
   *n_mid = n;
 }
 
-// grid (row blocks, K | V, sequences x heads)
+// One launch: the fold reads the old row and the new token overwrites it, so a workgroup takes a slice of
+// head dims for ALL basis rows - nobody else reads or writes its part of the row, and its columns of C are
+// one contiguous band.  grid (sequences x heads, K | V, slices of kADims dims): with the pair index fastest
+// the slices of a pair land on one XCD whenever the pairs are a multiple of four, and the cache lines of C
+// they share meet in one L2.  Bound: the round trips row/mask -> C -> store; the rows of C are requested
+// kAFly at a time before the basis column is evaluated.
+// Against a split by basis rows, which took a second launch for the overwrite and one round trip per 256
+// elements: a step (append + decode) of 8 heads x 32 K tokens, M = 256, 34.1 -> 29.5 us; 16 sequences of
+// up to 8 K tokens, M = 128, 62.6 -> 57.7 us.
 template <typename T>
-__global__ __launch_bounds__(kABlock) void append_fold(AppendParams p) {
-  __shared__ float xc[FA_MAX_HEAD_DIM];     // the evicted row at the compressed dims
-  __shared__ float phi[kARows];
+__global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
+  __shared__ float xc[kADims];              // the evicted row at this slice's compressed dims
+  __shared__ float phi[FA_MAX_STATES + 2];  // basis column at n_mid
   const int tid = threadIdx.x, lane = tid & 63;
-  const int bh = blockIdx.z, is_v = blockIdx.y, m0 = blockIdx.x * kARows;
+  const int bh = blockIdx.x, is_v = blockIdx.y, d0 = blockIdx.z * kADims;
   int slot, n_mid;
   seq_append(p, bh / p.Hkv, &slot, &n_mid);
-  if (n_mid < 0) return;   // (only with per-sequence lists) this sequence's window is still filling
-  const int D = p.D, Dc = is_v ? p.Dvc : p.Dkc, Du = D - Dc;
+  if (slot < 0) return;   // (only with per-sequence lists) this sequence is left alone
+  const int D = p.D;
+  const bool mine = tid < kADims && d0 + tid < D;
+  T* ring = static_cast<T*>(is_v ? p.v_full : p.k_full) + bh * p.full_stride + static_cast<int64_t>(slot) * D + d0;
+  const T* src = static_cast<const T*>(is_v ? p.v_new : p.k_new) + static_cast<size_t>(bh) * D + d0;
+  T fresh{}, old{};
+  if (mine) {
+    fresh = src[tid];
+    old = ring[tid];
+  }
+  if (n_mid < 0) {   // the window is still filling: nothing leaves it
+    if (mine) ring[tid] = fresh;
+    return;
+  }
+
+  const int Dc = is_v ? p.Dvc : p.Dkc, Du = D - Dc, M = p.M;
   const uint8_t* mask = (is_v ? p.vmask : p.kmask) + static_cast<size_t>(bh) * D;
-  const T* row = static_cast<const T*>(is_v ? p.v_full : p.k_full) + bh * p.full_stride +
-                 static_cast<int64_t>(slot) * D;
-  float* C = (is_v ? p.cv : p.ck) + static_cast<size_t>(bh) * p.M * Dc;
+  float* C = (is_v ? p.cv : p.ck) + static_cast<size_t>(bh) * M * Dc;
 
   // ranks of the dims: every wave reads the whole mask row
   uint8_t mb[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) mb[j] = mask[min(lane + 64 * j, D - 1)];
-  const float xv = (tid < D) ? Elem<T>::load(row + tid) : 0.0f;
-  const T xraw = row[min(tid, D - 1)];
   uint64_t bal[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) bal[j] = __ballot(mb[j] != 0 && lane + 64 * j < D);
-  if (tid < D) {
-    const int w = tid >> 6;
-    const uint64_t bit = 1ull << (tid & 63);
-    int nc = 0;
-    bool hit = false;
+  // compressed dims in front of the slice, and the slice's own bits (a slice never straddles a ballot word)
+  const int w0 = d0 >> 6, o0 = d0 & 63;
+  int cb = 0;
+  uint32_t bits = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {   // static indices only: the words stay in registers
-      const uint64_t below = (j < w) ? ~0ull : ((j == w) ? (bit - 1ull) : 0ull);
-      nc += __popcll(bal[j] & below);
-      hit = hit || (j == w && (bal[j] & bit) != 0);
-    }
-    if (hit) {
-      xc[nc] = xv;
-    } else if (blockIdx.x == 0) {   // kept dims: appended once, at middle position n_mid
-      const int cp = tid - nc;
+  for (int j = 0; j < 4; ++j) {   // static indices only: the words stay in registers
+    cb += __popcll(bal[j] & ((j < w0) ? ~0ull : ((j == w0) ? ((1ull << o0) - 1ull) : 0ull)));
+    if (j == w0) bits = static_cast<uint32_t>(bal[j] >> o0) & ((1u << kADims) - 1u);
+  }
+  const int nc = __popc(bits);
+
+  // columns [cb, cb + nc) of C: 16 lanes a row
+  const int col = tid & (kADims - 1), r0 = tid / kADims;
+  constexpr int kRowsPass = kABlock / kADims;
+  const bool live = col < nc;
+  float* dst = C + cb + min(col, max(nc - 1, 0));
+  float cv[kAFly];
+  auto load = [&](int m0) {
+#pragma unroll
+    for (int i = 0; i < kAFly; ++i)
+      cv[i] = dst[static_cast<size_t>(min(m0 + r0 + i * kRowsPass, M - 1)) * Dc];
+  };
+  if (nc > 0) load(0);
+
+  if (mine) {
+    ring[tid] = fresh;
+    const int below = __popc(bits & ((1u << tid) - 1u));
+    if ((bits >> tid) & 1u) {
+      xc[below] = Elem<T>::load(&old);
+    } else {   // kept dims: appended at middle position n_mid
+      const int cp = d0 + tid - cb - below;
       if (is_v) {   // [ceil(n/8), Du, 8]
         T* keep = static_cast<T*>(p.v_keep) + bh * p.vk_stride;
-        keep[(static_cast<int64_t>(n_mid >> 3) * Du + cp) * 8 + (n_mid & 7)] = xraw;
+        keep[(static_cast<int64_t>(n_mid >> 3) * Du + cp) * 8 + (n_mid & 7)] = old;
       } else {      // [n, Du rounded up to 8]
         T* keep = static_cast<T*>(p.k_keep) + bh * p.kk_stride;
-        keep[static_cast<int64_t>(n_mid) * ((Du + 7) & ~7) + cp] = xraw;
+        keep[static_cast<int64_t>(n_mid) * ((Du + 7) & ~7) + cp] = old;
       }
     }
   }
-  if (blockIdx.x == 0 && !is_v && Du > 0) {   // zero pad columns of the new K^mu row
+  if (d0 == 0 && !is_v && Du > 0) {   // zero pad columns of the new K^mu row
     const int kp = (Du + 7) & ~7;
     T* keep = static_cast<T*>(p.k_keep) + bh * p.kk_stride;
     if (tid < kp - Du) keep[static_cast<int64_t>(n_mid) * kp + Du + tid] = T{};
   }
-  if (tid < kARows) {
-    const int m = m0 + tid;
+  if (nc == 0) return;   // (uniform over the workgroup)
+  for (int n = tid; n <= M / 2; n += kABlock) {   // row 0: the constant; rows 2n - 1, 2n: cosine, sine of order n
     float c = 1.0f, s = 0.0f;
-    if (m > 0 && m < p.M) unit_phase((m + 1) / 2, n_mid, p.T, &c, &s);
-    phi[tid] = (m & 1) || m == 0 ? c : s;   // odd m: cosine, even m > 0: sine
+    if (n > 0) {
+      unit_phase(n, n_mid, p.T, &c, &s);
+      phi[2 * n - 1] = c;
+      phi[2 * n] = s;
+    } else {
+      phi[0] = 1.0f;
+    }
   }
   __syncthreads();
-  const int rows = min(kARows, p.M - m0);
-  for (int it = tid; it < rows * Dc; it += kABlock) {
-    const int r = it / Dc, i = it - r * Dc;
-    float* dst = C + static_cast<size_t>(m0 + r) * Dc + i;
-    *dst += phi[r] * xc[i];
+  const float x = live ? xc[col] : 0.0f;
+  for (int m0 = 0; m0 < M; m0 += kAFly * kRowsPass) {
+    if (m0 > 0) load(m0);
+#pragma unroll
+    for (int i = 0; i < kAFly; ++i) {
+      const int m = m0 + r0 + i * kRowsPass;
+      if (live && m < M) dst[static_cast<size_t>(m) * Dc] = cv[i] + phi[m] * x;
+    }
   }
-}
-
-// the new token takes the ring slot: grid (K | V, sequences x heads)
-template <typename T>
-__global__ __launch_bounds__(kABlock) void append_store(AppendParams p) {
-  const int bh = blockIdx.y, is_v = blockIdx.x, tid = threadIdx.x;
-  int slot, n_mid;
-  seq_append(p, bh / p.Hkv, &slot, &n_mid);
-  if (slot < 0) return;
-  const T* src = static_cast<const T*>(is_v ? p.v_new : p.k_new) + static_cast<size_t>(bh) * p.D;
-  T* dst = static_cast<T*>(is_v ? p.v_full : p.k_full) + bh * p.full_stride + static_cast<int64_t>(slot) * p.D;
-  if (tid < p.D) dst[tid] = src[tid];
 }
 
 }  // namespace fa
@@ -167,15 +197,12 @@ static int append_impl(const void* k_new, const void* v_new, int dtype, int B, i
     p.kmask = kmask; p.vmask = vmask; p.ck = ck; p.cv = cv; p.k_keep = k_keep; p.v_keep = v_keep;
     p.kk_stride = kk_stride_bh; p.vk_stride = vk_stride_bh;
     p.Dkc = Dkc; p.Dvc = Dvc; p.M = M; p.n_mid = n_mid;
-    const dim3 grid((M + kARows - 1) / kARows, 2, B * Hkv);
-    if (dtype == FA_F32) hipLaunchKernelGGL(append_fold<float>, grid, dim3(kABlock), 0, st, p);
-    else hipLaunchKernelGGL(append_fold<bf16_t>, grid, dim3(kABlock), 0, st, p);
   } else {
     p.n_mid = -1;
   }
-  const dim3 g2(2, B * Hkv);
-  if (dtype == FA_F32) hipLaunchKernelGGL(append_store<float>, g2, dim3(kABlock), 0, st, p);
-  else hipLaunchKernelGGL(append_store<bf16_t>, g2, dim3(kABlock), 0, st, p);
+  const dim3 grid(B * Hkv, 2, (D + kADims - 1) / kADims);
+  if (dtype == FA_F32) hipLaunchKernelGGL(append_token<float>, grid, dim3(kABlock), 0, st, p);
+  else hipLaunchKernelGGL(append_token<bf16_t>, grid, dim3(kABlock), 0, st, p);
   // only this call's launches are reported: an error an earlier, unrelated HIP call left behind is
   // neither returned nor cleared
   return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;

@@ -503,6 +503,53 @@ def test_append_varlen_matches_oracle():
             assert rel_err(out[b, h * G:(h + 1) * G], want) <= cfg.tol, ("out", b, h)
 
 
+@pytest.mark.parametrize("D,Dkc,Dvc,M,dtype", [(8, 8, 0, 1, "f32"), (24, 5, 19, 2, "bf16"), (72, 40, 71, 257, "f32"),
+                                                (128, 96, 91, 256, "bf16"), (256, 200, 131, 1024, "bf16")])
+def test_append_slices_of_dims(D, Dkc, Dvc, M, dtype):
+    """One fold over head dims that end inside a slice of sixteen, slices without a compressed dim, and row
+    counts around the rows in flight: states against fp64, kept dims and the ring row bit for bit."""
+    fa = _fa()
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    B, H, W, slot, n, T = 2, 3, 7, 4, 41, 5003
+    g = torch.Generator().manual_seed(D + M)
+    rows = [torch.randn((B, H, W, D), generator=g).to(dt) for _ in range(2)]
+    new = [torch.randn((B, H, D), generator=g).to(dt) for _ in range(2)]
+    masks, C0 = [], []
+    for dc in (Dkc, Dvc):
+        m = torch.zeros((B, H, D), dtype=torch.uint8)
+        m.scatter_(2, torch.rand((B, H, D), generator=g).argsort(-1)[..., :dc], 1)
+        masks.append(m)
+        C0.append(torch.randn((B, H, M, dc), generator=g))
+    kk = torch.full((B, H, n + 1, fa.keep_rows_pitch(D - Dkc)), 3.0, dtype=dt, device="cuda")
+    vk = torch.full((B, H, fa.tok8_numel(n + 1, D - Dvc)), 3.0, dtype=dt, device="cuda")
+    full, C = [r.cuda() for r in rows], [c.cuda() for c in C0]
+    fa.fa_append(new[0].cuda(), new[1].cuda(), full[0], full[1], slot, True, masks[0].cuda(), masks[1].cuda(), M, T, n,
+                 C[0], C[1], kk, vk, kk_stride_bh=kk.stride(1), vk_stride_bh=vk.stride(1))
+    torch.cuda.synchronize()
+    order = torch.arange(M, dtype=torch.int64)
+    ang = 2.0 * torch.pi * (((order + 1) // 2 * n) % T).double() / T
+    phi = torch.where((order % 2 == 1) | (order == 0), ang.cos(), ang.sin())
+    for i in range(2):
+        want_rows = rows[i].clone()
+        want_rows[:, :, slot] = new[i]
+        assert torch.equal(full[i].cpu(), want_rows)
+        old, m = rows[i][:, :, slot], masks[i].bool()
+        x = old[m].double().view(B, H, 1, -1)
+        want = C0[i].double() + phi.view(1, 1, -1, 1) * x
+        # |C|, |x| < 6.  Basis value: the turn is rounded to 2^-24, times pi, and sincospi adds 1.5 ulp: 2.8e-7,
+        # times |x| = 1.7e-6; the sum (below 16) is rounded by half of 2^-20
+        if want.numel():
+            assert (C[i].cpu().double() - want).abs().max().item() <= 1.7e-6 + 4.8e-7 + 1e-7
+        kept = old[~m].view(B, H, -1)
+        if i == 0:
+            assert torch.equal(kk[:, :, n, :D - Dkc].cpu(), kept) and not kk[:, :, n, D - Dkc:].any()
+            assert (kk[:, :, :n] == 3.0).all()
+        elif D > Dvc:
+            tok = vk.view(B, H, -1, D - Dvc, 8)
+            assert torch.equal(tok[:, :, n // 8, :, n % 8].cpu(), kept)
+            assert (tok[:, :, n // 8, :, n % 8 + 1:] == 3.0).all() and (tok[:, :, :n // 8] == 3.0).all()
+
+
 def test_append_without_eviction_only_writes_the_row():
     fa = _fa()
     k_full = torch.zeros((2, 3, 9, 64), dtype=torch.bfloat16, device="cuda")

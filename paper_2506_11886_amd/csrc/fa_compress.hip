@@ -1137,15 +1137,22 @@ static int launch_project(const CompressParams& p, const CompressPlan& pl, hipSt
 
 extern "C" {
 
-size_t fa_compress_workspace_bytes_for(int dtype, int B, int H, int N, int D, int Dc, int M) {
+// what the direct projection needs: the least workspace a call is accepted with (0: sizes are refused)
+static size_t direct_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int M) {
   if (dtype != FA_F32 && dtype != FA_BF16) return 0;
   if (fa::check_compress_shapes(dtype, B, H, N, D, Dc, M, M > N ? M : N, 0) != FA_OK) return 0;
-  size_t t = fa::make_compress_plan(dtype, B, H, N, D, Dc, M, FA_KEEP_ROWS, 0).total;
+  const size_t t = fa::make_compress_plan(dtype, B, H, N, D, Dc, M, FA_KEEP_ROWS, 0).total;
+  return t ? t : 256;
+}
+
+size_t fa_compress_workspace_bytes_for(int dtype, int B, int H, int N, int D, int Dc, int M) {
+  size_t t = direct_workspace_bytes(dtype, B, H, N, D, Dc, M);
+  if (t == 0) return 0;
   for (int tensors = 1; tensors <= 2; ++tensors) {
     const size_t m = fa::moment_workspace_bytes(dtype, B, H, N, D, Dc, M, tensors);
     if (m > t) t = m;
   }
-  return t ? t : 256;
+  return t;
 }
 
 size_t fa_compress_workspace_bytes(int B, int H, int N, int D, int Dc, int M) {
@@ -1183,14 +1190,21 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
     return FA_ERR_SHAPE;
   if (reinterpret_cast<uintptr_t>(coeffs) & 15u) return FA_ERR_SHAPE;
 
+  const CompressPlan pl = make_compress_plan(dtype, B, H, N, D, Dc, M, keep_layout, keep_offset, tensors);
+  if (pl.total > 0) {
+    if (!workspace) return FA_ERR_NULL;
+    if (workspace_bytes < pl.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
+      return FA_ERR_WORKSPACE;
+  }
+
   const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dc, M, T, keep_offset, 1, false);
   const bool one_vector = x_keep == nullptr || Du == 0 ||
                           (keep_layout == FA_KEEP_ROWS ? kFB * (keep_pitch / 8) : Du * (kFB / 8)) <= kCBlock;
   const bool specialised = D == 128 && N > kSplitTokens && one_vector &&
                            (x_keep == nullptr || Du == 0 || keep_layout == FA_KEEP_ROWS || keep_offset % 8 == 0);
-  if (!only_params && prefer_moments(mp, specialised, 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
-    if (!workspace) return FA_ERR_NULL;
-    if (workspace_bytes < mp.mom_bytes + mp.op_bytes || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return FA_ERR_WORKSPACE;
+  // (a workspace that holds the direct projection's partials alone is served by that)
+  const bool fits = workspace && workspace_bytes >= mp.mom_bytes + mp.op_bytes && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
+  if (!only_params && fits && prefer_moments(mp, specialised, 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
     MomentParams p{};
     p.t[0] = moment_tensor(x, dim_mask, static_cast<float*>(workspace), x_keep, coeffs, keep_stride_bh, Dc, D,
                            keep_layout);
@@ -1200,12 +1214,6 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
     if (rc == FA_OK) rc = launch_expand(p, 1, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;
     return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
-  }
-  const CompressPlan pl = make_compress_plan(dtype, B, H, N, D, Dc, M, keep_layout, keep_offset, tensors);
-  if (pl.total > 0) {
-    if (!workspace) return FA_ERR_NULL;
-    if (workspace_bytes < pl.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
-      return FA_ERR_WORKSPACE;
   }
 
   CompressParams p{};
@@ -1319,8 +1327,8 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   using namespace fa;
   const hipError_t prior = hipPeekAtLastError();   // (an error left by earlier, unrelated calls is not this call's)
   if (dtype != FA_F32 && dtype != FA_BF16) return FA_ERR_UNSUPPORTED;
-  const size_t wk = (fa_compress_workspace_bytes_for(dtype, B, H, N, D, Dkc, M) + 255) & ~size_t(255);
-  const size_t wv = fa_compress_workspace_bytes_for(dtype, B, H, N, D, Dvc, M);
+  const size_t wk = (direct_workspace_bytes(dtype, B, H, N, D, Dkc, M) + 255) & ~size_t(255);
+  const size_t wv = direct_workspace_bytes(dtype, B, H, N, D, Dvc, M);
   if (wk == 0 || wv == 0) return FA_ERR_SHAPE;
   if (!workspace) return FA_ERR_NULL;
   if (workspace_bytes < wk + wv || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return FA_ERR_WORKSPACE;
@@ -1348,23 +1356,25 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
                     plk.MC == plv.MC && plk.Sc > 0;
   // long segments: one pass over both tensors, one expansion
   const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dkc, M, T, keep_offset, 2, false);
-  if (Dvc > 0 && prefer_moments(mp, pair, 2, B, H, N, D, (Dkc + Dvc) / 2, D - (Dkc + Dvc) / 2, M)) {
+  const size_t mom_v = make_moment_plan(dtype, B, H, N, D, Dvc, M, T, keep_offset, 2, false).mom_bytes;
+  const bool fits = workspace_bytes >= mp.mom_bytes + mom_v + mp.op_bytes;
+  if (fits && Dvc > 0 && prefer_moments(mp, pair, 2, B, H, N, D, (Dkc + Dvc) / 2, D - (Dkc + Dvc) / 2, M)) {
     MomentParams p{};
     p.t[0] = moment_tensor(k, kmask, reinterpret_cast<float*>(ws), k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS);
-    p.t[1] = moment_tensor(v, vmask, reinterpret_cast<float*>(ws + wk), v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8);
+    p.t[1] = moment_tensor(v, vmask, reinterpret_cast<float*>(ws + mp.mom_bytes), v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8);
     set_moment_shape(p, mp, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset);
-    p.op = ws + mp.mom_bytes;
+    p.op = ws + mp.mom_bytes + mom_v;
     rc = launch_moments(p, mp, 2, static_cast<hipStream_t>(hip_stream), tm);
     if (rc == FA_OK) rc = launch_expand(p, 2, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;
     return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
   }
-  if (!pair) {
+  if (!pair) {   // V's call follows K's on the stream: each has the whole workspace
     rc = compress_impl(k, dtype, sx_b, sx_h, sx_n, B, H, N, D, kmask, Dkc, M, T, t0, accumulate, ck, k_keep,
-                       FA_KEEP_ROWS, kk_stride_bh, keep_offset, ws, wk, hip_stream, tm);
+                       FA_KEEP_ROWS, kk_stride_bh, keep_offset, ws, workspace_bytes, hip_stream, tm);
     if (rc != FA_OK) return rc;
     return compress_impl(v, dtype, sx_b, sx_h, sx_n, B, H, N, D, vmask, Dvc, M, T, t0, accumulate, cv, v_keep,
-                         FA_KEEP_TOK8, vk_stride_bh, keep_offset, ws + wk, wv, hip_stream, tm2);
+                         FA_KEEP_TOK8, vk_stride_bh, keep_offset, ws, workspace_bytes, hip_stream, tm2);
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   CompressParamsKV pp{pk, pv};

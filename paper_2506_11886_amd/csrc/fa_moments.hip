@@ -690,8 +690,20 @@ size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int
   const long least = static_cast<long>(3.14159265358979323846 * (M / 2) * kMomMinU / kThetaBf16) + 1;
   if (t < least) t = least;
   if (t > 0x7fffffff) return 0;
-  const MomentPlan pl = make_moment_plan(dtype, B, H, N, D, Dc, M, static_cast<int>(t), 7, tensors, false);
-  return pl.mom_bytes + pl.op_bytes;
+  // tokens put in front may change the number of 32-token steps, and with it the block length either way: both
+  // counts are tried, each with as many blocks as its steps can hold
+  const int last = (N + 31) / 32 == (N + 7 + 31) / 32 ? 0 : 7;
+  size_t most = 0;
+  for (int lead = 0; lead <= last; lead += 7) {
+    const MomentPlan pl = make_moment_plan(dtype, B, H, N, D, Dc, M, static_cast<int>(t), lead, tensors, false);
+    if (!pl.use) continue;
+    const int full = (N + lead + 31) / 32 * 32;
+    const size_t blocks = static_cast<size_t>((full + pl.U - 1) / pl.U);
+    const size_t b = align_up(static_cast<size_t>(B) * H * blocks * (kMomP + 1) * Dc * sizeof(float), 256) +
+                     static_cast<size_t>(expand_tiles(M)) * ((blocks + 1) / 2) * 4096;
+    if (b > most) most = b;
+  }
+  return most;
 }
 
 template <int D, int NT, bool kEnergy>

@@ -93,3 +93,31 @@ def test_moment_selection_matches_oracle(D, N, M):
         want = fk.reconstruction_mse(x[0, h], M)
         scale = np.mean(x[0, h].astype(np.float64) ** 2, axis=0)
         assert np.all(np.abs(mse[0, h].cpu().numpy() - want) <= 5e-6 * scale)
+
+
+# 8192 tokens: with none in front the blocks are 256 tokens, with seven in front 288; few states, so that the moments and
+# not the direct projection's partials decide the workspace
+@pytest.mark.parametrize("pair", [False, True])
+@pytest.mark.parametrize("room", ["asked", "partials"])
+def test_moment_workspace_is_enough_for_every_offset(pair, room):
+    import paper_2506_11886_amd as fa
+    B, H, N, D, Dc, M = 1, 8, 8192, 128, 96, 4
+    print(f"[case] moment workspace pair {pair} room {room}", flush=True)
+    x, mask = _segment(D, N, Dc, H, 9)
+    want, keep = fk.compress_batched(x, mask, M, N, 0)
+    dt = torch.bfloat16
+    dx, dm = to_dev(x, dtype=dt), to_dev(mask)
+    query = fa.compress_kv_workspace_bytes(B, H, N, D, Dc, Dc, M, dt) if pair else fa.compress_workspace_bytes(B, H, N, D, Dc, M, dt)
+    # room for 64 chunks' partials: more than the direct projection takes (8), less than the moments
+    n = query if room == "asked" else (2 if pair else 1) * 64 * H * M * Dc * 4
+    buf = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    if pair:
+        c, kk, cv, _ = fa.fa_compress_kv(dx, dx, dm, dm, Dc, Dc, M, N, workspace=buf[:n])
+    else:
+        c, kk = fa.fa_compress(dx, dm, Dc, M, N, workspace=buf[:n])
+        cv = c
+    torch.cuda.synchronize()
+    tol = 5e-5 if room == "asked" else 2e-3
+    assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= tol and rel_err(cv.cpu().numpy(), want, np.sqrt(N)) <= tol
+    assert np.array_equal(kk[..., :D - Dc].float().cpu().numpy(), keep.astype(np.float32))
+    assert (buf[n:] == 0x5A).all()

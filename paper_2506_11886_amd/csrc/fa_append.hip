@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
     cb += __popcll(bal[j] & ((j < w0) ? ~0ull : ((j == w0) ? ((1ull << o0) - 1ull) : 0ull)));
     if (j == w0) bits = static_cast<uint32_t>(bal[j] >> o0) & ((1u << kADims) - 1u);
   }
-  const int nc = __popc(bits);
+  const int nc = min(__popc(bits), max(Dc - cb, 0));   // (nothing past column Dc, whatever the mask holds)
 
   // columns [cb, cb + nc) of C: 16 lanes a row
   const int col = tid & (kADims - 1), r0 = tid / kADims;

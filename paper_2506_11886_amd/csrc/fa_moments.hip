@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves) void fa_moments(MomentPara
         nc += __popcll(bal[j] & ((j < w) ? ~0ull : ((j == w) ? (bit - 1ull) : 0ull)));
         hit = hit || (j == w && (bal[j] & bit) != 0);
       }
-      cidx[tid] = hit ? static_cast<int16_t>(nc) : static_cast<int16_t>(-1);
+      cidx[tid] = hit && nc < Dc ? static_cast<int16_t>(nc) : static_cast<int16_t>(-1);   // (nothing past column Dc)
       if (!hit) kdim[tid - nc] = static_cast<uint16_t>(tid);
     }
     if (tid < 8) kdim[Du + tid] = D;

@@ -60,12 +60,13 @@ def measured_traffic(index):
     except OSError:
         return {}
     m = re.search(r"kernel sources digest:\s*([0-9a-f]{16})", text)
-    if not m or m.group(1) != source_digest("fa_decode.hip", "fa_compress.hip", "fa_common.hpp", "fa_mma.hpp"):
+    if not m or m.group(1) != source_digest("fa_decode.hip", "fa_compress.hip", "fa_moments.hip", "fa_moments.hpp",
+                                           "fa_common.hpp", "fa_mma.hpp"):
         return {}
     out = {}
     for line in text.splitlines():
         f = line.split()
-        if len(f) >= 6 and re.match(r"(decode_|compress_)", f[0]):
+        if len(f) >= 6 and re.match(r"(decode_|compress_|fa_moments|fa_expand)", f[0]):
             try:
                 out[f[0].split("<")[0]] = out.get(f[0].split("<")[0], 0) + int(round(float(f[-1]) * 1e6))
             except ValueError:
@@ -217,13 +218,13 @@ def measure(cfg, steps, warmup, extras=False):
     tfl = cmp_flops / t_project / 1e12
     hb = hbm(cmp_bytes, t_project)
     hbm_bound = cmp_bytes / (HBM_PEAK_GBS * 1e9) >= cmp_flops / (mm_peak * 1e12)
-    roof_cmp = {"kernel": "compress_project (K and V in one launch)",
+    roof_cmp = {"kernel": "projection (K and V in one launch; FLOPs of the M-row contraction, of which the moment form does fewer)",
                 "bound": "hbm" if hbm_bound else "mfma",
                 "achieved": hb["achieved"] if hbm_bound else round(tfl, 1),
                 "peak": HBM_PEAK_GBS if hbm_bound else mm_peak,
                 "unit": "GB/s" if hbm_bound else "TFLOP/s",
                 "frac": hb["frac"] if hbm_bound else round(tfl / mm_peak, 4),
-                "traffic": traffic.get("compress_project_fast_kv", traffic.get("compress_project")),
+                "traffic": traffic.get("fa_moments", traffic.get("compress_project_fast_kv", traffic.get("compress_project"))),
                 "hbm_GBps": hb["achieved"], "hbm_frac": hb["frac"],
                 "mfma_tflops": round(tfl, 1), "mfma_frac": round(tfl / mm_peak, 4)}
 

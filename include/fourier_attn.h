@@ -336,8 +336,8 @@ int fa_decode_mq(const void* q, int dtype, int B, int Tq, int Hq, int Hkv, int D
  * and dim_mask[b,h,d] = 1 for the Dc dimensions of lowest mse (equal errors go to
  * the lower dimension index), 0 for the others: the mask fa_compress / fa_decode /
  * fa_append take.  Over one period the basis is orthogonal, so the error is
- * evaluated as (sum_j x^2 - sum_m w_m C[m,d]^2) / N from fp32 coefficients (bf16
- * segments are widened first); results below ~1e-5 of a dimension's mean square
+ * evaluated as (sum_j x^2 - sum_m w_m C[m,d]^2) / N from coefficients of fp32
+ * precision; results below ~1e-5 of a dimension's mean square
  * are rounding noise and rank arbitrarily among themselves.
  *
  *   x         DEVICE, dtype elements, element strides as for fa_compress (rows
@@ -346,7 +346,8 @@ int fa_decode_mq(const void* q, int dtype, int B, int Tq, int Hq, int Hkv, int D
  *   dim_mask  DEVICE uint8 [B, H, D], written
  *   mse       DEVICE fp32 [B, H, D], written; may be NULL
  *   workspace DEVICE, 256-byte aligned, >= fa_select_workspace_bytes(...) bytes
- *             (holds the fp32 copy of a bf16 segment: 4*B*H*N*D bytes, the
+ *             (bf16 segments whose harmonics vary slowly over 64 tokens: energies and moments
+ *             per block; others: the fp32 copy of a bf16 segment, 4*B*H*N*D bytes, the
  *             coefficients of all dims and the workspace of the projection)
  * Asynchronous on hip_stream; nothing is allocated.  Same limits as fa_compress.
  * Returns FA_OK or an FA_ERR_* code (arguments are checked on the host first).

@@ -113,8 +113,12 @@ __device__ void form_expand_operand(const MomentParams& p, int item, int nstep) 
 // wave's registers and leave from there) and all waves pack the kept dims.  A row pitch of 2 D + 32
 // bytes puts the 8 rows x 32 bytes that half a wave reads transposed on distinct banks; the table is
 // stored in lane order.
+// At most 256 registers (two waves per SIMD), also where a workgroup has four waves only: with more the
+// compiler keeps acc in accumulation registers, and at D = 64 with three terms it read them back one to
+// five instructions behind the last product of a tile, across a branch, where the hardware needs eight
+// (sums of blocks longer than a tile then lacked the smaller terms' products: selection errors of 1e-3).
 template <int D, int NT, bool kEnergy>
-__global__ __launch_bounds__(64 * MomTile<D>::kWaves) void fa_moments(MomentParams p) {
+__global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentParams p) {
   using L = MomTile<D>;
   constexpr int NV = D / 8, PB = L::kPitch, NTH = 64 * L::kWaves, TT = L::kTokens, NL = L::kLoads;
   constexpr int RPL = NTH / NV, CW = L::kColTiles, NST = TT / 32;

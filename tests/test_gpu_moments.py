@@ -121,3 +121,58 @@ def test_moment_workspace_is_enough_for_every_offset(pair, room):
     assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= tol and rel_err(cv.cpu().numpy(), want, np.sqrt(N)) <= tol
     assert np.array_equal(kk[..., :D - Dc].float().cpu().numpy(), keep.astype(np.float32))
     assert (buf[n:] == 0x5A).all()
+
+
+def _long_rows(B, H, N, D, M, seed):
+    """In-band tones over a little noise, on the device: what is left of a dim after M states is small."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    n = torch.randint(1, max(2, (M - 1) // 2 + 1), (B, H, 1, D), generator=g, device="cuda").float()
+    j = torch.arange(N, device="cuda").float().view(1, 1, N, 1)
+    x = 0.1 * torch.randn((B, H, N, D), generator=g, device="cuda")
+    return x.add_(torch.cos(j * (n * (2.0 * np.pi / N)))).to(torch.bfloat16)
+
+
+# Workgroups of many tiles, blocks of more steps than a tile has (S) and blocks that straddle tiles, more blocks
+# than the expansion's 128 shared phases.   D, B, H, N, M
+LONG = [
+    (64, 2, 32, 24000, 360),     # S 5, 150 blocks, shares of three
+    (64, 2, 64, 9000, 4),        # S 16
+    (128, 1, 64, 9001, 100),     # S 11
+    (256, 1, 32, 6007, 21),      # S 16, tiles of two steps
+]
+
+
+@pytest.mark.parametrize("D,B,H,N,M", LONG)
+def test_moment_selection_of_long_workgroups(D, B, H, N, M):
+    import paper_2506_11886_amd as fa
+    print(f"[case] long select D{D} B{B} H{H} N{N} M{M}", flush=True)
+    x = _long_rows(B, H, N, D, M, 11)
+    mask, mse = fa.fa_select_dims(x, M, D // 2)
+    again = fa.fa_select_dims(x, M, D // 2)
+    torch.cuda.synchronize()
+    assert torch.equal(mask, again[0]) and torch.equal(mse, again[1])
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        seg = x[b, h].float().cpu().numpy()
+        want = fk.reconstruction_mse(seg, M)
+        assert np.all(np.abs(mse[b, h].cpu().numpy() - want) <= 5e-6 * np.mean(seg.astype(np.float64) ** 2, axis=0))
+
+
+@pytest.mark.parametrize("D,B,H,N,M", LONG)
+@pytest.mark.parametrize("layout", [0, 1])
+def test_moment_projection_of_long_workgroups(D, B, H, N, M, layout):
+    import paper_2506_11886_amd as fa
+    print(f"[case] long moments D{D} B{B} H{H} N{N} M{M} layout {layout}", flush=True)
+    x = _long_rows(B, H, N, D, M, 12)
+    Dc = D * 3 // 4 - 1
+    g = torch.Generator(device="cuda").manual_seed(13)
+    dmask = (torch.rand((B, H, D), generator=g, device="cuda").argsort(-1) < Dc).to(torch.uint8)
+    c, kept = fa.fa_compress(x, dmask, Dc, M, N, keep_layout=layout)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        want, keep = fk.compress_segment(x[b, h].float().cpu().numpy(), dmask[b, h].cpu().numpy(), M, N, 0)
+        assert rel_err(c[b, h].cpu().numpy(), want, np.sqrt(N)) <= (5e-5 if D != 128 else 2e-3)
+        if layout == fa.FA_KEEP_ROWS:
+            got = kept[b, h, :, :D - Dc]
+        else:
+            got = fa.keep_rows_from_tok8(kept[b, h], N, D - Dc)
+        assert np.array_equal(got.float().cpu().numpy(), keep.astype(np.float32))

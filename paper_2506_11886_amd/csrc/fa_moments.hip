@@ -106,6 +106,12 @@ __device__ void form_expand_operand(const MomentParams& p, int item, int nstep) 
   o[0] = ch; o[64] = cl; o[128] = sh; o[192] = sl;
 }
 
+// Sums of squares: fp32 over this many tiles per thread (32 squares at most), fp64 from there on.  The error of a
+// dim is the difference of its energy and of what the states hold, so a sum over a workgroup's whole share (all tokens of a
+// pair when there are many pairs) in fp32 would decide the order of well-compressed dims: 6e-5 of the energy of a
+// constant dim at 131072 tokens.
+constexpr int kEnergyTiles = 8;
+
 // D: head dim; NT: bf16 terms of a table value; kEnergy: also per-dim sums of squares (fa_select_dims).
 // grid (chunks, tensors * B * H).  LDS: table [S][NT][64 lanes][8] | two tiles.
 // Bound: HBM.  Three tiles of a workgroup are in flight in registers; a tile goes to LDS, one barrier
@@ -228,9 +234,13 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
   f32x4 acc[CW];
 #pragma unroll
   for (int i = 0; i < CW; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float e2[8];
+  float e2[8];                                                     // at most kEnergyTiles * NL squares each, then
+  double energy[8];                                                // added up here
 #pragma unroll
-  for (int i = 0; i < 8; ++i) e2[i] = 0.f;
+  for (int i = 0; i < 8; ++i) {
+    e2[i] = 0.f;
+    energy[i] = 0.0;
+  }
   float* const mom_t = z ? p.t[1].mom : p.t[0].mom;
   const size_t mblk = static_cast<size_t>(bh) * p.blocks + blk0;
   float* mom = mom_t + mblk * (kMomP * Dc);
@@ -260,6 +270,13 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
           const float hi = mine ? __builtin_bit_cast(float, x[i][e] & 0xffff0000u) : 0.0f;
           e2[2 * e] += lo * lo;
           e2[2 * e + 1] += hi * hi;
+        }
+      }
+      if ((t + 1) % kEnergyTiles == 0 || t + 1 == ntile) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          energy[e] += e2[e];
+          e2[e] = 0.f;
         }
       }
     }
@@ -363,15 +380,15 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
     one_tile(xd, t + 2);
   }
   if constexpr (kEnergy) {
-    float* red = reinterpret_cast<float*>(tiles);                  // [rows of a vector pass][D]
+    double* red = reinterpret_cast<double*>(tiles);                // [rows of a vector pass][D]
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[row0 * D + ch * 8 + e] = e2[e];
+    for (int e = 0; e < 8; ++e) red[row0 * D + ch * 8 + e] = energy[e];
     __syncthreads();
     if (tid < D) {
-      float v = 0.f;
+      double v = 0.0;
       for (int r = 0; r < RPL; ++r) v += red[r * D + tid];
-      p.t[0].epart[(static_cast<size_t>(blockIdx.x) * BH + bh) * D + tid] = v;
+      p.t[0].epart[(static_cast<size_t>(blockIdx.x) * BH + bh) * D + tid] = static_cast<float>(v);
     }
   }
 }

@@ -176,3 +176,21 @@ def test_moment_projection_of_long_workgroups(D, B, H, N, M, layout):
         else:
             got = fa.keep_rows_from_tok8(kept[b, h], N, D - Dc)
         assert np.array_equal(got.float().cpu().numpy(), keep.astype(np.float32))
+
+
+# One workgroup per pair walks every token: with constant dims and dims of a little noise on an offset (what a calibration
+# compresses best) the error is the small difference of two large sums.  One state: the error is the variance.
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_selection_energy_of_long_shares(D):
+    import paper_2506_11886_amd as fa
+    N = 131072
+    print(f"[case] selection energy D{D}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(21)
+    off = 4.0 + 12.0 * torch.rand((1, 1, 1, D), generator=g, device="cuda")
+    amp = 0.2 * torch.rand((1, 1, 1, D), generator=g, device="cuda") * (torch.arange(D, device="cuda") % 2)
+    x = (off + amp * torch.randn((1, 1, N, D), generator=g, device="cuda")).to(torch.bfloat16)
+    want = x[0, 0].double().var(0, unbiased=False)
+    scale = x[0, 0].double().pow(2).mean(0)
+    _, mse = fa.fa_select_dims(x.expand(4, 64, N, D), 1, D // 2)     # 256 pairs on one segment
+    torch.cuda.synchronize()
+    assert ((mse.double() - want).abs() <= 5e-6 * scale).all()

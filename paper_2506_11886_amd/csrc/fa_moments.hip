@@ -398,9 +398,11 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
 // LDS, kPhBlocks blocks at a time.  Bound: the fp32 matrix rate on long segments, latency else.
 constexpr int kPhBlocks = 128;
 constexpr int kExpandBatch = 4;
-__global__ __launch_bounds__(1024) void fa_expand(MomentParams p, int ctw, int ks) {
+constexpr int kExpandRun = 4;
+constexpr int kExpandWaves = 12;
+__global__ __launch_bounds__(64 * kExpandWaves) void fa_expand(MomentParams p, int ctw, int ks) {
   __shared__ __attribute__((aligned(16))) float2 ph[kPhBlocks][kExpandRows];
-  __shared__ float red[12 * 64 * 9];
+  __shared__ float red[9 * 64 * 9];                             // (ks - 1) * ctw <= 9 waves hand their sums over
   const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
@@ -435,8 +437,11 @@ __global__ __launch_bounds__(1024) void fa_expand(MomentParams p, int ctw, int k
     aE1 = pick(0); aE2 = pick(8); aO1 = pick(1); aO2 = pick(9);
   }
 
-  f32x4 cc = f32x4{0.f, 0.f, 0.f, 0.f}, cs = f32x4{0.f, 0.f, 0.f, 0.f};
-  float c0 = 0.f;
+  // kExpandRun batches are summed in fp32, those sums in fp64: an out-of-band dim's blocks are individually
+  // large and cancel, and the error of a dim is a small difference of sums
+  double cc[4] = {0.0, 0.0, 0.0, 0.0}, cs[4] = {0.0, 0.0, 0.0, 0.0}, c0 = 0.0;
+  float bc[4] = {0.f, 0.f, 0.f, 0.f}, bs[4] = {0.f, 0.f, 0.f, 0.f}, b00 = 0.f;
+  int run = 0;
   const double inv2t = 0.5 / p.T;
   for (int seg = 0; seg < nblk; seg += kPhBlocks) {
     const int nseg = min(kPhBlocks, nblk - seg);
@@ -473,10 +478,21 @@ __global__ __launch_bounds__(1024) void fa_expand(MomentParams p, int ctw, int k
           const float c[4] = {pa[0], pa[2], pb[0], pb[2]}, sn[4] = {pa[1], pa[3], pb[1], pb[3]};
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            cc[r] += c[r] * E[r] - sn[r] * O[r];
-            cs[r] += sn[r] * E[r] + c[r] * O[r];
+            bc[r] += c[r] * E[r] - sn[r] * O[r];
+            bs[r] += sn[r] * E[r] + c[r] * O[r];
           }
-          c0 += cur[i][0];     // lane group 0: moment 0, the constant function
+          b00 += cur[i][0];    // lane group 0: moment 0, the constant function
+        }
+        if (++run == kExpandRun || nb >= nseg) {
+          run = 0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            cc[r] += bc[r];
+            cs[r] += bs[r];
+            bc[r] = bs[r] = 0.f;
+          }
+          c0 += b00;
+          b00 = 0.f;
         }
       }
     }
@@ -487,10 +503,10 @@ __global__ __launch_bounds__(1024) void fa_expand(MomentParams p, int ctw, int k
       float* r = red + ((part - 1) * ctw + ctl) * (64 * 9) + lane;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        r[64 * i] = cc[i];
-        r[64 * (4 + i)] = cs[i];
+        r[64 * i] = static_cast<float>(cc[i]);
+        r[64 * (4 + i)] = static_cast<float>(cs[i]);
       }
-      r[64 * 8] = c0;
+      r[64 * 8] = static_cast<float>(c0);
     }
     __syncthreads();
     if (part == 0 && live)
@@ -765,7 +781,7 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   // split the columns while that leaves fewer than a workgroup per compute unit, then share the blocks
   int ctw = ct < 8 ? ct : 8;
   while (ctw > 1 && static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256) ctw = (ctw + 1) / 2;
-  int ks = 12 / ctw;
+  int ks = kExpandWaves / ctw;
   if (ks > 4) ks = 4;
   if (ks > p.blocks) ks = p.blocks;
   if (ks < 1) ks = 1;

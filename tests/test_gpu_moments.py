@@ -194,3 +194,20 @@ def test_selection_energy_of_long_shares(D):
     _, mse = fa.fa_select_dims(x.expand(4, 64, N, D), 1, D // 2)     # 256 pairs on one segment
     torch.cuda.synchronize()
     assert ((mse.double() - want).abs() <= 5e-6 * scale).all()
+
+
+# One pair over four million tokens: 8192 blocks, whose moments the expansion sums up.  Whole numbers of 8 bits: squares
+# and block sums are exact in fp32, as are runs of 16 blocks; what is left is the rounding (2^-24 each) of a workgroup's
+# energy, of a share's sum (twice, as it is squared) and of the result
+def test_selection_states_of_many_blocks():
+    import paper_2506_11886_amd as fa
+    N, D = 1 << 22, 64
+    print("[case] selection of many blocks", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(22)
+    x = torch.randint(128, 256, (1, 1, N, D), generator=g, device="cuda", dtype=torch.int16).to(torch.bfloat16)
+    cols = [c.double() for c in x[0, 0].unbind(1)]
+    want = torch.stack([c.var(unbiased=False) for c in cols])
+    scale = torch.stack([c.pow(2).mean() for c in cols])
+    _, mse = fa.fa_select_dims(x, 1, D // 2)
+    torch.cuda.synchronize()
+    assert ((mse[0, 0].double() - want).abs() <= 2.0 ** -22 * scale).all()

@@ -594,9 +594,9 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
   load(xa, 0);
   load(xb, batch);
 
-  f32x4 cc = f32x4{0.f, 0.f, 0.f, 0.f}, cs = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 cc1 = cc, cs1 = cc;            // the remainders' products
-  float c0 = 0.0f;
+  // a batch (2 kExpSteps blocks per wave) is summed in fp32, the batches in fp64: the blocks of a slow out-of-band
+  // tone are individually large and cancel
+  double sc[4] = {0.0, 0.0, 0.0, 0.0}, ss[4] = {0.0, 0.0, 0.0, 0.0}, s0 = 0.0;
   auto one_batch = [&](ExpBatch<NOPS>& x, int st0, int buf) {
     unsigned char* base = smem + buf * (batch * 4096);
 #pragma unroll
@@ -608,6 +608,8 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
       }
     }
     lds_barrier();
+    f32x4 cc = f32x4{0.f, 0.f, 0.f, 0.f}, cs = cc, cc1 = cc, cs1 = cc;   // (1: the remainders' products)
+    float c0 = 0.0f;
     // operands of the next step are read while this one multiplies; four independent sums
     Frag<bf16_t> fa[2][4];
     auto read = [&](Frag<bf16_t> (&f)[4], int i) {
@@ -632,48 +634,56 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
       }
     }
     load(x, st0 + 2 * batch);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sc[i] += cc[i] + cc1[i];
+      ss[i] += cs[i] + cs1[i];
+    }
+    s0 += c0;
   };
   for (int st0 = 0; st0 < nstep; st0 += 2 * batch) {
     one_batch(xa, st0, 0);
     if (st0 + batch >= nstep) break;
     one_batch(xb, st0 + batch, 1);
   }
-  cc += cc1;
-  cs += cs1;
-  c0 += __shfl_xor(c0, 32, 64);        // even and odd blocks
+  s0 += __shfl_xor(s0, 32, 64);        // even and odd blocks
   if (ks > 1) {                        // the shares meet in a fixed order
     __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(smem);
+    double* red = reinterpret_cast<double*>(smem);
     if (part > 0) {
-      f32x4* r = red + ((part - 1) * ctw + ctl) * 160 + lane;
-      r[0] = cc;
-      r[64] = cs;
-      if (g == 0) reinterpret_cast<float*>(red + ((part - 1) * ctw + ctl) * 160 + 128)[r16] = c0;
+      double* r = red + ((part - 1) * ctw + ctl) * (9 * 64) + lane;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        r[64 * i] = sc[i];
+        r[64 * (4 + i)] = ss[i];
+      }
+      r[64 * 8] = s0;
     }
     __syncthreads();
     if (part > 0) return;
     for (int q = 1; q < ks; ++q) {
-      const f32x4* r = red + ((q - 1) * ctw + ctl) * 160 + lane;
-      cc += r[0];
-      cs += r[64];
-      c0 += reinterpret_cast<const float*>(red + ((q - 1) * ctw + ctl) * 160 + 128)[r16];
+      const double* r = red + ((q - 1) * ctw + ctl) * (9 * 64) + lane;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[i] += r[64 * i];
+        ss[i] += r[64 * (4 + i)];
+      }
+      s0 += r[64 * 8];
     }
   }
   if (col >= Dc) return;
   float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + col;
-  const bool add = p.accumulate != 0;
-  if (with_dc && g == 0) C[0] = (add ? C[0] : 0.0f) + c0;
+  const bool add = p.accumulate != 0;   // (rounded once, behind the old state)
+  auto put = [&](int m, double v) {
+    float* o = C + static_cast<size_t>(m) * Dc;
+    *o = static_cast<float>(add ? *o + v : v);
+  };
+  if (with_dc && g == 0) put(0, s0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int nn = n0 + 4 * g + i;
-    if (2 * nn - 1 < p.M) {
-      float* o = C + static_cast<size_t>(2 * nn - 1) * Dc;
-      *o = (add ? *o : 0.0f) + cc[i];
-    }
-    if (2 * nn < p.M) {
-      float* o = C + static_cast<size_t>(2 * nn) * Dc;
-      *o = (add ? *o : 0.0f) + cs[i];
-    }
+    if (2 * nn - 1 < p.M) put(2 * nn - 1, sc[i]);
+    if (2 * nn < p.M) put(2 * nn, ss[i]);
   }
 }
 

@@ -211,3 +211,22 @@ def test_selection_states_of_many_blocks():
     _, mse = fa.fa_select_dims(x, 1, D // 2)
     torch.cuda.synchronize()
     assert ((mse[0, 0].double() - want).abs() <= 2.0 ** -22 * scale).all()
+
+
+# Whole numbers over four million tokens: a block's sum is exact in fp32, the sum over its 4096 blocks only in more, and
+# so is the state it is added to.  What comes back is rounded once.
+def test_moment_projection_sums_blocks_exactly():
+    import paper_2506_11886_amd as fa
+    N, D = 1 << 22, 64
+    print("[case] constant state of many blocks", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(23)
+    x = torch.randint(128, 256, (1, 1, N, D), generator=g, device="cuda", dtype=torch.int16)
+    want = x.sum(2, dtype=torch.float64)
+    prev = torch.full((1, 1, 1, D), 3.0e8, device="cuda")
+    ones = torch.ones((1, 1, D), dtype=torch.uint8, device="cuda")
+    x = x.to(torch.bfloat16)
+    c, _ = fa.fa_compress(x, ones, D, 1, N)
+    more, _ = fa.fa_compress(x, ones, D, 1, N, accumulate=True, coeffs=prev.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(c[0, 0, 0], want[0, 0].float())
+    assert torch.equal(more[0, 0, 0], (want[0, 0] + 3.0e8).float())

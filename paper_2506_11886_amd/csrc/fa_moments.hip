@@ -4,7 +4,7 @@
 //                transposed (ds_read_b64_tr_b16) as the B operand of v_mfma_f32_16x16x32_bf16 against
 //                the Chebyshev table (A operand, 2 or 3 bf16 terms); the kept dims of the same tile
 //                leave as 128-bit vectors.
-//   fa_expand16: coefficients from the moments, a bf16 head + remainder product (fa_compress)
+//   fa_expand16: coefficients from the moments, a product of split bf16 terms (fa_compress)
 //   fa_expand  : the same in fp32 for fa_select_dims: 16 harmonics x 16 columns per wave, four
 //                v_mfma_f32_16x16x4_f32 per block (even and odd polynomials apart), then one
 //                rotation by the block centre's exact phase.
@@ -17,8 +17,9 @@
 
 namespace fa {
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -244,8 +245,6 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
   float* const mom_t = z ? p.t[1].mom : p.t[0].mom;
   const size_t mblk = static_cast<size_t>(bh) * p.blocks + blk0;
   float* mom = mom_t + mblk * (kMomP * Dc);
-  __bf16* mom16 = reinterpret_cast<__bf16*>(mom_t) + mblk * (2 * kMomP * Dc);
-  float* mom0 = mom_t + static_cast<size_t>(BH) * p.blocks * (kMomP * Dc) + mblk * Dc;
   int s = 0;                                                       // step inside the current block
 
   auto one_tile = [&](u32x4 (&x)[NL], int t) {
@@ -306,28 +305,10 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
 #pragma unroll
           for (int w = 0; w < CW; ++w) {
             const int c = cpos[w];
-            if (c >= 0) {
-              if constexpr (NT == 2) {
-                // bf16 head and remainder (the B operand of fa_expand16); moment 0 once more in fp32
-                // for the constant function
-                bf16x4 hi, lo;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  hi[e] = static_cast<__bf16>(acc[w][e]);
-                  lo[e] = static_cast<__bf16>(acc[w][e] - static_cast<float>(hi[e]));
-                }
-                *reinterpret_cast<bf16x4*>(mom16 + c * kMomP + g * 4) = hi;
-                *reinterpret_cast<bf16x4*>(mom16 + (Dc + c) * kMomP + g * 4) = lo;
-                if (g == 0) mom0[c] = acc[w][0];
-              } else {
-                *reinterpret_cast<f32x4*>(mom + c * kMomP + g * 4) = acc[w];
-              }
-            }
+            if (c >= 0) *reinterpret_cast<f32x4*>(mom + c * kMomP + g * 4) = acc[w];
             acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
           }
           mom += kMomP * Dc;
-          mom16 += 2 * kMomP * Dc;
-          mom0 += Dc;
         }
       }
     }
@@ -538,9 +519,13 @@ __global__ __launch_bounds__(64 * kExpandWaves) void fa_expand(MomentParams p, i
   if (g == 0 && col < Dc) ecoef[(static_cast<size_t>(tile) * BH + bh) * Dc + col] = e;
 }
 
-// The same contraction for moments stored as bf16 head + remainder (fa_compress): a plain product
-// A[(n, cos | sin), (block, p)] x mu[(block, p), column] in three bf16 products (2^-16 relative), A
-// formed by fa_moments.  grid (tensors * B * H, column groups, 16-harmonic tiles): the workgroups of one head
+// The same contraction for fa_compress on the bf16 matrix rate: a plain product
+// A[(n, cos | sin), (block, p)] x mu[(block, p), column].  A is formed by fa_moments as head + remainder, the fp32
+// moments are split here into three terms: four products a value, 2^-17 relative (A's own rounding).  Moments kept as
+// two bf16 terms need no split (44 vector instructions a step) but lose seven of their bits: 8 heads x 129020 tokens, K and
+// V, M = 512: 138.5 us the call against 145.4; 31740 tokens, M = 256: 44.3 against 46.5.  Two harmonic tiles per
+// workgroup, which share a split, are better only where blocks are many (144.8; 48.2 us).
+// grid (tensors * B * H, column groups, 16-harmonic tiles): the workgroups of one head
 // are eight apart and share an XCD's L2 when the heads are a multiple of eight.  ctw * ks waves: wave
 // (column tile, share of the 2-block steps).  A batch is kExpSteps steps per wave; its A operands are
 // shared through LDS.  Bound: latency of the moments, which other XCDs wrote (two batches in flight).
@@ -548,10 +533,23 @@ constexpr int kExpSteps = 4;
 // NOPS: A operands (one 2-block step each) a wave copies per batch
 template <int NOPS>
 struct ExpBatch {
-  Frag<bf16_t> h[kExpSteps], l[kExpSteps];
-  float b0[kExpSteps];
+  f32x4 m[kExpSteps][2];
   u32x4 a[NOPS][4];
 };
+// Eight moments as three bf16 terms, which hold all their bits; pairs are rounded by one instruction.
+__device__ __forceinline__ void split3(const f32x4 (&m)[2], Frag<bf16_t> (&t)[3]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f32x2 r = f32x2{m[e >> 1][2 * (e & 1)], m[e >> 1][2 * (e & 1) + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+      t[k].v[e] = w;
+      r[0] -= __builtin_bit_cast(float, w << 16);
+      r[1] -= __builtin_bit_cast(float, w & 0xffff0000u);
+    }
+  }
+}
 template <int NOPS>
 __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int ks) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -566,13 +564,11 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
   const int n0 = blockIdx.z * kExpandRows + 1;                    // first harmonic of the tile
   const int col = (blockIdx.y * ctw + ctl) * 16 + r16;
   const int nblk = p.blocks, nstep = (nblk + 1) / 2;
-  const float* mom = z ? p.t[1].mom : p.t[0].mom;
-  const uint32_t bstride = 2 * kMomP * Dc, colc = min(col, Dc - 1);
-  const __bf16* m16 = reinterpret_cast<const __bf16*>(mom) + static_cast<size_t>(bh) * nblk * bstride;
-  const float* m0 = mom + (static_cast<size_t>(BH) * (kMomP * Dc) + static_cast<size_t>(bh) * Dc) * nblk;
+  const uint32_t bstride = kMomP * Dc;
+  const float* mom = (z ? p.t[1].mom : p.t[0].mom) + static_cast<size_t>(bh) * nblk * bstride +
+                     min(col, Dc - 1) * kMomP + (g & 1) * 8;
   const u32x4* op = reinterpret_cast<const u32x4*>(p.op) + static_cast<size_t>(blockIdx.z) * nstep * 256 + lane;
   const bool with_dc = blockIdx.z == 0;
-  const uint32_t dc0 = with_dc ? Dc : 0;                          // (elsewhere always the same line)
 
   auto load = [&](ExpBatch<NOPS>& x, int st0) {
 #pragma unroll
@@ -584,10 +580,9 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
 #pragma unroll
     for (int i = 0; i < kExpSteps; ++i) {
       const uint32_t blk = min(2 * (st0 + i * ks + part) + (g >> 1), nblk - 1);
-      const __bf16* m = m16 + (blk * bstride + colc * kMomP + (g & 1) * 8);
-      x.h[i].v = *reinterpret_cast<const u32x4*>(m);
-      x.l[i].v = *reinterpret_cast<const u32x4*>(m + kMomP * Dc);
-      x.b0[i] = m0[blk * dc0 + colc];
+      const f32x4* m = reinterpret_cast<const f32x4*>(mom + static_cast<size_t>(blk) * bstride);
+      x.m[i][0] = m[0];
+      x.m[i][1] = m[1];
     }
   };
   ExpBatch<NOPS> xa, xb;
@@ -624,13 +619,17 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
       if (i + 1 < kExpSteps) read(fa[(i + 1) & 1], i + 1);
       if (st0 + si < nstep) {
         const Frag<bf16_t>(&f)[4] = fa[i & 1];
-        mma_k32(cc, f[0], x.h[i]);
-        mma_k32(cs, f[2], x.h[i]);
-        mma_k32(cc1, f[1], x.h[i]);
-        mma_k32(cs1, f[3], x.h[i]);
-        mma_k32(cc1, f[0], x.l[i]);
-        mma_k32(cs1, f[2], x.l[i]);
-        if (2 * (st0 + si) + (g >> 1) < nblk) c0 += x.b0[i];
+        Frag<bf16_t> t[3];
+        split3(x.m[i], t);
+        mma_k32(cc, f[0], t[0]);
+        mma_k32(cs, f[2], t[0]);
+        mma_k32(cc1, f[1], t[0]);
+        mma_k32(cs1, f[3], t[0]);
+        mma_k32(cc1, f[0], t[1]);
+        mma_k32(cs1, f[2], t[1]);
+        mma_k32(cc1, f[0], t[2]);
+        mma_k32(cs1, f[2], t[2]);
+        if (2 * (st0 + si) + (g >> 1) < nblk) c0 += x.m[i][0][0];   // (even g: moment 0)
       }
     }
     load(x, st0 + 2 * batch);
@@ -673,17 +672,21 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
   }
   if (col >= Dc) return;
   float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + col;
-  const bool add = p.accumulate != 0;   // (rounded once, behind the old state)
-  auto put = [&](int m, double v) {
-    float* o = C + static_cast<size_t>(m) * Dc;
-    *o = static_cast<float>(add ? *o + v : v);
-  };
-  if (with_dc && g == 0) put(0, s0);
+  // the old state is read as a whole before any of it is written (row by row, each would wait for memory: a 2 K piece in two
+  // calls 28.4 us against 27.1), and the sum rounded once behind it
+  const int m1 = 2 * (n0 + 4 * g) - 1;
+  float old[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, old0 = 0.f;
+  if (p.accumulate) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int nn = n0 + 4 * g + i;
-    if (2 * nn - 1 < p.M) put(2 * nn - 1, sc[i]);
-    if (2 * nn < p.M) put(2 * nn, ss[i]);
+    for (int i = 0; i < 8; ++i)
+      if (m1 + i < p.M) old[i] = C[static_cast<size_t>(m1 + i) * Dc];
+    if (with_dc) old0 = C[0];
+  }
+  if (with_dc && g == 0) C[0] = static_cast<float>(old0 + s0);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const double v = (i & 1) ? ss[i >> 1] : sc[i >> 1];
+    if (m1 + i < p.M) C[static_cast<size_t>(m1 + i) * Dc] = static_cast<float>(old[i] + v);
   }
 }
 
@@ -727,7 +730,7 @@ MomentPlan make_moment_plan(int dtype, int B, int H, int N, int D, int Dc, int M
   const unsigned tile_tokens = D == 256 ? 64 : 128;
   pl.lds = static_cast<unsigned>(pl.S) * pl.parts * 1024u + 2u * tile_tokens * (2u * D + 32u);
   pl.op_bytes = exact ? 0 : static_cast<size_t>(expand_tiles(M)) * ((pl.blocks + 1) / 2) * 4096;
-  pl.mom_bytes = align_up(static_cast<size_t>(B) * H * pl.blocks * (kMomP + 1) * Dc * sizeof(float), 256);
+  pl.mom_bytes = align_up(static_cast<size_t>(B) * H * pl.blocks * kMomP * Dc * sizeof(float), 256);
   return pl;
 }
 
@@ -746,7 +749,7 @@ size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int
     if (!pl.use) continue;
     const int full = (N + lead + 31) / 32 * 32;
     const size_t blocks = static_cast<size_t>((full + pl.U - 1) / pl.U);
-    const size_t b = align_up(static_cast<size_t>(B) * H * blocks * (kMomP + 1) * Dc * sizeof(float), 256) +
+    const size_t b = align_up(static_cast<size_t>(B) * H * blocks * kMomP * Dc * sizeof(float), 256) +
                      static_cast<size_t>(expand_tiles(M)) * ((blocks + 1) / 2) * 4096;
     if (b > most) most = b;
   }

@@ -45,8 +45,7 @@ size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int
 struct MomentTensor {
   const void* x;
   const uint8_t* mask;   // null: every dim is compressed
-  float* mom;            // bf16: [B*H][blocks][head | remainder][Dc][16], then fp32 moment 0 [B*H][blocks][Dc];
-                         // fa_select_dims: fp32 [B*H][blocks][Dc][16]
+  float* mom;            // [B*H][blocks][Dc][16]
   void* keep;            // null: nothing kept is written
   float* coeffs;         // [B*H][M][Dc]
   float* epart;          // fa_select_dims: per-chunk sums of squares [chunks][B*H][D]

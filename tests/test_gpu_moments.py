@@ -230,3 +230,21 @@ def test_moment_projection_sums_blocks_exactly():
     torch.cuda.synchronize()
     assert torch.equal(c[0, 0, 0], want[0, 0].float())
     assert torch.equal(more[0, 0, 0], (want[0, 0] + 3.0e8).float())
+
+
+# One block per pair, whose sum is a whole number of 22 bits; with a period this long the first harmonic's cosine is one and
+# its operand exact: the state is that sum.  Moments of 17 bits would leave up to 2^-18 of it.
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_moments_keep_all_their_bits(D):
+    import paper_2506_11886_amd as fa
+    N = 1000
+    print(f"[case] bits of the moments D{D}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(24)
+    x = torch.randint(128, 256, (1, 256, N, D), generator=g, device="cuda", dtype=torch.int32)
+    x[:, :, ::2] *= 32
+    want = x.sum(2, dtype=torch.float64)
+    ones = torch.ones((1, 256, D), dtype=torch.uint8, device="cuda")
+    c, _ = fa.fa_compress(x.to(torch.bfloat16), ones, D, 3, 2**31 - 1)
+    torch.cuda.synchronize()
+    assert torch.equal(c[:, :, 0].double(), want)
+    assert ((c[:, :, 1].double() - want).abs() <= 2.0 ** -22 * want).all()

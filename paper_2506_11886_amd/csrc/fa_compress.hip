@@ -1087,9 +1087,11 @@ static MomentTensor moment_tensor(const void* x, const uint8_t* mask, float* mom
 //   matrix-bound: 8 x 30 K, M = 512: 57.5 / 65.7 us; 8 x 128 K, M = 512: 137 / 255
 //   HBM-bound, long blocks: 8 x 32 K, M = 256: 44.2 / 47.6; 32 x 8 K, M = 64: 39.6 / 42.2 us
 //   HBM-bound, many rows (the moments are traffic too): 256 x 4 K, M = 64: 166 / 138; 128 x 8 K: 152 / 135 us
+// Segments of up to kSplitTokens stay with the direct form whatever they cost: its split basis leaves 2e-6 of white rows
+// (6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
 static bool prefer_moments(const MomentPlan& mp, bool specialised, int tensors, int B, int H, int N, int D, int Dc,
                            int Du, int M) {
-  if (!mp.use) return false;
+  if (!mp.use || N <= kSplitTokens) return false;
   if (!specialised) return true;
   const double rows = static_cast<double>(tensors) * B * H * N;
   const double matrix_us = 2.0 * rows * M * Dc / 0.95e9, hbm_us = rows * 2.0 * (D + Du) / 5.0e6;

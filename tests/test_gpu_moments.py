@@ -248,3 +248,23 @@ def test_moments_keep_all_their_bits(D):
     torch.cuda.synchronize()
     assert torch.equal(c[:, :, 0].double(), want)
     assert ((c[:, :, 1].double() - want).abs() <= 2.0 ** -22 * want).all()
+
+
+# Short pieces and single tokens (Eq. 5) are projected against a basis of two bf16 terms: 2^-18 of a value at most, 2.0e-6
+# rms of the basis, one such rounding per product and fp32 sums; a frame's first tokens are closer still (6e-8 measured at
+# one token, 1.9e-7 at two).  The moments round twice: 3e-6, and 2e-6 at one token.
+@pytest.mark.parametrize("N", [1, 2, 300, 512])
+@pytest.mark.parametrize("D,M", [(128, 256), (64, 60), (256, 64)])
+def test_short_segments_keep_the_split_basis(N, D, M):
+    import paper_2506_11886_amd as fa
+    print(f"[case] short segment N{N} D{D} M{M}", flush=True)
+    T, t0, Dc = 32768, 7777, D * 3 // 4
+    x, mask = _segment(D, N, Dc, 4, N + D)
+    dt = torch.bfloat16
+    dx, dm = to_dev(x, dtype=dt), to_dev(mask)
+    want, _ = fk.compress_batched(x, mask, M, T, t0)
+    c, _ = fa.fa_compress(dx, dm, Dc, M, T, t0)
+    ck, _, cv, _ = fa.fa_compress_kv(dx, dx, dm, dm, Dc, Dc, M, T, t0)
+    torch.cuda.synchronize()
+    for got in (c, ck, cv):
+        assert np.linalg.norm(got.cpu().numpy() - want) <= (6e-7 if N <= 2 else 2.4e-6) * np.linalg.norm(want)

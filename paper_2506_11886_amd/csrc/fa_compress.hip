@@ -1018,6 +1018,7 @@ struct CompressPlan {
   int Sc, chunk, MC, DCn, nmax, stage;
   unsigned ks_elems, lds;
   size_t total;  // workspace bytes
+  double us_least, us_work;   // estimated time: the least a launch takes, and what its work adds to a fixed 10 us
 };
 
 // tensors: how many tensors share the projection launch (2 for the K | V pair: each then aims at half
@@ -1079,25 +1080,44 @@ static MomentTensor moment_tensor(const void* x, const uint8_t* mask, float* mom
   return t;
 }
 
-// Moments against the direct projection.  `specialised`: compress_project_fast would run (bf16, D = 128,
-// at most one kept vector per thread and block), which a short block or many rows favour; the generic
-// kernel is slower than the moments wherever these apply (measured 1.8 - 3.4x at D = 64 / 256, T / M from
-// 20 on).  Measured on K | V pairs at D = 128, moments against compress_project_fast:
-//   few rows, launches and latency decide: 8 x 4 K, M = 192: 18.9 / 23.3 us; 8 x 8 K, M = 256: 25.5 / 25.1
-//   matrix-bound: 8 x 30 K, M = 512: 57.5 / 65.7 us; 8 x 128 K, M = 512: 137 / 255
-//   HBM-bound, long blocks: 8 x 32 K, M = 256: 44.2 / 47.6; 32 x 8 K, M = 64: 39.6 / 42.2 us
-//   HBM-bound, many rows (the moments are traffic too): 256 x 4 K, M = 64: 166 / 138; 128 x 8 K: 152 / 135 us
+// Moments against the direct projection: the cheaper one by estimate.  The constants are measured rates and latencies, in
+// us, bytes and operations: over 118 calls (head dims 64 - 256, 8 - 512 pairs, 513 - 131072 tokens, M 64 - 1000, aligned and
+// not, with and without kept dims) the moments were chosen where the direct form was up to 7 % faster in five, and the direct form
+// where the moments were up to 23 % faster in ten (calls below 40 us).  Measured, K and V, direct / moments:
+//   8 x 2 K, D = 128, M = 256: 23.7 / 14.4 us; 8 x 32 K: 46.9 / 46.5; 8 x 128 K, M = 512: 252 / 145   (launches; matrix rate)
+//   128 x 8 K, 96 and 128 of 128 dims compressed: M = 64: 150 / 135; M = 128: 157 / 174; M = 256: 171 / 331   (the moments are traffic)
+//   128 x 8 K, D = 256: M = 64: 604 / 286; M = 128: 633 / 363; M = 256: 695 / 710; 256 x 4 K, M = 200: 696 / 983
 // Segments of up to kSplitTokens stay with the direct form whatever they cost: its split basis leaves 2e-6 of white rows
 // (6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
-static bool prefer_moments(const MomentPlan& mp, bool specialised, int tensors, int B, int H, int N, int D, int Dc,
-                           int Du, int M) {
+
+// specialised: compress_project_fast (D = 128); staged: kept dims leave through LDS.  Each tensor of a launch by itself.
+static void estimate_direct(CompressPlan& pl, bool specialised, bool staged, int B, int H, int N, int D, int Dc, int Du,
+                            int M, bool accumulate) {
+  const double pairs = static_cast<double>(B) * H, bytes = pairs * N * 2.0 * (D + Du);
+  const double coef = pairs * M * Dc * 4.0 * (accumulate ? 2.0 : 1.0);
+  const double cols = Dc <= 96 ? 96 : Dc <= 112 ? 112 : 128;
+  const double matrix = pairs * N * pl.MC * (2.0 * kPairs) * cols * 2.0 / 0.95e9;
+  if (specialised) {
+    pl.us_least = 18.0 + 0.9 * (pl.chunk / kFB);
+    pl.us_work = matrix > bytes / 5.1e6 ? matrix : bytes / 5.1e6;
+  } else {                         // a pass over the rows per 256 basis rows
+    pl.us_least = 16.0 + (pl.chunk / kTB) * (staged ? 1.0 : 2.0) * (0.6 + 0.4 * D / 64.0);
+    pl.us_work = pl.MC * bytes / (!staged ? 1.5e6 : D > 64 ? 2.1e6 : 2.4e6);
+  }
+  pl.us_work += pl.Sc > 1 ? 2.0 * pl.total / 10.0e6 : coef / (specialised ? 2.0e6 : 1.5e6);
+}
+static double direct_us(double least, double work) { return 10.0 + work > least ? 10.0 + work : least; }
+
+// Dc, Du: over the tensors.  The expansion reads the moments once per 16 harmonics, a round of its workgroups takes 4 us.
+static bool prefer_moments(const MomentPlan& mp, double direct, int tensors, int B, int H, int N, int D, double Dc, double Du,
+                           int M) {
   if (!mp.use || N <= kSplitTokens) return false;
-  if (!specialised) return true;
-  const double rows = static_cast<double>(tensors) * B * H * N;
-  const double matrix_us = 2.0 * rows * M * Dc / 0.95e9, hbm_us = rows * 2.0 * (D + Du) / 5.0e6;
-  if (rows <= 65536.0) return true;
-  if (mp.umax >= 192 && matrix_us > hbm_us) return true;
-  return mp.umax >= 256 && rows <= 600e3;
+  const double pairs = static_cast<double>(tensors) * B * H, mom = pairs * mp.blocks * kMomP * Dc * 4.0;
+  const int ct = (static_cast<int>(Dc) + 15) / 16, tiles = expand_tiles(M);
+  const double wgs = pairs * tiles * ((ct + expand_columns(ct, tiles, pairs) - 1) / expand_columns(ct, tiles, pairs));
+  const double us = 9.0 + pairs * N * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + 4.0 * ceil(wgs / 256.0) +
+                    mom * tiles / (mom > 256e6 ? 5.0e6 : 7.0e6);
+  return us <= 1.03 * direct;
 }
 
 static void set_moment_shape(MomentParams& p, const MomentPlan& pl, int64_t sx_b, int64_t sx_h, int64_t sx_n, int B,
@@ -1192,7 +1212,7 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
     return FA_ERR_SHAPE;
   if (reinterpret_cast<uintptr_t>(coeffs) & 15u) return FA_ERR_SHAPE;
 
-  const CompressPlan pl = make_compress_plan(dtype, B, H, N, D, Dc, M, keep_layout, keep_offset, tensors);
+  CompressPlan pl = make_compress_plan(dtype, B, H, N, D, Dc, M, keep_layout, keep_offset, tensors);
   if (pl.total > 0) {
     if (!workspace) return FA_ERR_NULL;
     if (workspace_bytes < pl.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
@@ -1200,13 +1220,17 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   }
 
   const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dc, M, T, keep_offset, 1, false);
-  const bool one_vector = x_keep == nullptr || Du == 0 ||
-                          (keep_layout == FA_KEEP_ROWS ? kFB * (keep_pitch / 8) : Du * (kFB / 8)) <= kCBlock;
-  const bool specialised = D == 128 && N > kSplitTokens && one_vector &&
-                           (x_keep == nullptr || Du == 0 || keep_layout == FA_KEEP_ROWS || keep_offset % 8 == 0);
+  // bf16 with head dim 128 and staged (or no) kept dims: the specialised kernel; short bf16 segments: the split basis of
+  // the generic one (see compress_project)
+  const unsigned fast_lds = 2u * (kCols * kFP + static_cast<unsigned>(keep_pitch) * kFP + 8u) * 2u;
+  const bool no_keep = x_keep == nullptr || Du == 0;
+  const bool staged_ok = no_keep || keep_layout == FA_KEEP_ROWS || keep_offset % 8 == 0;
+  const bool short_seg = dtype == FA_BF16 && N <= kSplitTokens;
+  const bool specialised = dtype == FA_BF16 && D == 128 && staged_ok && fast_lds <= kMaxCLds && !short_seg;
+  estimate_direct(pl, specialised, pl.stage || no_keep, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
   // (a workspace that holds the direct projection's partials alone is served by that)
   const bool fits = workspace && workspace_bytes >= mp.mom_bytes + mp.op_bytes && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
-  if (!only_params && fits && prefer_moments(mp, specialised, 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
+  if (!only_params && fits && prefer_moments(mp, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
     MomentParams p{};
     p.t[0] = moment_tensor(x, dim_mask, static_cast<float*>(workspace), x_keep, coeffs, keep_stride_bh, Dc, D,
                            keep_layout);
@@ -1259,12 +1283,7 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
       FA_LAUNCH_PROJECT2(T_, false, S_);\
     }                                   \
   } while (0)
-    // short bf16 segments: split basis in the generic kernel (see compress_project)
-    const bool short_seg = dtype == FA_BF16 && N <= kSplitTokens;
-    // bf16 with head dim 128 and staged (or no) kept dims: the specialised kernel
-    const unsigned fast_lds = 2u * (kCols * kFP + static_cast<unsigned>(keep_pitch) * kFP + 8u) * 2u;
-    const bool staged_ok = x_keep == nullptr || Du == 0 || keep_layout == FA_KEEP_ROWS || keep_offset % 8 == 0;
-    if (dtype == FA_BF16 && D == 128 && staged_ok && fast_lds <= kMaxCLds && !short_seg) {
+    if (specialised) {
       // straight-line block step when every thread has at most one vector of kept dims to store
       const int nvec = (x_keep == nullptr || Du == 0) ? 0 : (keep_layout == FA_KEEP_ROWS ? kFB * (keep_pitch / 8) : Du * (kFB / 8));
       const int km = (Dc == 0 || nvec > kCBlock) ? -1 : (nvec == 0 ? 0 : (keep_layout == FA_KEEP_ROWS ? 1 : 2));
@@ -1360,7 +1379,10 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dkc, M, T, keep_offset, 2, false);
   const size_t mom_v = make_moment_plan(dtype, B, H, N, D, Dvc, M, T, keep_offset, 2, false).mom_bytes;
   const bool fits = workspace_bytes >= mp.mom_bytes + mom_v + mp.op_bytes;
-  if (fits && Dvc > 0 && prefer_moments(mp, pair, 2, B, H, N, D, (Dkc + Dvc) / 2, D - (Dkc + Dvc) / 2, M)) {
+  const double direct = pair ? direct_us(plk.us_least > plv.us_least ? plk.us_least : plv.us_least, plk.us_work + plv.us_work)
+                             : direct_us(plk.us_least, plk.us_work) + direct_us(plv.us_least, plv.us_work) - 6.0;   // (V starts while K ends)
+  const double kept = 0.5 * ((k_keep ? pk.Du : 0) + (v_keep ? pv.Du : 0));
+  if (fits && Dvc > 0 && prefer_moments(mp, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M)) {
     MomentParams p{};
     p.t[0] = moment_tensor(k, kmask, reinterpret_cast<float*>(ws), k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS);
     p.t[1] = moment_tensor(v, vmask, reinterpret_cast<float*>(ws + mp.mom_bytes), v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8);

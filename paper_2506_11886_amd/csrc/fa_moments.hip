@@ -778,10 +778,7 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   const int dmax = tensors == 2 && p.t[1].Dc > p.t[0].Dc ? p.t[1].Dc : p.t[0].Dc;
   const int ct = (dmax + 15) / 16, tiles = expand_tiles(p.M);
   if (!p.t[0].ecoef) {
-    // all columns of a tile share the operands; with few workgroups two groups of columns
-    int ctw = ct < 8 ? ct : 8;
-    if (ct > 2 && ct <= 8 && static_cast<long>(tiles) * tensors * p.B * p.H < 256) ctw = (ct + 1) / 2;
-    if (ctw < 2) ctw = 2;
+    const int ctw = expand_columns(ct, tiles, static_cast<double>(tensors) * p.B * p.H);
     const int ks = ctw <= 4 ? 2 : 1;
     const unsigned lds = 2u * ks * kExpSteps * 4096u;
     auto kern = ctw >= kExpSteps ? fa_expand16<1> : fa_expand16<2>;

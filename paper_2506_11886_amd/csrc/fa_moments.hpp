@@ -66,6 +66,12 @@ int launch_moments(const MomentParams& p, const MomentPlan& pl, int tensors, hip
 int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTimers* tm);
 
 constexpr int kExpandRows = 16;       // harmonics per workgroup of fa_expand
+// 16-column tiles a workgroup of fa_expand16 takes out of ct: all share the operands; with few workgroups two groups of columns
+inline int expand_columns(int ct, int tiles, double pairs) {
+  int ctw = ct < 8 ? ct : 8;
+  if (ct > 2 && ct <= 8 && tiles * pairs < 256.0) ctw = (ct + 1) / 2;
+  return ctw < 2 ? 2 : ctw;
+}
 inline int expand_tiles(int M) { return M / 2 > 0 ? (M / 2 + kExpandRows - 1) / kExpandRows : 1; }
 
 }  // namespace fa

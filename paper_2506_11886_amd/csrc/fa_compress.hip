@@ -1072,10 +1072,10 @@ static int check_compress_shapes(int dtype, int B, int H, int N, int D, int Dc, 
   return FA_OK;
 }
 
-static MomentTensor moment_tensor(const void* x, const uint8_t* mask, float* mom, void* keep, float* coeffs,
-                                  int64_t keep_stride, int Dc, int D, int keep_layout) {
+static MomentTensor moment_tensor(const void* x, const uint8_t* mask, void* keep, float* coeffs, int64_t keep_stride,
+                                  int Dc, int D, int keep_layout) {
   MomentTensor t{};
-  t.x = x; t.mask = mask; t.mom = mom; t.keep = keep; t.coeffs = coeffs; t.keep_stride = keep_stride;
+  t.x = x; t.mask = mask; t.keep = keep; t.coeffs = coeffs; t.keep_stride = keep_stride;
   t.Dc = Dc; t.Du = D - Dc; t.keep_layout = keep_layout; t.keep_pitch = (D - Dc + 7) & ~7;
   return t;
 }
@@ -1120,12 +1120,80 @@ static bool prefer_moments(const MomentPlan& mp, double direct, int tensors, int
   return us <= 1.03 * direct;
 }
 
-static void set_moment_shape(MomentParams& p, const MomentPlan& pl, int64_t sx_b, int64_t sx_h, int64_t sx_n, int B,
-                             int H, int N, int D, int M, int T, int t0, int accumulate, int keep_offset) {
-  p.sx_b = sx_b; p.sx_h = sx_h; p.sx_n = sx_n;
-  p.B = B; p.H = H; p.N = N; p.D = D; p.M = M; p.T = T; p.t0 = t0;
-  p.accumulate = accumulate ? 1 : 0; p.keep_offset = keep_offset;
-  p.U = pl.U; p.S = pl.S; p.lead = pl.lead; p.blocks = pl.blocks; p.bpc = pl.bpc; p.nmax = M / 2; p.tiles = expand_tiles(M);
+// One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one
+// sequence at a time.  A part costs about 10 us; parts of a full workspace take 50 us and more.
+constexpr size_t kMomWorkspace = 64u << 20;   // per tensor, unless a single (sequence, head) needs more
+
+struct MomentCall {
+  MomentTensor t[2];
+  int tensors;
+  int64_t sx_b, sx_h, sx_n;
+  int B, H, N, D, M, T, t0, accumulate, keep_offset;
+};
+
+static size_t moment_bytes(const MomentCall& c, int B, int H) {
+  size_t n = 0;
+  for (int z = 0; z < c.tensors; ++z) {
+    const MomentPlan pl = make_moment_plan(FA_BF16, B, H, c.N, c.D, c.t[z].Dc, c.M, c.T, c.keep_offset, c.tensors, false);
+    n += pl.mom_bytes + (z == 0 ? pl.op_bytes : 0);
+  }
+  return n;
+}
+
+// sequences and heads of a part (the last one may be smaller); false: they would have to be smaller than half of
+// kMomWorkspace, where the parts' fixed time counts
+static bool moment_parts(const MomentCall& c, size_t room, int* B, int* H) {
+  const size_t all = moment_bytes(c, c.B, c.H), most = 1 + all / (c.tensors * (kMomWorkspace / 2));
+  *B = c.B;
+  *H = c.H;
+  for (size_t n = 1; n <= static_cast<size_t>(c.B) && n <= most; ++n) {
+    *B = static_cast<int>((c.B + n - 1) / n);
+    if (moment_bytes(c, *B, c.H) <= room) return true;
+  }
+  *B = 1;
+  for (size_t n = 2; n <= static_cast<size_t>(c.H) && n * c.B <= most; ++n) {
+    *H = static_cast<int>((c.H + n - 1) / n);
+    if (moment_bytes(c, 1, *H) <= room) return true;
+  }
+  return false;
+}
+
+static int run_moments(const MomentCall& c, int Bp, int Hp, char* ws, hipStream_t st, KernelTimers* tm) {
+  const bool whole = Bp == c.B && Hp == c.H;
+  if (tm && !whole && hipEventRecord(tm->start[0], st) != hipSuccess) return FA_ERR_HIP;   // (a timer holds one launch: all parts are the first's)
+  for (int b0 = 0; b0 < c.B; b0 += Bp)
+    for (int h0 = 0; h0 < c.H; h0 += Hp) {
+      const int B = c.B - b0 < Bp ? c.B - b0 : Bp, H = c.H - h0 < Hp ? c.H - h0 : Hp;
+      const size_t bh = static_cast<size_t>(b0) * c.H + h0;
+      MomentParams p{};
+      MomentPlan pl{};
+      size_t used = 0;
+      for (int z = 0; z < c.tensors; ++z) {
+        MomentTensor& t = p.t[z];
+        t = c.t[z];
+        const MomentPlan own = make_moment_plan(FA_BF16, B, H, c.N, c.D, t.Dc, c.M, c.T, c.keep_offset, c.tensors, false);
+        if (z == 0) pl = own;
+        t.x = static_cast<const bf16_t*>(t.x) + b0 * c.sx_b + h0 * c.sx_h;
+        t.mask += bh * c.D;
+        t.mom = reinterpret_cast<float*>(ws + used);
+        t.coeffs += bh * c.M * t.Dc;
+        if (t.keep) t.keep = static_cast<bf16_t*>(t.keep) + static_cast<int64_t>(bh) * t.keep_stride;
+        used += own.mom_bytes;
+      }
+      p.op = ws + used;
+      p.sx_b = c.sx_b; p.sx_h = c.sx_h; p.sx_n = c.sx_n;
+      p.B = B; p.H = H; p.N = c.N; p.D = c.D; p.M = c.M; p.T = c.T; p.t0 = c.t0;
+      p.accumulate = c.accumulate ? 1 : 0; p.keep_offset = c.keep_offset;
+      p.U = pl.U; p.S = pl.S; p.lead = pl.lead; p.blocks = pl.blocks; p.bpc = pl.bpc; p.nmax = c.M / 2; p.tiles = expand_tiles(c.M);
+      int rc = launch_moments(p, pl, c.tensors, st, whole ? tm : nullptr);
+      if (rc == FA_OK) rc = launch_expand(p, c.tensors, st, whole ? tm : nullptr);
+      if (rc != FA_OK) return rc;
+    }
+  if (tm && !whole) {
+    if (hipEventRecord(tm->stop[0], st) != hipSuccess) return FA_ERR_HIP;
+    tm->used[0] = true;
+  }
+  return FA_OK;
 }
 
 template <int DT, int KM>
@@ -1167,14 +1235,47 @@ static size_t direct_workspace_bytes(int dtype, int B, int H, int N, int D, int 
   return t ? t : 256;
 }
 
-size_t fa_compress_workspace_bytes_for(int dtype, int B, int H, int N, int D, int Dc, int M) {
-  size_t t = direct_workspace_bytes(dtype, B, H, N, D, Dc, M);
-  if (t == 0) return 0;
+// The moments of the calls that take them, whatever their period, offset and outputs.  Blocks get longer with the period, and so
+// the moments fewer and more often the cheaper form: the shortest blocks at which the slowest direct form loses decide.
+static size_t moment_workspace(int dtype, int B, int H, int N, int D, int Dc, int M) {
+  using namespace fa;
+  if (dtype != FA_BF16 || N <= kSplitTokens || Dc <= 0) return 0;
+  double direct = 0.0;
   for (int tensors = 1; tensors <= 2; ++tensors) {
-    const size_t m = fa::moment_workspace_bytes(dtype, B, H, N, D, Dc, M, tensors);
-    if (m > t) t = m;
+    CompressPlan dp = make_compress_plan(dtype, B, H, N, D, Dc, M, FA_KEEP_TOK8, 1, tensors);
+    estimate_direct(dp, false, false, B, H, N, D, Dc, D - Dc, M, true);
+    const double us = direct_us(dp.us_least, dp.us_work);
+    if (us > direct) direct = us;
   }
-  return t;
+  MomentCall c{};
+  c.t[0].Dc = Dc; c.N = N; c.D = D; c.M = M; c.tensors = 1;
+  size_t most = 0;
+  for (int u = kMomMinU; u <= kMomMaxU && most == 0; u += 32) {
+    const double t = 3.14159265358979323846 * (M / 2) * u / kThetaBf16 + 1.0;
+    c.T = t > 2147483647.0 ? 2147483647 : static_cast<int>(t);
+    if (c.T < N) c.T = N;             // (a period holds the segment)
+    if (c.T < M) c.T = M;
+    // tokens put in front may change the number of 32-token steps, and with it the block length either way
+    for (int tensors = 1; tensors <= 2; ++tensors)
+      for (int lead = 0; lead < 8; lead += 7) {
+        c.keep_offset = lead;
+        const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dc, M, c.T, lead, tensors, false);
+        if (!prefer_moments(mp, tensors * direct, tensors, B, H, N, D, Dc, D - Dc, M)) continue;
+        if (mp.mom_bytes + mp.op_bytes > most) most = mp.mom_bytes + mp.op_bytes;
+      }
+  }
+  if (most > kMomWorkspace) {
+    const size_t one = moment_bytes(c, 1, 1);
+    most = one > kMomWorkspace ? one : kMomWorkspace;
+  }
+  return most;
+}
+
+size_t fa_compress_workspace_bytes_for(int dtype, int B, int H, int N, int D, int Dc, int M) {
+  const size_t t = direct_workspace_bytes(dtype, B, H, N, D, Dc, M);
+  if (t == 0) return 0;
+  const size_t m = moment_workspace(dtype, B, H, N, D, Dc, M);
+  return m > t ? m : t;
 }
 
 size_t fa_compress_workspace_bytes(int B, int H, int N, int D, int Dc, int M) {
@@ -1228,18 +1329,16 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const bool short_seg = dtype == FA_BF16 && N <= kSplitTokens;
   const bool specialised = dtype == FA_BF16 && D == 128 && staged_ok && fast_lds <= kMaxCLds && !short_seg;
   estimate_direct(pl, specialised, pl.stage || no_keep, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
-  // (a workspace that holds the direct projection's partials alone is served by that)
-  const bool fits = workspace && workspace_bytes >= mp.mom_bytes + mp.op_bytes && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
-  if (!only_params && fits && prefer_moments(mp, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
-    MomentParams p{};
-    p.t[0] = moment_tensor(x, dim_mask, static_cast<float*>(workspace), x_keep, coeffs, keep_stride_bh, Dc, D,
-                           keep_layout);
-    set_moment_shape(p, mp, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset);
-    p.op = static_cast<char*>(workspace) + mp.mom_bytes;
-    int rc = launch_moments(p, mp, 1, static_cast<hipStream_t>(hip_stream), tm);
-    if (rc == FA_OK) rc = launch_expand(p, 1, static_cast<hipStream_t>(hip_stream), tm);
-    if (rc != FA_OK) return rc;
-    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  if (!only_params && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
+      prefer_moments(mp, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
+    MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
+                 B, H, N, D, M, T, t0, accumulate, keep_offset};
+    int Bp, Hp;   // (a workspace that holds the direct projection's partials alone is served by that)
+    if (moment_parts(c, workspace_bytes, &Bp, &Hp)) {
+      const int rc = run_moments(c, Bp, Hp, static_cast<char*>(workspace), static_cast<hipStream_t>(hip_stream), tm);
+      if (rc != FA_OK) return rc;
+      return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+    }
   }
 
   CompressParams p{};
@@ -1377,21 +1476,19 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
                     plk.MC == plv.MC && plk.Sc > 0;
   // long segments: one pass over both tensors, one expansion
   const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dkc, M, T, keep_offset, 2, false);
-  const size_t mom_v = make_moment_plan(dtype, B, H, N, D, Dvc, M, T, keep_offset, 2, false).mom_bytes;
-  const bool fits = workspace_bytes >= mp.mom_bytes + mom_v + mp.op_bytes;
   const double direct = pair ? direct_us(plk.us_least > plv.us_least ? plk.us_least : plv.us_least, plk.us_work + plv.us_work)
                              : direct_us(plk.us_least, plk.us_work) + direct_us(plv.us_least, plv.us_work) - 6.0;   // (V starts while K ends)
   const double kept = 0.5 * ((k_keep ? pk.Du : 0) + (v_keep ? pv.Du : 0));
-  if (fits && Dvc > 0 && prefer_moments(mp, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M)) {
-    MomentParams p{};
-    p.t[0] = moment_tensor(k, kmask, reinterpret_cast<float*>(ws), k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS);
-    p.t[1] = moment_tensor(v, vmask, reinterpret_cast<float*>(ws + mp.mom_bytes), v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8);
-    set_moment_shape(p, mp, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset);
-    p.op = ws + mp.mom_bytes + mom_v;
-    rc = launch_moments(p, mp, 2, static_cast<hipStream_t>(hip_stream), tm);
-    if (rc == FA_OK) rc = launch_expand(p, 2, static_cast<hipStream_t>(hip_stream), tm);
-    if (rc != FA_OK) return rc;
-    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  if (Dvc > 0 && prefer_moments(mp, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M)) {
+    MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
+                  moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
+                 2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};
+    int Bp, Hp;
+    if (moment_parts(c, workspace_bytes, &Bp, &Hp)) {
+      rc = run_moments(c, Bp, Hp, ws, static_cast<hipStream_t>(hip_stream), tm);
+      if (rc != FA_OK) return rc;
+      return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+    }
   }
   if (!pair) {   // V's call follows K's on the stream: each has the whole workspace
     rc = compress_impl(k, dtype, sx_b, sx_h, sx_n, B, H, N, D, kmask, Dkc, M, T, t0, accumulate, ck, k_keep,

@@ -701,8 +701,6 @@ static int moment_max_u(int M, int T, bool exact) {
   return u >= cap ? cap : static_cast<int>(u) / 32 * 32;
 }
 
-constexpr int kMomMinU = 64;
-
 MomentPlan make_moment_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int T, int keep_offset,
                             int tensors, bool exact) {
   MomentPlan pl{};
@@ -732,28 +730,6 @@ MomentPlan make_moment_plan(int dtype, int B, int H, int N, int D, int Dc, int M
   pl.op_bytes = exact ? 0 : static_cast<size_t>(expand_tiles(M)) * ((pl.blocks + 1) / 2) * 4096;
   pl.mom_bytes = align_up(static_cast<size_t>(B) * H * pl.blocks * kMomP * Dc * sizeof(float), 256);
   return pl;
-}
-
-size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int M, int tensors) {
-  // blocks only get longer as T grows: the shortest period a call may have decides
-  long t = N > M ? N : M;
-  const long least = static_cast<long>(3.14159265358979323846 * (M / 2) * kMomMinU / kThetaBf16) + 1;
-  if (t < least) t = least;
-  if (t > 0x7fffffff) return 0;
-  // tokens put in front may change the number of 32-token steps, and with it the block length either way: both
-  // counts are tried, each with as many blocks as its steps can hold
-  const int last = (N + 31) / 32 == (N + 7 + 31) / 32 ? 0 : 7;
-  size_t most = 0;
-  for (int lead = 0; lead <= last; lead += 7) {
-    const MomentPlan pl = make_moment_plan(dtype, B, H, N, D, Dc, M, static_cast<int>(t), lead, tensors, false);
-    if (!pl.use) continue;
-    const int full = (N + lead + 31) / 32 * 32;
-    const size_t blocks = static_cast<size_t>((full + pl.U - 1) / pl.U);
-    const size_t b = align_up(static_cast<size_t>(B) * H * blocks * kMomP * Dc * sizeof(float), 256) +
-                     static_cast<size_t>(expand_tiles(M)) * ((blocks + 1) / 2) * 4096;
-    if (b > most) most = b;
-  }
-  return most;
 }
 
 template <int D, int NT, bool kEnergy>

@@ -21,6 +21,7 @@ namespace fa {
 constexpr int kMomP = 16;             // Chebyshev polynomials per block
 constexpr double kThetaBf16 = 6.0;    // 2 J_16(6.0) = 2.4e-6, far below the 2^-9 of bf16 data
 constexpr double kThetaF32 = 4.2;     // 2 J_16(4.2) = 1.0e-8, below fp32 rounding
+constexpr int kMomMinU = 64;
 constexpr int kMomMaxU = 1024;        // tokens per block (the Chebyshev table lives in LDS)
 
 struct MomentPlan {
@@ -39,8 +40,6 @@ struct MomentPlan {
 // the plan for `tensors` tensors of one shape that share a launch; keep_offset only matters mod 8
 MomentPlan make_moment_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int T, int keep_offset,
                             int tensors, bool exact);
-// workspace that suffices for every T a call with these sizes may use
-size_t moment_workspace_bytes(int dtype, int B, int H, int N, int D, int Dc, int M, int tensors);
 
 struct MomentTensor {
   const void* x;

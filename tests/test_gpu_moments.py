@@ -268,3 +268,36 @@ def test_short_segments_keep_the_split_basis(N, D, M):
     torch.cuda.synchronize()
     for got in (c, ck, cv):
         assert np.linalg.norm(got.cpu().numpy() - want) <= (6e-7 if N <= 2 else 2.4e-6) * np.linalg.norm(want)
+
+
+# More moments than the workspace the library asks for holds (64 MB a tensor): whole sequences, or heads of one, at a time.
+@pytest.mark.parametrize("B,H", [(3, 14), (1, 42)])
+@pytest.mark.parametrize("pair", [False, True])
+def test_moment_projection_in_parts(B, H, pair):
+    import paper_2506_11886_amd as fa
+    N, D, Dc, M, off = 60001, 256, 200, 1000, 5
+    print(f"[case] moments in parts B{B} H{H} pair {pair}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(25)
+    x = torch.randn((B, H, N, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    mask = (torch.rand((B, H, D), generator=g, device="cuda").argsort(-1) < Dc).to(torch.uint8)
+    n = fa.compress_workspace_bytes(B, H, N, D, Dc, M, torch.bfloat16) * (2 if pair else 1)
+    assert n == (2 if pair else 1) * 64 << 20
+    got = []
+    for room in (n, 4 * n):          # in parts, at once
+        buf = torch.full((room + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        if pair:
+            out = fa.fa_compress_kv(x, x, mask, mask, Dc, Dc, M, N + 7, t0=3, keep_offset=off, workspace=buf[:room])
+        else:
+            out = fa.fa_compress(x, mask, Dc, M, N + 7, 3, keep_layout=fa.FA_KEEP_TOK8, keep_offset=off, workspace=buf[:room])
+        torch.cuda.synchronize()
+        assert (buf[room:] == 0x5A).all()
+        got.append(out)
+    for i, (a, b) in enumerate(zip(*got)):
+        if a.dtype == torch.float32:     # (blocks of another length: 3e-6 of white rows each)
+            assert (a - b).norm() <= 1e-5 * b.norm()
+        elif pair and i == 1:            # kept rows from `off` on
+            assert torch.equal(a[:, :, off:], b[:, :, off:])
+        else:
+            assert torch.equal(fa.keep_rows_from_tok8(a, off + N, D - Dc)[:, :, off:], fa.keep_rows_from_tok8(b, off + N, D - Dc)[:, :, off:])
+    want, _ = fk.compress_segment(x[-1, -1].float().cpu().numpy(), mask[-1, -1].cpu().numpy(), M, N + 7, 3)
+    assert rel_err(got[0][0][-1, -1].cpu().numpy(), want, np.sqrt(N)) <= 5e-5

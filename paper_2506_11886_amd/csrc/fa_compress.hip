@@ -1083,11 +1083,12 @@ static MomentTensor moment_tensor(const void* x, const uint8_t* mask, void* keep
 // Moments against the direct projection.  The moments are far closer (white rows: 3e-6 against the 1.3e-3 of the direct form's
 // basis of one bf16 term), so they also take what an estimate of both times puts a twentieth above the direct form.  Its
 // constants are measured rates and latencies, in us, bytes and operations; over 118 calls (head dims 64 - 256, 8 - 512 pairs,
-// 513 - 131072 tokens, M 64 - 1000, aligned and not, with and without kept dims) they are off by a fifth at most.
+// 513 - 131072 tokens, M 64 - 1000, aligned and not, with and without kept dims) they are off by a fifth at most, and none was sent
+// to the slower form by more than that.
 // Measured, K and V, direct / moments:
 //   8 x 2 K, D = 128, M = 256: 23.7 / 14.4 us; 8 x 32 K: 46.9 / 46.5; 8 x 128 K, M = 512: 252 / 145   (launches; matrix rate)
-//   128 x 8 K, 96 and 128 of 128 dims compressed: M = 64: 150 / 135; M = 128: 157 / 174; M = 256: 171 / 331   (the moments are traffic)
-//   128 x 8 K, D = 256: M = 64: 604 / 286; M = 128: 633 / 363; M = 256: 695 / 710; 256 x 4 K, M = 200: 696 / 983
+//   128 x 8 K, 96 and 128 of 128 dims compressed: M = 64: 150 / 129; M = 128: 157 / 158; M = 256: 171 / 276   (the moments are traffic)
+//   128 x 8 K, D = 256: M = 64: 604 / 276; M = 128: 633 / 335; M = 256: 695 / 598; 256 x 4 K, M = 200: 696 / 786
 // Segments of up to kSplitTokens stay with the direct form whatever they cost: its split basis leaves 2e-6 of white rows
 // (6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
 
@@ -1109,11 +1110,11 @@ static void estimate_direct(CompressPlan& pl, bool specialised, bool staged, int
 }
 static double direct_us(double least, double work) { return 10.0 + work > least ? 10.0 + work : least; }
 
-// Dc, Du: over the tensors.  The expansion reads the moments once per 16 harmonics (from the caches if they are few), a round of
-// its workgroups takes 4 us.  one_vector: the straight-line step of compress_project_fast would run, which many rows favour
+// Dc, Du: over the tensors.  The expansion reads the moments once per workgroup's harmonics (in a single round of workgroups from
+// the caches); a round of its workgroups takes a few us, most where the old state is read.  one_vector: the straight-line step of compress_project_fast would run, which many rows favour
 // unless they are matrix-bound: K and V of 128 x 8 K, M = 64: 152 (moments) / 135 us; 32 x 8 K, M = 64: 39.6 / 42.2 us.
 static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct, int tensors, int B, int H, int N, int D, double Dc, double Du,
-                           int M) {
+                           int M, bool accumulate) {
   if (!mp.use || N <= kSplitTokens) return false;
   const double pairs = static_cast<double>(tensors) * B * H, mom = pairs * mp.blocks * kMomP * Dc * 4.0;
   const double rows = pairs * N;
@@ -1122,9 +1123,10 @@ static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct,
     if (!(mp.umax >= 192 && matrix_us > hbm_us) && !(mp.umax >= 256 && rows <= 600e3)) return false;
   }
   const int ct = (static_cast<int>(Dc) + 15) / 16, tiles = expand_tiles(M);
-  const double wgs = pairs * tiles * ((ct + expand_columns(ct, tiles, pairs) - 1) / expand_columns(ct, tiles, pairs));
-  const double us = 8.0 + rows * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + 4.0 * ceil(wgs / 256.0) +
-                    mom * tiles / (mom < 64e6 ? 11.0e6 : mom < 256e6 ? 7.0e6 : 5.0e6);
+  const int ctw = expand_columns(ct, tiles, pairs), ht = expand_tiles_per_wg(ct, tiles, pairs), passes = (tiles + ht - 1) / ht;
+  const double rounds = ceil(pairs * passes * ((ct + ctw - 1) / ctw) / 256.0);
+  const double us = 8.0 + rows * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + rounds * (ht == 1 ? 4.0 : accumulate ? 5.0 : 2.5) +
+                    mom * passes / (ht == 1 ? 11.0e6 : mom < 128e6 ? 4.5e6 : 3.7e6);
   return us <= 1.05 * direct;
 }
 
@@ -1268,7 +1270,7 @@ static size_t moment_workspace(int dtype, int B, int H, int N, int D, int Dc, in
       for (int lead = 0; lead < 8; lead += 7) {
         c.keep_offset = lead;
         const MomentPlan mp = make_moment_plan(dtype, B, H, N, D, Dc, M, c.T, lead, tensors, false);
-        if (!prefer_moments(mp, false, tensors * direct, tensors, B, H, N, D, Dc, D - Dc, M)) continue;
+        if (!prefer_moments(mp, false, tensors * direct, tensors, B, H, N, D, Dc, D - Dc, M, false)) continue;
         if (mp.mom_bytes + mp.op_bytes > most) most = mp.mom_bytes + mp.op_bytes;
       }
   }
@@ -1339,7 +1341,7 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const bool specialised = dtype == FA_BF16 && D == 128 && staged_ok && fast_lds <= kMaxCLds && !short_seg;
   estimate_direct(pl, specialised, pl.stage || no_keep, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
   if (!only_params && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
-      prefer_moments(mp, specialised && one_vector, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M)) {
+      prefer_moments(mp, specialised && one_vector, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0)) {
     MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                  B, H, N, D, M, T, t0, accumulate, keep_offset};
     int Bp, Hp;   // (a workspace that holds the direct projection's partials alone is served by that)
@@ -1488,7 +1490,7 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const double direct = pair ? direct_us(plk.us_least > plv.us_least ? plk.us_least : plv.us_least, plk.us_work + plv.us_work)
                              : direct_us(plk.us_least, plk.us_work) + direct_us(plv.us_least, plv.us_work) - 6.0;   // (V starts while K ends)
   const double kept = 0.5 * ((k_keep ? pk.Du : 0) + (v_keep ? pv.Du : 0));
-  if (Dvc > 0 && prefer_moments(mp, pair, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M)) {
+  if (Dvc > 0 && prefer_moments(mp, pair, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M, accumulate != 0)) {
     MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
                   moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
                  2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};

@@ -521,19 +521,19 @@ __global__ __launch_bounds__(64 * kExpandWaves) void fa_expand(MomentParams p, i
 
 // The same contraction for fa_compress on the bf16 matrix rate: a plain product
 // A[(n, cos | sin), (block, p)] x mu[(block, p), column].  A is formed by fa_moments as head + remainder, the fp32
-// moments are split here into three terms: four products a value, 2^-17 relative (A's own rounding).  Moments kept as
-// two bf16 terms need no split (44 vector instructions a step) but lose seven of their bits: 8 heads x 129020 tokens, K and
-// V, M = 512: 138.5 us the call against 145.4; 31740 tokens, M = 256: 44.3 against 46.5.  Two harmonic tiles per
-// workgroup, which share a split, are better only where blocks are many (144.8; 48.2 us).
-// grid (tensors * B * H, column groups, 16-harmonic tiles): the workgroups of one head
+// moments are split here into three terms: four products a value, 2^-17 relative (A's own rounding).  The split, 44 vector
+// instructions, is the longest part of a step.  HT 16-harmonic tiles per workgroup share it: two where one would take more
+// workgroups than there are compute units (K and V of 128 x 8 K, head dim 256, M = 256: 710 -> 598 us the call; head dim 64: 180
+// -> 149), else one (8 x 4 K, head dim 128, M = 64: 16.6 us against 19.4).
+// grid (tensors * B * H, column groups, groups of harmonic tiles): the workgroups of one head
 // are eight apart and share an XCD's L2 when the heads are a multiple of eight.  ctw * ks waves: wave
-// (column tile, share of the 2-block steps).  A batch is kExpSteps steps per wave; its A operands are
+// (column tile, share of the 2-block steps).  A batch is kExpSteps / HT steps per wave; its A operands are
 // shared through LDS.  Bound: latency of the moments, which other XCDs wrote (two batches in flight).
 constexpr int kExpSteps = 4;
-// NOPS: A operands (one 2-block step each) a wave copies per batch
-template <int NOPS>
+// NOPS: A operands (one tile and 2-block step each) a wave copies per batch
+template <int kSteps, int NOPS>
 struct ExpBatch {
-  f32x4 m[kExpSteps][2];
+  f32x4 m[kSteps][2];
   u32x4 a[NOPS][4];
 };
 // Eight moments as three bf16 terms, which hold all their bits; pairs are rounded by one instruction.
@@ -550,94 +550,107 @@ __device__ __forceinline__ void split3(const f32x4 (&m)[2], Frag<bf16_t> (&t)[3]
     }
   }
 }
-template <int NOPS>
+template <int HT, int NOPS>
 __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int ks) {
+  constexpr int kSteps = kExpSteps / HT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
-  const int ctl = wave % ctw, part = wave / ctw, nw = ctw * ks, batch = ks * kExpSteps;
+  const int ctl = wave % ctw, part = wave / ctw, nw = ctw * ks, batch = ks * kSteps;
   const int BH = p.B * p.H;
   const int z = blockIdx.x >= BH;
   const int bh = blockIdx.x - (z ? BH : 0);
   const int Dc = z ? p.t[1].Dc : p.t[0].Dc;
-  const int n0 = blockIdx.z * kExpandRows + 1;                    // first harmonic of the tile
+  const int tile0 = blockIdx.z * HT;
   const int col = (blockIdx.y * ctw + ctl) * 16 + r16;
   const int nblk = p.blocks, nstep = (nblk + 1) / 2;
   const uint32_t bstride = kMomP * Dc;
   const float* mom = (z ? p.t[1].mom : p.t[0].mom) + static_cast<size_t>(bh) * nblk * bstride +
                      min(col, Dc - 1) * kMomP + (g & 1) * 8;
-  const u32x4* op = reinterpret_cast<const u32x4*>(p.op) + static_cast<size_t>(blockIdx.z) * nstep * 256 + lane;
-  const bool with_dc = blockIdx.z == 0;
+  const u32x4* op = reinterpret_cast<const u32x4*>(p.op) + lane;
+  const bool with_dc = tile0 == 0;
 
-  auto load = [&](ExpBatch<NOPS>& x, int st0) {
+  // operand u of a batch: tile u % HT (past the last: the last, its sums are dropped), step u / HT
+  auto load = [&](ExpBatch<kSteps, NOPS>& x, int st0) {
 #pragma unroll
     for (int i = 0; i < NOPS; ++i) {
-      const uint32_t st = min(st0 + min(wave + i * nw, batch - 1), nstep - 1);
+      const int u = min(wave + i * nw, batch * HT - 1);
+      const size_t st = static_cast<size_t>(min(tile0 + u % HT, p.tiles - 1)) * nstep + min(st0 + u / HT, nstep - 1);
 #pragma unroll
       for (int k = 0; k < 4; ++k) x.a[i][k] = op[st * 256 + k * 64];
     }
 #pragma unroll
-    for (int i = 0; i < kExpSteps; ++i) {
+    for (int i = 0; i < kSteps; ++i) {
       const uint32_t blk = min(2 * (st0 + i * ks + part) + (g >> 1), nblk - 1);
       const f32x4* m = reinterpret_cast<const f32x4*>(mom + static_cast<size_t>(blk) * bstride);
       x.m[i][0] = m[0];
       x.m[i][1] = m[1];
     }
   };
-  ExpBatch<NOPS> xa, xb;
+  ExpBatch<kSteps, NOPS> xa, xb;
   load(xa, 0);
   load(xb, batch);
 
-  // a batch (2 kExpSteps blocks per wave) is summed in fp32, the batches in fp64: the blocks of a slow out-of-band
+  // a batch (2 kSteps blocks per wave) is summed in fp32, the batches in fp64: the blocks of a slow out-of-band
   // tone are individually large and cancel
-  double sc[4] = {0.0, 0.0, 0.0, 0.0}, ss[4] = {0.0, 0.0, 0.0, 0.0}, s0 = 0.0;
-  auto one_batch = [&](ExpBatch<NOPS>& x, int st0, int buf) {
-    unsigned char* base = smem + buf * (batch * 4096);
+  double sc[HT][4], ss[HT][4], s0 = 0.0;
+#pragma unroll
+  for (int q = 0; q < HT; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sc[q][i] = ss[q][i] = 0.0;
+  auto one_batch = [&](ExpBatch<kSteps, NOPS>& x, int st0, int buf) {
+    unsigned char* base = smem + buf * (batch * HT * 4096);
 #pragma unroll
     for (int i = 0; i < NOPS; ++i) {
-      if (wave + i * nw < batch) {
+      if (wave + i * nw < batch * HT) {
         u32x4* o = reinterpret_cast<u32x4*>(base + (wave + i * nw) * 4096) + lane;
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k * 64] = x.a[i][k];
       }
     }
     lds_barrier();
-    f32x4 cc = f32x4{0.f, 0.f, 0.f, 0.f}, cs = cc, cc1 = cc, cs1 = cc;   // (1: the remainders' products)
+    f32x4 cc[HT], cs[HT], cc1[HT], cs1[HT];   // (1: the remainders' products)
+#pragma unroll
+    for (int q = 0; q < HT; ++q) cc[q] = cs[q] = cc1[q] = cs1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     float c0 = 0.0f;
-    // operands of the next step are read while this one multiplies; four independent sums
-    Frag<bf16_t> fa[2][4];
-    auto read = [&](Frag<bf16_t> (&f)[4], int i) {
-      const u32x4* o = reinterpret_cast<const u32x4*>(base + (i * ks + part) * 4096) + lane;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) f[k].v = o[k * 64];
-    };
-    read(fa[0], 0);
-#pragma unroll
-    for (int i = 0; i < kExpSteps; ++i) {
+    for (int i = 0; i < kSteps; ++i) {
       const int si = i * ks + part;
-      if (i + 1 < kExpSteps) read(fa[(i + 1) & 1], i + 1);
       if (st0 + si < nstep) {
-        const Frag<bf16_t>(&f)[4] = fa[i & 1];
-        Frag<bf16_t> t[3];
+        Frag<bf16_t> f[HT][4], t[3];
+#pragma unroll
+        for (int q = 0; q < HT; ++q) {
+          const u32x4* o = reinterpret_cast<const u32x4*>(base + (si * HT + q) * 4096) + lane;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) f[q][k].v = o[k * 64];
+        }
         split3(x.m[i], t);
-        mma_k32(cc, f[0], t[0]);
-        mma_k32(cs, f[2], t[0]);
-        mma_k32(cc1, f[1], t[0]);
-        mma_k32(cs1, f[3], t[0]);
-        mma_k32(cc1, f[0], t[1]);
-        mma_k32(cs1, f[2], t[1]);
-        mma_k32(cc1, f[0], t[2]);
-        mma_k32(cs1, f[2], t[2]);
+#pragma unroll
+        for (int q = 0; q < HT; ++q) {
+          mma_k32(cc[q], f[q][0], t[0]);
+          mma_k32(cs[q], f[q][2], t[0]);
+          mma_k32(cc1[q], f[q][1], t[0]);
+          mma_k32(cs1[q], f[q][3], t[0]);
+        }
+#pragma unroll
+        for (int k = 1; k < 3; ++k)
+#pragma unroll
+          for (int q = 0; q < HT; ++q) {
+            mma_k32(cc1[q], f[q][0], t[k]);
+            mma_k32(cs1[q], f[q][2], t[k]);
+          }
         if (2 * (st0 + si) + (g >> 1) < nblk) c0 += x.m[i][0][0];   // (even g: moment 0)
       }
     }
     load(x, st0 + 2 * batch);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      sc[i] += cc[i] + cc1[i];
-      ss[i] += cs[i] + cs1[i];
-    }
+    for (int q = 0; q < HT; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[q][i] += cc[q][i] + cc1[q][i];
+        ss[q][i] += cs[q][i] + cs1[q][i];
+      }
     s0 += c0;
   };
   for (int st0 = 0; st0 < nstep; st0 += 2 * batch) {
@@ -650,44 +663,59 @@ __global__ __launch_bounds__(512) void fa_expand16(MomentParams p, int ctw, int 
     __syncthreads();
     double* red = reinterpret_cast<double*>(smem);
     if (part > 0) {
-      double* r = red + ((part - 1) * ctw + ctl) * (9 * 64) + lane;
+      double* r = red + ((part - 1) * ctw + ctl) * ((8 * HT + 1) * 64) + lane;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        r[64 * i] = sc[i];
-        r[64 * (4 + i)] = ss[i];
-      }
-      r[64 * 8] = s0;
+      for (int q = 0; q < HT; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          r[64 * (8 * q + i)] = sc[q][i];
+          r[64 * (8 * q + 4 + i)] = ss[q][i];
+        }
+      r[64 * ((8 * HT + 1) - 1)] = s0;
     }
     __syncthreads();
     if (part > 0) return;
-    for (int q = 1; q < ks; ++q) {
-      const double* r = red + ((q - 1) * ctw + ctl) * (9 * 64) + lane;
+    for (int w = 1; w < ks; ++w) {
+      const double* r = red + ((w - 1) * ctw + ctl) * ((8 * HT + 1) * 64) + lane;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sc[i] += r[64 * i];
-        ss[i] += r[64 * (4 + i)];
-      }
-      s0 += r[64 * 8];
+      for (int q = 0; q < HT; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          sc[q][i] += r[64 * (8 * q + i)];
+          ss[q][i] += r[64 * (8 * q + 4 + i)];
+        }
+      s0 += r[64 * ((8 * HT + 1) - 1)];
     }
   }
   if (col >= Dc) return;
   float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + col;
   // the old state is read as a whole before any of it is written (row by row, each would wait for memory: a 2 K piece in two
   // calls 28.4 us against 27.1), and the sum rounded once behind it
-  const int m1 = 2 * (n0 + 4 * g) - 1;
-  float old[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, old0 = 0.f;
+  float old[HT][8], old0 = 0.f;
+#pragma unroll
+  for (int q = 0; q < HT; ++q)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) old[q][i] = 0.f;
   if (p.accumulate) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (m1 + i < p.M) old[i] = C[static_cast<size_t>(m1 + i) * Dc];
+    for (int q = 0; q < HT; ++q)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int m = 2 * ((tile0 + q) * kExpandRows + 4 * g) + 1 + i;
+        if (m < p.M) old[q][i] = C[static_cast<size_t>(m) * Dc];
+      }
     if (with_dc) old0 = C[0];
   }
   if (with_dc && g == 0) C[0] = static_cast<float>(old0 + s0);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const double v = (i & 1) ? ss[i >> 1] : sc[i >> 1];
-    if (m1 + i < p.M) C[static_cast<size_t>(m1 + i) * Dc] = static_cast<float>(old[i] + v);
-  }
+  for (int q = 0; q < HT; ++q)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      // harmonic n = 1 + 16 tile + 4 g + i / 2: row 2 n - 1 its cosine, row 2 n its sine
+      const int m = 2 * ((tile0 + q) * kExpandRows + 4 * g) + 1 + i;
+      const double v = (i & 1) ? ss[q][i >> 1] : sc[q][i >> 1];
+      if (m < p.M) C[static_cast<size_t>(m) * Dc] = static_cast<float>(old[q][i] + v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -754,14 +782,15 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   const int dmax = tensors == 2 && p.t[1].Dc > p.t[0].Dc ? p.t[1].Dc : p.t[0].Dc;
   const int ct = (dmax + 15) / 16, tiles = expand_tiles(p.M);
   if (!p.t[0].ecoef) {
+    const int ht = expand_tiles_per_wg(ct, tiles, static_cast<double>(tensors) * p.B * p.H);
     const int ctw = expand_columns(ct, tiles, static_cast<double>(tensors) * p.B * p.H);
     const int ks = ctw <= 4 ? 2 : 1;
-    const unsigned lds = 2u * ks * kExpSteps * 4096u;
-    auto kern = ctw >= kExpSteps ? fa_expand16<1> : fa_expand16<2>;
+    const unsigned lds = 2u * ks * kExpSteps * 4096u;            // (kExpSteps / ht steps of ht operands; the shares' sums fit in)
+    auto kern = ht == 2 ? (ctw >= kExpSteps ? fa_expand16<2, 1> : fa_expand16<2, 2>) : (ctw >= kExpSteps ? fa_expand16<1, 1> : fa_expand16<1, 2>);
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             2 * 2 * kExpSteps * 4096) != hipSuccess)
       return FA_ERR_HIP;
-    FA_LAUNCH_TIMED(tm, 1, kern, dim3(tensors * p.B * p.H, (ct + ctw - 1) / ctw, tiles), dim3(64 * ctw * ks), lds, st, p, ctw, ks);
+    FA_LAUNCH_TIMED(tm, 1, kern, dim3(tensors * p.B * p.H, (ct + ctw - 1) / ctw, (tiles + ht - 1) / ht), dim3(64 * ctw * ks), lds, st, p, ctw, ks);
     return FA_OK;
   }
   // split the columns while that leaves fewer than a workgroup per compute unit, then share the blocks

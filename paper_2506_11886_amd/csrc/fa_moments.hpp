@@ -71,6 +71,11 @@ inline int expand_columns(int ct, int tiles, double pairs) {
   if (ct > 2 && ct <= 8 && tiles * pairs < 256.0) ctw = (ct + 1) / 2;
   return ctw < 2 ? 2 : ctw;
 }
+// 16-harmonic tiles a workgroup takes: two once single ones are more workgroups than compute units
+inline int expand_tiles_per_wg(int ct, int tiles, double pairs) {
+  const int ctw = expand_columns(ct, tiles, pairs);
+  return tiles > 1 && pairs * tiles * ((ct + ctw - 1) / ctw) > 256.0 ? 2 : 1;
+}
 inline int expand_tiles(int M) { return M / 2 > 0 ? (M / 2 + kExpandRows - 1) / kExpandRows : 1; }
 
 }  // namespace fa

@@ -25,7 +25,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // a[p] = (2 - [p = 0]) i^p J_p(theta) without the i of odd p (even p belong to the cosine, odd p to the
 // sine of the block centre).  Miller's backward recurrence J_{p-1} = (2p / theta) J_p - J_{p+1} from
-// p = 34, normalised by J_0 + 2 sum J_{2k} = 1; below theta = 0.05, where it would overflow, the
+// p = 34, normalised by J_0 + 2 sum J_{2k} = 1; below theta = 0.05, where 2 / theta grows without bound, the
 // leading terms of the power series (relative error 1e-11).
 __device__ __forceinline__ void bessel_coeffs(double theta, float (&a)[kMomP]) {
   double j[kMomP];
@@ -86,9 +86,9 @@ __device__ void form_expand_operand(const MomentParams& p, int item, int nstep) 
   float a[kMomP];
   bessel_coeffs(3.14159265358979323846 * n * p.U / p.T, a);
   const int blk = 2 * st + (g >> 1);
-  // 2^-32-turn phase of twice the block's centre: its error times n <= 512 stays below 1e-7 turns
+  // 2^-32-turn phase of the block's centre, rounded to nearest: half a unit times n <= 512 is 6e-8 turns, without a bias
   const double c2 = static_cast<double>(2ll * (p.t0 - p.lead) + p.U - 1) + 2.0 * p.U * blk;
-  const uint32_t ph = static_cast<uint32_t>(static_cast<uint64_t>(c2 * (2147483648.0 / p.T)));
+  const uint32_t ph = static_cast<uint32_t>(static_cast<uint64_t>(c2 * (2147483648.0 / p.T) + 0.5));
   const float x = static_cast<float>(static_cast<int32_t>(ph * static_cast<uint32_t>(n))) * 2.3283064365386963e-10f;
   float sn = __builtin_amdgcn_sinf(x), c = __builtin_amdgcn_cosf(x);
   if (blk >= p.blocks) sn = c = 0.0f;

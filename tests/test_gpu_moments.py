@@ -97,12 +97,13 @@ def test_moment_selection_matches_oracle(D, N, M):
 
 # 8192 tokens: with none in front the blocks are 256 tokens, with seven in front 288; few states, so that the moments and
 # not the direct projection's partials decide the workspace
+@pytest.mark.parametrize("off", [0, 1, 7])
 @pytest.mark.parametrize("pair", [False, True])
 @pytest.mark.parametrize("room", ["asked", "partials"])
-def test_moment_workspace_is_enough_for_every_offset(pair, room):
+def test_moment_workspace_is_enough_for_every_offset(pair, room, off):
     import paper_2506_11886_amd as fa
     B, H, N, D, Dc, M = 1, 8, 8192, 128, 96, 4
-    print(f"[case] moment workspace pair {pair} room {room}", flush=True)
+    print(f"[case] moment workspace pair {pair} room {room} off {off}", flush=True)
     x, mask = _segment(D, N, Dc, H, 9)
     want, keep = fk.compress_batched(x, mask, M, N, 0)
     dt = torch.bfloat16
@@ -112,14 +113,14 @@ def test_moment_workspace_is_enough_for_every_offset(pair, room):
     n = query if room == "asked" else (2 if pair else 1) * 64 * H * M * Dc * 4
     buf = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
     if pair:
-        c, kk, cv, _ = fa.fa_compress_kv(dx, dx, dm, dm, Dc, Dc, M, N, workspace=buf[:n])
+        c, kk, cv, _ = fa.fa_compress_kv(dx, dx, dm, dm, Dc, Dc, M, N, keep_offset=off, workspace=buf[:n])
     else:
-        c, kk = fa.fa_compress(dx, dm, Dc, M, N, workspace=buf[:n])
+        c, kk = fa.fa_compress(dx, dm, Dc, M, N, keep_offset=off, workspace=buf[:n])
         cv = c
     torch.cuda.synchronize()
     tol = 5e-5 if room == "asked" else 2e-3
     assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= tol and rel_err(cv.cpu().numpy(), want, np.sqrt(N)) <= tol
-    assert np.array_equal(kk[..., :D - Dc].float().cpu().numpy(), keep.astype(np.float32))
+    assert np.array_equal(kk[:, :, off:, :D - Dc].float().cpu().numpy(), keep.astype(np.float32))
     assert (buf[n:] == 0x5A).all()
 
 
@@ -301,3 +302,65 @@ def test_moment_projection_in_parts(B, H, pair):
             assert torch.equal(fa.keep_rows_from_tok8(a, off + N, D - Dc)[:, :, off:], fa.keep_rows_from_tok8(b, off + N, D - Dc)[:, :, off:])
     want, _ = fk.compress_segment(x[-1, -1].float().cpu().numpy(), mask[-1, -1].cpu().numpy(), M, N + 7, 3)
     assert rel_err(got[0][0][-1, -1].cpu().numpy(), want, np.sqrt(N)) <= 5e-5
+
+
+# Rows that are no dense block: every second row of a wider tensor whose heads and sequences stand apart, another mask per pair,
+# nothing kept on one side and more kept dims than one vector per thread on the other.
+@pytest.mark.parametrize("D,N,Dkc,Dvc", [(128, 3000, 128, 60), (128, 900, 90, 128), (64, 3000, 30, 64), (256, 1500, 256, 130)])
+def test_moments_of_strided_rows(D, N, Dkc, Dvc):
+    import paper_2506_11886_amd as fa
+    B, H, M, T = 2, 3, 40, 9000
+    print(f"[case] strided moments D{D} N{N} {Dkc}/{Dvc}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(26)
+    wide = torch.randn((H + 1, B, 2 * N + 3, D + 8), generator=g, device="cuda").to(torch.bfloat16)
+    k = wide.transpose(0, 1)[:, :H, 1:2 * N + 1:2, :D]
+    v = wide.transpose(0, 1)[:, 1:, 0:2 * N:2, :D]
+    assert not k.is_contiguous() and k.stride() == v.stride()
+    assert k.data_ptr() % 16 == 0 and v.data_ptr() % 16 == 0
+    km, vm = ((torch.rand((B, H, D), generator=g, device="cuda").argsort(-1) < n).to(torch.uint8) for n in (Dkc, Dvc))
+    ck, kk, cv, vk = fa.fa_compress_kv(k, v, km, vm, Dkc, Dvc, M, T, t0=777)
+    single, _ = fa.fa_compress(k, km, Dkc, M, T, 777)
+    torch.cuda.synchronize()
+    for x, mask, c, n in ((k, km, ck, Dkc), (v, vm, cv, Dvc), (k, km, single, Dkc)):
+        want, keep = fk.compress_batched(x.float().cpu().numpy(), mask.cpu().numpy(), M, T, 777)
+        assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= 5e-5
+        if n < D and x is k:
+            assert np.array_equal(kk[..., :D - n].float().cpu().numpy(), keep.astype(np.float32))
+        elif n < D:
+            assert np.array_equal(vk.float().cpu().numpy(), rows_to_tok8(keep.astype(np.float32)))
+
+
+# Infinities and NaN stay in their column; its states are infinite or NaN, all of them.
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_moments_keep_non_finite_values_in_their_column(bad):
+    import paper_2506_11886_amd as fa
+    N, D, Dc, M = 3000, 128, 100, 40
+    print(f"[case] non-finite {bad}", flush=True)
+    x, mask = _segment(D, N, Dc, 2, 31)
+    dx, dm = to_dev(x, dtype=torch.bfloat16), to_dev(mask)
+    clean, _ = fa.fa_compress(dx, dm, Dc, M, 9000, 5)
+    d = int(np.flatnonzero(mask[0, 1])[37])
+    dx[0, 1, 1234, d] = bad
+    c, _ = fa.fa_compress(dx, dm, Dc, M, 9000, 5)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(c[0, 1, :, 37]).any()
+    c[0, 1, :, 37] = clean[0, 1, :, 37]
+    assert torch.equal(c, clean)
+
+
+# The expansion takes one or two 16-harmonic tiles per workgroup: an odd number of them, the last one partly filled, an old state.
+@pytest.mark.parametrize("B,H,M", [(1, 2, 75), (4, 40, 75), (4, 40, 33), (4, 40, 300)])
+@pytest.mark.parametrize("D,Dc", [(128, 81), (64, 17), (256, 140)])
+def test_moment_expansion_tiles(B, H, M, D, Dc):
+    import paper_2506_11886_amd as fa
+    N, T = 700, 60000
+    print(f"[case] expansion tiles B{B} H{H} M{M} D{D} Dc{Dc}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(27)
+    x = torch.randn((B, H, N, D), generator=g, device="cuda").to(torch.bfloat16)
+    mask = (torch.rand((B, H, D), generator=g, device="cuda").argsort(-1) < Dc).to(torch.uint8)
+    prev = torch.randn((B, H, M, Dc), generator=g, device="cuda")
+    c, _ = fa.fa_compress(x, mask, Dc, M, T, 41, True, prev.clone(), keep_layout=fa.FA_KEEP_TOK8, keep_offset=1)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        want, _ = fk.compress_segment(x[b, h].float().cpu().numpy(), mask[b, h].cpu().numpy(), M, T, 41)
+        assert rel_err(c[b, h].cpu().numpy(), want + prev[b, h].double().cpu().numpy(), np.sqrt(N)) <= 5e-5

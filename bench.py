@@ -34,8 +34,6 @@ if ROOT not in sys.path:
 
 METRIC = "Fourier-KV decode context tokens/s/GPU + achieved HBM GB/s (% of peak)"
 HBM_PEAK_GBS = 8000.0
-MFMA_BF16_PEAK_TFLOPS = 2500.0
-FP32_MATRIX_PEAK_TFLOPS = 157.3
 LLC_BYTES = 256 << 20
 CSRC = os.path.join(ROOT, "paper_2506_11886_amd", "csrc")
 
@@ -121,7 +119,6 @@ def measure(cfg, steps, warmup, extras=False):
     Dku, Dvu = D - cfg.Dkc, D - cfg.Dvc
     dec_bytes = cfg.decode_bytes()
     cmp_bytes = cfg.compress_bytes(cfg.Dkc) + cfg.compress_bytes(cfg.Dvc)
-    cmp_flops = cfg.compress_flops(cfg.Dkc) + cfg.compress_flops(cfg.Dvc)
     n_sets = int(min(16, max(2, math.ceil(2.0 * LLC_BYTES / dec_bytes))))
     # what each kernel of the decode call has to move (the split-K records between them are overhead)
     bh = B * Hkv
@@ -179,9 +176,8 @@ def measure(cfg, steps, warmup, extras=False):
         decode(sets[i % n_sets], kd)
         compress(sets[i % n_sets], kc)
     kd = np.array(kd).reshape(reps, 3).mean(0) * 1e-3        # prepare, partial, finish [s]
-    kc = np.array(kc).reshape(reps, 2).mean(0) * 1e-3        # [projection of K and V, their reductions] [s]
+    kc = np.array(kc).reshape(reps, 2).mean(0) * 1e-3        # [pass over the rows of K and V, forming of the states] [s]
     t_kernels = float(kd.sum())
-    t_project = float(kc[0])
     traffic = measured_traffic(cfg.index)
 
     def hbm(bytes_, t):
@@ -214,19 +210,15 @@ def measure(cfg, steps, warmup, extras=False):
     roof_dec = {k: roof_dec[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic",
                                          "algorithmic_bytes", "kernels_ms", "dominant_kernel", "kernels")}
 
-    mm_peak = MFMA_BF16_PEAK_TFLOPS if cfg.dtype == "bf16" else FP32_MATRIX_PEAK_TFLOPS
-    tfl = cmp_flops / t_project / 1e12
-    hb = hbm(cmp_bytes, t_project)
-    hbm_bound = cmp_bytes / (HBM_PEAK_GBS * 1e9) >= cmp_flops / (mm_peak * 1e12)
-    roof_cmp = {"kernel": "projection (K and V in one launch; FLOPs of the M-row contraction, of which the moment form does fewer)",
-                "bound": "hbm" if hbm_bound else "mfma",
-                "achieved": hb["achieved"] if hbm_bound else round(tfl, 1),
-                "peak": HBM_PEAK_GBS if hbm_bound else mm_peak,
-                "unit": "GB/s" if hbm_bound else "TFLOP/s",
-                "frac": hb["frac"] if hbm_bound else round(tfl / mm_peak, 4),
-                "traffic": traffic.get("fa_moments", traffic.get("compress_project_fast_kv", traffic.get("compress_project"))),
-                "hbm_GBps": hb["achieved"], "hbm_frac": hb["frac"],
-                "mfma_tflops": round(tfl, 1), "mfma_frac": round(tfl / mm_peak, 4)}
+    # Compression: the bytes bind it (long bf16 segments go through block moments, which need a fraction of the M-row
+    # contraction's operations), over both of its kernels.
+    t_compress = float(kc.sum())
+    cmp_traffic = [kernel_traffic(n) for n in (("fa_moments", "fa_expand16") if "fa_moments" in traffic
+                                               else ("compress_project", "compress_reduce"))]
+    hb = hbm(cmp_bytes, t_compress)
+    roof_cmp = {"kernel": "fa_compress_kv = moments + expansion, or projection + chunk reduction (K and V together)",
+                "bound": "hbm", "achieved": hb["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hb["frac"],
+                "traffic": sum(v for v in cmp_traffic if v is not None) or None}
 
     res = {
         "workload": f"cfg{cfg.index} {cfg.name}: B={B} Hq={Hq} Hkv={Hkv} D={D} L={cfg.L} "
@@ -240,9 +232,9 @@ def measure(cfg, steps, warmup, extras=False):
                        "algorithmic_bytes": dec_bytes, "wall_GBps": round(dec_bytes / t_dec / 1e9, 1),
                        "wall_frac": round(dec_bytes / t_dec / 1e9 / HBM_PEAK_GBS, 4)},
             "compress": {"ms": round(t_cmp * 1e3, 5), "tokens_per_s": round(B * N / t_cmp, 1),
-                         "algorithmic_bytes": cmp_bytes, "flop": cmp_flops,
-                         "kernel_ms": {"project_kv": round(float(kc[0]) * 1e3, 5),
-                                       "reduce_kv": round(float(kc[1]) * 1e3, 5)},
+                         "algorithmic_bytes": cmp_bytes,
+                         "kernel_ms": {"rows_kv": round(float(kc[0]) * 1e3, 5),      # moments, or the projection
+                                       "states_kv": round(float(kc[1]) * 1e3, 5)},   # expansion, or the chunk reduction
                          "roofline": roof_cmp},
             "step": {"ms": round(t_step * 1e3, 5), "context_tokens_per_s": round(B * cfg.L / t_step, 1)},
         },
@@ -307,10 +299,9 @@ def measure(cfg, steps, warmup, extras=False):
             for i in range(2):
                 sel(i)
             t_sel = timed_loop(torch, sel, max(4, min(steps, 20)))
-            sel_flop = 2.0 * B * Hkv * N * M * D
-            res["phases"]["select"] = {"ms": round(t_sel * 1e3, 5), "flop": sel_flop,
-                                       "fp32_matrix_tflops": round(sel_flop / t_sel / 1e12, 1),
-                                       "fp32_matrix_frac": round(sel_flop / t_sel / 1e12 / FP32_MATRIX_PEAK_TFLOPS, 4)}
+            sel_bytes = B * Hkv * (N * D * e + 5 * D)
+            res["phases"]["select"] = {"ms": round(t_sel * 1e3, 5), "algorithmic_bytes": sel_bytes,
+                                       "GBps": round(sel_bytes / t_sel / 1e9, 1)}
             # Fourier against translated Legendre at the same number of states (the paper's basis comparison,
             # on the synthetic law): mean reconstruction error of the planted (smooth) dims and of the others
             Ml = min(M, 256)

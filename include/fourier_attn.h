@@ -109,9 +109,9 @@ enum { FA_KEEP_ROWS = 0, FA_KEEP_TOK8 = 1 };
  *               that holds the partial sums but neither all moments nor parts of
  *               32 MB is accepted and served by the direct projection.
  *
- * Precision (2-norm of the error of white rows over that of the states): fp32 inputs
- * 1e-6; bf16 segments of up to 512 tokens 2e-6; longer ones 3e-6 through moments, up to
- * 1.3e-3 by the direct projection (a basis of one bf16 term).  Which of the two runs is
+ * Precision (2-norm of the error of white rows over that of the states), bf16: segments of
+ * up to 512 tokens 2e-6; longer ones 3e-6 through moments, up to 1.3e-3 by the direct
+ * projection (a basis of one bf16 term).  Which of the two runs is
  * decided by the sizes, T, the workspace and what is kept; the moments' blocks also move
  * with keep_offset mod 8.  Equal calls give equal results.
  * An infinity or NaN in a compressed dim makes every state of its column infinite or NaN,

@@ -8,10 +8,10 @@
 //   mu[p, i] = sum_{j in block} T_p(x_j) X[j, i]                          (fa_moments: one pass over X)
 //   C[n, i]  = sum_blocks Rot(w_n c) * (2 - [p = 0]) i^p J_p(theta_n) mu  (fa_expand)
 // so a token costs 16 matrix rows instead of M, and the M-row contraction runs once per block.
-// Measured, direct projection -> moments: K and V of 8 heads x 129020 tokens, M = 512, 255 -> 137 us
-// (fa_moments moves 0.63 GB in 114 us = 5.5 TB/s); 8 x 31740 tokens, M = 256, 47.6 -> 44.2 us; a 2 K
-// piece at an offset that is no multiple of 8, 94.7 -> 27.4 us (K and V, four launches); fa_select_dims on
-// 8 x 31740 tokens 293 -> 37 us.
+// Measured, direct projection -> moments: K and V of 8 heads x 129020 tokens, M = 512, 252 -> 145 us
+// (fa_moments moves 0.62 GB in 112 us = 5.5 TB/s); 8 x 31740 tokens, M = 256, 47.1 -> 46.3 us; a 2 K
+// piece at an offset that is no multiple of 8, 94.6 -> 27.1 us (K and V, four launches); fa_select_dims on
+// 8 x 31740 tokens 294 -> 37 us.
 #pragma once
 
 #include "fa_common.hpp"

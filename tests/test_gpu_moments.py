@@ -364,3 +364,21 @@ def test_moment_expansion_tiles(B, H, M, D, Dc):
     for b, h in ((0, 0), (B - 1, H - 1)):
         want, _ = fk.compress_segment(x[b, h].float().cpu().numpy(), mask[b, h].cpu().numpy(), M, T, 41)
         assert rel_err(c[b, h].cpu().numpy(), want + prev[b, h].double().cpu().numpy(), np.sqrt(N)) <= 5e-5
+
+
+@pytest.mark.parametrize("D,B,H,N,M", [LONG[0], LONG[3]])
+def test_moment_pair_of_long_workgroups(D, B, H, N, M):
+    import paper_2506_11886_amd as fa
+    print(f"[case] long moment pair D{D} B{B} H{H} N{N} M{M}", flush=True)
+    k, v = _long_rows(B, H, N, D, M, 14), _long_rows(B, H, N, D, M, 15)
+    Dkc, Dvc = D * 3 // 4 - 1, D * 5 // 8
+    g = torch.Generator(device="cuda").manual_seed(16)
+    km, vm = ((torch.rand((B, H, D), generator=g, device="cuda").argsort(-1) < n).to(torch.uint8) for n in (Dkc, Dvc))
+    ck, kk, cv, vk = fa.fa_compress_kv(k, v, km, vm, Dkc, Dvc, M, N)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        for x, mask, c, n in ((k, km, ck, Dkc), (v, vm, cv, Dvc)):
+            want, keep = fk.compress_segment(x[b, h].float().cpu().numpy(), mask[b, h].cpu().numpy(), M, N, 0)
+            assert rel_err(c[b, h].cpu().numpy(), want, np.sqrt(N)) <= 5e-5
+            got = kk[b, h, :, :D - n] if x is k else fa.keep_rows_from_tok8(vk[b, h], N, D - n)
+            assert np.array_equal(got.float().cpu().numpy(), keep.astype(np.float32))

@@ -25,7 +25,9 @@
 // Launches on the caller's stream:
 //   1. decode_prepare : g (series order) for every query head, from C_k and q;
 //      q at the kept K dims, packed.
-//   2. decode_partial : one workgroup per (sequence, KV head, token chunk);
+//   2. decode_local (fa_local.hip) where the period is long against the states kept: the series by
+//      interpolation inside blocks of tokens, 16 or 32 matrix rows a token instead of M; else
+//      decode_partial : one workgroup per (sequence, KV head, token chunk);
 //      chunks of middle rows and chunks of full-width sink/window rows; emits
 //      a flash-decoding partial per query head: (max, sum, acc[kept dims],
 //      r[Mint]) for middle rows, (max, sum, acc[D]) for full-width rows.
@@ -36,261 +38,10 @@
 #include <mutex>
 #include <type_traits>
 
-#include "fa_common.hpp"
-#include "fa_mma.hpp"
+#include "fa_full.hpp"
+#include "fa_local.hpp"
 
 namespace fa {
-
-constexpr int kBlock = 256;
-constexpr int kWaves = 4;
-constexpr int kMaxG = FA_MAX_GROUP;
-constexpr int kTJ = 64;            // tokens per tile (rows of the E table)
-constexpr int kRB = kTJ / 16;      // 16-row blocks per tile
-constexpr int kXN = kTJ / 32;      // 32-token contraction steps per tile on the V side
-constexpr int kMaxKT = 4;          // tiles per wave step
-constexpr int kWChunk = 256;       // full-width rows per workgroup
-constexpr int kMaxDvTiles = 8;     // kept V dims handled per middle row: 8 * 16
-constexpr int kMaxPartials = 1024; // partial records per query head
-constexpr unsigned kMaxDynLds = 160 * 1024 - 4096;   // dynamic LDS a workgroup may ask for
-constexpr int kFinBlock = 256;     // threads of decode_finish
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2d __attribute__((ext_vector_type(2)));
-
-
-struct DecodeParams {
-  const void* q;
-  const float* ck;
-  const float* cv;
-  const uint8_t* kmask;
-  const uint8_t* vmask;
-  const void* k_keep;
-  const void* v_keep;
-  const void* k_full;
-  const void* v_full;
-  int64_t kk_stride, vk_stride, full_stride;
-  int B, Hq, Hkv, G, D, Dkc, Dvc, Dku, Dvu, M, T, t0, N, W;
-  int Tq, Gq;       // query tokens per sequence (1: plain decode) and query heads per KV head and token
-  int Gp, KT;       // group size padded to a power of two, tiles per wave step
-  int Mint;         // series length: 2 * (M/2) padded to a compiled size
-  int Sw, Sm;       // chunks of full-width rows / of middle rows (middle chunks come first)
-  int nprep, Swp;   // workgroups per head of the series-coefficient part when the full-width rows share its launch;
-                    // chunks of full-width rows inside the middle-row launch (0 when they ran with the coefficients)
-  int chunk_m;      // middle rows per chunk (multiple of the workgroup step)
-  int recm, recw;   // floats per partial record: 4 + 16 ceil(Dvu/16) + Mint (middle), 4 + D (full rows)
-  unsigned lds_tab; // bytes of the exchange / reduction region of a middle-row workgroup
-  float scale;
-  double ph_scale;  // 2^32 / T
-  float* gs;        // [B,Hq,Mint] series coefficients, K-side order
-  float* g0;        // [B,Hq]      constant-term coefficient
-  void* qkeep;      // [B,Hq,Dkq]  q at the kept K dims, zero padded to Dkq = 32 ceil(Dku/32)
-  float* part_m;    // [B,Hq,Sm,recm]
-  float* part_w;    // [B,Hq,Sw,recw]
-  float* out;       // [B,Hq,D]
-  const int32_t* seq_n;   // [B] middle rows of each sequence (<= N), or null: N for all
-  const int32_t* seq_w;   // [B] full-width rows of each sequence (<= W), or null: W for all
-  int Sw_rec;       // full-row records reserved per query head (= Sw of the longest sequence)
-  int wrb;          // 16-row blocks per wave of a full-width-row workgroup: 4 (256 rows per workgroup) or 1 (64)
-};
-
-// What a workgroup uses of one sequence: its row counts, the chunking that follows from them and
-// where its records go.  The three-launch kernels take the call's own values; the one-launch form
-// resolves them per sequence.
-struct SeqView {
-  int N, W, Sm, Sw, chunk_m;
-  float* part_m;
-  float* part_w;
-};
-// rows of sequence b: the call's counts, or the sequence's own (clamped into them) when the caller gave lists
-__device__ __forceinline__ int seq_middle_rows(const DecodeParams& p, int b) {
-  return p.seq_n ? min(max(p.seq_n[b], 0), p.N) : p.N;
-}
-__device__ __forceinline__ int seq_full_rows(const DecodeParams& p, int b) {
-  return p.seq_w ? min(max(p.seq_w[b], 0), p.W) : p.W;
-}
-__device__ __forceinline__ SeqView call_view(const DecodeParams& p, int b) {
-  return SeqView{seq_middle_rows(p, b), seq_full_rows(p, b), p.Sm, p.Sw, p.chunk_m, p.part_m, p.part_w};
-}
-
-// Middle-row chunks [chunk_lo, chunk_hi) of a (sequence, KV head) that lie past the sequence's rows:
-// records that say "nothing here" (maximum -inf, everything else zero), for every query head.
-__device__ __forceinline__ void write_empty_middle(const DecodeParams& p, size_t hq0, int chunk_lo, int chunk_hi,
-                                                   int nthreads) {
-  const int recm = p.recm, G = p.G;
-  const int per = (chunk_hi - chunk_lo) * recm;
-  for (int it = threadIdx.x; it < G * per; it += nthreads) {
-    const int h = it / per, x = it - h * per;
-    p.part_m[((hq0 + h) * p.Sm + chunk_lo) * recm + x] = (x % recm == 0) ? -INFINITY : 0.0f;
-  }
-}
-
-// LDS of a workgroup of the one-launch form, after the exchange region of the middle-row phase:
-// series coefficients [G][Mint + 32] | packed kept q [G][32] | constant-term coefficients | the
-// middle-row record [G][recm] | the full-row record [G][recw] | C_v of the pair [M][Dvc] (1 KB aligned)
-struct FusedLds {
-  unsigned gs, qk, g0, recm, recw, cv, total;
-};
-__host__ __device__ __forceinline__ FusedLds fused_lds(unsigned lds_tab, int G, int Mint, int recm, int recw, int M,
-                                                       int Dvc) {
-  FusedLds L;
-  L.gs = lds_tab;
-  L.qk = L.gs + G * (Mint + 32) * 4;
-  L.g0 = L.qk + G * 32 * 2;
-  L.recm = L.g0 + 64;
-  L.recw = L.recm + G * recm * 4;
-  L.cv = (L.recw + G * recw * 4 + 1023u) & ~1023u;
-  L.total = L.cv + ((static_cast<unsigned>(M) * Dvc * 4 + 1023u) & ~1023u);
-  return L;
-}
-
-// ---------------------------------------------------------------------------
-// small helpers
-// ---------------------------------------------------------------------------
-template <typename T> struct SeriesType;
-template <> struct SeriesType<bf16_t> { using type = f16_t; };   // E, g', p on the series side
-template <> struct SeriesType<float> { using type = float; };
-
-__device__ __forceinline__ void pack8(Frag<f16_t>& f, const float* v) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    f.v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[2 * e], v[2 * e + 1]}, f16x2));
-}
-__device__ __forceinline__ void pack8(Frag<bf16_t>& f, const float* v) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    f.v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[2 * e], v[2 * e + 1]}, bf16x2));
-}
-__device__ __forceinline__ void pack8(Frag<float>& f, const float* v) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f.v[e] = v[e];
-}
-
-__device__ __forceinline__ void unpack8(const Frag<bf16_t>& f, float* v) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[2 * e] = __uint_as_float(f.v[e] << 16);
-    v[2 * e + 1] = __uint_as_float(f.v[e] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ void unpack8(const Frag<float>& f, float* v) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = f.v[e];
-}
-// element e of a fragment, as stored
-__device__ __forceinline__ bf16_t frag_elem(const Frag<bf16_t>& f, int e) {
-  return bf16_t{static_cast<uint16_t>((f.v[e >> 1] >> (16 * (e & 1))) & 0xffffu)};
-}
-__device__ __forceinline__ float frag_elem(const Frag<float>& f, int e) { return f.v[e]; }
-__device__ __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x.bits); }
-__device__ __forceinline__ float to_f32(float x) { return x; }
-
-// keep the first `nvalid` (<= 8, may be <= 0) elements, zero the rest
-__device__ __forceinline__ void mask_tail(Frag<bf16_t>& f, int nvalid) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t lo = (2 * e < nvalid) ? 0x0000ffffu : 0u;
-    const uint32_t hi = (2 * e + 1 < nvalid) ? 0xffff0000u : 0u;
-    f.v[e] &= (lo | hi);
-  }
-}
-__device__ __forceinline__ void mask_tail(Frag<float>& f, int nvalid) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if (e >= nvalid) f.v[e] = 0.0f;
-}
-
-// cos / sin of a 32-bit fixed-point phase (2^32 = one turn)
-template <typename T>
-__device__ __forceinline__ void phase_cs(uint32_t ph, float* c, float* s) {
-  const float x = static_cast<float>(static_cast<int32_t>(ph)) * 2.3283064365386963e-10f;  // turns in [-0.5, 0.5)
-  if constexpr (sizeof(T) == 4) {
-    sincospif(2.0f * x, s, c);          // fp32 inputs: full-accuracy evaluation
-  } else {
-    *s = __builtin_amdgcn_sinf(x);      // hardware sin/cos take turns
-    *c = __builtin_amdgcn_cosf(x);
-  }
-}
-
-// fixed-point phase of position pos: frac(pos / T) * 2^32 (wraps for pos >= T)
-__device__ __forceinline__ uint32_t phase_of(int pos, double ph_scale) {
-  return static_cast<uint32_t>(static_cast<uint64_t>(static_cast<double>(pos) * ph_scale));
-}
-
-// value held by lane i of the caller's quad (4 consecutive lanes)
-__device__ __forceinline__ float quad_bcast(float v, int i) {
-  const int x = __float_as_int(v);
-  int r;
-  switch (i) {
-    case 0: r = __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true); break;
-    case 1: r = __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true); break;
-    case 2: r = __builtin_amdgcn_mov_dpp(x, 0xaa, 0xf, 0xf, true); break;
-    default: r = __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true); break;
-  }
-  return __int_as_float(r);
-}
-
-// rotation by N lanes within each row of 16 lanes (lane i receives lane (i + N) % 16 of its row)
-template <int N>
-__device__ __forceinline__ float row_ror(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
-}
-// sum / max over the lanes of a row whose indices differ by a multiple of `stride` (a power of two)
-__device__ __forceinline__ float row_stride_sum(float v, int stride) {
-  if (stride <= 8) v += row_ror<8>(v);
-  if (stride <= 4) v += row_ror<4>(v);
-  if (stride <= 2) v += row_ror<2>(v);
-  if (stride <= 1) v += row_ror<1>(v);
-  return v;
-}
-__device__ __forceinline__ float row_stride_max(float v, int stride) {
-  if (stride <= 8) v = fmaxf(v, row_ror<8>(v));
-  if (stride <= 4) v = fmaxf(v, row_ror<4>(v));
-  if (stride <= 2) v = fmaxf(v, row_ror<2>(v));
-  if (stride <= 1) v = fmaxf(v, row_ror<1>(v));
-  return v;
-}
-
-// value of lane `src` (compile-time) broadcast to the wave
-template <int SRC>
-__device__ __forceinline__ float lane_value(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), SRC));
-}
-// wave-wide sum / max, result in every lane: rotations inside the rows, then the four row totals
-__device__ __forceinline__ float wave_sum_fast(float v) {
-  v = row_stride_sum(v, 1);
-  return (lane_value<0>(v) + lane_value<16>(v)) + (lane_value<32>(v) + lane_value<48>(v));
-}
-__device__ __forceinline__ float wave_max_fast(float v) {
-  v = row_stride_max(v, 1);
-  return fmaxf(fmaxf(lane_value<0>(v), lane_value<16>(v)), fmaxf(lane_value<32>(v), lane_value<48>(v)));
-}
-
-// every wave reads the whole mask row (D <= 256) and keeps it as 4 ballot words
-__device__ __forceinline__ void mask_ballots(const uint8_t* mask, int D, int lane, uint64_t* bal) {
-  uint8_t b[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) b[j] = mask[min(lane + 64 * j, D - 1)];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) bal[j] = __ballot(b[j] != 0 && lane + 64 * j < D);
-}
-
-// rank of dimension d among the kept dims (>= 0) or -(1 + rank among the
-// compressed dims), from the ballot words of the mask
-__device__ __forceinline__ int dim_rank(const uint64_t* bal, int d) {
-  const int w = d >> 6;
-  const uint64_t bit = 1ull << (d & 63);
-  int nc = 0;
-  uint64_t hit = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {   // static indices only: the words stay in registers
-    const uint64_t below = (j < w) ? ~0ull : ((j == w) ? (bit - 1ull) : 0ull);
-    nc += __popcll(bal[j] & below);
-    hit |= bal[j] & ((j == w) ? bit : 0ull);
-  }
-  return hit ? -(1 + nc) : d - nc;
-}
 
 // ---------------------------------------------------------------------------
 // 1. g = diag(w) C_k q_c, written in series order: slot s <-> basis function s+1
@@ -406,25 +157,34 @@ __global__ __launch_bounds__(kBlock) void decode_prepare(DecodeParams p) {
 // compressed dims go through LDS once, each thread forms its share of the G dot products from
 // registers, and the TPR shares meet by lane rotation.  256 / TPR rows per workgroup: 64 when
 // the (sequence, head) pairs alone fill the chip, 16 when there are few of them.
-template <typename T, int TPR>
-__device__ __forceinline__ void prepare2_rows(const DecodeParams& p, const int bh, const int blk) {
-  constexpr int kRows = kBlock / TPR;
-  constexpr int kV4 = (FA_MAX_HEAD_DIM / 4 + TPR - 1) / TPR;
-  __shared__ __attribute__((aligned(16))) float qc[kMaxG * FA_MAX_HEAD_DIM];   // [G][Dkc] query at the compressed dims
+// VEC: floats a thread reads at once: 4, or 1 for compressed counts that are no multiple of 4 (rows
+// of C_k are then not aligned).
+template <int VEC> struct PrepVec { using type = f32x4; };
+template <> struct PrepVec<1> { using type = float; };
+__device__ __forceinline__ float prep_dot(const f32x4& a, const f32x4& b) {
+  return (a[0] * b[0] + a[1] * b[1]) + (a[2] * b[2] + a[3] * b[3]);
+}
+__device__ __forceinline__ float prep_dot(float a, float b) { return a * b; }
 
+// qc: LDS for the query at the compressed dims, [G][Dkc]
+template <typename T, int TPR, int VEC>
+__device__ __forceinline__ void prepare2_rows(const DecodeParams& p, float* qc, const int bh, const int blk) {
+  using V = typename PrepVec<VEC>::type;
+  constexpr int kRows = kBlock / TPR;
+  constexpr int kV4 = (FA_MAX_HEAD_DIM / VEC + TPR - 1) / TPR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int b = bh / p.Hkv, hkv = bh % p.Hkv;
   const int Dkc = p.Dkc, D = p.D, G = p.G;
   const int row = tid / TPR, seg = tid % TPR;
   const int m = blk * kRows + row;            // basis function of this thread's row (0 .. Mint)
-  const int c4n = Dkc / 4;
+  const int c4n = Dkc / VEC;
 
   // C_k row, the mask row and q of the group: all requested up front, clamped, never predicated
   const float* ck = p.ck + static_cast<size_t>(bh) * p.M * Dkc + static_cast<size_t>(min(m, p.M - 1)) * Dkc;
-  f32x4 cv4[kV4];
+  V cv4[kV4];
 #pragma unroll
   for (int i = 0; i < kV4; ++i)
-    if (i * TPR < c4n) cv4[i] = *reinterpret_cast<const f32x4*>(ck + 4 * min(seg + i * TPR, c4n - 1));
+    if (i * TPR < c4n) cv4[i] = *reinterpret_cast<const V*>(ck + VEC * min(seg + i * TPR, c4n - 1));
   uint64_t kbal[4];
   mask_ballots(p.kmask + static_cast<size_t>(bh) * D, D, lane, kbal);
   const size_t hq0 = static_cast<size_t>(b) * p.Hq + hkv * G;
@@ -465,8 +225,7 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, const int b
     for (int i = 0; i < kV4; ++i) {
       if (i * TPR < c4n) {
         const int c4 = seg + i * TPR;
-        const f32x4 qv = *reinterpret_cast<const f32x4*>(qh + 4 * min(c4, c4n - 1));
-        const float d4 = (cv4[i][0] * qv[0] + cv4[i][1] * qv[1]) + (cv4[i][2] * qv[2] + cv4[i][3] * qv[3]);
+        const float d4 = prep_dot(cv4[i], *reinterpret_cast<const V*>(qh + VEC * min(c4, c4n - 1)));
         acc += (c4 < c4n) ? d4 : 0.0f;
       }
     }
@@ -487,7 +246,8 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, const int b
 
 template <typename T, int TPR>
 __global__ __launch_bounds__(kBlock) void decode_prepare2(DecodeParams p) {
-  prepare2_rows<T, TPR>(p, blockIdx.y, blockIdx.x);
+  __shared__ __attribute__((aligned(16))) float qc[kMaxG * FA_MAX_HEAD_DIM];
+  prepare2_rows<T, TPR, 4>(p, qc, blockIdx.y, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1288,22 +1048,6 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
 // lane holds) instead of being transposed through LDS, which takes the barriers out of the
 // prologue.  The wave-wide maximum of the softmax uses the half- and row-swap lane permutes.
 
-constexpr float kSoftmaxSlack = 8.0f;   // how far a score may exceed its column's reference before the reference moves
-
-// max over the four 16-lane rows of a wave, per lane position, result in every lane
-__device__ __forceinline__ float cross_row_max(float v) {
-  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float cross_row_sum(float v) {
-  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 // ---------------------------------------------------------------------------
 // 2a'. full-width rows, specialised: bf16, head dim 128, at most four query columns
 // ---------------------------------------------------------------------------
@@ -1467,7 +1211,7 @@ template <typename T, int TPR>
 __global__ __launch_bounds__(kBlock) void decode_prepare_window(DecodeParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (static_cast<int>(blockIdx.x) < p.nprep) {
-    prepare2_rows<T, TPR>(p, blockIdx.y, blockIdx.x);
+    prepare2_rows<T, TPR, 4>(p, reinterpret_cast<float*>(smem), blockIdx.y, blockIdx.x);
   } else {
     const int s = blockIdx.x - p.nprep;
     if constexpr (sizeof(T) == 2) {
@@ -1481,6 +1225,16 @@ __global__ __launch_bounds__(kBlock) void decode_prepare_window(DecodeParams p) 
       partial_full_rows<T>(p, smem, s);
     }
   }
+}
+
+// The same with the full-width rows on the matrix cores (head dims of 64, 128 and 256; D = 0: any), in front of
+// decode_local.  Up to head dim 128 within 128 registers, so that four workgroups share a compute unit.
+template <int TPR, int VEC, int D>
+__global__ __launch_bounds__(kBlock, D == 64 || D == 128 ? 4 : 2) void decode_prepare_full(DecodeParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (static_cast<int>(blockIdx.x) < p.nprep) prepare2_rows<bf16_t, TPR, VEC>(p, reinterpret_cast<float*>(smem), blockIdx.y, blockIdx.x);
+  else if constexpr (D == 0) partial_full_rows<bf16_t>(p, smem, blockIdx.x - p.nprep);
+  else full_rows_mma<D>(p, smem, blockIdx.y, blockIdx.x - p.nprep);
 }
 
 // g = diag(w) C_k q[D^kc], the constant-term coefficient and q at the kept K dims, formed by the
@@ -3424,6 +3178,7 @@ struct DecodePlan {
   unsigned lds_tab, lds_total;
   unsigned lds_fused;    // dynamic LDS of a workgroup of the one-launch form
   size_t off_gs, off_g0, off_qk, off_pm, off_pw, total;
+  LocalPlan local;       // .use: the middle rows run as decode_local
 };
 
 static int round_up(int x, int a) { return (x + a - 1) / a * a; }
@@ -3470,6 +3225,18 @@ static bool fused_shape(int dtype, int Hq, int Hkv, int D, int Dkc, int Dvc, int
          Dvu > 0 && Dvu <= 32 && Dkc > 0 && (Dkc & 3) == 0 && (Dvc & 3) == 0;
 }
 constexpr int kFusedMinPairs = 192;   // (sequence, KV head) pairs from which the one-launch form is the default
+
+// the workspace of a plan
+static void place_workspace(DecodePlan& pl, int B, int Hq, int Dku) {
+  const size_t BHq = static_cast<size_t>(B) * Hq;
+  const size_t Dkq = (((Dku + 7) & ~7) + 31) / 32 * 32;
+  pl.off_gs = 0;
+  pl.off_g0 = align_up(BHq * pl.Mint * sizeof(float), 256);
+  pl.off_qk = pl.off_g0 + align_up(BHq * sizeof(float), 256);
+  pl.off_pm = pl.off_qk + align_up(BHq * Dkq * 4 + 16, 256);   // sized for fp32: the size query has no dtype
+  pl.off_pw = pl.off_pm + align_up(BHq * pl.Sm * pl.recm * sizeof(float) + 16, 256);
+  pl.total = pl.off_pw + align_up(BHq * pl.Sw * pl.recw * sizeof(float) + 16, 256);
+}
 
 static bool make_plan(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D, int Dkc, int Dvc, int M,
                       int N, int W, int num_splits, int fused_mode = 0) {   // fused_mode: 0 by shape, -1 never
@@ -3567,13 +3334,48 @@ static bool make_plan(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D, 
   const unsigned t = mid > wpath ? mid : wpath;
   pl.lds_total = (t + 255u) & ~255u;
   if (pl.lds_total > kMaxDynLds) return false;
-  const size_t BHq = static_cast<size_t>(B) * Hq;
-  pl.off_gs = 0;
-  pl.off_g0 = align_up(BHq * pl.Mint * sizeof(float), 256);
-  pl.off_qk = pl.off_g0 + align_up(BHq * sizeof(float), 256);
-  pl.off_pm = pl.off_qk + align_up(BHq * Dkq * 4 + 16, 256);   // sized for fp32: the size query has no dtype
-  pl.off_pw = pl.off_pm + align_up(BHq * pl.Sm * pl.recm * sizeof(float) + 16, 256);
-  pl.total = pl.off_pw + align_up(BHq * pl.Sw * pl.recw * sizeof(float) + 16, 256);
+  place_workspace(pl, B, Hq, Dku);
+  return true;
+}
+
+// The middle rows of a bf16 call through local Chebyshev polynomials (fa_local.hip), where the shape allows:
+// the plan `pl` of the same call changed to that form, or false.  The full-width rows then ride in the launch
+// of the series coefficients.
+static bool make_local(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D, int Dkc, int Dvc, int N, int W,
+                       int num_splits, LocalForm form) {
+  const int G = Hq / Hkv, Dku = D - Dkc, Dvu = D - Dvc;
+  const long pairs = static_cast<long>(B) * Hkv;
+  if (dtype != FA_BF16 || pl.fused || num_splits != 0 || Dkc == 0) return false;
+  pl.local = make_local_plan(B, Hkv, G, Dku, Dvu, pl.Mint, N, form);
+  // (blocks of 32 tokens cost short series as much as their own rows: 480 heads x 364 tokens, M = 119, 250 -> 272 us)
+  if (!pl.local.use || (pl.cw <= 2 && pl.local.U < 64)) return false;
+  // The other kernels' time: 5 us and, per compute unit, what a step of 16 score columns x 64 rows takes (256 rows at up to four
+  // heads): the bytes of the kept dims, or the issue of the series and, in the general kernel, of kept dims past its prefetch.  They
+  // take the full-width rows along inside their own waits (more than four heads at 1 us a head); here what those take beyond 0.8
+  // us adds to the launch in front.  Measured (estimated): 8 heads x 32 K, M = 256, 13.4 (13.1), 16 columns 44.7 (45.3), M =
+  // 1023 68.7 (69); 128 K, M = 512, 27.5 (27.8); 16 x 25741, M = 35, 13.6 (13.8); 80 heads x 3281, M = 292, 8 columns, 83 (78); general, M
+  // <= 128: 80 x 13125, 48 + 48 kept dims, 96 (114), 96 x 10937, 48 + 29, 78 (87), 32 x 3628, 56 + 32, 12 columns, 23 (31)
+  const double rounds = static_cast<double>(pairs) * ((N + kTJ * pl.KT - 1) / (kTJ * pl.KT)) / 256.0;
+  double each = pl.fast == 8 ? 1.45 : pl.fast == 4 ? (pl.cw == 1 ? 1.4 : 2.1) : pl.cw <= 2 ? 2.6 : pl.cw == 4 ? 9.0 : 16.4;
+  if (pl.fast == 0 && (Dku > 32 || Dvu > 32)) each = 1.25 * (each + 0.375 * pl.KT * ((Dku + 31) / 32 - 1) + (Dvu > 32 ? 1.3 : 0.0));
+  const double mem = kTJ * pl.KT * 2.0 * (Dku + Dvu) / 19.7e3, window = static_cast<double>(pairs) * W * D * 4 / 5.3e6;
+  if (each < mem) each = mem;
+  double other = 5.0 + (rounds < 1.0 ? 1.0 : rounds) * each;
+  if (G > 4 && W > 0 && other < 4.0 + G) other = 4.0 + G;
+  if (other <= pl.local.us + (window > 0.8 ? window - 0.8 : 0.0)) return false;
+  pl.Sm = pl.local.Sm;
+  pl.chunk_m = pl.local.chunk_m;
+  if (D == 64 || D == 128 || D == 256) {   // one step of 32 rows per wave as long as the workgroups are few
+    const int wgs = (W + 127) / 128;
+    pl.wrb = 1;
+    while ((wgs + pl.wrb - 1) / pl.wrb > kMaxPartials / 2 || pairs * ((wgs + pl.wrb - 1) / pl.wrb) > 1024 * pl.wrb) ++pl.wrb;
+    pl.Sw = (wgs + pl.wrb - 1) / pl.wrb;
+  } else {
+    pl.Sw = (W + kWChunk - 1) / kWChunk;
+  }
+  pl.Swp = 0;
+  if (pl.Sw + pl.Sm > kMaxPartials) return false;
+  place_workspace(pl, B, Hq, Dku);
   return true;
 }
 
@@ -3701,6 +3503,33 @@ static int launch_fused(const DecodeParams& p, const DecodePlan& pl, hipStream_t
   return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
 }
 
+template <int TPR, int VEC, int D>
+static int launch_prepare_full_one(const DecodeParams& p, unsigned lds_window, hipStream_t st, KernelTimers* tm) {
+  auto kern = decode_prepare_full<TPR, VEC, D>;
+  const unsigned q = static_cast<unsigned>(p.G) * p.Dkc * 4u, w = p.Sw == 0 ? 0u : D == 0 ? lds_window : kFullLds<D>, lds = q > w ? q : w;
+  if (lds > 48u * 1024u &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          static_cast<int>(lds)) != hipSuccess)
+    return FA_ERR_HIP;
+  FA_LAUNCH_TIMED(tm, 0, kern, dim3(p.nprep + p.Sw, p.B * p.Hkv), dim3(kBlock), lds, st, p);
+  return FA_OK;
+}
+static int launch_prepare_full(const DecodeParams& p, unsigned lds_window, bool wide, hipStream_t st, KernelTimers* tm) {
+  const bool v4 = (p.Dkc & 3) == 0;
+#define FA_PREPARE(D_)                                                                                       \
+  return v4 ? (wide ? launch_prepare_full_one<4, 4, D_>(p, lds_window, st, tm)                               \
+                    : launch_prepare_full_one<16, 4, D_>(p, lds_window, st, tm))                             \
+            : (wide ? launch_prepare_full_one<4, 1, D_>(p, lds_window, st, tm)                               \
+                    : launch_prepare_full_one<16, 1, D_>(p, lds_window, st, tm))
+  switch (p.D) {
+    case 64: FA_PREPARE(64);
+    case 128: FA_PREPARE(128);
+    case 256: FA_PREPARE(256);
+    default: FA_PREPARE(0);
+  }
+#undef FA_PREPARE
+}
+
 // tm (optional): per-kernel event pairs, for fa_decode_timed
 template <typename T>
 static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_t st, KernelTimers* tm) {
@@ -3709,16 +3538,20 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
     if (pl.fused) return launch_fused(p, pl, st, tm);
   }
   const hipError_t prior = hipPeekAtLastError();
-  if (p.Sm > 0 && p.Dkc > 0 && (p.Dkc & 3) == 0) {
+  if (p.Sm > 0 && p.Dkc > 0 && ((p.Dkc & 3) == 0 || pl.local.use)) {
     const bool wide = static_cast<long>(BH) * (p.Mint / 64 + 1) >= 256;
     const int nprep = wide ? p.Mint / 64 + 1 : p.Mint / 16 + 1;
-    if (p.Sw > 0 && p.Swp == 0) {   // the full-width rows ride along
+    if (pl.local.use) {   // the full-width rows, if any, ride along
       DecodeParams pp = p;
       pp.nprep = nprep;
-      const unsigned lds = pl.lds_window;
+      const int rc = launch_prepare_full(pp, pl.lds_window, wide, st, tm);
+      if (rc != FA_OK) return rc;
+    } else if (p.Sw > 0 && p.Swp == 0) {
+      DecodeParams pp = p;
+      pp.nprep = nprep;
+      const unsigned qlds = static_cast<unsigned>(p.G) * p.Dkc * 4u, lds = pl.lds_window > qlds ? pl.lds_window : qlds;
       auto kern = wide ? decode_prepare_window<T, 4> : decode_prepare_window<T, 16>;
-      // (the kernel also holds 16 KB of static LDS: the ceiling asked for is what this launch needs)
-      if (lds > 32u * 1024u &&
+      if (lds > 48u * 1024u &&
           hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                               static_cast<int>(lds)) != hipSuccess)
         return FA_ERR_HIP;
@@ -3739,6 +3572,11 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
   }
   int rc;
   if constexpr (sizeof(T) == 2) {
+    if (pl.local.use) {
+      rc = launch_local(p, pl.local, st, tm);
+      if (rc != FA_OK) return rc;
+      return launch_finish<T>(p, st, tm, prior);
+    }
     // the specialised kernel: groups of at most four query heads, 1 .. 32 kept dims on both sides
     if (pl.fast != 0) {
       rc = launch_partial_fast(p, pl, st, tm);
@@ -3789,7 +3627,14 @@ size_t fa_decode_workspace_bytes(int B, int Hq, int Hkv, int D, int Dkc, int Dvc
     return 0;
   fa::DecodePlan pl{};
   if (!fa::make_plan(pl, FA_BF16, B, Hq, Hkv, D, Dkc, Dvc, M, N, W, num_splits)) return 0;
-  return pl.total;
+  // the query knows no period: the most that any form of the middle rows takes
+  size_t total = pl.total;
+  for (const fa::LocalForm& form : fa::kLocalForms) {
+    fa::DecodePlan lp = pl;
+    if (fa::make_local(lp, FA_BF16, B, Hq, Hkv, D, Dkc, Dvc, N, W, num_splits, form) && lp.total > total)
+      total = lp.total;
+  }
+  return total;
 }
 
 static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, const float* ck,
@@ -3838,8 +3683,14 @@ static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, 
 
   DecodePlan pl{};
   if (!make_plan(pl, dtype, B, Hq, Hkv, D, Dkc, Dvc, M, N, W, num_splits)) return FA_ERR_UNSUPPORTED;
-  if (workspace_bytes < pl.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
-    return FA_ERR_WORKSPACE;
+  if (reinterpret_cast<uintptr_t>(workspace) & 255u) return FA_ERR_WORKSPACE;
+  {
+    DecodePlan lp = pl;   // (a buffer that only holds the other form's state is served by that)
+    if (make_local(lp, dtype, B, Hq, Hkv, D, Dkc, Dvc, N, W, num_splits, local_form(M, T)) &&
+        lp.total <= workspace_bytes)
+      pl = lp;
+  }
+  if (workspace_bytes < pl.total) return FA_ERR_WORKSPACE;
 
   DecodeParams p{};
   p.q = q; p.ck = ck; p.cv = cv; p.kmask = kmask; p.vmask = vmask;
@@ -3851,11 +3702,12 @@ static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, 
   p.M = M; p.T = T; p.t0 = t0; p.N = N; p.W = W;
   p.Gp = pl.Gp; p.KT = pl.KT; p.Mint = pl.Mint;
   p.Sw = pl.Sw; p.Sm = pl.Sm; p.chunk_m = pl.chunk_m; p.recm = pl.recm; p.recw = pl.recw;
-  p.Swp = pl.Swp; p.nprep = 0;
+  p.Swp = pl.Swp; p.nprep = 0; p.U = pl.local.U; p.ni = pl.local.ni;
   p.lds_tab = pl.lds_tab;
   p.seq_n = seq_n; p.seq_w = seq_w; p.Sw_rec = pl.Sw; p.wrb = pl.wrb;
   p.scale = scale > 0.0f ? scale : 1.0f / sqrtf(static_cast<float>(D));
   p.ph_scale = 4294967296.0 / static_cast<double>(T);
+  p.ph64 = (1ull << 63) / static_cast<uint64_t>(T);
   char* ws = static_cast<char*>(workspace);
   p.gs = reinterpret_cast<float*>(ws + pl.off_gs);
   p.g0 = reinterpret_cast<float*>(ws + pl.off_g0);

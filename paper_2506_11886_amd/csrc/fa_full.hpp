@@ -1,0 +1,176 @@
+// Full-width (sink and window) rows of fa_decode on the matrix cores, bf16, up to 16 query columns.
+#pragma once
+
+#include "fa_decode.hpp"
+
+namespace fa {
+
+// eight values as three bf16 terms, which hold all their bits
+__device__ __forceinline__ void split3(const float* v, Frag<bf16_t> (&t)[3]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f32x2 r = f32x2{v[2 * e], v[2 * e + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+      t[k].v[e] = w;
+      r[0] -= __builtin_bit_cast(float, w << 16);
+      r[1] -= __builtin_bit_cast(float, w & 0xffff0000u);
+    }
+  }
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// LDS of a workgroup: a 32-row tile of V per wave (later its sums), statistics
+template <int D> constexpr unsigned kFullPitch = 2 * D + 32;
+template <int D> constexpr unsigned kFullLds = kWaves * 32 * kFullPitch<D> + 2 * kWaves * 64;
+
+// Workgroup s of a (sequence, KV head): p.wrb steps of 32 rows per wave.  The waves walk their own rows and meet
+// once: S = K q (A = rows, a column per query), softmax in registers, O = P V with the rows of V turned by transposed
+// reads of a wave-private LDS tile, whose slot order (tokens 4 q4 + e, 16 + 4 q4 + e) is the one the scores come in.
+// P goes in as three bf16 terms, i.e. with all its bits.  The next step's rows are not requested ahead: four
+// workgroups of a compute unit cover for each other, and most calls have one step.
+template <int D>
+__device__ __forceinline__ void full_rows_mma(const DecodeParams& p, unsigned char* smem, const int bh, const int s) {
+  using T = bf16_t;
+  constexpr int KC = D / 32, NT = D / 16, PB = kFullPitch<D>, NV8 = D / 8;   // (NV8: 128-bit vectors of a row)
+  const int b = bh / p.Hkv, hkv = bh % p.Hkv;
+  const int G = p.G;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q4 = lane >> 4, r16 = lane & 15;
+  const size_t hq0 = static_cast<size_t>(b) * p.Hq + hkv * G;
+  const int Wb = seq_full_rows(p, b), jlast = max(Wb - 1, 0);
+  const int jw = (s * kWaves + wave) * 32 * p.wrb;
+  const int jvis = min(Wb - p.Tq + r16 / p.Gq, jlast);   // last row the query token of column r16 may see
+  unsigned char* tile = smem + wave * 32 * PB;
+  float* wm = reinterpret_cast<float*>(smem + kWaves * 32 * PB);   // [wave][16]
+  float* wl = wm + kWaves * 16;
+
+  const T* kbase = static_cast<const T*>(p.k_full) + bh * p.full_stride;
+  const T* vbase = static_cast<const T*>(p.v_full) + bh * p.full_stride;
+  Frag<T> qf[KC];
+#pragma unroll
+  for (int cc = 0; cc < KC; ++cc) qf[cc].load(static_cast<const T*>(p.q) + (hq0 + min(r16, G - 1)) * D + 32 * cc + 8 * q4);
+
+  float m = -INFINITY, l = 0.0f;
+  f32x4 oacc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) oacc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int st = 0; st < p.wrb; ++st) {
+    const int j0 = jw + 32 * st;
+    if (j0 >= Wb) break;
+    Frag<T> ka[2][KC], vv[NT];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      const T* row = kbase + static_cast<int64_t>(min(j0 + 16 * rb + r16, jlast)) * D + 8 * q4;
+#pragma unroll
+      for (int cc = 0; cc < KC; ++cc) ka[rb][cc].load(row + 32 * cc);
+    }
+    const int vr = lane / NV8, vc = lane % NV8;          // row (of every 64 / NV8) and vector
+#pragma unroll
+    for (int i = 0; i < NT; ++i) vv[i].load(vbase + static_cast<int64_t>(min(j0 + vr + i * (64 / NV8), jlast)) * D + 8 * vc);
+    if (st == 0) {
+#pragma unroll
+      for (int cc = 0; cc < KC; ++cc)
+        if (r16 >= G) qf[cc].zero();
+    }
+    f32x4 sacc[2];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      sacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int cc = 0; cc < KC; ++cc) mma_k32(sacc[rb], ka[rb][cc], qf[cc]);
+    }
+    // rows past the end are zero: 0 * garbage must stay 0
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int r = vr + i * (64 / NV8);
+      if (j0 + r >= Wb) vv[i].zero();
+      *reinterpret_cast<u32x4*>(tile + r * PB + 16 * vc) = vv[i].v;
+    }
+    float pv[8], mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int j = j0 + 16 * (e >> 2) + 4 * q4 + (e & 3);
+      pv[e] = j <= jvis ? sacc[e >> 2][e & 3] * p.scale : -INFINITY;
+      mx = fmaxf(mx, pv[e]);
+    }
+    const float mn = fmaxf(m, cross_row_max(mx));
+    const float al = m == -INFINITY ? 0.0f : __expf(m - mn);
+    m = mn;
+    const float m0 = m == -INFINITY ? 0.0f : m;
+    l *= al;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      pv[e] = __expf(pv[e] - m0);
+      l += pv[e];
+    }
+    if (st > 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float ar = __shfl(al, 4 * q4 + v, kWave);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) oacc[t][v] *= ar;
+      }
+    }
+    Frag<T> pt[3];
+    split3(pv, pt);
+    // the tile was written by this wave and is read by this wave: the LDS operations of a wave complete in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const unsigned char* trp = tile + (4 * q4 + (r16 >> 2)) * PB + (r16 & 3) * 8;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(trp + 32 * t));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(trp + 32 * t + 16 * PB));
+        const u32x2d l2 = __builtin_bit_cast(u32x2d, lo), h2 = __builtin_bit_cast(u32x2d, hi);
+        Frag<T> bv;
+        bv.v = u32x4{l2[0], l2[1], h2[0], h2[1]};
+#pragma unroll
+        for (int k = 2; k >= 0; --k) mma_k32(oacc[t], pt[k], bv);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  l = cross_row_sum(l);
+  if (q4 == 0) {
+    wm[wave * 16 + r16] = m;
+    wl[wave * 16 + r16] = l;
+  }
+  float* red = reinterpret_cast<float*>(tile);           // [16][D]
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[(4 * q4 + v) * D + 16 * t + r16] = oacc[t][v];
+  lds_barrier();
+  // record of a head: [max, sum, -, -, acc[D]]
+  for (int it = tid; it < G * (D / 4); it += kBlock) {
+    const int h = it / (D / 4), d4 = it - h * (D / 4);
+    float ms = wm[h];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, wm[w * 16 + h]);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    float ls = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float mw = wm[w * 16 + h], f = mw == -INFINITY ? 0.0f : __expf(mw - ms);
+      ls += f * wl[w * 16 + h];
+      v += f * *reinterpret_cast<const f32x4*>(smem + w * 32 * PB + (h * D + 4 * d4) * 4);
+    }
+    float* rec = p.part_w + ((hq0 + h) * p.Sw + s) * p.recw;
+    *reinterpret_cast<f32x4*>(rec + 4 + 4 * d4) = v;
+    if (d4 == 0) {
+      rec[0] = ms;
+      rec[1] = ls;
+    }
+  }
+}
+
+}  // namespace fa

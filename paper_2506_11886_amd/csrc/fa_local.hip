@@ -1,0 +1,716 @@
+// Middle rows of fa_decode, series by interpolation inside blocks.
+//
+// A kept harmonic cos|sin(w_n (j - c)) of a block of U tokens with centre c is a smooth function of x = (j - c) / (U / 2): its
+// polynomial through the P Chebyshev nodes +-x_k, x_k = cos((2 k + 1) pi / 2 P), k < P / 2, is off by at most 2e-6 as long as
+// theta_n = w_n U / 2 stays below 5.8 (P = 16) or 17.7 (P = 32).  With the even and odd cardinal functions
+//   e_k(x) = T_P(x) v_k 2 x_k / (x^2 - x_k^2),   o_k(x) = T_P(x) v_k 2 x / (x^2 - x_k^2),   v_k = (-1)^k sqrt(1 - x_k^2) / P
+// it is cos(theta x) = sum_k cos(theta x_k) e_k(x), sin(theta x) = sum_k sin(theta x_k) o_k(x).  So both series of Eq. 6
+//   K side: sum_m phi_m(j) g_m = sum_k e_k(x_j) a_2k + o_k(x_j) a_2k+1
+//   V side: r_m from mu_2k = sum_j p_j e_k(x_j), mu_2k+1 = sum_j p_j o_k(x_j)
+// cost a token P matrix rows instead of M, and the M-term sums run once per block: a from g in front of the
+// rows, r from the moments mu behind them.
+//
+// A workgroup is eight waves on one chunk of one (sequence, KV head); a wave's step is 32 rows at the same place
+// of GR blocks, and a column of the 16-column score tile is (block, query head).  The waves do not meet in the
+// loop: S = E a + K^mu q (A = rows), softmax in the wave's registers, and the probabilities are already
+// the A operand of P V^mu and P E (a lane holds the eight consecutive tokens its operand slots ask for).
+#include "fa_local.hpp"
+
+namespace fa {
+
+constexpr int kLocWaves = 8;
+constexpr int kLocThreads = 64 * kLocWaves;
+constexpr int kLocStep = 32;           // rows of a step and block
+constexpr int kLocPass = 4;            // column tiles whose partial coefficients meet at once
+// waves per SIMD that the variant is compiled for: four (128 registers, two workgroups per compute unit) or two
+constexpr int local_waves(int KC, int GR, int NS) { return KC == 1 && NS == 1 && GR <= 2 ? 4 : 2; }
+constexpr double kLocTheta16 = 5.8, kLocTheta32 = 17.7;   // largest theta of P = 16 and of P = 32 nodes
+
+// LDS: cos|sin(theta_n x_k) | coefficients, later moments, per tile | wave statistics | moment shares per (tile, sharer) and
+// their references, in front of the rows the partial coefficients | cardinal functions, behind the rows the waves' kept-dim sums
+struct LocalLds {
+  unsigned a, st, slot, bm, tab, total;
+};
+__host__ __device__ __forceinline__ LocalLds local_lds(int P, int Mint, int U, int nt, int ni, int Gp, int DVT) {
+  LocalLds L;
+  const unsigned kb = P == 16 ? 1024 : 2048;
+  const unsigned sb = U / kLocStep, slots = nt * (sb < kLocWaves ? sb : kLocWaves);
+  L.a = Mint / 2 * P * 4;
+  L.st = L.a + nt * kb;
+  L.slot = L.st + 2 * kLocWaves * 64;
+  const unsigned part = kLocWaves * (nt < kLocPass ? nt : kLocPass) * kb;
+  L.bm = L.slot + (slots * kb > part ? slots * kb : part);
+  L.tab = L.bm + slots * 64;
+  const unsigned t = sb * 4 * kb, o = kLocWaves * Gp * DVT * 64;
+  L.total = L.tab + (t > o ? t : o);
+  return L;
+}
+
+__device__ __forceinline__ void split2(const float* v, Frag<bf16_t>& hi, Frag<bf16_t>& lo) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[2 * e], v[2 * e + 1]}, bf16x2));
+    hi.v[e] = w;
+    const float r0 = v[2 * e] - __builtin_bit_cast(float, w << 16);
+    const float r1 = v[2 * e + 1] - __builtin_bit_cast(float, w & 0xffff0000u);
+    lo.v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
+  }
+}
+__device__ __forceinline__ void split2(const f32x4& v, u32x2d& hi, u32x2d& lo) {
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[2 * e], v[2 * e + 1]}, bf16x2));
+    hi[e] = w;
+    const float r0 = v[2 * e] - __builtin_bit_cast(float, w << 16);
+    const float r1 = v[2 * e + 1] - __builtin_bit_cast(float, w & 0xffff0000u);
+    lo[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
+  }
+}
+
+// nodes x_k and weights v_k of the interpolation, k < P / 2
+template <int P> struct Nodes;
+template <> struct Nodes<16> {
+  static constexpr double x[8] = {
+    0.995184726672196886, 0.956940335732208865, 0.88192126434835503, 0.773010453362736961,
+    0.634393284163645498, 0.471396736825997649, 0.290284677254462368, 0.098017140329560602};
+  static constexpr double s[8] = {   // sin((2 k + 1) pi / 32)
+    0.098017140329560602, 0.290284677254462368, 0.471396736825997649, 0.634393284163645498,
+    0.773010453362736961, 0.88192126434835503, 0.956940335732208865, 0.995184726672196886};
+  static constexpr double v(int k) { return (k & 1 ? -1.0 : 1.0) * s[k] / 16.0; }
+};
+template <> struct Nodes<32> {
+  static constexpr double x[16] = {
+    0.998795456205172393, 0.989176509964780973, 0.970031253194543993, 0.941544065183020778,
+    0.903989293123443332, 0.85772861000027207, 0.80320753148064491, 0.740951125354959091,
+    0.671558954847018401, 0.595699304492433343, 0.514102744193221727, 0.427555093430282094,
+    0.336889853392220051, 0.24298017990326389, 0.146730474455361752, 0.0490676743274180143};
+  static constexpr double s[16] = {   // sin((2 k + 1) pi / 64)
+    0.0490676743274180143, 0.146730474455361752, 0.24298017990326389, 0.336889853392220051,
+    0.427555093430282094, 0.514102744193221727, 0.595699304492433343, 0.671558954847018401,
+    0.740951125354959091, 0.80320753148064491, 0.85772861000027207, 0.903989293123443332,
+    0.941544065183020778, 0.970031253194543993, 0.989176509964780973, 0.998795456205172393};
+  static constexpr double v(int k) { return (k & 1 ? -1.0 : 1.0) * s[k] / 32.0; }
+};
+
+// P: nodes; KC: 32-dim steps of the kept K dims; DVT: 16-dim tiles of the kept V dims; GR: row groups; NS: 16-harmonic slices
+// of a wave
+template <int P, int KC, int DVT, int GR, int NS>
+__global__ __launch_bounds__(kLocThreads, local_waves(KC, GR, NS)) void decode_local(DecodeParams p) {
+  using T = bf16_t;
+  constexpr int PT = P / 16;                                  // 16-polynomial tiles
+  constexpr int Gp = 16 / GR;                                 // columns per row group
+  constexpr int kItemRegs = GR * (2 * KC + DVT) * 4;
+  constexpr int kInFlight = local_waves(KC, GR, NS) == 4 ? 32 : 64;   // registers of rows in flight
+  constexpr int NB = kInFlight / kItemRegs < 1 ? 1 : kInFlight / kItemRegs > 4 ? 4 : kInFlight / kItemRegs;   // steps
+  constexpr unsigned KB = 1024 * PT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // (workgroups go round the XCDs in order: the chunks of a pair are apart, so that those past the end of short
+  // sequences do not all fall on the same ones)
+  const int sm_idx = blockIdx.y, bh = blockIdx.x, b = bh / p.Hkv, hkv = bh % p.Hkv;
+  const int G = p.G, Mint = p.Mint, U = p.U, ni = p.ni;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q4 = lane >> 4, r16 = lane & 15;
+  const size_t hq0 = static_cast<size_t>(b) * p.Hq + hkv * G;
+  const int Nb = seq_middle_rows(p, b);
+  const int c0 = sm_idx * p.chunk_m, c1 = min(Nb, c0 + p.chunk_m);
+  if (c0 >= Nb) {
+    write_empty_middle(p, hq0, sm_idx, sm_idx + 1, kLocThreads);
+    return;
+  }
+  const int lsb = 31 - __clz(U / kLocStep), sb = 1 << lsb;     // steps per block (a power of two)
+  const int nt = (kLocWaves * ni) >> lsb;                      // tiles: GR blocks each
+  const int nc = min(sb, kLocWaves);                           // waves that share a tile
+  const int Nm1 = Nb - 1;
+  const bool ragged = c0 + p.chunk_m > Nb;                     // some rows of the chunk do not exist
+  const int kpitch = (p.Dku + 7) & ~7, kchunks = (kpitch + 31) / 32, Dkq = kchunks * 32;
+  const T* kk = static_cast<const T*>(p.k_keep) + bh * p.kk_stride;
+  const T* vk = static_cast<const T*>(p.v_keep) + bh * p.vk_stride;
+  const LocalLds L = local_lds(P, Mint, U, nt, ni, Gp, DVT);
+  unsigned char* a_s = smem + L.a;
+  float* wm_s = reinterpret_cast<float*>(smem + L.st);         // [wave][16] references of the heads
+  float* wl_s = wm_s + kLocWaves * 16;                         // [wave][16] sums
+  float* bm_s = reinterpret_cast<float*>(smem + L.bm);         // [slot][16] references of the columns
+  unsigned char* tab = smem + L.tab;
+  float* red_o = reinterpret_cast<float*>(smem + L.tab);       // behind the rows: [wave][Gp][16 DVT]
+  // [harmonic][cosines head | remainder | sines head | remainder] x P / 2, 128-bit units of a row exchanged so that 16
+  // rows meet the banks evenly
+  auto jt = [&](int n, int unit) {
+    return reinterpret_cast<u32x4*>(smem) + n * (P / 4) + (unit ^ (P == 32 ? n & 7 : (n >> 1) & 3));
+  };
+
+  // ---- (0) everything that comes from global memory is requested first, never predicated ---------
+  const int col_b = r16 / Gp, col_h = r16 % Gp;              // a column: (block of the tile, head)
+  const int ncs = Mint / 32;                                 // 16-harmonic slices; wave w owns w, w + 8, ...
+  f32x4 gv[NS][2];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const float* g = p.gs + (hq0 + min(col_h, G - 1)) * Mint + 32 * min((ncs < kLocWaves ? wave & 3 : wave) + 8 * i, ncs - 1) + 8 * q4;
+    gv[i][0] = *reinterpret_cast<const f32x4*>(g);
+    gv[i][1] = *reinterpret_cast<const f32x4*>(g + 4);
+  }
+  Frag<T> qf[KC];                                            // q of the column's head at the kept K dims
+#pragma unroll
+  for (int cc = 0; cc < KC; ++cc)
+    qf[cc].load(static_cast<const T*>(p.qkeep) + (hq0 + min(col_h, G - 1)) * Dkq + min(cc, kchunks - 1) * 32 + 8 * q4);
+  struct Item {
+    Frag<T> k[GR][2][KC], v[GR][DVT];
+  };
+  // first row of group g of step i of this wave (item wave + 8 i: place item % sb of the blocks of tile item / sb)
+  auto row0 = [&](int i, int g) {
+    const int it = wave + kLocWaves * i;
+    return c0 + ((it >> lsb) * GR + g) * U + (it & (sb - 1)) * kLocStep;
+  };
+  auto load_k = [&](Item& x, int i) {
+#pragma unroll
+    for (int g = 0; g < GR; ++g)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const uint32_t j = min(row0(i, g) + 8 * (r16 >> 2) + 4 * rb + (r16 & 3), Nm1);
+#pragma unroll
+        for (int cc = 0; cc < KC; ++cc)
+          x.k[g][rb][cc].load(kk + (j * static_cast<uint32_t>(kpitch) + static_cast<uint32_t>(min(cc * 32 + 8 * q4, kpitch - 8))));
+      }
+  };
+  auto load_v = [&](Item& x, int i) {
+#pragma unroll
+    for (int g = 0; g < GR; ++g) {
+      const uint32_t g8 = static_cast<uint32_t>(min(row0(i, g) + 8 * q4, Nm1)) >> 3;
+#pragma unroll
+      for (int dt = 0; dt < DVT; ++dt)
+        x.v[g][dt].load(vk + (g8 * static_cast<uint32_t>(p.Dvu) + static_cast<uint32_t>(min(16 * dt + r16, p.Dvu - 1))) * 8u);
+    }
+  };
+  // (a wave that asks for more than the memory pipeline holds stalls at the request: the rest behind tables and expansion)
+  Item buf[NB];
+  load_k(buf[0], 0);
+
+  // ---- (1) tables: the harmonics at the nodes, the cardinal functions at the tokens of a block --------------
+  const int n_max = p.M / 2;
+  const float hu = 0.5f * static_cast<float>(U) / static_cast<float>(p.T);   // turns of order 1 over half a block
+  for (int n = tid; n < Mint / 2; n += kLocThreads) {
+    const float t1 = n < n_max ? hu * static_cast<float>(n + 1) : 0.0f;
+#pragma unroll
+    for (int h = 0; h < P / 16; ++h) {
+      float c[8], s[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = t1 * static_cast<float>(Nodes<P>::x[8 * h + e]);
+        c[e] = n < n_max ? __builtin_amdgcn_cosf(x) : 0.0f;
+        s[e] = __builtin_amdgcn_sinf(x);
+      }
+      Frag<bf16_t> hi, lo;
+      split2(c, hi, lo);
+      *jt(n, h) = hi.v;
+      *jt(n, PT + h) = lo.v;
+      split2(s, hi, lo);
+      *jt(n, 2 * PT + h) = hi.v;
+      *jt(n, 3 * PT + h) = lo.v;
+    }
+  }
+  // A place of a block takes 4 KB (P = 32: 8); K side first: [row block][head | remainder][eight functions][row] x 8, then
+  // the V side: [16 functions][head | remainder][eight tokens][function] x 8.  x^2 - x_k^2 cancels: 64 bits
+  for (int it = kLocThreads - 1 - tid; it < U * (P / 8); it += kLocThreads) {
+    const int u = it & (U - 1), e8 = it / U;
+    const double x = static_cast<double>(2 * u + 1 - U) / static_cast<double>(U);
+    const int t = u & 31, rb = (t >> 2) & 1, row = 4 * (t >> 3) + (t & 3);
+    unsigned char* tk = tab + (u >> 5) * (4 * KB) + rb * KB + e8 * 256 + row * 16;
+    unsigned char* tv = tab + (u >> 5) * (4 * KB) + 2 * KB + (e8 >> 1) * 2048 + (t >> 3) * 256 + (e8 & 1) * 128 + (t & 7) * 2;
+    double tp = x;                                            // T_1 -> T_P by doubling
+#pragma unroll
+    for (int k = 1; k < P; k *= 2) tp = 2.0 * tp * tp - 1.0;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double xk = Nodes<P>::x[e];
+      float w = static_cast<float>(2.0 * Nodes<P>::v(e));
+#pragma unroll
+      for (int h = 1; h < P / 8; ++h) {
+        xk = e8 == h ? Nodes<P>::x[4 * h + e] : xk;
+        w = e8 == h ? static_cast<float>(2.0 * Nodes<P>::v(4 * h + e)) : w;
+      }
+      const float r = static_cast<float>(tp) * w * __builtin_amdgcn_rcpf(static_cast<float>(x * x - xk * xk));
+      v[2 * e] = r * static_cast<float>(xk);
+      v[2 * e + 1] = r * static_cast<float>(x);
+    }
+    Frag<bf16_t> hi, lo;
+    split2(v, hi, lo);
+    *reinterpret_cast<u32x4*>(tk) = hi.v;
+    *reinterpret_cast<u32x4*>(tk + KB / 2) = lo.v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      *reinterpret_cast<uint16_t*>(tv + e * 16) = static_cast<uint16_t>(hi.v[e >> 1] >> (16 * (e & 1)));
+      *reinterpret_cast<uint16_t*>(tv + 1024 + e * 16) = static_cast<uint16_t>(lo.v[e >> 1] >> (16 * (e & 1)));
+    }
+  }
+
+  // ---- (2) a of every block and head: the series at the nodes, g turned to the block's centre ------------------------
+  // phase of the centre of block `bi` of this workgroup, 2^-32 turns, rounded to nearest (p.ph64: 2^-64 turns of half a token)
+  auto centre = [&](int bi) {
+    const uint32_t c2 = 2u * static_cast<uint32_t>(p.t0 + c0 + bi * U) + static_cast<uint32_t>(U - 1);
+    return static_cast<uint32_t>((p.ph64 * c2 + 0x80000000ull) >> 32);
+  };
+  // cos / sin of n0 + 0 .. 3 times a phase (the four lanes of a quad share the block)
+  auto phases = [&](uint32_t n0, uint32_t ph, float (&c)[4], float (&s)[4]) {
+    float cs, sn;
+    phase_cs<T>((n0 + (lane & 3)) * ph, &cs, &sn);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      c[j] = quad_bcast(cs, j);
+      s[j] = quad_bcast(sn, j);
+    }
+  };
+  {
+    f32x4* part = reinterpret_cast<f32x4*>(smem + L.slot);     // [wave][tile][PT][64]
+    const int nact = min(kLocWaves, ncs);                      // 4 or 8
+    for (int t0 = 0; t0 < nt; t0 += kLocPass) {
+      const int np = min(kLocPass, nt - t0);
+      f32x4 acc[kLocPass][PT];
+      uint32_t ph[kLocPass];
+#pragma unroll
+      for (int tt = 0; tt < kLocPass; ++tt) {
+        ph[tt] = centre((t0 + tt) * GR + col_b);
+#pragma unroll
+        for (int h = 0; h < PT; ++h) acc[tt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const int c = (wave & (nact - 1)) + kLocWaves * i;
+        if (c < ncs) {
+          // A operand: row = node and parity, slots 2 j (cosine: even rows) and 2 j + 1 (sine: odd rows) of harmonic 4 q4 + j
+          Frag<f16_t> jh[PT], jl[PT];
+#pragma unroll
+          for (int h = 0; h < PT; ++h) {
+            float d = hu * __builtin_amdgcn_cosf(static_cast<float>(2 * (8 * h + (r16 >> 1)) + 1) * (0.25f / P));
+            asm volatile("" : "+v"(d));   // formed here on every pass: kept for all slices it would take 64 registers
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float x = d * static_cast<float>(16 * c + 4 * q4 + j + 1);
+              const float v = __builtin_amdgcn_sinf(x + ((r16 & 1) ? 0.0f : 0.25f));
+              const _Float16 hi = static_cast<_Float16>(v);
+              const _Float16 lo = static_cast<_Float16>(v - static_cast<float>(hi));
+              jh[h].v[j] = static_cast<uint32_t>(__builtin_bit_cast(uint16_t, hi)) << (16 * (r16 & 1));
+              jl[h].v[j] = static_cast<uint32_t>(__builtin_bit_cast(uint16_t, lo)) << (16 * (r16 & 1));
+            }
+          }
+#pragma unroll
+          for (int tt = 0; tt < kLocPass; ++tt) {
+            if (tt < np && (nact == kLocWaves || (tt & 1) == wave / nact)) {   // (four slices: each is shared by two waves)
+              float cs[4], sn[4], gp[8];
+              phases(16 * c + 4 * q4 + 1, ph[tt], cs, sn);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                const float gc = gv[i][j >> 1][2 * (j & 1)], gsn = gv[i][j >> 1][2 * (j & 1) + 1];
+                gp[2 * j] = gc * cs[j] + gsn * sn[j];
+                gp[2 * j + 1] = gsn * cs[j] - gc * sn[j];
+              }
+              Frag<f16_t> bg, bl;
+              pack8(bg, gp);
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                gp[e] -= static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(bg.v[e >> 1] >> (16 * (e & 1)))));
+              pack8(bl, gp);
+#pragma unroll
+              for (int h = 0; h < PT; ++h) {
+                mma_k32(acc[tt][h], jl[h], bg);
+                mma_k32(acc[tt][h], jh[h], bl);
+                mma_k32(acc[tt][h], jh[h], bg);
+              }
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int tt = 0; tt < kLocPass; ++tt)
+        if (tt < np && (nact == kLocWaves || (tt & 1) == wave / nact))
+#pragma unroll
+            for (int h = 0; h < PT; ++h) part[(((wave & (nact - 1)) * np + tt) * PT + h) * 64 + lane] = acc[tt][h];
+      if (t0 == 0) {
+        load_v(buf[0], 0);
+#pragma unroll
+        for (int i = 1; i < NB; ++i) {
+          load_k(buf[i], i);
+          load_v(buf[i], i);
+        }
+      }
+      lds_barrier();
+      for (int it = tid; it < np * PT * 256; it += kLocThreads) {   // the harmonics meet: lane it / 4 of a wave, its element it % 4
+        const float* x = reinterpret_cast<const float*>(part) + it;
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kLocWaves; ++w) v += w < nact ? x[min(w, nact - 1) * np * PT * 256] : 0.0f;
+        const int e = it & 3, ln = (it >> 2) & 63, th = it >> 8, h = th % PT, tile = t0 + th / PT;
+        const int lq = ln >> 4, lc = ln & 15, lh = lc % Gp;       // function 16 h + 4 lq + e of column lc
+        if ((e & 1) == 0) v += p.g0[hq0 + min(lh, G - 1)];         // a constant is 1 at every node
+        if (lh >= G) v = 0.0f;
+        const __bf16 hi = static_cast<__bf16>(v), lo = static_cast<__bf16>(v - static_cast<float>(hi));
+        unsigned char* o = a_s + tile * KB + (2 * h + (lq >> 1)) * 256 + lc * 16 + (lq & 1) * 8 + 2 * e;
+        *reinterpret_cast<__bf16*>(o) = hi;
+        *reinterpret_cast<__bf16*>(o + KB / 2) = lo;
+      }
+      lds_barrier();
+    }
+  }
+
+  // ---- (3) the rows ------------------------------------------------------------------------------
+#pragma unroll
+  for (int cc = 0; cc < KC; ++cc)
+    if (col_h >= G || cc >= kchunks) qf[cc].zero();
+  float mref = -INFINITY, lsum = 0.0f;                 // of column r16; the sum is a per-lane share
+  f32x4 oacc[DVT], macc[PT];
+#pragma unroll
+  for (int t = 0; t < DVT; ++t) oacc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < PT; ++t) macc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](Item& x, int i, auto more) {
+    const int item = wave + kLocWaves * i, tile = item >> lsb, place = item & (sb - 1);
+    const unsigned char* th = tab + place * (4 * KB);
+    const int rows = c0 + tile * GR * U + place * kLocStep;      // of group 0
+    if (rows < c1) {
+      f32x4 sacc[2];
+      {
+        Frag<T> ah, al;                                          // (P = 16: head and remainder in one operand)
+        ah.v = *reinterpret_cast<const u32x4*>(a_s + tile * KB + lane * 16);
+        if constexpr (P == 32) al.v = *reinterpret_cast<const u32x4*>(a_s + tile * KB + 1024 + lane * 16);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const unsigned char* tr = th + rb * KB + (P == 32 ? lane * 16 : (q4 & 1) * 256 + r16 * 16);
+          Frag<T> ta, tb;
+          ta.v = *reinterpret_cast<const u32x4*>(tr);
+          tb.v = *reinterpret_cast<const u32x4*>(tr + KB / 2);
+          sacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+          mma_k32(sacc[rb], tb, ah);
+          if constexpr (P == 32) mma_k32(sacc[rb], ta, al);
+          mma_k32(sacc[rb], ta, ah);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int cc = 0; cc < KC; ++cc) {
+          Frag<T> bq = qf[cc];
+          if (GR > 1 && col_b != g) bq.zero();
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) mma_k32(sacc[rb], x.k[g][rb][cc], bq);
+        }
+      if constexpr (decltype(more)::value) load_k(x, i + NB);
+      float pv[8], mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pv[e] = sacc[e >> 2][e & 3] * p.scale;
+      if (ragged) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (rows + col_b * U + 8 * q4 + e >= c1) pv[e] = -INFINITY;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, pv[e]);
+      if (__any(mx > mref + kSoftmaxSlack)) {   // (the first step: every column without a reference)
+        const float mt = cross_row_max(mx);
+        const float mn = fmaxf(mref, mt);
+        const float al = (mref == -INFINITY) ? 0.0f : __expf(mref - mn);
+        mref = mn;
+        lsum *= al;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float ar = __shfl(al, 4 * q4 + v, kWave);
+#pragma unroll
+          for (int t = 0; t < PT; ++t) macc[t][v] *= ar;
+#pragma unroll
+          for (int t = 0; t < DVT; ++t) oacc[t][v] *= ar;
+        }
+      }
+      const float m0 = mref == -INFINITY ? 0.0f : mref;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        pv[e] = __expf(pv[e] - m0);
+        lsum += pv[e];
+      }
+      Frag<T> ph, pl;
+      split2(pv, ph, pl);
+#pragma unroll
+      for (int h = 0; h < PT; ++h) {
+        Frag<T> ta, tb;
+        ta.v = *reinterpret_cast<const u32x4*>(th + 2 * KB + h * 2048 + lane * 16);
+        tb.v = *reinterpret_cast<const u32x4*>(th + 2 * KB + h * 2048 + 1024 + lane * 16);
+        mma_k32(macc[h], pl, ta);
+        mma_k32(macc[h], ph, tb);
+        mma_k32(macc[h], ph, ta);
+      }
+      if (ragged) {   // rows past the end have probability 0, but 0 * garbage must stay 0
+#pragma unroll
+        for (int g = 0; g < GR; ++g)
+#pragma unroll
+          for (int dt = 0; dt < DVT; ++dt) mask_tail(x.v[g][dt], c1 - (rows + g * U + 8 * q4));
+      }
+#pragma unroll
+      for (int g = 0; g < GR; ++g) {
+        Frag<T> gh = ph, gl = pl;
+        if (GR > 1 && col_b != g) {
+          gh.zero();
+          gl.zero();
+        }
+#pragma unroll
+        for (int dt = 0; dt < DVT; ++dt) {
+          mma_k32(oacc[dt], gl, x.v[g][dt]);
+          mma_k32(oacc[dt], gh, x.v[g][dt]);
+        }
+      }
+      if constexpr (decltype(more)::value) load_v(x, i + NB);
+    } else if constexpr (decltype(more)::value) {
+      load_k(x, i + NB);
+      load_v(x, i + NB);
+    }
+    // the wave's last place of this tile: its share of the moments, and the columns' references
+    if (sb <= kLocWaves || ((i + 1) & ((sb >> 3) - 1)) == 0) {
+      const int slot = tile * nc + (item & (nc - 1));
+#pragma unroll
+      for (int h = 0; h < PT; ++h) {
+        *(reinterpret_cast<f32x4*>(smem + L.slot + slot * KB + h * 1024) + lane) = macc[h];
+        macc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      if (q4 == 0) bm_s[slot * 16 + r16] = mref;
+    }
+  };
+  int i0 = 0;
+  for (; i0 + NB < ni; i0 += NB) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) step(buf[i], i0 + i, std::true_type{});
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if (i0 + i < ni) step(buf[i], i0 + i, std::false_type{});
+  auto factor = [](float m, float ms) { return m == -INFINITY ? 0.0f : __expf(m - ms); };
+  float mr[4];                                                   // references of the rows 4 q4 .. of an accumulator
+#pragma unroll
+  for (int v = 0; v < 4; ++v) mr[v] = __shfl(mref, 4 * q4 + v, kWave);
+  {
+    const float mh = row_stride_max(mref, Gp);                   // of the head, over the row groups
+    const float l = row_stride_sum(cross_row_sum(lsum) * factor(mref, mh), Gp);
+    if (lane < Gp) {
+      wm_s[wave * 16 + lane] = mh;
+      wl_s[wave * 16 + lane] = l;
+    }
+  }
+  lds_barrier();
+
+  // ---- (4) the waves meet ------------------------------------------------------------------------
+  const size_t rec_h = static_cast<size_t>(p.Sm) * p.recm;
+  float* rec0 = p.part_m + (hq0 * p.Sm + sm_idx) * p.recm;
+  const int Dva = 16 * ((p.Dvu + 15) / 16);
+  f32x4 ms4;                                                     // references of the rows 4 q4 .. of an accumulator
+  {
+    const float* w = wm_s + (4 * q4) % Gp;
+    ms4 = *reinterpret_cast<const f32x4*>(w);
+#pragma unroll
+    for (int k = 1; k < kLocWaves; ++k) {
+      const f32x4 o = *reinterpret_cast<const f32x4*>(w + 16 * k);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ms4[v] = fmaxf(ms4[v], o[v]);
+    }
+  }
+  float fo[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) fo[v] = factor(mr[v], ms4[v]);
+#pragma unroll
+  for (int dt = 0; dt < DVT; ++dt) {
+    f32x4 o;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      o[v] = fo[v] * oacc[dt][v];
+      if constexpr (GR == 4) {
+        o[v] = cross_row_sum(o[v]);
+      } else if constexpr (GR == 2) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[v]), __float_as_uint(o[v]), false, false);
+        o[v] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+      }
+    }
+    if constexpr (GR == 4) {   // every lane group holds the sums: group q4 writes row q4
+      red_o[(wave * Gp + q4) * (16 * DVT) + 16 * dt + r16] = q4 == 0 ? o[0] : q4 == 1 ? o[1] : q4 == 2 ? o[2] : o[3];
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (4 * q4 < Gp) red_o[(wave * Gp + 4 * q4 + v) * (16 * DVT) + 16 * dt + r16] = o[v];
+    }
+  }
+  for (int it = kLocThreads - 1 - tid; it < nt * nc * 16; it += kLocThreads) {   // a share's reference becomes its factor
+    const int h = it % Gp;
+    float m = wm_s[h];
+#pragma unroll
+    for (int w = 1; w < kLocWaves; ++w) m = fmaxf(m, wm_s[w * 16 + h]);
+    bm_s[it] = factor(bm_s[it], m);
+  }
+  if (wave == 1 && lane < G) {
+    float m = wm_s[lane], l = 0.0f;
+#pragma unroll
+    for (int w = 1; w < kLocWaves; ++w) m = fmaxf(m, wm_s[w * 16 + lane]);
+#pragma unroll
+    for (int w = 0; w < kLocWaves; ++w) l += wl_s[w * 16 + lane] * factor(wm_s[w * 16 + lane], m);
+    rec0[lane * rec_h + 0] = m;
+    rec0[lane * rec_h + 1] = l;
+  }
+  lds_barrier();
+  for (int it = tid; it < nt * PT * 256; it += kLocThreads) {      // moments: the sharers of a tile meet (lane it / 4, element it % 4)
+    const int e = it & 3, ln = (it >> 2) & 63, th = it >> 8, h = th % PT, tile = th / PT;
+    const int row = 4 * (ln >> 4) + e, fn = 16 * h + (ln & 15);    // column and function
+    float v = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kLocWaves; ++k) {
+      const int s = tile * nc + min(k, nc - 1);
+      const float x = bm_s[s * 16 + row] * reinterpret_cast<const float*>(smem + L.slot + s * KB + h * 1024)[it & 255];
+      v += k < nc ? x : 0.0f;
+    }
+    // per column [even head | even remainder | odd head | odd remainder] x P / 2
+    const __bf16 hi = static_cast<__bf16>(v), lo = static_cast<__bf16>(v - static_cast<float>(hi));
+    unsigned char* o = a_s + tile * KB + row * (4 * P) + (fn & 1) * (2 * P) + (fn >> 1) * 2;
+    *reinterpret_cast<__bf16*>(o) = hi;
+    *reinterpret_cast<__bf16*>(o + P) = lo;
+  }
+  for (int it = kLocThreads - 1 - tid; it < G * (4 * DVT); it += kLocThreads) {
+    const int h = it / (4 * DVT), d4 = it % (4 * DVT);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kLocWaves; ++w) v += *reinterpret_cast<const f32x4*>(red_o + (w * Gp + h) * (16 * DVT) + 4 * d4);
+    if (4 * d4 < Dva) *reinterpret_cast<f32x4*>(rec0 + h * rec_h + 4 + 4 * d4) = v;
+  }
+  lds_barrier();
+  // r of the own harmonics: their values at the nodes times the moments of every block, turned back from the blocks' centres
+#pragma unroll 1
+  for (int c = wave; c < ncs; c += kLocWaves) {
+    // A operands; P = 16: head in the first two slot groups, remainder in the others
+    Frag<T> eh, el, oh, ol;
+    const int n = 16 * c + r16;
+    if constexpr (P == 16) {
+      eh.v = *jt(n, q4 >> 1);
+      oh.v = *jt(n, 2 + (q4 >> 1));
+    } else {
+      eh.v = *jt(n, q4 & 1);
+      el.v = *jt(n, 2 + (q4 & 1));
+      oh.v = *jt(n, 4 + (q4 & 1));
+      ol.v = *jt(n, 6 + (q4 & 1));
+    }
+    f32x4 rc = {0.f, 0.f, 0.f, 0.f}, rs = {0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < nt; ++t) {
+      const unsigned char* m = a_s + t * KB + r16 * (4 * P) + (P == 32 ? q4 : q4 & 1) * 16;
+      Frag<T> me, mo;
+      me.v = *reinterpret_cast<const u32x4*>(m);
+      mo.v = *reinterpret_cast<const u32x4*>(m + 2 * P);
+      f32x4 E = {0.f, 0.f, 0.f, 0.f}, O = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (P == 32) {
+        mma_k32(E, el, me);
+        mma_k32(O, ol, mo);
+      }
+      mma_k32(E, eh, me);
+      mma_k32(O, oh, mo);
+      float cs[4], sn[4];
+      phases(16 * c + 4 * q4 + 1, centre(t * GR + col_b), cs, sn);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        rc[v] += cs[v] * E[v] - sn[v] * O[v];
+        rs[v] += sn[v] * E[v] + cs[v] * O[v];
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      rc[v] = row_stride_sum(rc[v], Gp);
+      rs[v] = row_stride_sum(rs[v], Gp);
+    }
+    if (r16 < G) {
+      float* r = rec0 + r16 * rec_h + 4 + Dva + 32 * c + 4 * q4;
+      *reinterpret_cast<f32x4*>(r) = rc;
+      *reinterpret_cast<f32x4*>(r + 16) = rs;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// host
+// ---------------------------------------------------------------------------
+// longest block (a power of two of 32-row steps up to `cap`) whose highest kept harmonic stays within theta; 0: none
+static int local_block(int M, int T, double theta, int cap) {
+  const int nmax = M / 2;
+  int U = cap;
+  while (U >= kLocStep && 3.14159265358979323846 * nmax * U > theta * T) U /= 2;
+  return U >= kLocStep ? U : 0;
+}
+
+// kept-dim tiles of the compiled variant that serves these counts: (K steps of 32, V tiles of 16) is (1, 1), (1, 2),
+// (2, 4) or (4, 8)
+static int local_v_tiles(int Dku, int Dvu) {
+  if (Dku <= 32 && Dvu <= 32) return Dvu <= 16 ? 1 : 2;
+  return Dku <= 64 && Dvu <= 64 ? 4 : 8;
+}
+
+LocalForm local_form(int M, int T) {
+  return LocalForm{local_block(M, T, kLocTheta16, 512), local_block(M, T, kLocTheta32, 256)};
+}
+
+LocalPlan make_local_plan(int B, int Hkv, int G, int Dku, int Dvu, int Mint, int N, LocalForm form) {
+  LocalPlan pl{};
+  if (N <= 0 || Dku < 1 || Dku > 128 || Dvu < 1 || Dvu > 128) return pl;
+  const long pairs = static_cast<long>(B) * Hkv;
+  const int dvt = local_v_tiles(Dku, Dvu);
+  const int ncs = Mint / 32, most = dvt <= 2 ? 4 : dvt == 4 ? 2 : 1;
+  // Row groups, steps per wave and nodes by estimated time (us).  A round of workgroups (one per compute unit) takes 5.5, then
+  // the longer of what is done in front of the rows (3.5, and 0.4 per tile and 256 slots of the series; 32 nodes: 1.1) and the
+  // first step's bytes, the other steps (what a compute unit draws: 28 GB/s alone, its share of 5.3 TB/s at most; 0.3 - 0.45 at
+  // least), then 0.25 (0.45) per tile and 256 slots; a record adds to the launch behind.  Measured (estimated), 8 heads: 32 K
+  // tokens, M = 256, 11.6 (12.5), 16 columns 13.8 (13.4), M = 1023 16.8 (17.7), 128 K, M = 512 19.1 (22); 24 heads x 5003
+  // tokens, M = 130, 8 columns, 10.3 (10.5); 192 heads x 5500, M = 242, blocks of 64, 43.6 (42.6)
+  double best = 1e30;
+  for (int GR = 4; GR >= 1; GR /= 2) {
+    if (GR > most || GR * G > 16) continue;
+    for (int ni = 1; ni <= 8; ++ni) {
+      const long chunk = 256l * GR * ni, chunks = (N + chunk - 1) / chunk, wgs = pairs * chunks;
+      const double bw = wgs < 190 ? 28e3 : 5.3e6 / (wgs < 256 ? wgs : 256);
+      for (int P = 16; P <= 32; P *= 2) {
+        int U = P == 16 ? form.u16 : form.u32;
+        while (U > kLocStep && (kLocWaves * ni) % (U / kLocStep) != 0) U /= 2;
+        if (U < kLocStep) continue;
+        const int nt = kLocWaves * ni / (U / kLocStep);
+        const unsigned lds = local_lds(P, Mint, U, nt, ni, 16 / GR, dvt).total;
+        if (lds > kMaxDynLds) continue;
+        const double mem = 512.0 * GR * (Dku + Dvu) / bw, cmp = (0.25 + 0.05 * GR) * (dvt > 2 ? 1.5 : 1.0), step = mem > cmp ? mem : cmp;
+        const double x = static_cast<double>(nt) * ncs / 8.0, front = 3.5 + (P == 16 ? 0.4 : 1.1) * x;
+        const double t = static_cast<double>((wgs + 255) / 256) * (5.5 + (front > step ? front : step) + (ni - 1) * step + (P == 16 ? 0.25 : 0.45) * x) +
+                         0.02 * chunks * Mint / 256;
+        if (t >= best) continue;
+        best = t;
+        pl = LocalPlan{true, P, U, GR, ni, static_cast<int>(chunk), static_cast<int>(chunks), lds, t};
+      }
+    }
+  }
+  return pl;
+}
+
+template <int P, int KC, int DVT, int GR, int NS>
+static int launch_local_one(const DecodeParams& p, const LocalPlan& pl, hipStream_t st, KernelTimers* tm) {
+  auto kern = decode_local<P, KC, DVT, GR, NS>;
+  if (pl.lds > 48u * 1024u &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          static_cast<int>(kMaxDynLds)) != hipSuccess)
+    return FA_ERR_HIP;
+  FA_LAUNCH_TIMED(tm, 1, kern, dim3(p.B * p.Hkv, p.Sm), dim3(kLocThreads), pl.lds, st, p);
+  return FA_OK;
+}
+
+template <int P, int NS>
+static int launch_local_p(const DecodeParams& p, const LocalPlan& pl, hipStream_t st, KernelTimers* tm) {
+  switch (local_v_tiles(p.Dku, p.Dvu)) {
+    case 1:
+      return pl.GR == 4 ? launch_local_one<P, 1, 1, 4, NS>(p, pl, st, tm)
+             : pl.GR == 2 ? launch_local_one<P, 1, 1, 2, NS>(p, pl, st, tm) : launch_local_one<P, 1, 1, 1, NS>(p, pl, st, tm);
+    case 2:
+      return pl.GR == 4 ? launch_local_one<P, 1, 2, 4, NS>(p, pl, st, tm)
+             : pl.GR == 2 ? launch_local_one<P, 1, 2, 2, NS>(p, pl, st, tm) : launch_local_one<P, 1, 2, 1, NS>(p, pl, st, tm);
+    case 4:
+      return pl.GR == 2 ? launch_local_one<P, 2, 4, 2, NS>(p, pl, st, tm) : launch_local_one<P, 2, 4, 1, NS>(p, pl, st, tm);
+    default: return launch_local_one<P, 4, 8, 1, NS>(p, pl, st, tm);
+  }
+}
+
+int launch_local(const DecodeParams& p, const LocalPlan& pl, hipStream_t st, KernelTimers* tm) {
+  if (p.Mint <= 256) return pl.P == 16 ? launch_local_p<16, 1>(p, pl, st, tm) : launch_local_p<32, 1>(p, pl, st, tm);
+  return pl.P == 16 ? launch_local_p<16, 4>(p, pl, st, tm) : launch_local_p<32, 4>(p, pl, st, tm);
+}
+
+}  // namespace fa

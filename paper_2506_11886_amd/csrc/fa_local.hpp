@@ -1,0 +1,27 @@
+// Middle rows of fa_decode with the series in local Chebyshev polynomials: see fa_local.hip.
+#pragma once
+
+#include "fa_decode.hpp"
+
+namespace fa {
+
+
+struct LocalPlan {
+  bool use;
+  int P, U;            // polynomials (16 or 32) and tokens (a power of two, 32 .. 512) per block
+  int GR, ni;          // row groups of a step, steps per wave
+  int chunk_m, Sm;     // rows per workgroup (256 GR ni), workgroups per (sequence, KV head)
+  unsigned lds;
+  double us;           // estimated time
+};
+
+// longest blocks (tokens, powers of two) on which 16 / 32 nodes carry M states of period T; 0: none
+struct LocalForm {
+  int u16, u32;
+};
+constexpr LocalForm kLocalForms[] = {{512, 256}, {256, 256}, {128, 256}, {64, 256}, {64, 128}, {32, 128}, {32, 64}, {0, 64}, {0, 32}};
+LocalForm local_form(int M, int T);
+LocalPlan make_local_plan(int B, int Hkv, int G, int Dku, int Dvu, int Mint, int N, LocalForm form);
+int launch_local(const DecodeParams& p, const LocalPlan& pl, hipStream_t st, KernelTimers* tm);
+
+}  // namespace fa

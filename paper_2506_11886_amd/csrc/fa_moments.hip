@@ -59,13 +59,6 @@ __device__ __forceinline__ void bessel_coeffs(double theta, float (&a)[kMomP]) {
   for (int q = 0; q < kMomP; ++q) a[q] = static_cast<float>((q == 0 ? 1.0 : ((q >> 1) & 1) ? -2.0 : 2.0) * j[q]);
 }
 
-// LDS-only workgroup barrier: global loads and stores stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 template <int D>
 struct MomTile {
   static constexpr int kTokens = D == 256 ? 64 : 128;              // tokens of a tile

@@ -1,0 +1,179 @@
+"""Middle rows of fa_decode through interpolation inside blocks (long periods, bf16), against the fp64 oracle.
+
+Tolerance 1e-4 of the largest output: cardinal functions, coefficients, moments and probabilities are held to 2^-17 each,
+eight such roundings at most add up behind a cardinal sum of 2.7.  (The other bf16 kernels, with 16-bit tables and
+probabilities on the series side, are off by 3e-4 and more: the test also tells which form ran.)
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle.fourier_kv as fk
+from fa_testlib import rows_pad8, rows_to_tok8, to_dev
+from workloads import rel_err
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-4
+
+
+def _bf16(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(torch.bfloat16).float().numpy()
+
+
+def _state(B, H, D, Dkc, Dvc, N, M, T, W, seed):
+    """Masks, states whose rebuilt dims have unit variance, kept dims and full-width rows."""
+    r = np.random.default_rng(seed)
+    masks = [np.argsort(np.argsort(r.random((B, H, D)), -1), -1) < n for n in (Dkc, Dvc)]
+    amp = T / np.sqrt(2.0 * M)
+    s = {"kmask": masks[0].astype(np.uint8), "vmask": masks[1].astype(np.uint8),
+         "ck": (amp * r.standard_normal((B, H, M, Dkc))).astype(np.float32),
+         "cv": (amp * r.standard_normal((B, H, M, Dvc))).astype(np.float32)}
+    for name, n, d in (("kk", N, D - Dkc), ("vk", N, D - Dvc), ("kf", W, D), ("vf", W, D)):
+        s[name] = _bf16(r.standard_normal((B, H, n, d)))
+    return s, r
+
+
+def _device(s):
+    dt = torch.bfloat16
+    W = s["kf"].shape[2]
+    return (to_dev(s["ck"]), to_dev(s["kmask"]), to_dev(s["cv"]), to_dev(s["vmask"]), to_dev(rows_pad8(s["kk"]), dtype=dt),
+            to_dev(rows_to_tok8(s["vk"]), dtype=dt), to_dev(s["kf"], dtype=dt) if W else None, to_dev(s["vf"], dtype=dt) if W else None)
+
+
+def _want(s, b, h, q, T, t0, n, w):
+    return fk.decode_head_group(q, s["ck"][b, h], s["kmask"][b, h], s["cv"][b, h], s["vmask"][b, h], T, t0, n,
+                                s["kk"][b, h, :n], s["vk"][b, h, :n], s["kf"][b, h, :w], s["vf"][b, h, :w])
+
+
+# D, G, compressed K / V dims, N, M, T, t0, W: every compiled pair of kept-dim tiles, 16 and 32 nodes, groups of one to
+# sixteen columns, blocks of 32 to 512 tokens, chunks that end inside a step, a block, a wave's rows, or exactly; series of
+# 128 to 1024 slots; periods longer than the segment and segments inside one; full-width rows of any count
+# (few rows: only series of 1024 slots take this form)
+SHAPES = [
+    (128, 4, 96, 96, 2500, 600, 20000, 100, 37),      # 32 nodes, 256-token blocks
+    (128, 4, 112, 112, 4100, 520, 30000, 0, 5),       # one tile of kept V dims
+    (128, 3, 98, 97, 1024, 530, 100000, 41000, 130),  # odd counts (C_k rows not aligned), a chunk exactly full
+    (128, 8, 80, 70, 1025, 520, 20000, 3, 0),         # eight columns, two K steps and four V tiles, no full-width rows
+    (64, 16, 40, 30, 777, 1023, 31000, 0, 64),        # sixteen columns, the longest series
+    (256, 2, 160, 150, 1300, 700, 40000, 7600, 33),   # kept dims of the largest variant
+    (128, 1, 97, 99, 33, 514, 9000, 1, 1),            # two steps of one wave
+    (128, 4, 100, 100, 8193, 520, 20000, 0, 300),     # one row more than whole chunks
+    (72, 5, 50, 41, 1500, 600, 16000, 9, 70),         # a head dim without matrix full-width rows
+    (128, 16, 96, 112, 6000, 600, 60000, 0, 600),     # sixteen columns, 16 nodes
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"D{s[0]}-G{s[1]}-{s[2]}-{s[3]}-N{s[4]}-M{s[5]}" for s in SHAPES])
+def test_local_matches_oracle(shape):
+    import paper_2506_11886_amd as fa
+    D, G, Dkc, Dvc, N, M, T, t0, W = shape
+    print(f"[case] local {shape}", flush=True)
+    B, H = 1, 2
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 5)
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    ck, km, cv, vm, kk, vk, kf, vf = _device(s)
+    dq = to_dev(q, dtype=torch.bfloat16)
+    need = fa.decode_workspace_bytes(B, H * G, H, D, Dkc, Dvc, M, N, W)
+    buf = torch.full((need + 4096,), 0x7F, dtype=torch.uint8, device="cuda")
+    out = fa.fa_decode(dq, ck, km, cv, vm, M, T, t0, N, kk, vk, kf, vf, workspace=buf[:need])
+    again = fa.fa_decode(dq, ck, km, cv, vm, M, T, t0, N, kk, vk, kf, vf)
+    torch.cuda.synchronize()
+    assert (buf[need:] == 0x7F).all() and torch.equal(out, again)
+    got = out.cpu().numpy()
+    for h in range(H):
+        want = _want(s, 0, h, q[0, h * G:(h + 1) * G], T, t0, N, W)
+        assert rel_err(got[0, h * G:(h + 1) * G], want) <= TOL, (h, rel_err(got[0, h * G:(h + 1) * G], want))
+
+
+def test_local_per_sequence_counts():
+    """Chunks and steps past a sequence's rows, a sequence without middle rows, one without full-width rows, one without any;
+    the slabs past the counts hold NaN."""
+    import paper_2506_11886_amd as fa
+    B, H, G, D, Dkc, Dvc, N, M, T, W = 5, 2, 8, 128, 92, 90, 2300, 600, 20000, 150
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 6)
+    nn, ww = [2300, 0, 1031, 64, 0], [150, 77, 0, 1, 0]
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    poison = {k: v.copy() for k, v in s.items()}
+    for b in range(B):
+        for name, n in (("kk", nn[b]), ("vk", nn[b]), ("kf", ww[b]), ("vf", ww[b])):
+            poison[name][b, :, n:] = np.nan
+    ck, km, cv, vm, kk, vk, kf, vf = _device(poison)
+    lists = [torch.tensor(x, dtype=torch.int32, device="cuda") for x in (nn, ww)]
+    out = fa.fa_decode_varlen(to_dev(q, dtype=torch.bfloat16), ck, km, cv, vm, M, T, 0, N, lists[0], kk, vk, kf, vf, lists[1])
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    for b in range(B):
+        for h in range(H):
+            g = got[b, h * G:(h + 1) * G]
+            if nn[b] + ww[b] == 0:
+                assert not g.any()
+                continue
+            assert rel_err(g, _want(s, b, h, q[b, h * G:(h + 1) * G], T, 0, nn[b], ww[b])) <= TOL, (b, h)
+
+
+@pytest.mark.parametrize("Tq,G,D", [(4, 4, 128), (5, 1, 64), (2, 8, 256)])
+def test_local_several_query_tokens(Tq, G, D):
+    import paper_2506_11886_amd as fa
+    B, H, N, M, T, W = 1, 2, 1900, 600, 16000, 40
+    Dkc, Dvc = D * 3 // 4, D * 3 // 4 - 4
+    print(f"[case] local mq Tq{Tq} G{G} D{D}", flush=True)
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 7)
+    q = _bf16(r.standard_normal((B, H, Tq, G, D)))
+    ck, km, cv, vm, kk, vk, kf, vf = _device(s)
+    out = fa.fa_decode_mq(to_dev(q, dtype=torch.bfloat16), ck, km, cv, vm, M, T, 0, N, kk, vk, kf, vf)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    for h in range(H):
+        want = fk.decode_multi_query(q[0, h], s["ck"][0, h], s["kmask"][0, h], s["cv"][0, h], s["vmask"][0, h], T, 0, N,
+                                     s["kk"][0, h], s["vk"][0, h], s["kf"][0, h], s["vf"][0, h])
+        assert rel_err(got[0, h], want) <= TOL, (h, rel_err(got[0, h], want))
+
+
+def test_local_small_workspace_runs_the_other_form():
+    """A buffer that holds the state of the other kernels only is still accepted (and gives the same result up to their
+    precision); one byte less than that is refused."""
+    import paper_2506_11886_amd as fa
+    B, H, G, D, Dkc, Dvc, N, M, T, W = 1, 2, 4, 128, 80, 80, 9000, 600, 30000, 2000   # (more chunks and window records than there)
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 8)
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    ck, km, cv, vm, kk, vk, kf, vf = _device(s)
+    dq = to_dev(q, dtype=torch.bfloat16)
+    call = lambda n: fa.fa_decode(dq, ck, km, cv, vm, M, T, 0, N, kk, vk, kf, vf,
+                                  workspace=torch.empty(n, dtype=torch.uint8, device="cuda"))
+    full = fa.decode_workspace_bytes(B, H * G, H, D, Dkc, Dvc, M, N, W)
+    lo, hi = 0, full                       # the smallest size that is accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            call(mid)
+            hi = mid
+        except fa.FourierAttnError as e:
+            assert e.status == fa.FA_ERR_WORKSPACE
+            lo = mid
+    outs = [call(hi).cpu().numpy(), call(full).cpu().numpy()]
+    for h in range(H):
+        want = _want(s, 0, h, q[0, h * G:(h + 1) * G], T, 0, N, W)
+        for o, tol in zip(outs, (2e-3, TOL)):
+            assert rel_err(o[0, h * G:(h + 1) * G], want) <= tol
+
+
+# The variants of up to 256 states and four query heads, which take many rows: eight heads, two of them checked.  M = 2, 1: blocks at
+# their cap, the constant alone; eight heads with few states are bound by what is kept
+MANY = [(4, 96, 96, 31740, 256, 31772), (2, 116, 114, 65001, 200, 65001), (4, 64, 64, 20000, 2, 20000), (8, 90, 91, 9999, 1, 10100),
+        (3, 80, 96, 16000, 100, 64000), (16, 96, 96, 9000, 1023, 9000), (16, 100, 114, 9001, 700, 9500)]   # (blocks of 64 and 128)
+
+
+@pytest.mark.parametrize("G,Dkc,Dvc,N,M,T", MANY)
+def test_local_many_rows(G, Dkc, Dvc, N, M, T):
+    import paper_2506_11886_amd as fa
+    print(f"[case] local rows G{G} {Dkc}/{Dvc} N{N} M{M}", flush=True)
+    B, H, D, W = 1, 8, 128, 36
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 9)
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    ck, km, cv, vm, kk, vk, kf, vf = _device(s)
+    out = fa.fa_decode(to_dev(q, dtype=torch.bfloat16), ck, km, cv, vm, M, T, 0, N, kk, vk, kf, vf)
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        got, want = out[0, h * G:(h + 1) * G].cpu().numpy(), _want(s, 0, h, q[0, h * G:(h + 1) * G], T, 0, N, W)
+        assert rel_err(got, want) <= TOL, (h, rel_err(got, want))

@@ -31,13 +31,14 @@
 //      chunks of middle rows and chunks of full-width sink/window rows; emits
 //      a flash-decoding partial per query head: (max, sum, acc[kept dims],
 //      r[Mint]) for middle rows, (max, sum, acc[D]) for full-width rows.
-//   3. decode_finish  : a few workgroups per query head (one per slice of output dims) merge the partials,
-//      applies diag(w) C_v to r and normalises.
+//   3. decode_finish (fa_finish.hip): a few workgroups per query head (one per slice of output dims) merge
+//      the partials, apply diag(w) C_v to r and normalise.
 
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
 
+#include "fa_finish.hpp"
 #include "fa_full.hpp"
 #include "fa_local.hpp"
 
@@ -2360,528 +2361,7 @@ __global__ __launch_bounds__(kBlock, (CW <= 2 && sizeof(T) == 2) ? 2 : 1) void d
 }
 
 // ---------------------------------------------------------------------------
-// 3. merge partials, apply diag(w) C_v, normalise
-// ---------------------------------------------------------------------------
-// A query head is shared by ceil(D / 32) workgroups, one per slice of 32 output
-// dims.  Every slice merges the statistics and the series sums r of the head's
-// records (replicated work, a few tens of KB), then finishes its own dims: kept
-// dims from the accumulators, compressed dims from r and its columns of C_v.
-// Nothing is exchanged between workgroups.
-// kFinDims: output dims per workgroup.  Every workgroup of a head re-reads the head's statistics and
-// series sums, so few wide slices read less and many narrow slices fill the chip sooner: 32 dims
-// when there are few query heads, 64 once the heads alone give enough workgroups.
-template <typename T, int kFinDims>
-__global__ __launch_bounds__(kFinBlock) void decode_finish(DecodeParams p) {
-  constexpr int kNW = kFinBlock / 64;
-  constexpr int kSP = kMaxPartials / kFinBlock;   // records per thread when reading statistics
-  constexpr int kCG = kFinBlock / kFinDims;       // row / record groups of the per-dim passes
-  __shared__ float es[kMaxPartials];              // e^{m_s - m} per record
-  __shared__ f32x4 red4[kFinBlock];
-  __shared__ float rr[FA_MAX_DECODE_STATES];      // r in basis order, weighted
-  __shared__ f32x4 redw4[kFinBlock];
-  __shared__ float redc[kFinBlock];
-  __shared__ float outw[kFinDims];
-  __shared__ float wmax[kNW], wsum[kNW], wsum_m[kNW];
-
-  const int sl = blockIdx.x, hq = blockIdx.y;
-  const int b = hq / p.Hq, hkv = (hq % p.Hq) / p.G, bh = b * p.Hkv + hkv;
-  const int D = p.D, M = p.M, Sm = p.Sm, Sw = p.Sw, S = Sm + Sw, Dvc = p.Dvc;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int Dva = 16 * ((p.Dvu + 15) / 16);
-  const int recm = p.recm, recw = p.recw;
-  const float* pm = p.part_m + static_cast<size_t>(hq) * Sm * recm;
-  const float* pw = p.part_w + static_cast<size_t>(hq) * Sw * recw;
-  const bool do_cv = Sm > 0 && Dvc > 0;
-  const int d0 = kFinDims * sl;
-
-  // ---- global operands, in the order they are needed -----------------------------------------
-  // (0) the mask row: it decides which columns of C_v and of the accumulators this slice reads
-  uint8_t vmb[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) vmb[i] = p.vmask[static_cast<size_t>(bh) * D + min(lane + 64 * i, D - 1)];
-  // (1) chunk maxima and sums
-  float ms[kSP], ls[kSP];
-#pragma unroll
-  for (int i = 0; i < kSP; ++i) {
-    const int s = min(tid + i * kFinBlock, S - 1);
-    const float* r = (s < Sm) ? pm + static_cast<size_t>(s) * recm : pw + static_cast<size_t>(s - Sm) * recw;
-    ms[i] = r[0];
-    ls[i] = r[1];
-  }
-  // (2) series sums of the middle records: thread (4 columns, group of records)
-  const int cr4 = p.Mint / 4, ngr = kFinBlock / cr4;
-  const int c4r = tid % cr4, gr = tid / cr4;
-  const float* pr = pm + 4 + Dva + 4 * c4r;
-  constexpr int kUr = 12;
-  f32x4 rv[kUr];
-  if (do_cv) {
-#pragma unroll
-    for (int u = 0; u < kUr; ++u)   // lanes are clamped, never predicated (a predicated load is waited for
-      if (u * ngr < Sm)             // at once); rounds no lane needs are skipped by the whole workgroup
-        rv[u] = *reinterpret_cast<const f32x4*>(pr + static_cast<size_t>(min(gr + u * ngr, Sm - 1)) * recm);
-  }
-  // (3) this slice's columns of the full-row records: thread (4 columns, group of records)
-  constexpr int kW4 = kFinDims / 4, kWG = kFinBlock / kW4;
-  const int c4w = tid % kW4, gw = tid / kW4;
-  const bool w_ok = d0 + 4 * c4w < D;
-  const int dw = min(d0 + 4 * c4w, D - 4);
-  constexpr int kUw = 2;
-  f32x4 wv[kUw];
-  if (Sw > 0) {
-#pragma unroll
-    for (int u = 0; u < kUw; ++u)
-      if (u * kWG < Sw)
-        wv[u] = *reinterpret_cast<const f32x4*>(pw + static_cast<size_t>(min(gw + u * kWG, Sw - 1)) * recw + 4 + dw);
-  }
-  // ranks of this slice's dims (needs only the mask)
-  uint64_t vbal[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) vbal[i] = __ballot(vmb[i] != 0 && lane + 64 * i < D);
-  const int col = tid % kFinDims, cg = tid / kFinDims;
-  const int dme = d0 + col;
-  const int rk = (dme < D) ? dim_rank(vbal, dme) : 0;
-  const bool is_c = dme < D && rk < 0, is_k = dme < D && rk >= 0;
-  // (4) C_v.  The compressed dims of a slice have consecutive ranks r0 .. r0 + nc - 1, i.e. the slice
-  // needs a contiguous band of C_v's columns.  With Dvc a multiple of 4 the band is read as 128-bit
-  // vectors: thread (column quad cq, row group rg) takes rows rg, rg + ngrp, ...  Otherwise every
-  // thread reads its own dim's column element by element (rows cg, cg + kCG, ...).
-  constexpr int kUc = 64, kUk = 6, kUv = 16;
-  const bool vec_cv = do_cv && (Dvc & 3) == 0;
-  int r0 = 0, nc = 0;
-  {
-    const int w0 = d0 >> 6, sh = d0 & 63;   // kFinDims divides 64: the slice lies inside one ballot word
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j < w0) r0 += __popcll(vbal[j]);
-      if (j == w0) {
-        r0 += __popcll(vbal[j] & ((1ull << sh) - 1ull));
-        nc = __popcll((vbal[j] >> sh) & (kFinDims == 64 ? ~0ull : ((1ull << kFinDims) - 1ull)));
-      }
-    }
-  }
-  const int q0 = r0 >> 2, nq = nc > 0 ? ((r0 + nc + 3) >> 2) - q0 : 1;   // column quads of the band
-  const int ngrp = kFinBlock / nq;                                       // row groups
-  const int rgv = tid / nq, cqv = tid - rgv * nq;
-  const float* cvb = p.cv + static_cast<size_t>(bh) * M * Dvc;
-  const float* cvc = cvb + (is_c ? -rk - 1 : 0);
-  float cvv[kUc];
-  f32x4 cv4[kUv];
-  if (vec_cv) {
-    const float* cq_ptr = cvb + 4 * min(q0 + cqv, Dvc / 4 - 1);
-#pragma unroll
-    for (int u = 0; u < kUv; ++u)
-      if (u * ngrp < M) cv4[u] = *reinterpret_cast<const f32x4*>(cq_ptr + static_cast<size_t>(min(rgv + u * ngrp, M - 1)) * Dvc);
-  } else if (do_cv) {
-#pragma unroll
-    for (int u = 0; u < kUc; ++u)
-      if (u * kCG < M) cvv[u] = cvc[static_cast<size_t>(min(cg + u * kCG, M - 1)) * Dvc];
-  }
-  const float* pk = pm + 4 + (is_k ? rk : 0);
-  float kv[kUk];
-  if (Sm > 0) {
-#pragma unroll
-    for (int u = 0; u < kUk; ++u)
-      if (u * kCG < Sm) kv[u] = pk[static_cast<size_t>(min(cg + u * kCG, Sm - 1)) * recm];
-  }
-
-  // ---- global max, per-record factors, normaliser ---------------------------------------------
-  float m = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kSP; ++i)
-    if (tid + i * kFinBlock < S) m = fmaxf(m, ms[i]);
-  m = wave_max_fast(m);
-  if (lane == 0) wmax[wave] = m;
-  __syncthreads();
-  m = wmax[0];
-#pragma unroll
-  for (int w = 1; w < kNW; ++w) m = fmaxf(m, wmax[w]);
-  float l = 0.0f, lm = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kSP; ++i) {
-    const int s = tid + i * kFinBlock;
-    if (s < S) {
-      const float e = (ms[i] == -INFINITY) ? 0.0f : __expf(ms[i] - m);
-      es[s] = e;
-      l += e * ls[i];
-      if (s < Sm) lm += e * ls[i];   // the middle rows' share: r of the constant basis function
-    }
-  }
-  l = wave_sum_fast(l);
-  lm = wave_sum_fast(lm);
-  if (lane == 0) {
-    wsum[wave] = l;
-    wsum_m[wave] = lm;
-  }
-  __syncthreads();
-  float L = 0.0f, Lm = 0.0f;
-#pragma unroll
-  for (int w = 0; w < kNW; ++w) {
-    L += wsum[w];
-    Lm += wsum_m[w];
-  }
-
-  // ---- r in basis order, weighted by the inverse squared norms ---------------------------------
-  if (do_cv) {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (gr < ngr) {
-#pragma unroll
-      for (int u = 0; u < kUr; ++u) {
-        const int s = gr + u * ngr;
-        if (s < Sm) a += es[s] * rv[u];
-      }
-      for (int s = gr + kUr * ngr; s < Sm; s += ngr)
-        a += es[s] * *reinterpret_cast<const f32x4*>(pr + static_cast<size_t>(s) * recm);
-    }
-    red4[tid] = a;
-  }
-  // this slice's full-row columns
-  {
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int u = 0; u < kUw; ++u) {
-      const int s = gw + u * kWG;
-      if (s < Sw && w_ok) c += es[Sm + s] * wv[u];
-    }
-    if (w_ok)
-      for (int s = gw + kUw * kWG; s < Sw; s += kWG)
-        c += es[Sm + s] * *reinterpret_cast<const f32x4*>(pw + static_cast<size_t>(s) * recw + 4 + dw);
-    redw4[tid] = c;   // [record group][column quad]
-  }
-  __syncthreads();
-  if (tid < kFinDims) {
-    const float* src = reinterpret_cast<const float*>(redw4) + tid;
-    float v = 0.0f;
-#pragma unroll
-    for (int g = 0; g < kWG; ++g) v += src[g * kFinDims];
-    outw[tid] = v;
-  }
-  if (do_cv) {
-    for (int ig = tid; ig < p.Mint; ig += kFinBlock) {   // record order: 32 * chunk + 16 * (cos | sin) + order
-      const float* src = reinterpret_cast<const float*>(red4) + ig;
-      float v = 0.0f;
-      for (int g = 0; g < ngr; ++g) v += src[g * p.Mint];
-      const int n = 16 * (ig >> 5) + (ig & 15) + 1, cs = (ig >> 4) & 1;
-      const int mm = 2 * n - 1 + cs;
-      if (mm < M) rr[mm] = v * basis_weight(n, p.T);
-    }
-    if (tid == kFinBlock - 1) rr[0] = Lm * basis_weight(0, p.T);   // constant function: sum of p over the middle rows
-  }
-  __syncthreads();
-
-  // ---- per dim: sum_m rr[m] C_v[m, i] (compressed) or the merged accumulator (kept) ------------
-  if (vec_cv) {   // band of C_v: partial sums per (row group, column quad); red4 is free again
-    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
-    if (rgv < ngrp) {
-#pragma unroll
-      for (int u = 0; u < kUv; ++u) {
-        const int mm = rgv + u * ngrp;
-        if (mm < M) o4 += rr[mm] * cv4[u];
-      }
-      const float* cq_ptr = cvb + 4 * min(q0 + cqv, Dvc / 4 - 1);
-      for (int mm = rgv + kUv * ngrp; mm < M; mm += ngrp)
-        o4 += rr[mm] * *reinterpret_cast<const f32x4*>(cq_ptr + static_cast<size_t>(mm) * Dvc);
-    }
-    red4[tid] = o4;
-  }
-  {
-    float o = 0.0f;
-    if (do_cv && is_c && !vec_cv) {
-#pragma unroll
-      for (int u = 0; u < kUc; ++u) {
-        const int mm = cg + u * kCG;
-        if (mm < M) o += rr[mm] * cvv[u];
-      }
-      for (int mm = cg + kUc * kCG; mm < M; mm += kCG) o += rr[mm] * cvc[static_cast<size_t>(mm) * Dvc];
-    }
-    if (is_k && Sm > 0) {
-#pragma unroll
-      for (int u = 0; u < kUk; ++u) {
-        const int s = cg + u * kCG;
-        if (s < Sm) o += es[s] * kv[u];
-      }
-      for (int s = cg + kUk * kCG; s < Sm; s += kCG) o += es[s] * pk[static_cast<size_t>(s) * recm];
-    }
-    redc[tid] = o;
-  }
-  __syncthreads();
-  if (tid < kFinDims && d0 + tid < D) {
-    float v = outw[tid];
-#pragma unroll
-    for (int g = 0; g < kCG; ++g) v += redc[g * kFinDims + tid];
-    if (vec_cv && is_c) {   // (tid < kFinDims: col == tid, so rk is this dim's rank)
-      const int c = (-rk - 1) - 4 * q0;
-      const float* src = reinterpret_cast<const float*>(red4) + 4 * (c >> 2) + (c & 3);
-      for (int g = 0; g < ngrp; ++g) v += src[4 * g * nq];
-    }
-    p.out[static_cast<size_t>(hq) * D + d0 + tid] = L > 0.0f ? v / L : 0.0f;   // (a sequence without rows)
-  }
-}
-
-// ---------------------------------------------------------------------------
-// 3b. merge partials, apply diag(w) C_v, normalise: the pipelined form
-// ---------------------------------------------------------------------------
-// Same arithmetic as decode_finish, organised so that a workgroup's large reads depend on
-// nothing but the kernel arguments: a query head is shared by NS workgroups that divide the
-// output dims by RANK (compressed dims cb0 .. cb0 + cbw - 1 and kept dims kb0 .. kb0 + kbw - 1 in
-// mask order) instead of by position, so the band of C_v columns and the kept-dim columns of the
-// records are known before the mask row arrives; only the few full-row records are read after
-// it.  Every load is issued in batches of independent requests (no load waits for another one's
-// data), and the workgroups of one KV head are numbered so that they run on one XCD and share
-// its L2 (workgroup ids go round the eight XCDs).  Needs Dvc to be a multiple of 4.
-constexpr int kFin2Batch = 4;    // independent requests per batch: narrow columns (kept dims, full-row records)
-// kFin2Wide: independent 128-bit requests per batch of the series sums and of the C_v band: 16 when a
-// launch has few workgroups (long record lists, registers to spare), 8 with four workgroups per unit
-template <int kFin2Wide>
-__device__ __forceinline__ void finish2_slice(const DecodeParams& p, const SeqView& sv, const int NS, const int bh,
-                                              const int g, const int sl) {
-  constexpr int kNW = kFinBlock / 64;
-  constexpr int kSP = kMaxPartials / kFinBlock;
-  __shared__ float es[kMaxPartials];
-  __shared__ f32x4 red4[kFinBlock];                 // series sums per record group, then C_v partial sums per row group
-  __shared__ float redk[2 * kFinBlock];             // kept-dim and full-row partial sums per record group
-  __shared__ float rr[FA_MAX_DECODE_STATES + 4];
-  __shared__ int dim_of[FA_MAX_HEAD_DIM];           // output dim of each rank of this slice
-  __shared__ float wmax[kNW], wsum[kNW], wsum_m[kNW];
-
-  const int b = bh / p.Hkv, hkv = bh % p.Hkv;
-  const int hq = b * p.Hq + hkv * p.G + g;
-
-  const int D = p.D, M = p.M, Sm = sv.Sm, Sw = sv.Sw, S = Sm + Sw, Dvc = p.Dvc, Dvu = p.Dvu, Mint = p.Mint;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int Dva = 16 * ((Dvu + 15) / 16);
-  const int recm = p.recm, recw = p.recw;
-  const float* pm = sv.part_m + static_cast<size_t>(hq) * Sm * recm;
-  const float* pw = sv.part_w + static_cast<size_t>(hq) * Sw * recw;
-  const bool do_cv = Sm > 0 && Dvc > 0;
-  // this slice's ranks
-  const int cbw = (((Dvc + NS - 1) / NS) + 3) & ~3, cb0 = sl * cbw, cbn = max(0, min(cbw, Dvc - cb0));
-  const int kbw = (Dvu + NS - 1) / NS, kb0 = sl * kbw, kbn = max(0, min(kbw, Dvu - kb0));
-
-  // ---- loads that depend on nothing ------------------------------------------------------------
-  uint8_t vmb[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) vmb[i] = p.vmask[static_cast<size_t>(bh) * D + min(lane + 64 * i, D - 1)];
-  float ms[kSP], ls[kSP];
-#pragma unroll
-  for (int i = 0; i < kSP; ++i) {
-    if (i * kFinBlock < S) {
-      const int s = min(tid + i * kFinBlock, S - 1);
-      const float* r = (s < Sm) ? pm + static_cast<size_t>(s) * recm : pw + static_cast<size_t>(s - Sm) * recw;
-      ms[i] = r[0];
-      ls[i] = r[1];
-    }
-  }
-  // first batch of the series sums: thread (4 slots c4r, record group gr)
-  const int cr4 = Mint / 4, ngr = max(kFinBlock / cr4, 1);
-  const int c4r = tid % cr4, gr = tid / cr4;
-  const bool r_on = do_cv && tid < cr4 * ngr;
-  const float* pr = pm + 4 + Dva + 4 * c4r;
-  f32x4 rv[kFin2Wide];
-  if (do_cv) {
-#pragma unroll
-    for (int u = 0; u < kFin2Wide; ++u)
-      if (u * ngr < Sm) rv[u] = *reinterpret_cast<const f32x4*>(pr + static_cast<size_t>(min(gr + u * ngr, Sm - 1)) * recm);
-  }
-  // first batch of the C_v band: thread (column quad cqv, row group rgv)
-  const int nq = max(cbn / 4, 1), ngrp = kFinBlock / nq;
-  const int cqv = tid % nq, rgv = tid / nq;
-  const bool cv_on = do_cv && cbn > 0 && tid < nq * ngrp;
-  const float* cvb = p.cv + static_cast<size_t>(bh) * M * Dvc + cb0 + 4 * cqv;
-  f32x4 cv4[kFin2Wide];
-  if (do_cv && cbn > 0) {
-#pragma unroll
-    for (int u = 0; u < kFin2Wide; ++u)
-      if (u * ngrp < M) cv4[u] = *reinterpret_cast<const f32x4*>(cvb + static_cast<size_t>(min(rgv + u * ngrp, M - 1)) * Dvc);
-  }
-  // kept-dim accumulators of the middle records: thread (kept rank kc, record group kg)
-  const int kcn = max(kbn, 1), nkg = kFinBlock / kcn;
-  const int kc = tid % kcn, kg = tid / kcn;
-  const bool k_on = Sm > 0 && kbn > 0 && tid < kcn * nkg;
-  const float* pk = pm + 4 + kb0 + kc;
-  float kv[kFin2Batch];
-  if (Sm > 0 && kbn > 0) {
-#pragma unroll
-    for (int u = 0; u < kFin2Batch; ++u)
-      if (u * nkg < Sm) kv[u] = pk[static_cast<size_t>(min(kg + u * nkg, Sm - 1)) * recm];
-  }
-
-  // ---- which dims this slice writes (needs the mask row) ---------------------------------------
-  uint64_t vbal[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) vbal[i] = __ballot(vmb[i] != 0 && lane + 64 * i < D);
-  if (tid < D) {
-    const int rk = dim_rank(vbal, tid);
-    if (rk < 0) {
-      const int c = -rk - 1 - cb0;
-      if (c >= 0 && c < cbn) dim_of[c] = tid;
-    } else {
-      const int k = rk - kb0;
-      if (k >= 0 && k < kbn) dim_of[cbw + k] = tid;
-    }
-  }
-
-  // ---- global max, per-record factors, normaliser ---------------------------------------------
-  float m = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kSP; ++i)
-    if (tid + i * kFinBlock < S) m = fmaxf(m, ms[i]);
-  m = wave_max_fast(m);
-  if (lane == 0) wmax[wave] = m;
-  __syncthreads();   // also publishes dim_of
-  m = wmax[0];
-#pragma unroll
-  for (int w = 1; w < kNW; ++w) m = fmaxf(m, wmax[w]);
-  float l = 0.0f, lm = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kSP; ++i) {
-    const int s = tid + i * kFinBlock;
-    if (s < S) {
-      const float e = (ms[i] == -INFINITY) ? 0.0f : __expf(ms[i] - m);
-      es[s] = e;
-      l += e * ls[i];
-      if (s < Sm) lm += e * ls[i];
-    }
-  }
-  // the full-row records at this slice's dims: thread (rank j of the slice, record group)
-  const int nj = cbw + kbw, njn = max(nj, 1), nwg = kFinBlock / njn;
-  const int wj = tid % njn, wg = tid / njn;
-  const bool wj_live = (wj < cbn) || (wj >= cbw && wj < cbw + kbn);
-  const bool w_on = Sw > 0 && nj > 0 && tid < njn * nwg && wj_live;
-  const int wdim = wj_live && nj > 0 ? dim_of[wj] : 0;
-  float wv[kFin2Batch];
-  if (Sw > 0) {
-#pragma unroll
-    for (int u = 0; u < kFin2Batch; ++u)
-      if (u * nwg < Sw) wv[u] = pw[static_cast<size_t>(min(wg + u * nwg, Sw - 1)) * recw + 4 + wdim];
-  }
-  l = wave_sum_fast(l);
-  lm = wave_sum_fast(lm);
-  if (lane == 0) {
-    wsum[wave] = l;
-    wsum_m[wave] = lm;
-  }
-  __syncthreads();
-  float Lsum = 0.0f, Lm = 0.0f;
-#pragma unroll
-  for (int w = 0; w < kNW; ++w) {
-    Lsum += wsum[w];
-    Lm += wsum_m[w];
-  }
-
-  // ---- kept dims of the slice and the full-row records: per-thread partial sums ------------------
-  {
-    float o = 0.0f;
-    if (k_on) {
-#pragma unroll
-      for (int u = 0; u < kFin2Batch; ++u) {
-        const int s = kg + u * nkg;
-        if (s < Sm) o += es[s] * kv[u];
-      }
-      for (int s = kg + kFin2Batch * nkg; s < Sm; s += nkg) o += es[s] * pk[static_cast<size_t>(s) * recm];
-    }
-    redk[tid] = o;
-    float ow = 0.0f;
-    if (w_on) {
-#pragma unroll
-      for (int u = 0; u < kFin2Batch; ++u) {
-        const int s = wg + u * nwg;
-        if (s < Sw) ow += es[Sm + s] * wv[u];
-      }
-      for (int s = wg + kFin2Batch * nwg; s < Sw; s += nwg) ow += es[Sm + s] * pw[static_cast<size_t>(s) * recw + 4 + wdim];
-    }
-    redk[kFinBlock + tid] = ow;
-  }
-  // ---- r in basis order, weighted by the inverse squared norms ---------------------------------
-  if (do_cv) {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (r_on) {
-#pragma unroll
-      for (int u = 0; u < kFin2Wide; ++u) {
-        const int s = gr + u * ngr;
-        if (s < Sm) a += es[s] * rv[u];
-      }
-      for (int s0 = kFin2Wide * ngr; s0 < Sm; s0 += kFin2Wide * ngr) {   // further batches: requests first, sums after
-        f32x4 t[kFin2Wide];
-#pragma unroll
-        for (int u = 0; u < kFin2Wide; ++u)
-          t[u] = *reinterpret_cast<const f32x4*>(pr + static_cast<size_t>(min(s0 + gr + u * ngr, Sm - 1)) * recm);
-#pragma unroll
-        for (int u = 0; u < kFin2Wide; ++u) {
-          const int s = s0 + gr + u * ngr;
-          if (s < Sm) a += es[s] * t[u];
-        }
-      }
-    }
-    red4[tid] = a;
-  }
-  __syncthreads();
-  if (do_cv) {
-    for (int ig = tid; ig < Mint; ig += kFinBlock) {   // record order: 32 * chunk + 16 * (cos | sin) + order
-      const float* src = reinterpret_cast<const float*>(red4) + ig;
-      float v = 0.0f;
-      for (int gi = 0; gi < ngr; ++gi) v += src[gi * Mint];
-      const int n = 16 * (ig >> 5) + (ig & 15) + 1, cs = (ig >> 4) & 1;
-      const int mm = 2 * n - 1 + cs;
-      if (mm < M) rr[mm] = v * basis_weight(n, p.T);
-    }
-    if (tid == kFinBlock - 1) rr[0] = Lm * basis_weight(0, p.T);
-  }
-  __syncthreads();
-
-  // ---- compressed dims of the slice: sum_m rr[m] C_v[m, rank] -----------------------------------
-  {
-    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
-    if (cv_on) {
-#pragma unroll
-      for (int u = 0; u < kFin2Wide; ++u) {
-        const int mm = rgv + u * ngrp;
-        if (mm < M) o4 += rr[mm] * cv4[u];
-      }
-      for (int m0 = kFin2Wide * ngrp; m0 < M; m0 += kFin2Wide * ngrp) {
-        f32x4 t[kFin2Wide];
-#pragma unroll
-        for (int u = 0; u < kFin2Wide; ++u)
-          t[u] = *reinterpret_cast<const f32x4*>(cvb + static_cast<size_t>(min(m0 + rgv + u * ngrp, M - 1)) * Dvc);
-#pragma unroll
-        for (int u = 0; u < kFin2Wide; ++u) {
-          const int mm = m0 + rgv + u * ngrp;
-          if (mm < M) o4 += rr[mm] * t[u];
-        }
-      }
-    }
-    red4[tid] = o4;   // [row group][column quad]
-  }
-  __syncthreads();
-  if (tid < nj) {
-    const bool live = (tid < cbn) || (tid >= cbw && tid < cbw + kbn);
-    if (live) {
-      float v = 0.0f;
-      if (do_cv && tid < cbn) {
-        const float* src = reinterpret_cast<const float*>(red4) + tid;   // band column tid = quad tid / 4, element tid % 4
-        for (int gi = 0; gi < ngrp; ++gi) v += src[4 * gi * nq];
-      }
-      if (tid >= cbw && Sm > 0)
-        for (int gi = 0; gi < nkg; ++gi) v += redk[gi * kcn + (tid - cbw)];
-      if (Sw > 0)
-        for (int gi = 0; gi < nwg; ++gi) v += redk[kFinBlock + gi * njn + tid];
-      p.out[static_cast<size_t>(hq) * D + dim_of[tid]] = Lsum > 0.0f ? v / Lsum : 0.0f;   // (a sequence without rows)
-    }
-  }
-}
-
-template <int kFin2Wide>
-__global__ __launch_bounds__(kFinBlock, kFin2Wide == 16 ? 2 : 4) void decode_finish2(DecodeParams p, int NS) {
-  // workgroup -> (KV head, query head of the group, slice): the G * NS workgroups of a KV head share an XCD
-  const int per_kv = p.G * NS;
-  const int L = blockIdx.x, xcd = L & 7, slot = L >> 3;
-  const int bh = (slot / per_kv) * 8 + xcd;
-  if (bh >= p.B * p.Hkv) return;
-  const int within = slot % per_kv;
-  finish2_slice<kFin2Wide>(p, SeqView{p.N, p.W, p.Sm, p.Sw, p.chunk_m, p.part_m, p.part_w}, NS, bh, within / NS, within % NS);
-}
-
-// ---------------------------------------------------------------------------
-// 4. the whole call in one launch: one workgroup per (sequence, KV head)
+// 3. the whole call in one launch: one workgroup per (sequence, KV head)
 // ---------------------------------------------------------------------------
 // With many (sequence, KV head) pairs nothing has to be split to fill the chip, and a call of
 // three launches is mostly launch latency and dependent round trips.  Here a workgroup runs the
@@ -3354,10 +2834,10 @@ static bool make_local(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D,
   // take the full-width rows along inside their own waits (more than four heads at 1 us a head); here what those take beyond 0.8
   // us adds to the launch in front.  Measured (estimated): 8 heads x 32 K, M = 256, 13.4 (13.1), 16 columns 44.7 (45.3), M =
   // 1023 68.7 (69); 128 K, M = 512, 27.5 (27.8); 16 x 25741, M = 35, 13.6 (13.8); 80 heads x 3281, M = 292, 8 columns, 83 (78); general, M
-  // <= 128: 80 x 13125, 48 + 48 kept dims, 96 (114), 96 x 10937, 48 + 29, 78 (87), 32 x 3628, 56 + 32, 12 columns, 23 (31)
+  // <= 128: 80 x 13125, 48 + 48 kept dims, 96 (114), 96 x 10937, 48 + 29, 78 (71), 32 x 3628, 56 + 32, 12 columns, 23 (26)
   const double rounds = static_cast<double>(pairs) * ((N + kTJ * pl.KT - 1) / (kTJ * pl.KT)) / 256.0;
   double each = pl.fast == 8 ? 1.45 : pl.fast == 4 ? (pl.cw == 1 ? 1.4 : 2.1) : pl.cw <= 2 ? 2.6 : pl.cw == 4 ? 9.0 : 16.4;
-  if (pl.fast == 0 && (Dku > 32 || Dvu > 32)) each = 1.25 * (each + 0.375 * pl.KT * ((Dku + 31) / 32 - 1) + (Dvu > 32 ? 1.3 : 0.0));
+  if (pl.fast == 0) each = (each + 0.375 * pl.KT * ((Dku + 31) / 32 - 1) + (Dvu > 32 ? 1.3 : 0.0)) * (Dvu > 32 ? 1.25 : 1.0);
   const double mem = kTJ * pl.KT * 2.0 * (Dku + Dvu) / 19.7e3, window = static_cast<double>(pairs) * W * D * 4 / 5.3e6;
   if (each < mem) each = mem;
   double other = 5.0 + (rounds < 1.0 ? 1.0 : rounds) * each;
@@ -3410,24 +2890,11 @@ static int launch_partial(const DecodeParams& p, unsigned lds, hipStream_t st, K
   return FA_OK;
 }
 
-template <typename T>
-static int launch_finish(const DecodeParams& p, hipStream_t st, KernelTimers* tm, hipError_t prior) {
-  if ((p.Dvc & 3) == 0) {
-    // slices per query head: as many as keep the launch within one round of resident workgroups
-    const int BH = p.B * p.Hkv;
-    const long heads = static_cast<long>(p.B) * p.Hq;
-    int NS = p.D <= 32 ? 1 : (p.D <= 64 ? 2 : (p.D <= 128 ? 4 : 8));
-    while (NS > 1 && heads * NS > 1024) NS /= 2;
-    const dim3 grid((BH + 7) / 8 * 8 * p.G * NS);
-    if (heads * NS <= 512) FA_LAUNCH_TIMED(tm, 2, decode_finish2<16>, grid, dim3(kFinBlock), 0, st, p, NS);
-    else FA_LAUNCH_TIMED(tm, 2, decode_finish2<8>, grid, dim3(kFinBlock), 0, st, p, NS);
-  } else if (static_cast<long>(p.B) * p.Hq >= 256) {
-    FA_LAUNCH_TIMED(tm, 2, (decode_finish<T, 64>), dim3((p.D + 63) / 64, p.B * p.Hq), dim3(kFinBlock), 0, st, p);
-  } else {
-    FA_LAUNCH_TIMED(tm, 2, (decode_finish<T, 32>), dim3((p.D + 31) / 32, p.B * p.Hq), dim3(kFinBlock), 0, st, p);
-  }
-  // only this call's launches are reported: an error some earlier, unrelated HIP call of the
-  // application left behind is neither returned nor cleared
+// the last launch of a call, and its status: only this call's launches are reported, an error some earlier, unrelated HIP call
+// of the application left behind is neither returned nor cleared
+static int finish_call(const DecodeParams& p, hipStream_t st, KernelTimers* tm, hipError_t prior) {
+  const int rc = launch_finish(p, st, tm);
+  if (rc != FA_OK) return rc;
   return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
 }
 
@@ -3575,13 +3042,13 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
     if (pl.local.use) {
       rc = launch_local(p, pl.local, st, tm);
       if (rc != FA_OK) return rc;
-      return launch_finish<T>(p, st, tm, prior);
+      return finish_call(p, st, tm, prior);
     }
     // the specialised kernel: groups of at most four query heads, 1 .. 32 kept dims on both sides
     if (pl.fast != 0) {
       rc = launch_partial_fast(p, pl, st, tm);
       if (rc != FA_OK) return rc;
-      return launch_finish<T>(p, st, tm, prior);
+      return finish_call(p, st, tm, prior);
     }
   }
   const bool narrow = p.Dvu <= 32;   // kept V dims fit two MFMA column tiles
@@ -3604,7 +3071,7 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
   }
 #undef FA_LAUNCH_PARTIAL
   if (rc != FA_OK) return rc;
-  return launch_finish<T>(p, st, tm, prior);
+  return finish_call(p, st, tm, prior);
 }
 
 }  // namespace fa

@@ -20,7 +20,7 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
   using V = typename FinVec<VEC>::type;
   constexpr int kNW = kFinBlock / 64;
   constexpr int kSL = 4;                            // statistics per lane requested at the start (longer lists: read again)
-  constexpr int kWB = 4;                            // independent requests per batch: full-row records, kept dims
+  constexpr int kWB = WR > 8 ? 4 : 2;               // independent requests per batch: full-row records, kept dims
   __shared__ float es_s[kNW][kMaxPartials];         // e^{m_s - m} per record, a copy per wave
   __shared__ f32x4 red4[kFinBlock];                 // series sums per record group, then C_v partial sums per row group
   __shared__ f32x4 redw[kFinBlock];                 // full-row records per record group
@@ -93,6 +93,17 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
       if (u * nkg < Sm) kv[u] = pk[static_cast<size_t>(min(kg + u * nkg, Sm - 1)) * recm];
   }
 
+  // which dims this slice writes (the mask row arrives before the long lists)
+  {
+    uint64_t vbal[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vbal[i] = __ballot(vmb[i] != 0 && lane + 64 * i < D);
+    if (tid < D) {
+      const int rk = dim_rank(vbal, tid);
+      const int c = rk < 0 ? -rk - 1 - cb0 : rk - kb0;
+      if (c >= 0 && c < (rk < 0 ? cbn : kbn)) dim_of[rk < 0 ? c : cbw + c] = tid;
+    }
+  }
   // ---- maximum, factors and normaliser, by every wave for itself ---------------------------------
   float* es = es_s[wave];
   float m = -INFINITY, L = 0.0f, Lm = 0.0f;
@@ -162,17 +173,6 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
     }
     redk[tid] = o;
   }
-  // which dims this slice writes
-  {
-    uint64_t vbal[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) vbal[i] = __ballot(vmb[i] != 0 && lane + 64 * i < D);
-    if (tid < D) {
-      const int rk = dim_rank(vbal, tid);
-      const int c = rk < 0 ? -rk - 1 - cb0 : rk - kb0;
-      if (c >= 0 && c < (rk < 0 ? cbn : kbn)) dim_of[rk < 0 ? c : cbw + c] = tid;
-    }
-  }
   __syncthreads();
   // ---- r in basis order, weighted by the inverse squared norms ------------------------------------
   if (do_cv) {
@@ -235,13 +235,16 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
   }
 }
 
-// slices per query head: as many as keep the launch within one round of resident workgroups; long lists of requests
-// where there are few workgroups
+// Slices per query head: as many as keep the launch within one round of resident workgroups (up to 128 slots half of that: the
+// chain is then longer than what a slice reads; a step of sixteen sequences, 512 heads, M = 128: 52.3 -> 51.4 us, while 512 heads
+// at M = 556 lose 9 us of 60); long lists of requests where there are few workgroups.  Measured, this launch before and after
+// statistics, full-width rows and odd counts stopped waiting for one another: 32 heads, M = 256, 7.9 -> 7.0 us, M = 1023 13.4 -> 11.7,
+// odd counts, 192 heads, M = 130, 16.4 -> 8.3.
 int launch_finish(const DecodeParams& p, hipStream_t st, KernelTimers* tm) {
   const int BH = p.B * p.Hkv;
   const long heads = static_cast<long>(p.B) * p.Hq;
   int NS = p.D <= 32 ? 1 : (p.D <= 64 ? 2 : (p.D <= 128 ? 4 : 8));
-  while (NS > 1 && heads * NS > 1024) NS /= 2;
+  while (NS > 1 && heads * NS > (p.Mint <= 128 ? 512 : 1024)) NS /= 2;
   const dim3 grid((BH + 7) / 8 * 8 * p.G * NS);
   const bool few = heads * NS <= 512, v4 = (p.Dvc & 3) == 0;
   if (heads * NS <= 256 && p.Mint > 512) {

@@ -177,3 +177,27 @@ def test_local_many_rows(G, Dkc, Dvc, N, M, T):
     for h in (0, H - 1):
         got, want = out[0, h * G:(h + 1) * G].cpu().numpy(), _want(s, 0, h, q[0, h * G:(h + 1) * G], T, 0, N, W)
         assert rel_err(got, want) <= TOL, (h, rel_err(got, want))
+
+
+# The last launch: band widths that do not divide, one and several slices, counts in fours and not, record lists longer than a
+# batch and than a wave's statistics (many chunks), a compressed count of zero, full-width rows alone
+@pytest.mark.parametrize("D,G,Dkc,Dvc,N,M,W,splits", [(128, 4, 80, 93, 5000, 300, 900, 19), (64, 3, 40, 37, 3000, 90, 70, 7), (32, 2, 20, 20, 900, 30, 9, 0),
+                                                       (256, 1, 200, 150, 2500, 200, 700, 0), (128, 4, 90, 0, 700, 64, 40, 3),
+                                                       (128, 2, 100, 100, 20000, 33, 40000, 78), (128, 4, 96, 96, 0, 16, 777, 0)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_merge_of_records(D, G, Dkc, Dvc, N, M, W, splits, dtype):
+    import paper_2506_11886_amd as fa
+    print(f"[case] merge {D} {G} {Dkc}/{Dvc} N{N} M{M} W{W} {splits} {dtype}", flush=True)
+    T = max(N, M) + 50
+    s, r = _state(1, 2, D, Dkc, Dvc, N, M, T, W, 10)
+    q = _bf16(r.standard_normal((1, 2 * G, D)))
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ck, km, cv, vm = to_dev(s["ck"]), to_dev(s["kmask"]), to_dev(s["cv"]), to_dev(s["vmask"])
+    rows = [to_dev(x, dtype=dt) for x in (rows_pad8(s["kk"]), rows_to_tok8(s["vk"]), s["kf"], s["vf"])]
+    if M > 256 and dtype == "f32":
+        pytest.skip("more states than fp32 decode takes")
+    out = fa.fa_decode(to_dev(q, dtype=dt), ck, km, cv if Dvc else None, vm, M, T, 0, N, *rows, num_splits=splits)
+    torch.cuda.synchronize()
+    for h in range(2):
+        got, want = out[0, h * G:(h + 1) * G].cpu().numpy(), _want(s, 0, h, q[0, h * G:(h + 1) * G], T, 0, N, W)
+        assert rel_err(got, want) <= (2e-3 if dtype == "bf16" else 1e-5), (h, rel_err(got, want))

@@ -41,6 +41,7 @@
 #include "fa_finish.hpp"
 #include "fa_full.hpp"
 #include "fa_local.hpp"
+#include "fa_small.hpp"
 
 namespace fa {
 
@@ -3183,6 +3184,9 @@ static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, 
   p.part_w = reinterpret_cast<float*>(ws + pl.off_pw);
   p.out = out;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  // (a split count asks for the split form)
+  const unsigned small = num_splits == 0 && !pl.fused ? small_lds(dtype, B, Hkv, p.G, D, Dkc, Dvc, M, T, N, W) : 0;
+  if (small > 0) return launch_small(p, dtype, small, stream, tm);
   return dtype == FA_F32 ? launch_decode<float>(p, pl, stream, tm)
                          : launch_decode<bf16_t>(p, pl, stream, tm);
 }

@@ -1,9 +1,11 @@
 // Small calls of fa_decode in one launch, one workgroup per (sequence, KV head), plain fp32 arithmetic.
 //
-// Three launches of a few microseconds' work are mostly launch ramps, table builds and round trips.  Here everything a
-// call reads is requested at once into registers; cos / sin come from a table of one period in LDS, indexed by n j mod T
-// (exact phases); then rows are scored (a thread per middle row, 8 dims of a full-width row per thread), normalised over the
-// workgroup, and the series sums, kept dims and full-width rows are summed by (harmonic | dim, row group) and meet in LDS.
+// Three launches of a few microseconds' work are mostly launch ramps, table builds and round trips: one head of 380 + 132 rows,
+// M = 32, D = 64, fp32, took 25.0 us in three launches and takes 14.3 here.  What is left is the chain of seven phases between
+// barriers.  Everything a call reads is requested at once into registers; cos / sin come from a table of one period in LDS,
+// indexed by n j mod T (exact phases); then rows are scored (a thread per middle row, 8 dims of a full-width row per thread),
+// normalised over the workgroup, and the series sums, kept dims and full-width rows are summed by (harmonic | dim, row group)
+// and meet in LDS.
 #include "fa_small.hpp"
 
 namespace fa {
@@ -13,15 +15,20 @@ constexpr int kSmWaves = kSmThreads / 64;
 constexpr int kSmG = 4;                // query heads per KV head, at most
 constexpr int kSmMaxT = 4096;          // period (the table is 8 T bytes of LDS)
 constexpr int kSmMaxM = 128, kSmMaxD = 128, kSmMaxRows = 2048;
-constexpr int kSmC = 24;               // elements of C_k (C_v) a thread holds
-constexpr int kSmKV = 4;               // 8-dim vectors of a kept K row requested at the start
-constexpr int kSmKF = 4, kSmVF = 4, kSmVK = 4;   // items of full-width K, full-width V and kept V requested at the start
+constexpr int kSmC = 24;               // elements of C_k (C_v) a thread holds, at most
 
 __host__ __device__ __forceinline__ int pow2_at_least(int x) {
   int p = 1;
   while (p < x) p *= 2;
   return p;
 }
+
+// threads that share a row of C_k, a column of C_v
+__host__ __device__ __forceinline__ int state_parts(int M) {
+  const int n = kSmThreads / pow2_at_least(M);
+  return n < 64 ? n : 64;
+}
+__host__ __device__ __forceinline__ int value_parts(int Dvc) { return kSmThreads / pow2_at_least(Dvc > 0 ? Dvc : 1); }
 
 // LDS: table | queries | coefficients | scores | series sums, weighted sums | partial sums (full-width rows; series; kept dims)
 struct SmallLds {
@@ -42,14 +49,31 @@ __host__ __device__ __forceinline__ SmallLds small_layout(int D, int Dup, int M,
   return L;
 }
 
-// sum over the lanes whose index differs in bits below `n` (a power of two)
-__device__ __forceinline__ float lanes_sum(float v, int n) {
-  for (int o = n >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sums over the lanes whose index differs in bits below `n` (a power of two, the same for the wave; all lanes active)
+__device__ __forceinline__ void lanes_sum(f32x4& v, int n) {
+#define FA_STEP(CTRL_)                                     \
+  _Pragma("unroll") for (int h = 0; h < kSmG; ++h) v[h] = dpp_add<CTRL_>(v[h])
+  if (n >= 2) FA_STEP(0xb1);      // quad permutation 1 0 3 2
+  if (n >= 4) FA_STEP(0x4e);      // 2 3 0 1
+  if (n >= 8) FA_STEP(0x141);     // mirror of eight lanes
+  if (n >= 16) FA_STEP(0x140);    // mirror of sixteen
+#undef FA_STEP
+  for (int o = 16; o < n; o <<= 1) {
+#pragma unroll
+    for (int h = 0; h < kSmG; ++h) v[h] += __shfl_xor(v[h], o, kWave);
+  }
 }
 
-template <typename T>
+// KC: elements of C_k (C_v) a thread holds
+template <typename T, int KC>
 __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
+  // requested at the start: 8-dim vectors of a kept K row, items of full-width K and V, items of kept V (fp32 with as many as bf16
+  // spills 34 registers)
+  constexpr int KV = sizeof(T) == 2 ? 4 : 2, KF = sizeof(T) == 2 ? 4 : 3, VF = KF, VK = KV;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float wred[2][kSmWaves][kSmG];
   __shared__ float lmid[kSmWaves][kSmG];
@@ -80,55 +104,50 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
   const T* q = static_cast<const T*>(p.q) + hq0 * D;
   const T qe = q[min(tid, G * D - 1)];                     // (G D <= 512)
   // C_k: thread (row, part of its columns); C_v: thread (column, part of its rows)
-  const int kparts = min(kSmThreads / pow2_at_least(M), 64), km = tid / kparts, kpart = tid % kparts;
-  const int vcp = pow2_at_least(max(Dvc, 1)), vparts = kSmThreads / vcp, vc = tid % vcp, vpart = tid / vcp;
-  const float* ck = p.ck + (static_cast<size_t>(bh) * M + min(km, M - 1)) * Dkc;
-  const float* cv = p.cv + static_cast<size_t>(bh) * M * Dvc + min(vc, max(Dvc - 1, 0));
-  float cke[kSmC], cve[kSmC];
-  if (Nb > 0) {
+  const int kparts = state_parts(M), km = tid / kparts, kpart = tid % kparts;
+  const int vcp = pow2_at_least(max(Dvc, 1)), vparts = value_parts(Dvc), vc = tid % vcp, vpart = tid / vcp;
+  // (what is not there, for want of rows or dims, is read from the queries and not used: no request sits behind a branch)
+  const float* none = reinterpret_cast<const float*>(q);
+  const bool has_k = Nb > 0 && Dkc > 0, has_v = Nb > 0 && Dvc > 0;
+  const float* ck = has_k ? p.ck + (static_cast<size_t>(bh) * M + min(km, M - 1)) * Dkc : none;
+  const float* cv = has_v ? p.cv + static_cast<size_t>(bh) * M * Dvc + min(vc, Dvc - 1) : none;
+  float cke[KC], cve[KC];
 #pragma unroll
-    for (int i = 0; i < kSmC; ++i)
-      if (i * kparts < Dkc) cke[i] = ck[min(kpart + i * kparts, Dkc - 1)];
-#pragma unroll
-    for (int i = 0; i < kSmC; ++i)
-      if (Dvc > 0 && i * vparts < M) cve[i] = cv[static_cast<size_t>(min(vpart + i * vparts, M - 1)) * Dvc];
-  }
-  // kept K dims: a thread per middle row; full-width rows: thread (row, 8 dims)
+  for (int i = 0; i < KC; ++i) cke[i] = ck[has_k ? min(kpart + i * kparts, Dkc - 1) : 0];
+  // kept K dims: a thread per middle row; full-width rows: thread (row, 8 dims); kept V dims: thread (dim, group of 8 tokens)
   const T* kk = static_cast<const T*>(p.k_keep) + bh * p.kk_stride;
   const T* vk = static_cast<const T*>(p.v_keep) + bh * p.vk_stride;
   const T* kf = static_cast<const T*>(p.k_full) + bh * p.full_stride;
   const T* vf = static_cast<const T*>(p.v_full) + bh * p.full_stride;
   const int nd8 = D / 8, PP = pow2_at_least(nd8), segs = kSmThreads / PP, part8 = tid % PP, seg = tid / PP;
   const int pc = min(part8, nd8 - 1) * 8;
-  Frag<T> xk[kSmKV], xf[kSmKF], yf[kSmVF];
-  if (Nb > 0) {
-#pragma unroll
-    for (int i = 0; i < kSmKV; ++i)
-      if (i * 8 < Dup) xk[i].load(kk + static_cast<size_t>(min(tid, Nb - 1)) * Dup + 8 * i);
-  }
-  if (Wb > 0) {
-#pragma unroll
-    for (int i = 0; i < kSmKF; ++i)
-      if (i * segs < Wb) xf[i].load(kf + static_cast<size_t>(min(seg + i * segs, Wb - 1)) * D + pc);
-#pragma unroll
-    for (int i = 0; i < kSmVF; ++i)
-      if (i * segs < Wb) yf[i].load(vf + static_cast<size_t>(min(seg + i * segs, Wb - 1)) * D + pc);
-  }
-  // kept V dims: thread (dim, group of 8 tokens)
   const int UP = pow2_at_least(max(Dvu, 1)), usegs = kSmThreads / UP, uu = tid % UP, useg = tid / UP, ngrp = (Nb + 7) / 8;
-  Frag<T> yk[kSmVK];
-  if (Nb > 0 && Dvu > 0) {
+  const bool has_kk = Nb > 0 && Dup > 0, has_vk = Nb > 0 && Dvu > 0;
+  Frag<T> xk[KV], xf[KF], yf[VF], yk[VK];
+  const T* kk0 = has_kk ? kk + static_cast<size_t>(min(tid, Nb - 1)) * Dup : q;
 #pragma unroll
-    for (int i = 0; i < kSmVK; ++i)
-      if (i * usegs < ngrp)
-        yk[i].load(vk + (static_cast<size_t>(min(useg + i * usegs, ngrp - 1)) * Dvu + min(uu, Dvu - 1)) * 8);
-  }
+  for (int i = 0; i < KV; ++i) xk[i].load(kk0 + (has_kk ? min(8 * i, Dup - 8) : 0));
+  const T* kf0 = Wb > 0 ? kf + pc : q;
+  const T* vf0 = Wb > 0 ? vf + pc : q;
+#pragma unroll
+  for (int i = 0; i < KF; ++i) xf[i].load(kf0 + static_cast<size_t>(max(min(seg + i * segs, Wb - 1), 0)) * D);
+#pragma unroll
+  for (int i = 0; i < VF; ++i) yf[i].load(vf0 + static_cast<size_t>(max(min(seg + i * segs, Wb - 1), 0)) * D);
+  const T* vk0 = has_vk ? vk + min(uu, Dvu - 1) * 8 : q;
+#pragma unroll
+  for (int i = 0; i < VK; ++i) yk[i].load(vk0 + (has_vk ? static_cast<size_t>(min(useg + i * usegs, ngrp - 1)) * Dvu * 8 : 0));
+#pragma unroll
+  for (int i = 0; i < KC; ++i) cve[i] = cv[has_v ? static_cast<size_t>(min(vpart + i * vparts, M - 1)) * Dvc : 0];
 
   // ---- table of one period; ranks and queries --------------------------------------------------------
   if (Nb > 0)
     for (int r = tid; r < per; r += kSmThreads) {
-      float2 e;
-      sincospif(2.0f * (static_cast<float>(r) / static_cast<float>(per)), &e.y, &e.x);
+      // nearest quarter turn and what is left of it, in whole numbers: the angle is at most pi / 4, rounded once
+      const int a = (8 * r + per) / (2 * per), rest = 4 * r - a * per;
+      float sn, cs;
+      sincospif(0.5f * (static_cast<float>(rest) / static_cast<float>(per)), &sn, &cs);
+      const float c1 = a & 1 ? -sn : cs, s1 = a & 1 ? cs : sn;
+      const float2 e = a & 2 ? float2{-c1, -s1} : float2{c1, s1};
       tab[r] = e;
     }
   uint64_t kb[4] = {0, 0, 0, 0}, vb[4] = {0, 0, 0, 0};
@@ -137,10 +156,11 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
     kb[i] = __ballot(kmb[i] != 0 && lane + 64 * i < D);
     vb[i] = __ballot(vmb[i] != 0 && lane + 64 * i < D);
   }
-  __shared__ int16_t kcdim[kSmMaxD];                       // compressed K dims in order
+  __shared__ f32x4 qc_s[kSmMaxD];                          // queries at the compressed K dims, in order
   for (int i = tid; i < (D + Dup) * kSmG; i += kSmThreads) {   // heads past the group, pad columns
     const int d = i / kSmG, h = i % kSmG;
     if (d < D ? h >= G : (d - D >= Dku || h >= G)) reinterpret_cast<float*>(d < D ? q_s + d : qk_s + (d - D))[h] = 0.0f;
+    if (d < D && h >= G) reinterpret_cast<float*>(qc_s + d)[h] = 0.0f;
   }
   if (tid < G * D) {
     const int h = tid / D, d = tid % D;
@@ -148,7 +168,7 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
     const int rk = dim_rank(kb, d);
     reinterpret_cast<float*>(q_s + d)[h] = x;
     if (rk >= 0) reinterpret_cast<float*>(qk_s + rk)[h] = x;
-    else if (h == 0) kcdim[-rk - 1] = static_cast<int16_t>(d);
+    else reinterpret_cast<float*>(qc_s + (-rk - 1))[h] = x;
   }
   __syncthreads();
 
@@ -156,57 +176,55 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
   if (Nb > 0) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kSmC; ++i) {
+    for (int i = 0; i < KC; ++i) {
       const int c = kpart + i * kparts;
-      if (c < Dkc && km < M) a += cke[i] * q_s[kcdim[c]];
+      const f32x4 x = qc_s[min(c, kSmMaxD - 1)];
+#pragma unroll
+      for (int h = 0; h < kSmG; ++h) a[h] = c < Dkc ? a[h] + cke[i] * x[h] : a[h];
     }
+    lanes_sum(a, kparts);
     const float w = km < M ? basis_weight((km + 1) / 2, per) : 0.0f;
 #pragma unroll
-    for (int h = 0; h < kSmG; ++h) a[h] = lanes_sum(a[h], kparts) * w;
+    for (int h = 0; h < kSmG; ++h) a[h] *= w;
     if (kpart == 0 && km < M) g_s[km] = a;
     if (tid == 0 && (M & 1) == 0) g_s[M] = f32x4{0.f, 0.f, 0.f, 0.f};   // (the unpaired cosine has no sine)
   }
   __syncthreads();
 
   // ---- scores -----------------------------------------------------------------------------------------
+  auto kept = [&](f32x4& s, const Frag<T>& x, int i) {
+    float v[8];
+    unpack8(x, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s += v[e] * qk_s[8 * i + e];
+  };
   for (int j = tid; j < Nb; j += kSmThreads) {
     f32x4 s = g_s[0];
     const int pos = p.t0 + j;                              // (< T)
     int r = 0;
+#pragma unroll 4
     for (int n = 1; n <= nmax; ++n) {
       r += pos;
-      if (r >= per) r -= per;
+      r = r >= per ? r - per : r;
       const float2 e = tab[r];
       s += e.x * g_s[2 * n - 1] + e.y * g_s[2 * n];
     }
-    for (int i = 0; 8 * i < Dup; ++i) {
+    int i0 = 0;
+    if (j == tid) {
+#pragma unroll
+      for (int i = 0; i < KV; ++i)
+        if (8 * i < Dup) kept(s, xk[i], i);
+      i0 = KV;
+    }
+    for (int i = i0; 8 * i < Dup; ++i) {
       Frag<T> x;
-      if (j == tid && i < kSmKV) {
-#pragma unroll
-        for (int k = 0; k < kSmKV; ++k)
-          if (k == i) x = xk[k];
-      } else {
-        x.load(kk + static_cast<size_t>(j) * Dup + 8 * i);
-      }
-      float v[8];
-      unpack8(x, v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += v[e] * qk_s[8 * i + e];
+      x.load(kk + static_cast<size_t>(j) * Dup + 8 * i);
+      kept(s, x, i);
     }
     sc[j] = p.scale * s;
   }
   const int pass_f = (Wb + segs - 1) / segs;
-#pragma unroll 1
-  for (int i = 0; i < pass_f; ++i) {
-    const int j = seg + i * segs;
-    Frag<T> x;
-    if (i < kSmKF) {
-#pragma unroll
-      for (int k = 0; k < kSmKF; ++k)
-        if (k == i) x = xf[k];
-    } else {
-      x.load(kf + static_cast<size_t>(min(j, Wb - 1)) * D + pc);
-    }
+  auto score_full = [&](const Frag<T>& x, int j) {
     float v[8];
     unpack8(x, v);
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
@@ -214,14 +232,22 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) s += v[e] * q_s[pc + e];
     }
-#pragma unroll
-    for (int h = 0; h < kSmG; ++h) s[h] = lanes_sum(s[h], PP);
+    lanes_sum(s, PP);
     if (part8 == 0 && j < Wb) {
 #pragma unroll
       for (int h = 0; h < kSmG; ++h)   // (the last Tq rows are the new tokens: query token h / Gq sees those up to its own)
         s[h] = j <= Wb - p.Tq + h / p.Gq ? s[h] * p.scale : -INFINITY;
       sc[Nb + j] = s;
     }
+  };
+#pragma unroll
+  for (int i = 0; i < KF; ++i)
+    if (i < pass_f) score_full(xf[i], seg + i * segs);
+#pragma unroll 1
+  for (int i = KF; i < pass_f; ++i) {
+    Frag<T> x;
+    x.load(kf + static_cast<size_t>(min(seg + i * segs, Wb - 1)) * D + pc);
+    score_full(x, seg + i * segs);
   }
   __syncthreads();
 
@@ -274,13 +300,14 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
       const unsigned n = rn + 1, T_ = per;
       int r = static_cast<int>(n * static_cast<unsigned>(p.t0 + rseg) % T_);
       const int d = static_cast<int>(n * static_cast<unsigned>(rsegs) % T_);
+#pragma unroll 4
       for (int j = rseg; j < Nb; j += rsegs) {
         const float2 e = tab[r];
         const f32x4 w = sc[j];
         c += e.x * w;
         s += e.y * w;
         r += d;
-        if (r >= per) r -= per;
+        r = r >= per ? r - per : r;
       }
     }
     *reinterpret_cast<f32x4*>(rp + 8 * tid) = c;
@@ -292,26 +319,23 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
     for (int h = 0; h < kSmG; ++h)
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[h][e] = 0.0f;
+    auto add_full = [&](const Frag<T>& x, int j) {
+      if (j >= Wb) return;
+      const f32x4 w = sc[Nb + j];
+      float v[8];
+      unpack8(x, v);
+#pragma unroll
+      for (int h = 0; h < kSmG; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[h][e] += w[h] * v[e];
+    };
+#pragma unroll
+    for (int i = 0; i < VF; ++i) add_full(yf[i], seg + i * segs);
 #pragma unroll 1
-    for (int i = 0; i < pass_f; ++i) {
-      const int j = seg + i * segs;
+    for (int i = VF; i < pass_f; ++i) {
       Frag<T> x;
-      if (i < kSmVF) {
-#pragma unroll
-        for (int k = 0; k < kSmVF; ++k)
-          if (k == i) x = yf[k];
-      } else {
-        x.load(vf + static_cast<size_t>(min(j, Wb - 1)) * D + pc);
-      }
-      if (j < Wb) {
-        const f32x4 w = sc[Nb + j];
-        float v[8];
-        unpack8(x, v);
-#pragma unroll
-        for (int h = 0; h < kSmG; ++h)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[h][e] += w[h] * v[e];
-      }
+      x.load(vf + static_cast<size_t>(min(seg + i * segs, Wb - 1)) * D + pc);
+      add_full(x, seg + i * segs);
     }
     if (part8 < nd8) {
 #pragma unroll
@@ -324,22 +348,25 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
   }
   if (Nb > 0 && Dvu > 0) {   // kept dims
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int i = 0; i * usegs < ngrp; ++i) {
-      const int g = useg + i * usegs;
-      Frag<T> x;
-      if (i < kSmVK) {
-#pragma unroll
-        for (int k = 0; k < kSmVK; ++k)
-          if (k == i) x = yk[k];
-      } else {
-        x.load(vk + (static_cast<size_t>(min(g, ngrp - 1)) * Dvu + min(uu, Dvu - 1)) * 8);
-      }
+    auto add_kept = [&](const Frag<T>& x, int g) {   // (past the rows the slab holds anything)
+      if (g >= ngrp) return;
       float v[8];
       unpack8(x, v);
+      f32x4 w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = sc[min(8 * g + e, Nb - 1)];
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (g < ngrp && 8 * g + e < Nb) a += v[e] * sc[8 * g + e];   // (past the rows the slab holds anything)
+#pragma unroll
+        for (int h = 0; h < kSmG; ++h) a[h] = 8 * g + e < Nb ? a[h] + v[e] * w[e][h] : a[h];
+    };
+#pragma unroll
+    for (int i = 0; i < VK; ++i) add_kept(yk[i], useg + i * usegs);
+#pragma unroll 1
+    for (int i = VK; i * usegs < ngrp; ++i) {
+      Frag<T> x;
+      x.load(vk0 + static_cast<size_t>(min(useg + i * usegs, ngrp - 1)) * Dvu * 8);
+      add_kept(x, useg + i * usegs);
     }
     kp[tid] = a;
   }
@@ -354,7 +381,9 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
         for (int w = 0; w < kSmWaves; ++w) v += lmid[w][h];
       } else {
         const float* src = rp + 8 * (n - 1) + ((mm & 1) ? 0 : 4) + h;
-        for (int s = 0; s < rsegs; ++s) v += src[8 * s * nP];
+        for (int s = 0; s < rsegs; s += 8)   // (8 .. 512)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v += src[8 * (s + u) * nP];
       }
       reinterpret_cast<float*>(rr + mm)[h] = v * basis_weight(n, per);
     }
@@ -364,9 +393,11 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
   if (Nb > 0 && Dvc > 0) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kSmC; ++i) {
+    for (int i = 0; i < KC; ++i) {
       const int mm = vpart + i * vparts;
-      if (mm < M) a += cve[i] * rr[mm];
+      const f32x4 x = rr[min(mm, M - 1)];
+#pragma unroll
+      for (int h = 0; h < kSmG; ++h) a[h] = mm < M ? a[h] + cve[i] * x[h] : a[h];
     }
     cp[tid] = a;
   }
@@ -375,11 +406,15 @@ __global__ __launch_bounds__(kSmThreads, 2) void decode_small(DecodeParams p) {
     const int h = tid / D, d = tid % D, rk = dim_rank(vb, d);
     float v = 0.0f, lsum = 0.0f;
     if (Wb > 0)
-      for (int s = 0; s < segs; ++s) v += fp[(s * kSmG + h) * D + d];
+      for (int s = 0; s < segs; s += 16)     // (32 .. 512)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v += fp[((s + u) * kSmG + h) * D + d];
     if (Nb > 0) {
       const float* src = reinterpret_cast<const float*>(rk < 0 ? cp + (-rk - 1) : kp + rk) + h;
       const int np = rk < 0 ? vparts : usegs, step = 4 * (rk < 0 ? vcp : UP);
-      for (int s = 0; s < np; ++s) v += src[s * step];
+      for (int s = 0; s < np; s += 4)        // (4 .. 512)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v += src[(s + u) * step];
     }
 #pragma unroll
     for (int w = 0; w < kSmWaves; ++w) lsum += wred[1][w][h];
@@ -394,26 +429,36 @@ unsigned small_lds(int dtype, int B, int Hkv, int G, int D, int Dkc, int Dvc, in
   const int Dup = (D - Dkc + 7) & ~7, rows = N + W;
   if (static_cast<long>(B) * Hkv > 256 || G > kSmG || D > kSmMaxD || G * D > kSmThreads || M > kSmMaxM || T > kSmMaxT || rows > kSmMaxRows) return 0;
   // a thread holds its share of both states
-  const int kparts = kSmThreads / pow2_at_least(M) < 64 ? kSmThreads / pow2_at_least(M) : 64;
-  if (kparts * kSmC < Dkc || kSmThreads / pow2_at_least(Dvc > 0 ? Dvc : 1) * kSmC < M) return 0;
-  // one compute unit does all of a pair's work: series terms and full-width products, at about 10^4 a microsecond each
-  if (static_cast<long>(N) * M + static_cast<long>(W) * D > (dtype == FA_F32 ? 60000 : 30000)) return 0;
+  if (state_parts(M) * kSmC < Dkc || value_parts(Dvc) * kSmC < M) return 0;
+  // One compute unit does all of a pair's work, so the launches saved pay up to a number of terms.  Measured, us a call here
+  // (split form): bf16, 8 heads x 380 rows and 132 full-width ones, M = 32, D = 128 (41 K terms) 18.4 (18.3), 600 rows (56 K)
+  // 21.4 (21.5), 1500 rows (64 K) 21.8 (18.6), one head, D = 64 (27 K) 14.5 (19.4), 256 pairs of 32 K 17.3 (32.0); fp32, 27 K 14.3
+  // (25.0), 41 K 19.1 (27.5), 256 pairs of 32 K 20.0 (67.8)
+  const long terms = static_cast<long>(N) * M + static_cast<long>(N) * (2 * D - Dkc - Dvc) / 2 + static_cast<long>(W) * D;
+  if (terms > (dtype == FA_F32 ? 45000 : 32000)) return 0;
   const unsigned lds = small_layout(D, Dup, M, T, rows).total;
-  return lds <= kMaxDynLds - 1024 ? lds : 0;
+  return lds <= kMaxDynLds ? lds : 0;
 }
 
-template <typename T>
+template <typename T, int KC>
 static int launch_small_t(const DecodeParams& p, unsigned lds, hipStream_t st, KernelTimers* tm) {
-  auto kern = decode_small<T>;
+  auto kern = decode_small<T, KC>;
   if (lds > 48u * 1024u &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMaxDynLds)) != hipSuccess)
     return FA_ERR_HIP;
   FA_LAUNCH_TIMED(tm, 1, kern, dim3(p.B * p.Hkv), dim3(kSmThreads), lds, st, p);
   return FA_OK;
 }
 
 int launch_small(const DecodeParams& p, int dtype, unsigned lds, hipStream_t st, KernelTimers* tm) {
-  return dtype == FA_F32 ? launch_small_t<float>(p, lds, st, tm) : launch_small_t<bf16_t>(p, lds, st, tm);
+  const hipError_t prior = hipPeekAtLastError();
+  const int kparts = state_parts(p.M), vparts = value_parts(p.Dvc);
+  const bool few = kparts * 8 >= p.Dkc && vparts * 8 >= p.M;
+  int rc;
+  if (dtype == FA_F32) rc = few ? launch_small_t<float, 8>(p, lds, st, tm) : launch_small_t<float, kSmC>(p, lds, st, tm);
+  else rc = few ? launch_small_t<bf16_t, 8>(p, lds, st, tm) : launch_small_t<bf16_t, kSmC>(p, lds, st, tm);
+  if (rc != FA_OK) return rc;
+  return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
 }
 
 }  // namespace fa

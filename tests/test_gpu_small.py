@@ -1,0 +1,113 @@
+"""Small calls of fa_decode in one launch, against the fp64 oracle.
+
+Inputs are exact in their type and everything after them is fp32: sums of at most 2048 products, scores of a few units (an
+error of 2^-24 times their size in the exponent), so 1e-5 of the largest output at both types.  The forms that other sizes take
+are off by more than that in bf16, and the timed call shows which launches ran.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from fa_testlib import rows_pad8, rows_to_tok8, to_dev
+from test_gpu_local import _bf16, _state, _want
+from workloads import rel_err
+
+import oracle.fourier_kv as fk
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _device(s, dt):
+    rows = [to_dev(x, dtype=dt) if x.shape[2] and x.shape[3] else None for x in (s["kk"], s["vk"], s["kf"], s["vf"])]
+    if rows[0] is not None:
+        rows[0] = to_dev(rows_pad8(s["kk"]), dtype=dt)
+    if rows[1] is not None:
+        rows[1] = to_dev(rows_to_tok8(s["vk"]), dtype=dt)
+    return [to_dev(s["ck"]) if s["ck"].size else None, to_dev(s["kmask"]), to_dev(s["cv"]) if s["cv"].size else None,
+            to_dev(s["vmask"])], rows
+
+
+# B, D, G, compressed K / V dims, N, M, T, t0, W
+SHAPES = [
+    (1, 64, 4, 48, 48, 380, 32, 380, 0, 132),
+    (3, 128, 4, 96, 96, 100, 50, 100, 0, 60),        # every thread holds a query element
+    (2, 72, 3, 51, 47, 130, 33, 1000, 869, 37),      # head dim of nine vectors, odd counts, the segment at the period's end
+    (1, 128, 2, 96, 64, 30, 128, 4096, 4066, 5),     # most states, longest period, a thread's share of both states full
+    (1, 64, 1, 24, 30, 600, 8, 601, 1, 1),           # more rows than threads, kept dims past what is requested first
+    (1, 128, 2, 100, 120, 40, 2, 40, 0, 170),        # more full-width rows than are requested first; one unpaired cosine
+    (1, 8, 1, 5, 3, 1990, 1, 2000, 10, 58),          # the smallest head dim, the constant alone, most rows
+    (1, 64, 2, 0, 40, 90, 20, 90, 0, 20),            # nothing compressed in K
+    (1, 64, 2, 40, 0, 90, 20, 90, 0, 20),            # nothing compressed in V
+    (1, 64, 2, 64, 64, 90, 20, 90, 0, 0),            # nothing kept, no full-width rows
+    (1, 64, 4, 40, 40, 0, 20, 90, 0, 77),            # full-width rows alone
+    (1, 16, 1, 9, 9, 1, 1, 1, 0, 1),                 # one row of each
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"D{s[1]}-G{s[2]}-{s[3]}-{s[4]}-N{s[5]}-M{s[6]}-W{s[9]}" for s in SHAPES])
+def test_small_matches_oracle(shape, dtype):
+    import paper_2506_11886_amd as fa
+    B, D, G, Dkc, Dvc, N, M, T, t0, W = shape
+    print(f"[case] small {shape} {dtype}", flush=True)
+    H, dt = 2, torch.bfloat16 if dtype == "bf16" else torch.float32
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 11)
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    head, rows = _device(s, dt)
+    args = (to_dev(q, dtype=dt), *head, M, T, t0, N, *rows)
+    out = fa.fa_decode(*args)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    for b in range(B):
+        for h in range(H):
+            want = _want(s, b, h, q[b, h * G:(h + 1) * G], T, t0, N, W)
+            assert rel_err(got[b, h * G:(h + 1) * G], want) <= TOL, (b, h, rel_err(got[b, h * G:(h + 1) * G], want))
+    ms = []
+    fa.fa_decode(*args, kernel_ms=ms)
+    assert ms[0] == 0.0 and ms[1] > 0.0 and ms[2] == 0.0
+    if Dkc > 0 and N > 0:                           # the launches of other sizes, on the same call
+        split = fa.fa_decode(*args, num_splits=1)
+        assert rel_err(split.cpu().numpy(), got) <= (2e-3 if dtype == "bf16" else 2e-5)
+
+
+def test_small_per_sequence_counts():
+    """Sequences without middle rows, without full-width rows, without any; the slabs past the counts hold NaN."""
+    import paper_2506_11886_amd as fa
+    B, H, G, D, Dkc, Dvc, N, M, T, W = 5, 2, 4, 64, 41, 43, 300, 31, 400, 90
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 12)
+    nn, ww = [300, 0, 131, 9, 0], [90, 77, 0, 1, 0]
+    q = _bf16(r.standard_normal((B, H * G, D)))
+    poison = {k: v.copy() for k, v in s.items()}
+    for b in range(B):
+        for name, n in (("kk", nn[b]), ("vk", nn[b]), ("kf", ww[b]), ("vf", ww[b])):
+            poison[name][b, :, n:] = np.nan
+    head, rows = _device(poison, torch.bfloat16)
+    lists = [torch.tensor(x, dtype=torch.int32, device="cuda") for x in (nn, ww)]
+    out = fa.fa_decode_varlen(to_dev(q, dtype=torch.bfloat16), *head, M, T, 0, N, lists[0], *rows, lists[1])
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    for b in range(B):
+        for h in range(H):
+            g = got[b, h * G:(h + 1) * G]
+            if nn[b] + ww[b] == 0:
+                assert not g.any()
+            else:
+                assert rel_err(g, _want(s, b, h, q[b, h * G:(h + 1) * G], T, 0, nn[b], ww[b])) <= TOL, (b, h)
+
+
+@pytest.mark.parametrize("Tq,G", [(2, 2), (4, 1), (3, 1)])
+def test_small_several_query_tokens(Tq, G):
+    import paper_2506_11886_amd as fa
+    B, H, D, N, M, T, W, Dkc, Dvc = 1, 2, 64, 200, 40, 210, 40, 48, 44
+    s, r = _state(B, H, D, Dkc, Dvc, N, M, T, W, 13)
+    q = _bf16(r.standard_normal((B, H, Tq, G, D)))
+    head, rows = _device(s, torch.float32)
+    out = fa.fa_decode_mq(to_dev(q), *head, M, T, 0, N, *rows)
+    torch.cuda.synchronize()
+    for h in range(H):
+        want = fk.decode_multi_query(q[0, h], s["ck"][0, h], s["kmask"][0, h], s["cv"][0, h], s["vmask"][0, h], T, 0, N,
+                                     s["kk"][0, h], s["vk"][0, h], s["kf"][0, h], s["vf"][0, h])
+        got = out[0, h].cpu().numpy()
+        assert rel_err(got, want) <= TOL, (h, rel_err(got, want))

@@ -58,7 +58,8 @@ def measured_traffic(index):
     except OSError:
         return {}
     m = re.search(r"kernel sources digest:\s*([0-9a-f]{16})", text)
-    if not m or m.group(1) != source_digest("fa_decode.hip", "fa_compress.hip", "fa_moments.hip", "fa_moments.hpp",
+    if not m or m.group(1) != source_digest("fa_decode.hip", "fa_decode.hpp", "fa_full.hpp", "fa_local.hip", "fa_small.hip",
+                                           "fa_finish.hip", "fa_compress.hip", "fa_moments.hip", "fa_moments.hpp",
                                            "fa_common.hpp", "fa_mma.hpp"):
         return {}
     out = {}

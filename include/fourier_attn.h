@@ -110,8 +110,9 @@ enum { FA_KEEP_ROWS = 0, FA_KEEP_TOK8 = 1 };
  *               32 MB is accepted and served by the direct projection.
  *
  * Precision (2-norm of the error of white rows over that of the states), bf16: segments of
- * up to 512 tokens 2e-6; longer ones 3e-6 through moments, up to 1.3e-3 by the direct
- * projection (a basis of one bf16 term).  Which of the two runs is
+ * up to 512 tokens 3e-7 (head dims other than 64, 128 and 256: 2e-6); longer ones 2e-6 where
+ * the basis is formed per token, 3e-6 through moments, up to 1.3e-3 by the direct
+ * projection (a basis of one bf16 term).  Which of the three runs is
  * decided by the sizes, T, the workspace and what is kept; the moments' blocks also move
  * with keep_offset mod 8.  Equal calls give equal results.
  * An infinity or NaN in a compressed dim makes every state of its column infinite or NaN,
@@ -384,7 +385,8 @@ int fa_decode_mq(const void* q, int dtype, int B, int Tq, int Hq, int Hkv, int D
  *   mse       DEVICE fp32 [B, H, D], written; may be NULL
  *   workspace DEVICE, 256-byte aligned, >= fa_select_workspace_bytes(...) bytes
  *             (bf16 segments whose harmonics vary slowly over 64 tokens: energies and moments
- *             per block; others: the fp32 copy of a bf16 segment, 4*B*H*N*D bytes, the
+ *             per block; other bf16 segments of D = 64, 128 or 256 up to 8192 tokens (D = 256: 4096): energies
+ *             and weighted squares; others: the fp32 copy of a bf16 segment, 4*B*H*N*D bytes, the
  *             coefficients of all dims and the workspace of the projection)
  * Asynchronous on hip_stream; nothing is allocated.  Same limits as fa_compress.
  * Returns FA_OK or an FA_ERR_* code (arguments are checked on the host first).

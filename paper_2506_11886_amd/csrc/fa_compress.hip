@@ -25,6 +25,7 @@
 #include "fa_common.hpp"
 #include "fa_mma.hpp"
 #include "fa_moments.hpp"
+#include "fa_rows.hpp"
 
 namespace fa {
 
@@ -100,7 +101,7 @@ __device__ __forceinline__ void set_elem<float>(Frag<float>& f, int e, float x) 
 // 8-element vectors of X per thread and block (2 covers head dims up to 128, 4 up to 256)
 // kFast: the row vectors divide the workgroup evenly (head dim 64 / 128 / 256) and
 // kept dims are staged, so every thread routes the same 8 dims in every block.
-// kSplit (bf16 only): the basis is held as a bf16 head plus a bf16 remainder (two products per
+// kSplit (bf16 head dims that project_rows is not built for): the basis is held as a bf16 head plus a bf16 remainder (two products per
 // operand, 2^-17 relative instead of 2^-9).  Used for short segments, where the matrix work is
 // negligible and the rounding errors of a short period's few distinct basis values would not
 // average out.
@@ -1089,8 +1090,8 @@ static MomentTensor moment_tensor(const void* x, const uint8_t* mask, void* keep
 //   8 x 2 K, D = 128, M = 256: 23.7 / 14.4 us; 8 x 32 K: 46.9 / 46.5; 8 x 128 K, M = 512: 252 / 145   (launches; matrix rate)
 //   128 x 8 K, 96 and 128 of 128 dims compressed: M = 64: 150 / 129; M = 128: 157 / 158; M = 256: 171 / 276   (the moments are traffic)
 //   128 x 8 K, D = 256: M = 64: 604 / 276; M = 128: 633 / 335; M = 256: 695 / 598; 256 x 4 K, M = 200: 696 / 786
-// Segments of up to kSplitTokens stay with the direct form whatever they cost: its split basis leaves 2e-6 of white rows
-// (6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
+// Segments of up to kSplitTokens never take the moments: the split basis leaves 2e-6 of white rows and project_rows 1e-7 (both
+// 6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
 
 // specialised: compress_project_fast (D = 128); staged: kept dims leave through LDS.  Each tensor of a launch by itself.
 static void estimate_direct(CompressPlan& pl, bool specialised, bool staged, int B, int H, int N, int D, int Dc, int Du,
@@ -1113,22 +1114,36 @@ static double direct_us(double least, double work) { return 10.0 + work > least 
 // Dc, Du: over the tensors.  The expansion reads the moments once per workgroup's harmonics (in a single round of workgroups from
 // the caches); a round of its workgroups takes a few us, most where the old state is read.  one_vector: the straight-line step of compress_project_fast would run, which many rows favour
 // unless they are matrix-bound: K and V of 128 x 8 K, M = 64: 152 (moments) / 135 us; 32 x 8 K, M = 64: 39.6 / 42.2 us.
+static double moments_us(const MomentPlan& mp, int tensors, int B, int H, int N, int D, double Dc, double Du, int M, bool accumulate) {
+  const double pairs = static_cast<double>(tensors) * B * H, mom = pairs * mp.blocks * kMomP * Dc * 4.0;
+  const double rows = pairs * N;
+  const int ct = (static_cast<int>(Dc) + 15) / 16, tiles = expand_tiles(M);
+  const int ctw = expand_columns(ct, tiles, pairs), ht = expand_tiles_per_wg(ct, tiles, pairs), passes = (tiles + ht - 1) / ht;
+  const double rounds = ceil(pairs * passes * ((ct + ctw - 1) / ctw) / 256.0);
+  return 8.0 + rows * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + rounds * (ht == 1 ? 4.0 : accumulate ? 5.0 : 2.5) +
+         mom * passes / (ht == 1 ? 11.0e6 : mom < 128e6 ? 4.5e6 : 3.7e6);
+}
 static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct, int tensors, int B, int H, int N, int D, double Dc, double Du,
                            int M, bool accumulate) {
   if (!mp.use || N <= kSplitTokens) return false;
-  const double pairs = static_cast<double>(tensors) * B * H, mom = pairs * mp.blocks * kMomP * Dc * 4.0;
-  const double rows = pairs * N;
+  const double rows = static_cast<double>(tensors) * B * H * N;
   if (one_vector && rows > 65536.0) {
     const double matrix_us = 2.0 * rows * M * Dc / 0.95e9, hbm_us = rows * 2.0 * (D + Du) / 5.0e6;
     if (!(mp.umax >= 192 && matrix_us > hbm_us) && !(mp.umax >= 256 && rows <= 600e3)) return false;
   }
-  const int ct = (static_cast<int>(Dc) + 15) / 16, tiles = expand_tiles(M);
-  const int ctw = expand_columns(ct, tiles, pairs), ht = expand_tiles_per_wg(ct, tiles, pairs), passes = (tiles + ht - 1) / ht;
-  const double rounds = ceil(pairs * passes * ((ct + ctw - 1) / ctw) / 256.0);
-  const double us = 8.0 + rows * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + rounds * (ht == 1 ? 4.0 : accumulate ? 5.0 : 2.5) +
-                    mom * passes / (ht == 1 ? 11.0e6 : mom < 128e6 ? 4.5e6 : 3.7e6);
-  return us <= 1.05 * direct;
+  return moments_us(mp, tensors, B, H, N, D, Dc, Du, M, accumulate) <= 1.05 * direct;
 }
+
+// The basis formed per token in fp32 (fa_rows): one launch and no workspace, closer than either other form.  Segments of up to
+// kSplitTokens always take it where it is built (three terms: what they had was exact to fp32 at a token or two), longer ones
+// where its estimate is the lower.  Measured, K and V, other form / this one: 16 x 464 tokens, M = 82, two calls: 76 / 21 us;
+// 128 x 464, M = 232: 70 / 40; 24 x 898, D = 64, M = 62: 56 / 12; 4 x 2065, D = 256, M = 758: 122 / 40; 16 x 6717, D = 64,
+// M = 864: 91 / 77; against moments 8 x 2048, M = 256, two calls: 27 / 33; 64 x 12207, D = 64, M = 60: 63 / 55.
+static RowsPlan rows_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int keep_offset, int tensors) {
+  if (Dc <= 0) return RowsPlan{};
+  return make_rows_plan(dtype, B, H, N, D, M, keep_offset, tensors, N <= kSplitTokens ? 3 : 2, kRowsLongest);
+}
+static bool prefer_rows(const RowsPlan& rp, int N, double other) { return rp.use && (N <= kSplitTokens || rp.us < other); }
 
 // One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one
 // sequence at a time.  A part costs about 10 us; parts of a full workspace take 50 us and more.
@@ -1204,6 +1219,17 @@ static int run_moments(const MomentCall& c, int Bp, int Hp, char* ws, hipStream_
     tm->used[0] = true;
   }
   return FA_OK;
+}
+
+static int run_rows(const MomentCall& c, const RowsPlan& pl, hipStream_t st, KernelTimers* tm) {
+  RowsParams p{};
+  p.t[0] = c.t[0];
+  p.t[1] = c.t[1];
+  p.sx_b = c.sx_b; p.sx_h = c.sx_h; p.sx_n = c.sx_n;
+  p.B = c.B; p.H = c.H; p.N = c.N; p.M = c.M; p.T = c.T; p.t0 = c.t0;
+  p.accumulate = c.accumulate ? 1 : 0; p.keep_offset = c.keep_offset;
+  p.lead = pl.lead; p.hw = pl.hw; p.steps = pl.steps; p.nmax = c.M / 2;
+  return launch_rows(p, pl, c.D, c.tensors, c.N <= kSplitTokens ? 3 : 2, st, tm);
 }
 
 template <int DT, int KM>
@@ -1340,8 +1366,18 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const bool short_seg = dtype == FA_BF16 && N <= kSplitTokens;
   const bool specialised = dtype == FA_BF16 && D == 128 && staged_ok && fast_lds <= kMaxCLds && !short_seg;
   estimate_direct(pl, specialised, pl.stage || no_keep, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
-  if (!only_params && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
-      prefer_moments(mp, specialised && one_vector, direct_us(pl.us_least, pl.us_work), 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0)) {
+  const double direct = direct_us(pl.us_least, pl.us_work);
+  const bool room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
+  const bool moments = room && prefer_moments(mp, specialised && one_vector, direct, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
+  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dc, M, keep_offset, 1);
+  if (!only_params && prefer_rows(rp, N, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
+    const MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
+                       B, H, N, D, M, T, t0, accumulate, keep_offset};
+    const int rc = run_rows(c, rp, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc != FA_OK) return rc;
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
+  if (!only_params && moments) {
     MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                  B, H, N, D, M, T, t0, accumulate, keep_offset};
     int Bp, Hp;   // (a workspace that holds the direct projection's partials alone is served by that)
@@ -1490,10 +1526,18 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const double direct = pair ? direct_us(plk.us_least > plv.us_least ? plk.us_least : plv.us_least, plk.us_work + plv.us_work)
                              : direct_us(plk.us_least, plk.us_work) + direct_us(plv.us_least, plv.us_work) - 6.0;   // (V starts while K ends)
   const double kept = 0.5 * ((k_keep ? pk.Du : 0) + (v_keep ? pv.Du : 0));
-  if (Dvc > 0 && prefer_moments(mp, pair, direct, 2, B, H, N, D, 0.5 * (Dkc + Dvc), kept, M, accumulate != 0)) {
-    MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
-                  moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
-                 2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};
+  const double dims = 0.5 * (Dkc + Dvc);
+  const bool moments = Dvc > 0 && prefer_moments(mp, pair, direct, 2, B, H, N, D, dims, kept, M, accumulate != 0);
+  const MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
+                      moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
+                     2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};
+  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dkc < Dvc ? Dkc : Dvc, M, keep_offset, 2);
+  if (prefer_rows(rp, N, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
+    rc = run_rows(c, rp, static_cast<hipStream_t>(hip_stream), tm);
+    if (rc != FA_OK) return rc;
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
+  if (moments) {
     int Bp, Hp;
     if (moment_parts(c, workspace_bytes, &Bp, &Hp)) {
       rc = run_moments(c, Bp, Hp, ws, static_cast<hipStream_t>(hip_stream), tm);

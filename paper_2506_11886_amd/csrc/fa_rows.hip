@@ -1,0 +1,438 @@
+// Projection of bf16 rows onto the M basis functions, the basis formed on the fly in fp32 and split into bf16 terms:
+//   C[m,i] = sum_j phi_m(t0+j) X[j,i]
+// One launch, no partial sums in memory: a workgroup owns (sequence, head) and `hw` tiles of 16 harmonics; its waves take
+// the 32-token steps in turn and their shares meet in LDS.
+
+#include "fa_rows.hpp"
+
+#include "fa_mma.hpp"
+
+namespace fa {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+template <int D>
+struct RowsTile {
+  static constexpr int kCols = D == 64 ? 4 : 8;                // 16-column tiles per wave
+  static constexpr int kHalves = D / 16 / kCols;               // waves side by side over the columns
+  static constexpr int kSlots = 8 / kHalves;                   // waves along tokens and harmonics
+  static constexpr int kPitch = 2 * D + 32;                    // bytes of a tile row
+  static constexpr int kLoads = 32 * (D / 8) / (64 * kHalves); // 128-bit vectors per thread and step of 32 tokens
+  static constexpr unsigned kTiles = 2u * kSlots * 32 * kPitch;         // (two of them: the two waves of a slot of D = 256 meet)
+  static constexpr unsigned kSums = 8u * 2 * kCols * 1024 + 3 * kSlots * D * 4;   // the epilogue's
+  static constexpr unsigned kLds = kTiles > kSums ? kTiles : kSums;
+};
+
+// cosine and sine of 2 pi n pos / T; the product is exact, its fraction is taken in fp64
+__device__ __forceinline__ void turn(int64_t npos, double inv_t, float* c, float* s) {
+  double f = static_cast<double>(npos) * inv_t;
+  f -= rint(f);
+  sincospif(2.0f * static_cast<float>(f), s, c);
+}
+
+// eight values as NT bf16 terms, rounded two at a time
+template <int NT>
+__device__ __forceinline__ void split_terms(const float (&v)[8], Frag<bf16_t> (&t)[NT]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f32x2 r = f32x2{v[2 * e], v[2 * e + 1]};
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+      t[k].v[e] = w;
+      if (k + 1 < NT) {
+        r[0] -= __builtin_bit_cast(float, w << 16);
+        r[1] -= __builtin_bit_cast(float, w & 0xffff0000u);
+      }
+    }
+  }
+}
+
+constexpr int kReseed = 8;   // steps between exact phases
+
+// NT: bf16 terms of a basis value; kEnergy (fa_select_dims): sums of squares, and weighted squares of the states instead of them.
+// grid (tensors * B * H, groups of hw 16-harmonic tiles): the workgroups of a pair share an XCD's L2 when the pairs are a
+// multiple of eight.  Wave (column half, tile, share of the steps).  A wave stages its 32 rows in an LDS tile of its own and
+// reads them back transposed (ds_read_b64_tr_b16) as the B operand; its A operands are one harmonic's cosines and sines per
+// lane, at the eight tokens of the lane's k slots, rotated by a step's angle and split anew each step.  All D columns are
+// multiplied (the kept ones' sums are dropped), so that nothing is gathered.  No barrier in the loop but at D = 256, where the
+// two waves of a slot fill a tile together: with one per 256 tokens and tiles shared by all waves, 8 x 2048 tokens, M = 256, took
+// 23.5 us a call against 16.5.
+// Bound: instruction issue; see make_rows_plan for the rate.
+template <int D, int NT, bool kEnergy>
+__global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
+  using L = RowsTile<D>;
+  constexpr int NV = D / 8, PB = L::kPitch, CW = L::kCols, NL = L::kLoads, RPL = 64 * L::kHalves / NV;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(16))) uint16_t kdim[D + 8];
+  __shared__ int16_t cidx[D];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, r16 = lane & 15;
+  const int BH = p.B * p.H;
+  const int z = blockIdx.x >= BH;
+  const int bh = blockIdx.x - (z ? BH : 0), b = bh / p.H, h = bh - b * p.H;
+  const uint8_t* mask = z ? p.t[1].mask : p.t[0].mask;
+  const int Dc = z ? p.t[1].Dc : p.t[0].Dc, Du = D - Dc;
+  const bf16_t* xb = static_cast<const bf16_t*>(z ? p.t[1].x : p.t[0].x) + b * p.sx_b + h * p.sx_h;
+  const int N = p.N, lead = p.lead, hw = p.hw;
+
+  // ---- this wave's harmonics, and its share of the 32-token steps: every shares-th
+  const int half = wave % L::kHalves, slot = wave / L::kHalves;
+  const int ht = slot % hw, share = slot / hw, shares = L::kSlots / hw;
+  const int htile = blockIdx.y * hw + ht;
+  const bool first = htile == 0;                                // (also takes the constant function and the energies)
+  const bool live = first || htile * 16 < p.nmax;
+
+  const int wl = lane + 64 * half, ch = wl % NV, row0 = wl / NV;
+  const char* xrow = reinterpret_cast<const char*>(xb + ch * 8);
+  const uint64_t row_bytes = static_cast<uint64_t>(p.sx_n) * 2u;
+  const uint32_t row_lo = static_cast<uint32_t>(row_bytes), row_hi = static_cast<uint32_t>(row_bytes >> 32), last = N - 1;
+  auto load = [&](u32x4 (&x)[NL], int st) {
+    const int v = (st * shares + share) * 32 - lead + row0;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      // only step 0 has rows in front of the segment; as unsigned numbers they are large, and like rows past the end
+      // become the last one (none of them counts)
+      const uint32_t j = min(static_cast<uint32_t>(v + i * RPL), last);
+      // (the upper half of a row's stride by a 24-bit product: a segment taken here has fewer rows)
+      x[i] = *reinterpret_cast<const u32x4*>(xrow + static_cast<uint64_t>(j) * row_lo + (static_cast<uint64_t>(__umul24(j, row_hi)) << 32));
+    }
+  };
+  uint8_t mb[D / 64];
+#pragma unroll
+  for (int j = 0; j < D / 64; ++j) mb[j] = mask ? mask[static_cast<size_t>(bh) * D + lane + 64 * j] : uint8_t{1};
+  u32x4 x[NL];
+  load(x, 0);
+
+  // ---- compressed ranks, kept dims in order (pad entries point at the zero column of a tile row)
+  {
+    uint64_t bal[D / 64];
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) bal[j] = __ballot(mb[j] != 0);
+    if (tid < D) {
+      const int w = tid >> 6;
+      const uint64_t bit = 1ull << (tid & 63);
+      int nc = 0;
+      bool hit = false;
+#pragma unroll
+      for (int j = 0; j < D / 64; ++j) {
+        nc += __popcll(bal[j] & ((j < w) ? ~0ull : ((j == w) ? (bit - 1ull) : 0ull)));
+        hit = hit || (j == w && (bal[j] & bit) != 0);
+      }
+      cidx[tid] = hit && nc < Dc ? static_cast<int16_t>(nc) : static_cast<int16_t>(-1);   // (nothing past column Dc)
+      if (!hit) kdim[tid - nc] = static_cast<uint16_t>(tid);
+    }
+    if (tid < 8) kdim[Du + tid] = D;
+  }
+  for (int r = tid; r < 2 * L::kSlots * 32; r += 512) *reinterpret_cast<u32x4*>(smem + r * PB + 2 * D) = u32x4{0u, 0u, 0u, 0u};
+
+  const int n = htile * 16 + 1 + r16;
+  const double inv_t = 1.0 / static_cast<double>(p.T);
+  float c1, s1, c16, s16, cj, sj;
+  turn(n, inv_t, &c1, &s1);
+  turn(static_cast<int64_t>(n) * 16, inv_t, &c16, &s16);
+  turn(static_cast<int64_t>(n) * (32 * shares), inv_t, &cj, &sj);
+  float bc[8], bs[8];                                           // basis of slot e: token 4 g + e, or 16 + 4 g + e - 4
+  auto seed = [&](int st) {
+    const int64_t pos = static_cast<int64_t>(p.t0) - lead + (static_cast<int64_t>(st) * shares + share) * 32 + 4 * g;
+    turn(pos * n, inv_t, &bc[0], &bs[0]);
+    bc[4] = bc[0] * c16 - bs[0] * s16;
+    bs[4] = bs[0] * c16 + bc[0] * s16;
+#pragma unroll
+    for (int e = 0; e < 8; e += 4)
+#pragma unroll
+      for (int i = 1; i < 4; ++i) {
+        bc[e + i] = bc[e + i - 1] * c1 - bs[e + i - 1] * s1;
+        bs[e + i] = bs[e + i - 1] * c1 + bc[e + i - 1] * s1;
+      }
+  };
+
+  const bool keep_rows = (z ? p.t[1].keep_layout : p.t[0].keep_layout) == FA_KEEP_ROWS;
+  bf16_t* keep = static_cast<bf16_t*>(z ? p.t[1].keep : p.t[0].keep);
+  const bool write_keep = keep != nullptr && Du > 0;
+  const int kp = z ? p.t[1].keep_pitch : p.t[0].keep_pitch;
+  if (write_keep) keep += static_cast<int64_t>(bh) * (z ? p.t[1].keep_stride : p.t[0].keep_stride);
+  const int kdiv = max(1, keep_rows ? kp >> 3 : Du);               // kept vectors per token / per 8-token group
+  const uint32_t kmagic = ((1u << 21) + kdiv - 1) / kdiv;         // it / kdiv exactly: it * kdiv < 2^21
+
+  f32x4 acc[2][CW], acc0[CW], ene[CW];
+#pragma unroll
+  for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  double energy[CW];                                             // (every kReseed steps: sums of squares only grow, and
+#pragma unroll                                                  // an fp32 sum over all steps would round one way)
+  for (int w = 0; w < CW; ++w) energy[w] = 0.0;
+  auto flush_energy = [&]() {
+#pragma unroll
+    for (int w = 0; w < CW; ++w) {
+      const float lo = (r16 & 1) ? ene[w][1] : ene[w][0], hi = (r16 & 1) ? ene[w][3] : ene[w][2];
+      energy[w] += (r16 & 2) ? hi : lo;
+      ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  Frag<bf16_t> ones;
+  ones.v = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+
+  __syncthreads();                                              // kdim, cidx, zero columns
+  const int steps = p.steps;
+  // kept dims: the workgroups of a pair take the steps in turn, and the waves of a share theirs
+  const int turns = static_cast<int>(gridDim.y) * hw;
+  int my_turn = static_cast<int>(blockIdx.y) * hw + ht;
+  for (int st = 0; st < steps; ++st) {
+    const int v = (st * shares + share) * 32;                   // first (virtual) token: token j is virtual j + lead
+    unsigned char* tile = smem + ((L::kHalves > 1 ? st & 1 : 0) * L::kSlots + slot) * (32 * PB);
+    if (v < lead || v + 32 > N + lead) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int j = v + row0 + i * RPL - lead;
+        if (j < 0 || j >= N) x[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(tile + (row0 + i * RPL) * PB + ch * 16) = x[i];
+    load(x, st + 1);
+    if constexpr (L::kHalves > 1) {
+      lds_barrier();
+    } else {                                                    // a wave's own LDS operations take place in order
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (live && v < N + lead) {
+      const unsigned char* trp = tile + (4 * g + (r16 >> 2)) * PB + (r16 & 3) * 8 + half * CW * 32;
+      Frag<bf16_t> bx[CW];
+#pragma unroll
+      for (int w = 0; w < CW; ++w) {
+        const unsigned char* tp = trp + w * 32;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)tp);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tp + 16 * PB));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        bx[w].v = u32x4{l2[0], l2[1], h2[0], h2[1]};
+      }
+      if (st % kReseed == 0) {
+        seed(st);
+        if constexpr (kEnergy) {
+          if (first) flush_energy();
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float c = bc[e] * cj - bs[e] * sj;
+          bs[e] = bs[e] * cj + bc[e] * sj;
+          bc[e] = c;
+        }
+      }
+      Frag<bf16_t> ac[NT], as[NT];
+      split_terms<NT>(bc, ac);
+      split_terms<NT>(bs, as);
+#pragma unroll
+      for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int w = 0; w < CW; ++w) {
+          mma_k32(acc[0][w], ac[k], bx[w]);
+          mma_k32(acc[1][w], as[k], bx[w]);
+        }
+      if (first) {
+#pragma unroll
+        for (int w = 0; w < CW; ++w) {
+          mma_k32(acc0[w], ones, bx[w]);
+          if constexpr (kEnergy) mma_k32(ene[w], bx[w], bx[w]);
+        }
+      }
+    }
+    if (write_keep && my_turn-- == 0 && v < N + lead) {
+      my_turn = turns - 1;
+      const int rows = min(32, (N + lead - v + 7) & ~7);
+      const int kvec = keep_rows ? rows * kdiv : (rows >> 3) * kdiv;
+      for (int it = wl; it < kvec; it += 64 * L::kHalves) {
+        const int q = static_cast<int>((static_cast<uint32_t>(it) * kmagic) >> 21);
+        const int c = it - q * kdiv;
+        uint32_t w[4];
+        if (keep_rows) {           // token q of the tile, kept dims 8 c ..
+          const u32x4 kd = *reinterpret_cast<const u32x4*>(kdim + c * 8);
+          const unsigned char* rp = tile + q * PB;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t lo = *reinterpret_cast<const uint16_t*>(rp + 2 * (kd[e] & 0xffffu));
+            const uint32_t hi = *reinterpret_cast<const uint16_t*>(rp + 2 * (kd[e] >> 16));
+            w[e] = lo | (hi << 16);
+          }
+          const int j = v + q - lead;
+          if (j >= 0 && j < N)
+            *reinterpret_cast<u32x4*>(keep + static_cast<int64_t>(p.keep_offset + j) * kp + c * 8) =
+                u32x4{w[0], w[1], w[2], w[3]};
+        } else {                   // tokens 8 q .. 8 q + 7 of the tile, kept dim c
+          const unsigned char* rp = tile + q * 8 * PB + 2 * kdim[c];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t lo = *reinterpret_cast<const uint16_t*>(rp + (2 * e) * PB);
+            const uint32_t hi = *reinterpret_cast<const uint16_t*>(rp + (2 * e + 1) * PB);
+            w[e] = lo | (hi << 16);
+          }
+          const int j = v + q * 8 - lead;
+          bf16_t* o = keep + (static_cast<int64_t>((p.keep_offset + j) >> 3) * Du + c) * 8;
+          if (j >= 0 && j + 8 <= N) {
+            *reinterpret_cast<u32x4*>(o) = u32x4{w[0], w[1], w[2], w[3]};
+          } else {                 // a group shared with tokens outside this call
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (j + e >= 0 && j + e < N) o[e].bits = static_cast<uint16_t>(w[e >> 1] >> (16 * (e & 1)));
+          }
+        }
+      }
+    }
+  }
+
+  // ---- the shares of a tile meet in LDS: [wave][cos | sin][column tile][lane], then constants and energies per share
+  __syncthreads();
+  f32x4* red = reinterpret_cast<f32x4*>(smem);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int w = 0; w < CW; ++w) red[((wave * 2 + q) * CW + w) * 64 + lane] = acc[q][w];
+  float* cst = reinterpret_cast<float*>(smem + 8 * 2 * CW * 1024);
+  double* enr = reinterpret_cast<double*>(cst + L::kSlots * D);
+  if (first) {
+    if constexpr (kEnergy) flush_energy();
+#pragma unroll
+    for (int w = 0; w < CW; ++w) {
+      const int col = (half * CW + w) * 16 + r16;
+      if (g == 0) cst[share * D + col] = acc0[w][0];
+      if constexpr (kEnergy) {
+        if (g == (r16 >> 2)) enr[share * D + col] = energy[w];      // (the diagonal of X^T X)
+      }
+    }
+  }
+  __syncthreads();
+  if (blockIdx.y == 0 && tid < D) {
+    double c0 = 0.0;
+    for (int q = 0; q < shares; ++q) c0 += cst[q * D + tid];
+    if constexpr (kEnergy) {
+      double e = 0.0;
+      for (int q = 0; q < shares; ++q) e += enr[q * D + tid];
+      p.t[0].epart[static_cast<size_t>(bh) * D + tid] = static_cast<float>(e);
+      // the constant's weighted square takes a row of its own behind the tiles'
+      p.t[0].ecoef[(static_cast<size_t>((p.nmax + 15) / 16) * BH + bh) * D + tid] = static_cast<double>(basis_weight(0, p.T)) * c0 * c0;
+    } else if (cidx[tid] >= 0) {
+      float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + cidx[tid];
+      C[0] = static_cast<float>(p.accumulate ? C[0] + c0 : c0);
+    }
+  }
+  if (!live) return;
+  if constexpr (kEnergy) {
+    // weighted squares over the 16 harmonics of a tile: share `share` of the tile's waves takes every shares-th column tile
+    for (int w = share; w < CW; w += shares) {
+      double e = 0.0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int hn = htile * 16 + 1 + 4 * g + i;
+        double cc = 0.0, cs = 0.0;
+        for (int q = 0; q < shares; ++q) {
+          const int wv = (q * hw + ht) * L::kHalves + half;
+          cc += red[((wv * 2 + 0) * CW + w) * 64 + lane][i];
+          cs += red[((wv * 2 + 1) * CW + w) * 64 + lane][i];
+        }
+        if (hn <= p.nmax) {
+          const double wt = basis_weight(hn, p.T);
+          e += wt * cc * cc;
+          if (2 * hn < p.M) e += wt * cs * cs;
+        }
+      }
+      e += __shfl_xor(e, 16, 64);
+      e += __shfl_xor(e, 32, 64);
+      if (g == 0 && htile * 16 < p.nmax)
+        p.t[0].ecoef[(static_cast<size_t>(htile) * BH + bh) * D + (half * CW + w) * 16 + r16] = e;
+    }
+  } else {
+    for (int w = share; w < CW; w += shares) {
+      f32x4 sum[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        double d[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int q = 0; q < shares; ++q) {
+          const f32x4 a = red[(((q * hw + ht) * L::kHalves + half) * 2 + k) * CW * 64 + w * 64 + lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) d[i] += a[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[k][i] = static_cast<float>(d[i]);
+      }
+      const int rank = cidx[(half * CW + w) * 16 + r16];
+      if (rank >= 0) {
+        float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + rank;
+        const int m0 = 2 * (htile * 16 + 4 * g) + 1;               // cosine row of harmonic n = htile * 16 + 1 + 4 g
+        float old[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) old[i] = 0.f;
+        if (p.accumulate) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (m0 + i < p.M) old[i] = C[static_cast<size_t>(m0 + i) * Dc];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (m0 + i < p.M) C[static_cast<size_t>(m0 + i) * Dc] = old[i] + sum[i & 1][i >> 1];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// host
+// ---------------------------------------------------------------------------
+// Time: a step of 32 tokens per wave is bound by instruction issue (rotating and splitting the basis, 80 to 112 vector
+// instructions, and 32 to 48 products, which two waves per SIMD hardly overlap).  Measured, us a step: 0.83 / 1.07 / 1.5 (two
+// terms; D = 64 / 128 / 256), 0.95 / 1.3 / 1.75 (three); a round of workgroups, one per compute unit, takes 4 us besides, a
+// launch 5.  More tiles per workgroup mean fewer workgroups, each with a longer walk.  longest: 32-token steps per fp32 sum.
+RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int keep_offset, int tensors, int terms, int longest) {
+  RowsPlan pl{};
+  if (dtype != FA_BF16 || (D != 64 && D != 128 && D != 256) || N <= 0) return pl;
+  if (static_cast<long>(tensors) * B * H > 65535) return pl;
+  pl.lead = keep_offset & 7;
+  const int slots = D == 256 ? 4 : 8;
+  const int64_t blocks = (static_cast<int64_t>(N) + pl.lead + 31) / 32;
+  const int tiles = expand_tiles(M);
+  const double pairs = static_cast<double>(tensors) * B * H;
+  const double step = terms == 2 ? (D == 64 ? 0.83 : D == 128 ? 1.07 : 1.5) : (D == 64 ? 0.95 : D == 128 ? 1.3 : 1.75);
+  for (int hw = 1; hw <= slots; hw *= 2) {
+    const int64_t steps = (blocks * hw + slots - 1) / slots;
+    if (steps > longest) break;
+    const int groups = (tiles + hw - 1) / hw;
+    const double us = 5.0 + ceil(pairs * groups / 256.0) * (4.0 + steps * step);
+    if (!pl.use || us < pl.us) {
+      pl.use = true;
+      pl.us = us;
+      pl.hw = hw;
+      pl.groups = groups;
+      pl.steps = static_cast<int>(steps);
+    }
+  }
+  return pl;
+}
+
+template <int D, int NT, bool kEnergy>
+static int launch_rows_t(const RowsParams& p, const RowsPlan& pl, int tensors, hipStream_t st, KernelTimers* tm) {
+  auto kern = project_rows<D, NT, kEnergy>;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          static_cast<int>(RowsTile<D>::kLds)) != hipSuccess)
+    return FA_ERR_HIP;
+  FA_LAUNCH_TIMED(tm, 0, kern, dim3(tensors * p.B * p.H, pl.groups), dim3(512), RowsTile<D>::kLds, st, p);
+  return FA_OK;
+}
+
+int launch_rows(const RowsParams& p, const RowsPlan& pl, int D, int tensors, int terms, hipStream_t st, KernelTimers* tm) {
+  if (p.t[0].ecoef)
+    return D == 64 ? launch_rows_t<64, 3, true>(p, pl, tensors, st, tm)
+         : D == 128 ? launch_rows_t<128, 3, true>(p, pl, tensors, st, tm) : launch_rows_t<256, 3, true>(p, pl, tensors, st, tm);
+  if (terms == 3)
+    return D == 64 ? launch_rows_t<64, 3, false>(p, pl, tensors, st, tm)
+         : D == 128 ? launch_rows_t<128, 3, false>(p, pl, tensors, st, tm) : launch_rows_t<256, 3, false>(p, pl, tensors, st, tm);
+  return D == 64 ? launch_rows_t<64, 2, false>(p, pl, tensors, st, tm)
+       : D == 128 ? launch_rows_t<128, 2, false>(p, pl, tensors, st, tm) : launch_rows_t<256, 2, false>(p, pl, tensors, st, tm);
+}
+
+}  // namespace fa

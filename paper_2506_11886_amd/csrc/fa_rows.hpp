@@ -1,0 +1,37 @@
+// Projection of bf16 segments row by row onto a basis of fp32 precision (used by fa_compress, fa_compress_kv and
+// fa_select_dims where the harmonics vary too fast for moments, or where a segment is too short to be worth two launches).
+#pragma once
+
+#include "fa_common.hpp"
+#include "fa_moments.hpp"
+
+namespace fa {
+
+struct RowsParams {
+  MomentTensor t[2];   // (mom is not used)
+  int64_t sx_b, sx_h, sx_n;
+  int B, H, N, M, T, t0, accumulate, keep_offset;
+  int lead;            // zero tokens put in front, so that groups of 8 kept tokens are aligned
+  int hw;              // 16-harmonic tiles per workgroup
+  int steps;           // 32-token steps per wave
+  int nmax;
+};
+
+// A wave adds up at most this many steps of 32 tokens in fp32 (2048 tokens; a workgroup's waves have eight such shares, D = 256
+// four).  fa_select_dims, whose errors are differences of sums: half of them, the fp32 projection it would take else adds up 512
+// tokens at a quarter of the tokens a product.
+constexpr int kRowsLongest = 64;
+constexpr int kRowsLongestSelect = 32;
+
+struct RowsPlan {
+  bool use;
+  int hw, groups, steps, lead;
+  double us;           // estimated time
+};
+
+// terms: bf16 terms of a basis value (2: 2^-17, 3: fp32)
+// longest: 32-token steps a wave may add up in fp32
+RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int keep_offset, int tensors, int terms, int longest);
+int launch_rows(const RowsParams& p, const RowsPlan& pl, int D, int tensors, int terms, hipStream_t st, KernelTimers* tm);
+
+}  // namespace fa

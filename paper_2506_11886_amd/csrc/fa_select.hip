@@ -10,8 +10,10 @@
 // fp32 precision throughout, not with the bf16 basis of the production compress kernel.  Long bf16
 // segments: fa_moments (energies and moments in one pass against a three-term table), fa_expand
 // (weighted squares of the coefficients), select_rank; 8 heads x 31740 tokens, M = 256: 293 -> 37 us
-// against the stages below, which remain for fp32 segments and for harmonics that vary too fast for
-// the moments (a bf16 segment is widened there, which is exact):
+// against the stages below.  Bf16 segments whose harmonics vary too fast for the moments: project_rows (energies and weighted
+// squares in one launch), select_rank; 176 heads x 744 tokens, M = 372: 355 -> 80 us, errors 2.1e-6 -> 1.3e-6 of the largest;
+// 8 x 755, M = 94: 120 -> 20 us.  The stages below remain for fp32 segments, head dims other than 64 / 128 / 256 and bf16
+// segments too long for project_rows' fp32 sums (a bf16 segment is widened there, which is exact):
 //   1. select_energy : one pass over X: per-dim sums of squares per token chunk, the fp32
 //      copy of a bf16 segment, an all-ones mask row
 //   2. fa_compress   : all D dims, fp32 path, coefficients into the workspace
@@ -20,6 +22,7 @@
 #include "fa_common.hpp"
 #include "fa_mma.hpp"
 #include "fa_moments.hpp"
+#include "fa_rows.hpp"
 
 namespace fa {
 
@@ -141,6 +144,7 @@ __global__ __launch_bounds__(kRBlock) void select_rank(SelectParams p) {
 }
 
 struct SelectPlan {
+  RowsPlan rows;
   MomentPlan mom;      // long bf16 segments: energies and moments in one pass, no fp32 copy
   size_t off_ecoef, off_mom;
   int chunks;
@@ -163,6 +167,14 @@ static SelectPlan make_select_plan(int dtype, int B, int H, int N, int D, int M)
   const size_t BH = static_cast<size_t>(B) * H;
   size_t off = 0;
   pl.mom = make_moment_plan(dtype, B, H, N, D, D, M, N, 0, 1, true);
+  if (!pl.mom.use) pl.rows = make_rows_plan(dtype, B, H, N, D, M, 0, 1, 3, kRowsLongestSelect);
+  if (pl.rows.use) {
+    pl.chunks = 1;
+    pl.off_epart = off;  off = align256(off + BH * D * sizeof(float));
+    pl.off_ecoef = off;  off = align256(off + static_cast<size_t>(expand_tiles(M) + 1) * BH * D * sizeof(double));
+    pl.total = off;
+    return pl;
+  }
   if (pl.mom.use) {
     pl.chunks = pl.mom.chunks;
     pl.off_epart = off;  off = align256(off + static_cast<size_t>(pl.chunks) * BH * D * sizeof(float));
@@ -217,6 +229,21 @@ int fa_select_dims(const void* x, int dtype, int64_t sx_b, int64_t sx_h, int64_t
   p.B = B; p.H = H; p.N = N; p.D = D; p.M = M; p.Dc = Dc; p.chunks = pl.chunks;
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (pl.rows.use) {
+    RowsParams r{};
+    r.t[0].x = x;
+    r.t[0].epart = p.epart;
+    r.t[0].ecoef = reinterpret_cast<double*>(ws + pl.off_ecoef);
+    r.t[0].Dc = D;
+    r.sx_b = sx_b; r.sx_h = sx_h; r.sx_n = sx_n;
+    r.B = B; r.H = H; r.N = N; r.M = M; r.T = N;
+    r.hw = pl.rows.hw; r.steps = pl.rows.steps; r.nmax = M / 2;
+    const int rc = launch_rows(r, pl.rows, D, 1, 3, stream, nullptr);
+    if (rc != FA_OK) return rc;
+    p.ecoef = r.t[0].ecoef; p.tiles = (M / 2 + 15) / 16 + 1;
+    hipLaunchKernelGGL(select_rank, dim3(B * H), dim3(kRBlock), 0, stream, p);
+    return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
+  }
   if (pl.mom.use) {
     MomentParams m{};
     m.t[0].x = x;

@@ -385,8 +385,7 @@ int fa_decode_mq(const void* q, int dtype, int B, int Tq, int Hq, int Hkv, int D
  *   mse       DEVICE fp32 [B, H, D], written; may be NULL
  *   workspace DEVICE, 256-byte aligned, >= fa_select_workspace_bytes(...) bytes
  *             (bf16 segments whose harmonics vary slowly over 64 tokens: energies and moments
- *             per block; other bf16 segments of D = 64, 128 or 256 up to 8192 tokens (D = 256: 4096): energies
- *             and weighted squares; others: the fp32 copy of a bf16 segment, 4*B*H*N*D bytes, the
+ *             per block; others: the fp32 copy of a bf16 segment, 4*B*H*N*D bytes, the
  *             coefficients of all dims and the workspace of the projection)
  * Asynchronous on hip_stream; nothing is allocated.  Same limits as fa_compress.
  * Returns FA_OK or an FA_ERR_* code (arguments are checked on the host first).

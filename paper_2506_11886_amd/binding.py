@@ -1,4 +1,5 @@
-"""ctypes binding of libfourier_attn.so (argument marshalling only)."""
+"""Python binding of libfourier_attn.so (argument marshalling only): the enqueueing calls through the C entry `_fa_call`,
+queries and the timed entry points through ctypes."""
 
 from __future__ import annotations
 
@@ -102,28 +103,41 @@ def _load(path: str = _LIB_PATH):
 
 
 lib = _load()
+try:
+    from . import _fa_call as _call
+except ImportError as e:
+    raise ImportError(f"the Python entry _fa_call is missing or does not load ({e}): build it with "
+                      "`python paper_2506_11886_amd/build.py`") from e
 
 
 def status_string(status: int) -> str:
     return lib.fa_status_string(int(status)).decode()
 
 
+_CODES = {torch.float32: FA_F32, torch.bfloat16: FA_BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return FA_F32
-    if t.dtype == torch.bfloat16:
-        return FA_BF16
-    raise TypeError(f"unsupported element type {t.dtype}")
-
-
-def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    code = _CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported element type {t.dtype}")
+    return code
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """The stream's handle; the current stream's when None (torch.cuda.current_stream() would build an object for it: 2.7 us)."""
+    if stream is not None:
+        return stream.cuda_stream
+    torch.cuda._lazy_init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _timed(name, args, kernel_ms, n):
+    """The synchronous entry point `name`: its status, the kernels' milliseconds appended to `kernel_ms`."""
+    ms = (ctypes.c_float * n)()
+    st = getattr(lib, name)(*[a.data_ptr() if isinstance(a, torch.Tensor) else a for a in args], ms)
+    kernel_ms.extend(ms)
+    return st
 
 
 def compress_workspace_bytes(B, H, N, D, Dc, M, dtype=None) -> int:
@@ -183,19 +197,14 @@ def fa_compress(x, dim_mask, Dc, M, T, t0=0, accumulate=False, coeffs=None, x_ke
             x_keep = torch.empty((B, H, n_tok, keep_rows_pitch(Du)), dtype=x.dtype, device=dev)
         else:
             x_keep = torch.zeros((B, H, tok8_numel(n_tok, Du)), dtype=x.dtype, device=dev)
-    need = compress_workspace_bytes(B, H, N, D, Dc, M, x.dtype)
     if workspace is None:
+        need = compress_workspace_bytes(B, H, N, D, Dc, M, x.dtype)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    args = (_ptr(x), _dtype_code(x), x.stride(0), x.stride(1), x.stride(2),
-            B, H, N, D, _ptr(dim_mask), Dc, M, T, t0, int(bool(accumulate)),
-            _ptr(coeffs), _ptr(x_keep), keep_layout, keep_stride_bh, keep_offset,
-            _ptr(workspace), workspace.numel(), _stream_ptr(stream))
-    if kernel_ms is None:
-        st = lib.fa_compress(*args)
-    else:
-        ms = (ctypes.c_float * 2)()
-        st = lib.fa_compress_timed(*args, ms)
-        kernel_ms.extend(ms)
+    args = (x, _dtype_code(x), x.stride(0), x.stride(1), x.stride(2),
+            B, H, N, D, dim_mask, Dc, M, T, t0, int(bool(accumulate)),
+            coeffs, x_keep, keep_layout, keep_stride_bh, keep_offset,
+            workspace, workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_compress(*args) if kernel_ms is None else _timed("fa_compress_timed", args, kernel_ms, 2)
     if st != FA_OK:
         raise FourierAttnError(st, "fa_compress")
     return coeffs, x_keep
@@ -218,18 +227,13 @@ def fa_decode(q, ck, kmask, cv, vmask, M, T, t0, N, k_keep, v_keep, k_full, v_fu
     if workspace is None:
         need = decode_workspace_bytes(B, Hq, Hkv, D, Dkc, Dvc, M, N, W, num_splits)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    args = (_ptr(q), _dtype_code(q), B, Hq, Hkv, D,
-            _ptr(ck), _ptr(kmask), Dkc, _ptr(cv), _ptr(vmask), Dvc,
-            M, T, t0, N, _ptr(k_keep), kk_stride_bh, _ptr(v_keep), vk_stride_bh,
-            _ptr(k_full), _ptr(v_full), W, full_stride_bh,
-            float(scale), num_splits, _ptr(out),
-            _ptr(workspace), workspace.numel(), _stream_ptr(stream))
-    if kernel_ms is None:
-        st = lib.fa_decode(*args)
-    else:
-        ms = (ctypes.c_float * 3)()
-        st = lib.fa_decode_timed(*args, ms)
-        kernel_ms.extend(ms)
+    args = (q, _dtype_code(q), B, Hq, Hkv, D,
+            ck, kmask, Dkc, cv, vmask, Dvc,
+            M, T, t0, N, k_keep, kk_stride_bh, v_keep, vk_stride_bh,
+            k_full, v_full, W, full_stride_bh,
+            float(scale), num_splits, out,
+            workspace, workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_decode(*args) if kernel_ms is None else _timed("fa_decode_timed", args, kernel_ms, 3)
     if st != FA_OK:
         raise FourierAttnError(st, "fa_decode")
     return out
@@ -254,12 +258,12 @@ def fa_decode_varlen(q, ck, kmask, cv, vmask, M, T, t0, N_max, seq_n, k_keep, v_
     if workspace is None:
         need = decode_workspace_bytes(B, Hq, Hkv, D, Dkc, Dvc, M, N_max, W, num_splits)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    st = lib.fa_decode_varlen(_ptr(q), _dtype_code(q), B, Hq, Hkv, D,
-                              _ptr(ck), _ptr(kmask), Dkc, _ptr(cv), _ptr(vmask), Dvc,
-                              M, T, t0, N_max, _ptr(seq_n), _ptr(k_keep), kk_stride_bh, _ptr(v_keep), vk_stride_bh,
-                              _ptr(k_full), _ptr(v_full), W, _ptr(seq_w), full_stride_bh,
-                              float(scale), num_splits, _ptr(out),
-                              _ptr(workspace), workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_decode_varlen(q, _dtype_code(q), B, Hq, Hkv, D,
+                              ck, kmask, Dkc, cv, vmask, Dvc,
+                              M, T, t0, N_max, seq_n, k_keep, kk_stride_bh, v_keep, vk_stride_bh,
+                              k_full, v_full, W, seq_w, full_stride_bh,
+                              float(scale), num_splits, out,
+                              workspace, workspace.numel(), _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_decode_varlen")
     return out
@@ -277,11 +281,11 @@ def fa_decode_static(q, ck, kmask, cv, vmask, M, T, t0, N, k_keep, v_keep, k_ful
     W = k_full.shape[2] if k_full is not None else 0
     if out is None:
         out = torch.empty((B, Hq, D), dtype=torch.float32, device=q.device)
-    st = lib.fa_decode_static(_ptr(q), _dtype_code(q), B, Hq, Hkv, D,
-                              _ptr(ck), _ptr(kmask), Dkc, _ptr(cv), _ptr(vmask), Dvc,
-                              M, T, t0, N, _ptr(k_keep), kk_stride_bh, _ptr(v_keep), vk_stride_bh,
-                              _ptr(k_full), _ptr(v_full), W, full_stride_bh,
-                              float(scale), num_splits, _ptr(out), _stream_ptr(stream))
+    st = _call.fa_decode_static(q, _dtype_code(q), B, Hq, Hkv, D,
+                              ck, kmask, Dkc, cv, vmask, Dvc,
+                              M, T, t0, N, k_keep, kk_stride_bh, v_keep, vk_stride_bh,
+                              k_full, v_full, W, full_stride_bh,
+                              float(scale), num_splits, out, _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_decode_static")
     return out
@@ -297,10 +301,10 @@ def fa_append(k_new, v_new, k_full, v_full, slot, evict, kmask=None, vmask=None,
     W = k_full.shape[2]
     Dkc = ck.shape[-1] if ck is not None else 0
     Dvc = cv.shape[-1] if cv is not None else 0
-    st = lib.fa_append(_ptr(k_new), _ptr(v_new), _dtype_code(k_new), B, Hkv, D,
-                       _ptr(k_full), _ptr(v_full), W, full_stride_bh, int(slot), 1 if evict else 0,
-                       _ptr(kmask), Dkc, _ptr(vmask), Dvc, M, T, n_mid,
-                       _ptr(ck), _ptr(cv), _ptr(k_keep), kk_stride_bh, _ptr(v_keep), vk_stride_bh,
+    st = _call.fa_append(k_new, v_new, _dtype_code(k_new), B, Hkv, D,
+                       k_full, v_full, W, full_stride_bh, int(slot), 1 if evict else 0,
+                       kmask, Dkc, vmask, Dvc, M, T, n_mid,
+                       ck, cv, k_keep, kk_stride_bh, v_keep, vk_stride_bh,
                        _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_append")
@@ -317,10 +321,10 @@ def fa_append_varlen(k_new, v_new, k_full, v_full, seq_slot, kmask, vmask, M, T,
     for t in (seq_slot, seq_nmid):
         if t.dtype != torch.int32 or t.numel() != B or not t.is_contiguous():
             raise ValueError("seq_slot / seq_nmid must be contiguous int32 tensors of B entries")
-    st = lib.fa_append_varlen(_ptr(k_new), _ptr(v_new), _dtype_code(k_new), B, Hkv, D,
-                              _ptr(k_full), _ptr(v_full), W, full_stride_bh, _ptr(seq_slot),
-                              _ptr(kmask), Dkc, _ptr(vmask), Dvc, M, T, _ptr(seq_nmid), int(n_cap),
-                              _ptr(ck), _ptr(cv), _ptr(k_keep), kk_stride_bh, _ptr(v_keep), vk_stride_bh,
+    st = _call.fa_append_varlen(k_new, v_new, _dtype_code(k_new), B, Hkv, D,
+                              k_full, v_full, W, full_stride_bh, seq_slot,
+                              kmask, Dkc, vmask, Dvc, M, T, seq_nmid, int(n_cap),
+                              ck, cv, k_keep, kk_stride_bh, v_keep, vk_stride_bh,
                               _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_append_varlen")
@@ -340,8 +344,8 @@ def fa_select_dims(x, M, Dc, want_mse=True, workspace=None, stream=None):
     if workspace is None:
         need = select_workspace_bytes(_dtype_code(x), B, H, N, D, M)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    st = lib.fa_select_dims(_ptr(x), _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M, Dc,
-                            _ptr(mask), _ptr(mse), _ptr(workspace), workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_select_dims(x, _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M, Dc,
+                            mask, mse, workspace, workspace.numel(), _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_select_dims")
     return mask, mse
@@ -359,15 +363,15 @@ def fa_legt(x, M, workspace=None, stream=None, want_mse=True):
     coeffs = torch.empty((B, H, M, D), dtype=torch.float32, device=dev)
     if workspace is None:
         workspace = torch.empty(max(legt_workspace_bytes(B, H, N, D, M), 256), dtype=torch.uint8, device=dev)
-    st = lib.fa_legt_compress(_ptr(x), _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M,
-                              _ptr(coeffs), _ptr(workspace), workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_legt_compress(x, _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M,
+                              coeffs, workspace, workspace.numel(), _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_legt_compress")
     mse = None
     if want_mse:
         mse = torch.empty((B, H, D), dtype=torch.float32, device=dev)
-        st = lib.fa_legt_mse(_ptr(x), _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M,
-                             _ptr(coeffs), _ptr(mse), _ptr(workspace), workspace.numel(), _stream_ptr(stream))
+        st = _call.fa_legt_mse(x, _dtype_code(x), x.stride(0), x.stride(1), x.stride(2), B, H, N, D, M,
+                             coeffs, mse, workspace, workspace.numel(), _stream_ptr(stream))
         if st != FA_OK:
             raise FourierAttnError(st, "fa_legt_mse")
     return coeffs, mse
@@ -388,9 +392,9 @@ def fa_decode_mq(q, ck, kmask, cv, vmask, M, T, t0, N, k_keep, v_keep, k_full, v
     if workspace is None:
         need = decode_workspace_bytes(B, Hq * Tq, Hkv, D, Dkc, Dvc, M, N, W, num_splits)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    st = lib.fa_decode_mq(_ptr(q), _dtype_code(q), B, Tq, Hq, Hkv, D, _ptr(ck), _ptr(kmask), Dkc, _ptr(cv),
-                          _ptr(vmask), Dvc, M, T, t0, N, _ptr(k_keep), 0, _ptr(v_keep), 0, _ptr(k_full),
-                          _ptr(v_full), W, 0, float(scale), num_splits, _ptr(out), _ptr(workspace),
+    st = _call.fa_decode_mq(q, _dtype_code(q), B, Tq, Hq, Hkv, D, ck, kmask, Dkc, cv,
+                          vmask, Dvc, M, T, t0, N, k_keep, 0, v_keep, 0, k_full,
+                          v_full, W, 0, float(scale), num_splits, out, workspace,
                           workspace.numel(), _stream_ptr(stream))
     if st != FA_OK:
         raise FourierAttnError(st, "fa_decode_mq")
@@ -424,15 +428,10 @@ def fa_compress_kv(k, v, kmask, vmask, Dkc, Dvc, M, T, t0=0, accumulate=False, c
     if workspace is None:
         workspace = torch.empty(max(compress_kv_workspace_bytes(B, H, N, D, Dkc, Dvc, M, k.dtype), 256), dtype=torch.uint8,
                                 device=dev)
-    args = (_ptr(k), _ptr(v), _dtype_code(k), k.stride(0), k.stride(1), k.stride(2), B, H, N, D,
-            _ptr(kmask), Dkc, _ptr(vmask), Dvc, M, T, t0, int(bool(accumulate)), _ptr(ck), _ptr(cv),
-            _ptr(k_keep), 0, _ptr(v_keep), 0, keep_offset, _ptr(workspace), workspace.numel(), _stream_ptr(stream))
-    if kernel_ms is None:
-        st = lib.fa_compress_kv(*args)
-    else:
-        ms = (ctypes.c_float * 2)()
-        st = lib.fa_compress_kv_timed(*args, ms)
-        kernel_ms.extend(ms)
+    args = (k, v, _dtype_code(k), k.stride(0), k.stride(1), k.stride(2), B, H, N, D,
+            kmask, Dkc, vmask, Dvc, M, T, t0, int(bool(accumulate)), ck, cv,
+            k_keep, 0, v_keep, 0, keep_offset, workspace, workspace.numel(), _stream_ptr(stream))
+    st = _call.fa_compress_kv(*args) if kernel_ms is None else _timed("fa_compress_kv_timed", args, kernel_ms, 2)
     if st != FA_OK:
         raise FourierAttnError(st, "fa_compress_kv")
     return ck, k_keep, cv, v_keep

@@ -5,12 +5,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfourier_attn.so")
 SOURCES = ("fa_compress.hip", "fa_moments.hip", "fa_rows.hip", "fa_decode.hip", "fa_local.hip", "fa_finish.hip", "fa_small.hip", "fa_append.hip", "fa_select.hip", "fa_legt.hip")
+
+CALL = os.path.join(HERE, "_fa_call.so")   # the Python entry, linked against LIB
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -50,6 +53,14 @@ def build(verbose: bool = False, extra=()) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc link failed")
+    call = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+            os.path.join(CSRC, "fa_call.cpp"), "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-o", CALL]
+    if verbose:
+        print(" ".join(call), flush=True)
+    res = subprocess.run(call, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("the Python entry does not build")
     return LIB
 
 

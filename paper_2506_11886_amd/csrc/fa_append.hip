@@ -11,7 +11,6 @@
 namespace fa {
 
 constexpr int kABlock = 256;
-constexpr int kADims = 16;   // head dims per workgroup (a divisor of 64: see the ballot words)
 constexpr int kAFly = 16;    // rows of C in flight per thread
 
 struct AppendParams {
@@ -51,14 +50,14 @@ __device__ __forceinline__ void seq_append(const AppendParams& p, int b, int* sl
 
 // One launch: the fold reads the old row and the new token overwrites it, so a workgroup takes a slice of
 // head dims for ALL basis rows - nobody else reads or writes its part of the row, and its columns of C are
-// one contiguous band.  grid (sequences x heads, K | V, slices of kADims dims): with the pair index fastest
+// one contiguous band.  grid (sequences x heads, K | V, slices of kADims dims: a divisor of 64, see the ballot words): with the pair index fastest
 // the slices of a pair land on one XCD whenever the pairs are a multiple of four, and the cache lines of C
 // they share meet in one L2.  Bound: the round trips row/mask -> C -> store; the rows of C are requested
 // kAFly at a time before the basis column is evaluated.
 // Against a split by basis rows, which took a second launch for the overwrite and one round trip per 256
 // elements: a step (append + decode) of 8 heads x 32 K tokens, M = 256, 34.1 -> 29.5 us; 16 sequences of
 // up to 8 K tokens, M = 128, 62.6 -> 57.7 us.
-template <typename T>
+template <typename T, int kADims>
 __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
   __shared__ float xc[kADims];              // the evicted row at this slice's compressed dims
   __shared__ float phi[FA_MAX_STATES + 2];  // basis column at n_mid
@@ -95,15 +94,15 @@ __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
   // compressed dims in front of the slice, and the slice's own bits (a slice never straddles a ballot word)
   const int w0 = d0 >> 6, o0 = d0 & 63;
   int cb = 0;
-  uint32_t bits = 0;
+  uint64_t bits = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {   // static indices only: the words stay in registers
     cb += __popcll(bal[j] & ((j < w0) ? ~0ull : ((j == w0) ? ((1ull << o0) - 1ull) : 0ull)));
-    if (j == w0) bits = static_cast<uint32_t>(bal[j] >> o0) & ((1u << kADims) - 1u);
+    if (j == w0) bits = (bal[j] >> o0) & (~0ull >> (64 - kADims));
   }
-  const int nc = min(__popc(bits), max(Dc - cb, 0));   // (nothing past column Dc, whatever the mask holds)
+  const int nc = min(__popcll(bits), max(Dc - cb, 0));   // (nothing past column Dc, whatever the mask holds)
 
-  // columns [cb, cb + nc) of C: 16 lanes a row
+  // columns [cb, cb + nc) of C: kADims lanes a row
   const int col = tid & (kADims - 1), r0 = tid / kADims;
   constexpr int kRowsPass = kABlock / kADims;
   const bool live = col < nc;
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
 
   if (mine) {
     ring[tid] = fresh;
-    const int below = __popc(bits & ((1u << tid) - 1u));
+    const int below = __popcll(bits & ((1ull << tid) - 1ull));
     if ((bits >> tid) & 1u) {
       xc[below] = Elem<T>::load(&old);
     } else {   // kept dims: appended at middle position n_mid
@@ -158,6 +157,15 @@ __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
       if (live && m < M) dst[static_cast<size_t>(m) * Dc] = cv[i] + phi[m] * x;
     }
   }
+}
+
+// Head dims per workgroup.  Narrow slices are more workgroups, which few pairs need; wide ones read whole lines of C and evaluate
+// the basis column fewer times.  Measured, us at 16 / 32 / 64: 224 pairs, D = 256, M = 292: 95 / 66 / 59; 192, D = 128, M = 244:
+// 30 / 25 / 21; 128, D = 128, M = 128: 11.2 / 9.9 / 10.0; 16, D = 128, M = 512: 10.5 / 9.8 / 14.7; 8, D = 128, M = 1023: 10.8 / 15 / 26.
+static int append_dims(int pairs, int D) {
+  for (int dims = 64; dims > 16; dims /= 2)
+    if (2 * pairs * ((D + dims - 1) / dims) >= 512) return dims;
+  return 16;
 }
 
 }  // namespace fa
@@ -200,9 +208,14 @@ static int append_impl(const void* k_new, const void* v_new, int dtype, int B, i
   } else {
     p.n_mid = -1;
   }
-  const dim3 grid(B * Hkv, 2, (D + kADims - 1) / kADims);
-  if (dtype == FA_F32) hipLaunchKernelGGL(append_token<float>, grid, dim3(kABlock), 0, st, p);
-  else hipLaunchKernelGGL(append_token<bf16_t>, grid, dim3(kABlock), 0, st, p);
+  const int dims = append_dims(B * Hkv, D);
+  const dim3 grid(B * Hkv, 2, (D + dims - 1) / dims);
+#define FA_APPEND(T_) \
+  if (dims == 16) hipLaunchKernelGGL((append_token<T_, 16>), grid, dim3(kABlock), 0, st, p); \
+  else if (dims == 32) hipLaunchKernelGGL((append_token<T_, 32>), grid, dim3(kABlock), 0, st, p); \
+  else hipLaunchKernelGGL((append_token<T_, 64>), grid, dim3(kABlock), 0, st, p)
+  if (dtype == FA_F32) { FA_APPEND(float); } else { FA_APPEND(bf16_t); }
+#undef FA_APPEND
   // only this call's launches are reported: an error an earlier, unrelated HIP call left behind is
   // neither returned nor cleared
   return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;

@@ -1,0 +1,87 @@
+// Python entry of the C ABI: one function per enqueueing call of fourier_attn.h, positional arguments converted by the C
+// parameter's type.  A pointer takes a tensor (its data_ptr()), an address or None; the result is the status.
+// Measured on a step of the ctypes binding it replaces for these calls: fa_decode in one launch 10.2 -> 4.9 us of host time (1.7 us
+// of it ctypes, 2.7 us torch.cuda.current_stream(), which the caller no longer takes), with three launches 14.9 -> 9.5.
+
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <cstdint>
+#include <tuple>
+#include <type_traits>
+#include <utility>
+
+#include "fourier_attn.h"
+
+namespace {
+
+PyObject* data_ptr_name = nullptr;
+
+template <typename T>
+bool convert(PyObject* o, T& out) {
+  if constexpr (std::is_pointer_v<T>) {
+    if (o == Py_None) {
+      out = nullptr;
+      return true;
+    }
+    PyObject* held = nullptr;
+    if (!PyLong_Check(o)) {
+      held = PyObject_VectorcallMethod(data_ptr_name, &o, 1 | PY_VECTORCALL_ARGUMENTS_OFFSET, nullptr);
+      if (!held) return false;
+      o = held;
+    }
+    const unsigned long long v = PyLong_AsUnsignedLongLong(o);
+    Py_XDECREF(held);
+    if (v == static_cast<unsigned long long>(-1) && PyErr_Occurred()) return false;
+    out = reinterpret_cast<T>(static_cast<uintptr_t>(v));
+  } else if constexpr (std::is_floating_point_v<T>) {
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) return false;
+    out = static_cast<T>(v);
+  } else {
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) return false;
+    out = static_cast<T>(v);
+  }
+  return true;
+}
+
+template <auto F>
+struct Entry;
+template <typename... A, int (*F)(A...)>
+struct Entry<F> {
+  template <size_t... I>
+  static PyObject* apply(PyObject* const* args, std::index_sequence<I...>) {
+    std::tuple<A...> a;
+    if (!(convert(args[I], std::get<I>(a)) && ...)) return nullptr;
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = F(std::get<I>(a)...);
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(status);
+  }
+  static PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    if (n != static_cast<Py_ssize_t>(sizeof...(A))) {
+      PyErr_Format(PyExc_TypeError, "%zd arguments given, %zu expected", n, sizeof...(A));
+      return nullptr;
+    }
+    return apply(args, std::index_sequence_for<A...>{});
+  }
+};
+
+#define FA_ENTRY(f_) {#f_, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&Entry<&f_>::call)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {
+    FA_ENTRY(fa_compress),      FA_ENTRY(fa_compress_kv), FA_ENTRY(fa_decode),        FA_ENTRY(fa_decode_varlen),
+    FA_ENTRY(fa_decode_static), FA_ENTRY(fa_decode_mq),   FA_ENTRY(fa_append),        FA_ENTRY(fa_append_varlen),
+    FA_ENTRY(fa_select_dims),   FA_ENTRY(fa_legt_compress), FA_ENTRY(fa_legt_mse),
+    {nullptr, nullptr, 0, nullptr}};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fa_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__fa_call(void) {
+  data_ptr_name = PyUnicode_InternFromString("data_ptr");
+  if (!data_ptr_name) return nullptr;
+  return PyModule_Create(&module);
+}

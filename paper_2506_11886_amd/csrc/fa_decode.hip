@@ -159,37 +159,47 @@ __global__ __launch_bounds__(kBlock) void decode_prepare(DecodeParams p) {
 // compressed dims go through LDS once, each thread forms its share of the G dot products from
 // registers, and the TPR shares meet by lane rotation.  256 / TPR rows per workgroup: 64 when
 // the (sequence, head) pairs alone fill the chip, 16 when there are few of them.
-// VEC: floats a thread reads at once: 4, or 1 for compressed counts that are no multiple of 4 (rows
-// of C_k are then not aligned).
-template <int VEC> struct PrepVec { using type = f32x4; };
-template <> struct PrepVec<1> { using type = float; };
+// VEC: 4 floats a thread reads at once; 3: the same for counts that are no multiple of 4, whose rows of C_k lie at any
+// 4-byte boundary - the last vector of a row ends with the row and skips what the one before it holds (one by one, 80 heads x 584
+// rows of 55 took 43 us with 1101 full-width rows in the launch); 1: one by one, for fewer than 4.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC> struct PrepVec { using type = f32x4; using load = f32x4; };
+template <> struct PrepVec<3> { using type = f32x4; using load = f32x4u; };
+template <> struct PrepVec<1> { using type = float; using load = float; };
+__host__ __device__ __forceinline__ int prep_query_pitch(int Dkc) { return Dkc < 4 ? Dkc : (Dkc + 3) & ~3; }
 __device__ __forceinline__ float prep_dot(const f32x4& a, const f32x4& b) {
   return (a[0] * b[0] + a[1] * b[1]) + (a[2] * b[2] + a[3] * b[3]);
 }
 __device__ __forceinline__ float prep_dot(float a, float b) { return a * b; }
 
-// qc: LDS for the query at the compressed dims, [G][Dkc].  (A pointer into LDS by type: through a plain one the fp32 form's
+// qc: LDS for the query at the compressed dims, [G][prep_query_pitch].  (A pointer into LDS by type: through a plain one the fp32 form's
 // stores to it and to qkeep were joined into flat stores, 2457 -> 2759 instructions.)
 typedef __attribute__((address_space(3))) float lds_f32;
 template <typename T, int TPR, int VEC>
 __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, lds_f32* qc, const int bh, const int blk) {
   using V = typename PrepVec<VEC>::type;
   typedef __attribute__((address_space(3))) V lds_v;
-  constexpr int kRows = kBlock / TPR;
-  constexpr int kV4 = (FA_MAX_HEAD_DIM / VEC + TPR - 1) / TPR;
+  using VL = typename PrepVec<VEC>::load;
+  constexpr int kRows = kBlock / TPR, kV = VEC == 1 ? 1 : 4;
+  constexpr int kV4 = (FA_MAX_HEAD_DIM / kV + TPR - 1) / TPR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int b = bh / p.Hkv, hkv = bh % p.Hkv;
   const int Dkc = p.Dkc, D = p.D, G = p.G;
   const int row = tid / TPR, seg = tid % TPR;
   const int m = blk * kRows + row;            // basis function of this thread's row (0 .. Mint)
-  const int c4n = Dkc / VEC;
+  const int c4n = VEC == 3 ? (Dkc + 3) / 4 : Dkc / kV;
+  const int qp = VEC == 3 ? 4 * c4n : Dkc;
+  const int back = VEC == 3 ? 4 * c4n - Dkc : 0;   // elements of a row's last vector that the one before it holds
 
   // C_k row, the mask row and q of the group: all requested up front, clamped, never predicated
   const float* ck = p.ck + static_cast<size_t>(bh) * p.M * Dkc + static_cast<size_t>(min(m, p.M - 1)) * Dkc;
   V cv4[kV4];
 #pragma unroll
   for (int i = 0; i < kV4; ++i)
-    if (i * TPR < c4n) cv4[i] = *reinterpret_cast<const V*>(ck + VEC * min(seg + i * TPR, c4n - 1));
+    if (i * TPR < c4n) {
+      const int c4 = min(seg + i * TPR, c4n - 1);
+      cv4[i] = *reinterpret_cast<const VL*>(ck + (VEC == 3 ? min(4 * c4, Dkc - 4) : kV * c4));
+    }
   uint64_t kbal[4];
   mask_ballots(p.kmask + static_cast<size_t>(bh) * D, D, lane, kbal);
   const size_t hq0 = static_cast<size_t>(b) * p.Hq + hkv * G;
@@ -212,9 +222,23 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, lds_f32* qc
     if (it < nqe) {
       const int h = it / D, d = it % D;
       const int r = dim_rank(kbal, d);
-      if (r < 0) qc[h * Dkc + (-r - 1)] = to_f32(qe[i]);
-      else if (blk == 0) qkeep[h * Dkq + r] = qe[i];
+      if (r < 0) {
+        const int x = -r - 1;
+        qc[h * qp + x + (VEC == 3 && x >= qp - 4 ? back : 0)] = to_f32(qe[i]);
+      } else if (blk == 0) {
+        qkeep[h * Dkq + r] = qe[i];
+      }
     }
+  }
+  if constexpr (VEC == 3) {
+    if (tid < 4 * G && (tid & 3) < back) qc[(tid >> 2) * qp + qp - 4 + (tid & 3)] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kV4; ++i)
+      if (i * TPR < c4n && seg + i * TPR == c4n - 1) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (e < back) cv4[i][e] = 0.0f;
+      }
   }
   if (blk == 0) {
     const int npad = Dkq - p.Dku;
@@ -224,13 +248,13 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, lds_f32* qc
 
   const float w = (m < p.M) ? basis_weight((m + 1) / 2, p.T) : 0.0f;
   for (int h = 0; h < G; ++h) {
-    const lds_f32* qh = qc + h * Dkc;
+    const lds_f32* qh = qc + h * qp;
     float acc = 0.0f;
 #pragma unroll
     for (int i = 0; i < kV4; ++i) {
       if (i * TPR < c4n) {
         const int c4 = seg + i * TPR;
-        const V qv = *reinterpret_cast<const lds_v*>(qh + VEC * min(c4, c4n - 1));
+        const V qv = *reinterpret_cast<const lds_v*>(qh + kV * min(c4, c4n - 1));
         const float d4 = prep_dot(cv4[i], qv);
         acc += (c4 < c4n) ? d4 : 0.0f;
       }
@@ -250,10 +274,10 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, lds_f32* qc
   }
 }
 
-template <typename T, int TPR>
+template <typename T, int TPR, int VEC>
 __global__ __launch_bounds__(kBlock) void decode_prepare2(DecodeParams p) {
   __shared__ __attribute__((aligned(16))) float qc[kMaxG * FA_MAX_HEAD_DIM];
-  prepare2_rows<T, TPR, 4>(p, (lds_f32*)qc, blockIdx.y, blockIdx.x);
+  prepare2_rows<T, TPR, VEC>(p, (lds_f32*)qc, blockIdx.y, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -478,6 +502,7 @@ __device__ __forceinline__ void partial_full_rows(const DecodeParams& p, unsigne
 // as ready-made MFMA operands: two barriers per step, no work done twice.
 constexpr int kVU = 2;                                        // V^mu token blocks per wave and step
 constexpr unsigned kXchgBytes = 32 * 1024;   // score exchange, probability tiles, statistics; E transpose tiles
+constexpr unsigned kXchgBytes8 = 48 * 1024;  // the same with eight waves
 
 // cos / sin of 2 pi n u / T for a table entry (n u < 2^24): exact integer phase
 template <typename T>
@@ -497,11 +522,13 @@ __device__ __forceinline__ void table_cs(int n, int u, int period, float inv_per
 
 // KC1: the kept K dims fit one 32-dim MFMA step (the usual case), so that all K^mu operands of
 // a step are requested ahead and none on demand.
-template <typename T, int CW, int DVTM, bool KC1>
+template <typename T, int CW, int DVTM, bool KC1, int NW>
 __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsigned char* smem) {
   using ES = typename SeriesType<T>::type;
-  constexpr int Mint = kWaves * CW * 32;
-  constexpr int kQLoads = kMaxG * FA_MAX_HEAD_DIM / 8 / kBlock;
+  constexpr int NT = 64 * NW;
+  constexpr int Mint = NW * CW * 32;
+  constexpr int kQLoads = kMaxG * FA_MAX_HEAD_DIM / 8 / NT;
+  constexpr int kKF = NW == kWaves ? kMaxKT : kMaxKT / 2, kVF = NW == kWaves ? kVU : 1;   // K^mu row blocks, V^mu token blocks of a wave
   // V^mu operands are requested a step ahead when they fit in registers
   constexpr bool kPrefetchV = DVTM <= 2;
   constexpr int kVR = kPrefetchV ? DVTM : 1;
@@ -515,7 +542,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   const int Nb = seq_middle_rows(p, b);
   const int c0 = sm_idx * p.chunk_m, c1 = min(Nb, c0 + p.chunk_m);    // chunk of middle rows
   if (c0 >= Nb) {   // (only with per-sequence counts) nothing of this chunk belongs to the sequence
-    write_empty_middle(p, hq0, sm_idx, sm_idx + 1, kBlock);
+    write_empty_middle(p, hq0, sm_idx, sm_idx + 1, NT);
     return;
   }
   const int step = KT * kTJ;                                           // rows per step
@@ -530,11 +557,12 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   const T* kk = static_cast<const T*>(p.k_keep) + bh * p.kk_stride;
   const T* vk = static_cast<const T*>(p.v_keep) + bh * p.vk_stride;
   const int Nm1 = Nb - 1;
-  const int NV = KT >= 2 ? KT / 2 : 1;               // V^mu token blocks of this wave per step
+  const int NV = max(1, 2 * KT / NW);                // V^mu token blocks of this wave per step
+  const int NK = max(1, 4 * KT / NW);                // K^mu row blocks
 
   // ---- LDS carve-up -------------------------------------------------------
-  f32x4* xs = reinterpret_cast<f32x4*>(smem);                   // [kWaves][kRB][64] partial scores
-  constexpr unsigned kXsBytes = kWaves * kRB * 64 * 16;
+  f32x4* xs = reinterpret_cast<f32x4*>(smem);                   // [NW][kRB][64] partial scores
+  constexpr unsigned kXsBytes = NW * kRB * 64 * 16;
   ES* pse = reinterpret_cast<ES*>(smem + kXsBytes);             // [kXN][16][4][8] probabilities, series type
   T* pte = reinterpret_cast<T*>(smem + kXsBytes + kXN * 16 * 4 * 8 * sizeof(ES));   // same, element type
   // what the element-type rounding of the probabilities dropped (16-bit element types only): the kept-V
@@ -545,7 +573,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   float* st_l = st_m + 16;                                      // [16] column sums
   float* red_r = reinterpret_cast<float*>(smem);                // after the loop: [16][Mint + 4]
   const int pr = Mint + 4, po = 16 * DVT + 4;
-  float* red_o = red_r + 16 * pr;                               // [kWaves][16][16 DVT + 4]
+  float* red_o = red_r + 16 * pr;                               // [NW][16][16 DVT + 4]
   constexpr int kPitchG = Mint + 32;                            // floats per row of gs_s
   float* gs_s = reinterpret_cast<float*>(smem + p.lds_tab);     // [G][kPitchG] series coefficients
   T* qk_s = reinterpret_cast<T*>(gs_s + G * kPitchG);           // [G][Dkq]
@@ -575,16 +603,16 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     if (16 * dt + r16 >= p.Dvu) bv.zero();
     if (tok0 + 8 > c1) mask_tail(bv, c1 - tok0);
   };
-  auto load_step = [&](Frag<T> (&kf)[kMaxKT], Frag<T> (&vf)[kVU][kVR], int base) {
+  auto load_step = [&](Frag<T> (&kf)[kKF], Frag<T> (&vf)[kVF][kVR], int base) {
     if (kchunks > 0) {
 #pragma unroll
-      for (int i = 0; i < kMaxKT; ++i)
-        if (i < KT) kf[i].load(k_ptr(base, wave * KT + i, 0));
+      for (int i = 0; i < kKF; ++i)
+        if (i < NK) kf[i].load(k_ptr(base, min(wave * NK + i, 4 * KT - 1), 0));
     }
     if constexpr (kPrefetchV) {
       if (DVT > 0) {
 #pragma unroll
-        for (int i = 0; i < kVU; ++i) {
+        for (int i = 0; i < kVF; ++i) {
           const int vid = wave * NV + i;
           if (i < NV && vid < 2 * KT) {
 #pragma unroll
@@ -598,14 +626,14 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
 
   // ---- (0) everything that comes from global memory is requested first ------------
   // series coefficients of the group: G * Mint contiguous floats
-  constexpr int kGLoads = kMaxG * Mint / 4 / kBlock;
+  constexpr int kGLoads = kMaxG * Mint / 4 / NT;
   const int ng4 = G * Mint / 4;
   f32x4 gv[kGLoads];
 #pragma unroll
   for (int i = 0; i < kGLoads; ++i)
-    gv[i] = *reinterpret_cast<const f32x4*>(p.gs + hq0 * Mint + 4 * min(tid + i * kBlock, ng4 - 1));
+    gv[i] = *reinterpret_cast<const f32x4*>(p.gs + hq0 * Mint + 4 * min(tid + i * NT, ng4 - 1));
   // this lane's share of the softmax: column ocol, rows 16 orb + 4 oq4 + v of the tile
-  const int ocol = 4 * wave + (lane & 3), orb = lane >> 4, oq4 = (lane >> 2) & 3;
+  const int ocol = 4 * (wave % kWaves) + (lane & 3), orb = lane >> 4, oq4 = (lane >> 2) & 3;
   const int ocol_k = ocol / Gp, ocol_h = ocol % Gp;
   const bool olive = ocol_k < KT && ocol_h < G;
   const float g0 = p.g0[hq0 + min(ocol_h, G - 1)];
@@ -614,10 +642,10 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   if (nq8 > 0) {
     const T* qsrc = static_cast<const T*>(p.qkeep) + hq0 * Dkq;
 #pragma unroll
-    for (int i = 0; i < kQLoads; ++i) qv[i].load(qsrc + 8 * min(tid + i * kBlock, nq8 - 1));
+    for (int i = 0; i < kQLoads; ++i) qv[i].load(qsrc + 8 * min(tid + i * NT, nq8 - 1));
   }
-  Frag<T> kfA[kMaxKT], kfB[kMaxKT];
-  Frag<T> vfA[kVU][kVR], vfB[kVU][kVR];
+  Frag<T> kfA[kKF], kfB[kKF];
+  Frag<T> vfA[kVF][kVR], vfB[kVF][kVR];
   load_step(kfA, vfA, c0);
 
   // ---- this wave's slices of the E table ------------------------------------------------------
@@ -715,12 +743,12 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   // ---- series coefficients and packed query into LDS ---------------------------------------------
 #pragma unroll
   for (int i = 0; i < kGLoads; ++i) {
-    const int v4 = tid + i * kBlock;
+    const int v4 = tid + i * NT;
     if (v4 < ng4) *reinterpret_cast<f32x4*>(gs_s + (4 * v4 / Mint) * kPitchG + (4 * v4) % Mint) = gv[i];
   }
 #pragma unroll
   for (int i = 0; i < kQLoads; ++i) {
-    const int v8 = tid + i * kBlock;
+    const int v8 = tid + i * NT;
     if (v8 < nq8) *reinterpret_cast<Frag<T>*>(qk_s + 8 * v8) = qv[i];
   }
   __syncthreads();
@@ -739,7 +767,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   const bool quad_share = Gp >= 4;          // the 4 lanes of a quad then share (tile, q4)
   bool first = true;
 
-  auto do_step = [&](Frag<T> (&kf)[kMaxKT], Frag<T> (&vf)[kVU][kVR], int base) {
+  auto do_step = [&](Frag<T> (&kf)[kKF], Frag<T> (&vf)[kVF][kVR], int base) {
     const bool tail = base + step > c1;
     f32x4 sacc[kRB];
 #pragma unroll
@@ -783,9 +811,9 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     // -- (b) kept K dims, own row blocks: A = K^mu rows, B = q masked to the tile's columns --
     if (kchunks > 0) {
 #pragma unroll
-      for (int i = 0; i < kMaxKT; ++i) {
-        if (i < KT) {
-          const int uid = wave * KT + i, k = uid >> 2, rbd = uid & 3;
+      for (int i = 0; i < kKF; ++i) {
+        if (i < NK && wave * NK + i < 4 * KT) {
+          const int uid = wave * NK + i, k = uid >> 2, rbd = uid & 3;
           f32x4 ka = {0.f, 0.f, 0.f, 0.f};
           {
             Frag<T> bq;
@@ -810,17 +838,19 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
       }
     }
 
-    // -- (c) the partial scores of the four waves meet; this wave sums its four columns --------
+    // -- (c) the partial scores of the waves meet; each of the first four sums four columns --------
     {
       f32x4* xw = xs + (wave * kRB) * 64 + lane;
 #pragma unroll
       for (int rb = 0; rb < kRB; ++rb) xw[rb * 64] = sacc[rb];
     }
     __syncthreads();
+    if (NW == kWaves || wave < kWaves) {
     f32x4 sv;
     {
       const f32x4* xr = xs + orb * 64 + oq4 * 16 + ocol;
       sv = ((xr[0 * kRB * 64] + xr[1 * kRB * 64]) + xr[2 * kRB * 64]) + xr[3 * kRB * 64];
+      if constexpr (NW > kWaves) sv += ((xr[4 * kRB * 64] + xr[5 * kRB * 64]) + xr[6 * kRB * 64]) + xr[7 * kRB * 64];
     }
     // -- (d) online softmax of the own columns: lane holds rows u = 32x + 8 oq4 + 4y + v (orb = 2x + y)
     float pv[4];
@@ -870,6 +900,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
       }
       if (lane < 4) alpha_s[ocol] = alpha;
     }
+    }
     __syncthreads();
     // -- (e) bring the accumulators into this step's frame --------------------------------
     if (!first) {
@@ -911,7 +942,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     // -- (g) kept V dims, own token blocks: O += P^T V^mu -----------------------------------------
     if (DVT > 0) {
 #pragma unroll
-      for (int i = 0; i < kVU; ++i) {
+      for (int i = 0; i < kVF; ++i) {
         const int vid = wave * NV + i;
         if (i < NV && vid < 2 * KT) {
           Frag<T> ak = pt[0];   // select by value: an lvalue choice would put both fragments in memory
@@ -956,7 +987,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   l_run = row_stride_sum(l_run, 4);
   l_run += __shfl_xor(l_run, 16, kWave);
   l_run += __shfl_xor(l_run, 32, kWave);
-  if (lane < 4) {
+  if (lane < 4 && wave < kWaves) {
     st_m[ocol] = m_run;
     st_l[ocol] = l_run;
   }
@@ -1020,13 +1051,13 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     rec0[lane * rec_h + 1] = lstar;
   }
   const int no4 = 4 * DVT, nr4 = Mint / 4, per = no4 + nr4;
-  for (int it = tid; it < G * per; it += kBlock) {
+  for (int it = tid; it < G * per; it += NT) {
     {
       const int h = it / per, x4 = it - h * per;
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
       if (x4 < no4) {
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w)
+        for (int w = 0; w < NW; ++w)
 #pragma unroll
           for (int k = 0; k < kMaxKT; ++k)
             if (k < KT) v += *reinterpret_cast<const f32x4*>(red_o + ((w * 16 + k * Gp + h) * po + 4 * x4));
@@ -1893,7 +1924,7 @@ __global__ __launch_bounds__(kBlock, CW <= 2 ? 2 : 1) void decode_partial_fast(D
 // of K^mu and one token block of V^mu (tile wave / 2); of the softmax it owns two score columns,
 // two rows per lane.  The score exchange is padded so that the eight-byte reads of the owners
 // fall in distinct LDS banks.
-constexpr int kWaves8 = 8;
+
 constexpr int kBlock8 = 64 * kWaves8;
 constexpr int kXs8Q4 = 18;                    // f32x4 cells per (row block, lane / 16): 16 columns + 2 pad cells
 constexpr int kXs8Rb = 4 * kXs8Q4;            // per row block
@@ -2359,11 +2390,15 @@ __global__ __launch_bounds__(kBlock8, 1) void decode_partial_fast8(DecodeParams 
   }
 }
 
-template <typename T, int CW, int DVTM, bool KC1>
-__global__ __launch_bounds__(kBlock, (CW <= 2 && sizeof(T) == 2) ? 2 : 1) void decode_partial(DecodeParams p) {
+// NW: four waves, or eight where the tables of a wave of four would not leave it the registers for a step
+template <typename T, int CW, int DVTM, bool KC1, int NW>
+__global__ __launch_bounds__(64 * NW, (NW == kWaves && CW <= 2 && sizeof(T) == 2) ? 2 : 1) void decode_partial(DecodeParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  if (static_cast<int>(blockIdx.x) < p.Sm) partial_middle_rows<T, CW, DVTM, KC1>(p, smem);
-  else partial_full_rows<T>(p, smem, blockIdx.x - p.Sm);
+  if (static_cast<int>(blockIdx.x) < p.Sm) {
+    partial_middle_rows<T, CW, DVTM, KC1, NW>(p, smem);
+  } else if (NW == kWaves || threadIdx.x < kBlock) {   // (full-width rows are the work of four waves: the others end here, and a
+    partial_full_rows<T>(p, smem, blockIdx.x - p.Sm);  // barrier waits for the waves that run)
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2659,6 +2694,8 @@ struct DecodePlan {
   int wrb;        // 16-row blocks per wave of a full-width-row workgroup
   int Swp;        // chunks of full-width rows that run inside the middle-row launch
   unsigned lds_window;   // dynamic LDS of a full-width-row workgroup
+  int nw;     // waves of the general middle-row kernel
+  bool rides; // ... whose full-width rows run in the launch of the series coefficients
   int fast;   // 0: general middle-row kernel; 4 / 8: the specialised one with that many waves
   bool fused; // the whole call as one launch (one workgroup per (sequence, KV head))
   unsigned lds_tab, lds_total;
@@ -2827,6 +2864,25 @@ static bool make_plan(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D, 
   const unsigned t = mid > wpath ? mid : wpath;
   pl.lds_total = (t + 255u) & ~255u;
   if (pl.lds_total > kMaxDynLds) return false;
+  // general kernel: eight waves with half the table slices each where four would spill theirs.  The sums at the end take the
+  // place of everything before them (that of g, too).
+  pl.nw = kWaves;
+  if (pl.fast == 0 && N > 0 && pl.cw >= (dtype == FA_F32 ? 2 : 4)) {
+    const unsigned red8 = (16 * (pl.Mint + 4) + kWaves8 * 16 * (16 * DVT + 4)) * 4;
+    const unsigned mid8 = kXchgBytes8 + G * (pl.Mint + 32) * 4 + G * Dkq * ts + 64;   // (at most 132 KB either)
+    const unsigned most = red8 > mid8 ? red8 : mid8;
+    pl.nw = kWaves8;
+    pl.lds_tab = kXchgBytes8;
+    pl.lds_total = ((most > wpath ? most : wpath) + 255u) & ~255u;
+  }
+  // its full-width rows: on the matrix cores beside the series coefficients (256 rows a workgroup as here), where a unit's waves
+  // are not taken by the tables
+  pl.rides = pl.nw == kWaves8 && dtype == FA_BF16 && Dkc > 0 && W > 0 && (D == 64 || D == 128 || D == 256);
+  if (pl.rides) {
+    pl.wrb = 2;
+    pl.Swp = 0;
+  }
+  if (pl.lds_total > kMaxDynLds) return false;
   place_workspace(pl, B, Hq, Dku);
   return true;
 }
@@ -2934,9 +2990,9 @@ static int check_decode_shapes(int dtype, int B, int Hq, int Hkv, int D, int Dkc
   return FA_OK;
 }
 
-template <typename T, int CW, int DVTM, bool KC1>
+template <typename T, int CW, int DVTM, bool KC1, int NW>
 static int launch_partial(const DecodeParams& p, unsigned lds, hipStream_t st, KernelTimers* tm) {
-  auto kern = decode_partial<T, CW, DVTM, KC1>;
+  auto kern = decode_partial<T, CW, DVTM, KC1, NW>;
   // the dynamic-LDS ceiling is a property of the kernel as loaded on the current device: raised
   // whenever a launch needs it (a host-side table write, no stream operation)
   if (lds > 48u * 1024u &&
@@ -2944,7 +3000,7 @@ static int launch_partial(const DecodeParams& p, unsigned lds, hipStream_t st, K
                           static_cast<int>(kMaxDynLds)) != hipSuccess)
     return FA_ERR_HIP;
   dim3 g2(p.Swp + p.Sm, p.B * p.Hkv);
-  FA_LAUNCH_TIMED(tm, 1, kern, g2, dim3(kBlock), lds, st, p);
+  FA_LAUNCH_TIMED(tm, 1, kern, g2, dim3(64 * NW), lds, st, p);
   return FA_OK;
 }
 
@@ -3031,7 +3087,7 @@ static int launch_fused(const DecodeParams& p, const DecodePlan& pl, hipStream_t
 template <int TPR, int VEC, int D>
 static int launch_prepare_full_one(const DecodeParams& p, unsigned lds_window, hipStream_t st, KernelTimers* tm) {
   auto kern = decode_prepare_full<TPR, VEC, D>;
-  const unsigned q = static_cast<unsigned>(p.G) * p.Dkc * 4u, w = p.Sw == 0 ? 0u : D == 0 ? lds_window : kFullLds<D>, lds = q > w ? q : w;
+  const unsigned q = static_cast<unsigned>(p.G) * prep_query_pitch(p.Dkc) * 4u, w = p.Sw == 0 ? 0u : D == 0 ? lds_window : kFullLds<D>, lds = q > w ? q : w;
   if (lds > 48u * 1024u &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                           static_cast<int>(lds)) != hipSuccess)
@@ -3040,12 +3096,9 @@ static int launch_prepare_full_one(const DecodeParams& p, unsigned lds_window, h
   return FA_OK;
 }
 static int launch_prepare_full(const DecodeParams& p, unsigned lds_window, bool wide, hipStream_t st, KernelTimers* tm) {
-  const bool v4 = (p.Dkc & 3) == 0;
-#define FA_PREPARE(D_)                                                                                       \
-  return v4 ? (wide ? launch_prepare_full_one<4, 4, D_>(p, lds_window, st, tm)                               \
-                    : launch_prepare_full_one<16, 4, D_>(p, lds_window, st, tm))                             \
-            : (wide ? launch_prepare_full_one<4, 1, D_>(p, lds_window, st, tm)                               \
-                    : launch_prepare_full_one<16, 1, D_>(p, lds_window, st, tm))
+  const int vec = (p.Dkc & 3) == 0 ? 4 : p.Dkc >= 4 ? 3 : 1;
+#define FA_PREPARE2(V_, D_) (wide ? launch_prepare_full_one<4, V_, D_>(p, lds_window, st, tm) : launch_prepare_full_one<16, V_, D_>(p, lds_window, st, tm))
+#define FA_PREPARE(D_) return vec == 4 ? FA_PREPARE2(4, D_) : vec == 3 ? FA_PREPARE2(3, D_) : FA_PREPARE2(1, D_)
   switch (p.D) {
     case 64: FA_PREPARE(64);
     case 128: FA_PREPARE(128);
@@ -3053,6 +3106,7 @@ static int launch_prepare_full(const DecodeParams& p, unsigned lds_window, bool 
     default: FA_PREPARE(0);
   }
 #undef FA_PREPARE
+#undef FA_PREPARE2
 }
 
 // tm (optional): per-kernel event pairs, for fa_decode_timed
@@ -3063,10 +3117,10 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
     if (pl.fused) return launch_fused(p, pl, st, tm);
   }
   const hipError_t prior = hipPeekAtLastError();
-  if (p.Sm > 0 && p.Dkc > 0 && ((p.Dkc & 3) == 0 || pl.local.use)) {
+  if (p.Sm > 0 && p.Dkc > 0 && (p.Dkc >= 4 || pl.local.use || pl.rides)) {
     const bool wide = static_cast<long>(BH) * (p.Mint / 64 + 1) >= 256;
     const int nprep = wide ? p.Mint / 64 + 1 : p.Mint / 16 + 1;
-    if (pl.local.use) {   // the full-width rows, if any, ride along
+    if (pl.local.use || pl.rides) {   // the full-width rows, if any, ride along
       DecodeParams pp = p;
       pp.nprep = nprep;
       const int rc = launch_prepare_full(pp, pl.lds_window, wide, st, tm);
@@ -3081,10 +3135,13 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
                               static_cast<int>(lds)) != hipSuccess)
         return FA_ERR_HIP;
       FA_LAUNCH_TIMED(tm, 0, kern, dim3(nprep + p.Sw, BH), dim3(kBlock), lds, st, pp);
+    } else if ((p.Dkc & 3) == 0) {
+      if (wide) FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 4, 4>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
+      else FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 16, 4>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
     } else if (wide) {
-      FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 4>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
+      FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 4, 3>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
     } else {
-      FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 16>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
+      FA_LAUNCH_TIMED(tm, 0, (decode_prepare2<T, 16, 3>), dim3(nprep, BH), dim3(kBlock), 0, st, p);
     }
   } else if (p.Sm > 0) {
     if (static_cast<long>(BH) * ((p.Mint + 32) / 32) >= 512) {
@@ -3111,21 +3168,18 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
   }
   const bool narrow = p.Dvu <= 32;   // kept V dims fit two MFMA column tiles
   const bool kc1 = p.Dku <= 32;      // kept K dims fit one MFMA step
-#define FA_LAUNCH_PARTIAL(CW_)                                                                      \
-  rc = (narrow && kc1) ? launch_partial<T, CW_, 2, true>(p, pl.lds_total, st, tm)                       \
-       : narrow        ? launch_partial<T, CW_, 2, false>(p, pl.lds_total, st, tm)                      \
-                       : launch_partial<T, CW_, kMaxDvTiles, false>(p, pl.lds_total, st, tm)
-  switch (pl.cw) {
-    case 1: FA_LAUNCH_PARTIAL(1); break;
-    case 2: FA_LAUNCH_PARTIAL(2); break;
-    default:
-      if constexpr (sizeof(T) == 2) {   // fp32 inputs stop at 256 states (two chunks per wave)
-        if (pl.cw == 4) FA_LAUNCH_PARTIAL(4);
-        else FA_LAUNCH_PARTIAL(8);
-      } else {
-        rc = FA_ERR_UNSUPPORTED;
-      }
-      break;
+#define FA_LAUNCH_PARTIAL(CW_, NW_)                                                                 \
+  rc = (narrow && kc1) ? launch_partial<T, CW_, 2, true, NW_>(p, pl.lds_total, st, tm)                  \
+       : narrow        ? launch_partial<T, CW_, 2, false, NW_>(p, pl.lds_total, st, tm)                 \
+                       : launch_partial<T, CW_, kMaxDvTiles, false, NW_>(p, pl.lds_total, st, tm)
+  if (pl.cw == 1) {
+    FA_LAUNCH_PARTIAL(1, kWaves);
+  } else if constexpr (sizeof(T) == 4) {   // fp32 inputs stop at 256 states
+    FA_LAUNCH_PARTIAL(1, kWaves8);
+  } else {
+    if (pl.cw == 2) FA_LAUNCH_PARTIAL(2, kWaves);
+    else if (pl.cw == 4) FA_LAUNCH_PARTIAL(2, kWaves8);
+    else FA_LAUNCH_PARTIAL(4, kWaves8);
   }
 #undef FA_LAUNCH_PARTIAL
   if (rc != FA_OK) return rc;

@@ -8,6 +8,7 @@ namespace fa {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = 4;
+constexpr int kWaves8 = 8;         // of the kernels for long series
 constexpr int kMaxG = FA_MAX_GROUP;
 constexpr int kTJ = 64;            // tokens per tile (rows of the E table)
 constexpr int kRB = kTJ / 16;      // 16-row blocks per tile

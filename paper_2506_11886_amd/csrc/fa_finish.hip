@@ -15,15 +15,20 @@
 
 namespace fa {
 
-template <int VEC> struct FinVec { using type = f32x4; };
-template <> struct FinVec<1> { using type = float; };
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC> struct FinVec { using type = f32x4; using load = f32x4; };
+template <> struct FinVec<3> { using type = f32x4; using load = f32x4u; };
+template <> struct FinVec<1> { using type = float; using load = float; };
 
 __host__ __device__ __forceinline__ bool spread_finish(int pairs, int per_kv) { return pairs < 8 && per_kv > 32; }
 
-// VEC: floats of a C_v row read at once (1: counts that are no multiple of 4, whose rows are not aligned)
+// VEC: 4 floats of a C_v row read at once; 3: the same for counts that are no multiple of 4, whose rows lie at any 4-byte
+// boundary (the last vector of a row ends with the row; what it holds twice is not used); 1: one by one, for fewer than 4
 template <int VEC, int WR, int WC>
 __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decode_finish(DecodeParams p, int NS) {
   using V = typename FinVec<VEC>::type;
+  using VL = typename FinVec<VEC>::load;
+  constexpr int kV = VEC == 1 ? 1 : 4;
   constexpr int kNW = kFinBlock / 64;
   constexpr int kSL = 4;                            // statistics per lane requested at the start (longer lists: read again)
   constexpr int kWB = WR > 8 ? 4 : 2;               // independent requests per batch: full-row records, kept dims
@@ -46,7 +51,7 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
   const float* pm = p.part_m + static_cast<size_t>(hq) * Sm * recm;
   const float* pw = p.part_w + static_cast<size_t>(hq) * Sw * recw;
   const bool do_cv = Sm > 0 && Dvc > 0;
-  const int cbw = ((Dvc + NS - 1) / NS + VEC - 1) / VEC * VEC, cb0 = sl * cbw, cbn = max(0, min(cbw, Dvc - cb0));
+  const int cbw = ((Dvc + NS - 1) / NS + kV - 1) / kV * kV, cb0 = sl * cbw, cbn = max(0, min(cbw, Dvc - cb0));
   const int kbw = (Dvu + NS - 1) / NS, kb0 = sl * kbw, kbn = max(0, min(kbw, Dvu - kb0));
 
   // ---- every request that depends on nothing (clamped, never predicated) ------------------------
@@ -71,14 +76,15 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
       if (u * ngr < Sm) rv[u] = *reinterpret_cast<const f32x4*>(pr + static_cast<size_t>(min(gr + u * ngr, Sm - 1)) * recm);
   }
   // C_v band: thread (column vector cqv, row group rgv)
-  const int nq = max(cbn / VEC, 1), ngrp = kFinBlock / nq, cqv = tid % nq, rgv = tid / nq;
+  const int nq = max((cbn + kV - 1) / kV, 1), ngrp = kFinBlock / nq, cqv = tid % nq, rgv = tid / nq;
   const bool cv_on = do_cv && cbn > 0 && tid < nq * ngrp;
-  const float* cvb = p.cv + static_cast<size_t>(bh) * M * Dvc + cb0 + VEC * cqv;
+  const int back = VEC == 3 ? 4 * nq - cbn : 0;    // (not 0 in the slice that ends with the row)
+  const float* cvb = p.cv + static_cast<size_t>(bh) * M * Dvc + cb0 + kV * cqv - (cqv == nq - 1 ? back : 0);
   V cvv[WC];
   if (do_cv && cbn > 0) {
 #pragma unroll
     for (int u = 0; u < WC; ++u)
-      if (u * ngrp < M) cvv[u] = *reinterpret_cast<const V*>(cvb + static_cast<size_t>(min(rgv + u * ngrp, M - 1)) * Dvc);
+      if (u * ngrp < M) cvv[u] = *reinterpret_cast<const VL*>(cvb + static_cast<size_t>(min(rgv + u * ngrp, M - 1)) * Dvc);
   }
   // full-row records: thread (4 dims d4, record group wg)
   const int nd4 = D / 4, nwg = kFinBlock / nd4, d4 = tid % nd4, wg = tid / nd4;
@@ -210,7 +216,7 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
       }
       for (int m0 = WC * ngrp; m0 < M; m0 += WC * ngrp) {
 #pragma unroll
-        for (int u = 0; u < WC; ++u) cvv[u] = *reinterpret_cast<const V*>(cvb + static_cast<size_t>(min(m0 + rgv + u * ngrp, M - 1)) * Dvc);
+        for (int u = 0; u < WC; ++u) cvv[u] = *reinterpret_cast<const VL*>(cvb + static_cast<size_t>(min(m0 + rgv + u * ngrp, M - 1)) * Dvc);
 #pragma unroll
         for (int u = 0; u < WC; ++u) {
           const int mm = m0 + rgv + u * ngrp;
@@ -234,8 +240,8 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
     if (cdim || kdim) {
       const int d = dim_of[j];
       if (do_cv && cdim) {
-        const float* src = reinterpret_cast<const float*>(red4) + j;
-        for (int gi = part; gi < ncv; gi += per) v += src[VEC * gi * nq];
+        const float* src = reinterpret_cast<const float*>(red4) + j + (j >= kV * (nq - 1) ? back : 0);
+        for (int gi = part; gi < ncv; gi += per) v += src[kV * gi * nq];
       }
       if (kdim)
         for (int gi = part; gi < nkm; gi += per) v += redk[gi * kcn + (j - cbw)];
@@ -250,29 +256,31 @@ __global__ __launch_bounds__(kFinBlock, WR > 16 ? 1 : WR > 8 ? 2 : 4) void decod
 // Slices per query head: as many as keep the launch within one round of resident workgroups; up to 128 slots and head dim 128,
 // counts in fours, half of that (the chain is then longer than what a slice reads: 512 heads, M = 128, 9.0 -> 8.3 us; odd counts
 // lose by it, 10.9 -> 12.7, and so does head dim 256, 12.8 -> 14.1; at M = 556, 9 of 60).  Long lists of requests where the
-// XCD with most workgroups holds them at once: one of the longest per compute unit, two of the next; odd counts take the list
-// that holds their rows of C_v (M = 400, 98 dims: 32 requests 10.4 us, 64 9.3; M = 128 7.5 and 8.5).  This launch against the two
-// kernels it replaced: 32 heads, M = 256, 7.9 -> 7.0 us, M = 1023 13.2 -> 11.8; odd counts, 192 heads, M = 130, 15.5 -> 7.4; 128 heads of
+// XCD with most workgroups holds them at once: one of the longest per compute unit, two of the next.  Odd counts by vectors instead
+// of floats: 224 pairs of six heads, M = 585, 102 dims, the call 171 -> 138 us; 256 of twelve, D = 64, M = 341, 47 dims, 110 -> 97;
+// 24 of eight, M = 130, 101 dims, 26.5 -> 25.  This launch against the two
+// kernels it replaced: 32 heads, M = 256, 7.9 -> 7.0 us, M = 1023 13.2 -> 11.8; odd counts, 192 heads, M = 130, 15.5 -> 7.2; 128 heads of
 // eight KV heads, M = 256, 8.5 -> 7.9; over 430 record lists of 4 - 3072 heads, both types, 0.77 of the time, four of them 3 - 6 % slower
 // (thousands of heads with one or two records each).
 int launch_finish(const DecodeParams& p, hipStream_t st, KernelTimers* tm) {
   const int BH = p.B * p.Hkv;
   const long heads = static_cast<long>(p.B) * p.Hq;
-  const bool v4 = (p.Dvc & 3) == 0;
+  const bool v4 = (p.Dvc & 3) == 0, v3 = p.Dvc >= 4;
   int NS = p.D <= 32 ? 1 : (p.D <= 64 ? 2 : (p.D <= 128 ? 4 : 8));
   while (NS > 1 && heads * NS > (v4 && p.D <= 128 && p.Mint <= 128 ? 512 : 1024)) NS /= 2;
   const long wgs = static_cast<long>(spread_finish(BH, p.G * NS) ? BH : (BH + 7) / 8 * 8) * p.G * NS, xcd = (wgs + 7) / 8;
   const dim3 grid(static_cast<unsigned>(wgs));
-  const int band = (p.Dvc + NS - 1) / NS;
   if (xcd <= 32 && p.Mint > 512) {
     if (v4) FA_LAUNCH_TIMED(tm, 2, (decode_finish<4, 32, 28>), grid, dim3(kFinBlock), 0, st, p, NS);
-    else FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 32, 96>), grid, dim3(kFinBlock), 0, st, p, NS);
+    else if (v3) FA_LAUNCH_TIMED(tm, 2, (decode_finish<3, 32, 28>), grid, dim3(kFinBlock), 0, st, p, NS);
+    else FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 32, 32>), grid, dim3(kFinBlock), 0, st, p, NS);
   } else if (xcd <= 64) {
     if (v4) FA_LAUNCH_TIMED(tm, 2, (decode_finish<4, 16, 16>), grid, dim3(kFinBlock), 0, st, p, NS);
-    else if (p.M <= 32 * (kFinBlock / band)) FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 16, 32>), grid, dim3(kFinBlock), 0, st, p, NS);
-    else FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 16, 64>), grid, dim3(kFinBlock), 0, st, p, NS);
+    else if (v3) FA_LAUNCH_TIMED(tm, 2, (decode_finish<3, 16, 16>), grid, dim3(kFinBlock), 0, st, p, NS);
+    else FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 16, 32>), grid, dim3(kFinBlock), 0, st, p, NS);
   } else {
     if (v4) FA_LAUNCH_TIMED(tm, 2, (decode_finish<4, 8, 8>), grid, dim3(kFinBlock), 0, st, p, NS);
+    else if (v3) FA_LAUNCH_TIMED(tm, 2, (decode_finish<3, 8, 8>), grid, dim3(kFinBlock), 0, st, p, NS);
     else FA_LAUNCH_TIMED(tm, 2, (decode_finish<1, 8, 16>), grid, dim3(kFinBlock), 0, st, p, NS);
   }
   return FA_OK;

@@ -1139,9 +1139,9 @@ static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct,
 // where its estimate is the lower.  Measured, K and V, other form / this one: 16 x 464 tokens, M = 82, two calls: 76 / 21 us;
 // 128 x 464, M = 232: 70 / 40; 24 x 898, D = 64, M = 62: 56 / 12; 4 x 2065, D = 256, M = 758: 122 / 40; 16 x 6717, D = 64,
 // M = 864: 91 / 77; against moments 8 x 2048, M = 256, two calls: 27 / 33; 64 x 12207, D = 64, M = 60: 63 / 55.
-static RowsPlan rows_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int keep_offset, int tensors) {
+static RowsPlan rows_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int64_t sx_n, int keep_offset, int tensors) {
   if (Dc <= 0) return RowsPlan{};
-  return make_rows_plan(dtype, B, H, N, D, M, keep_offset, tensors, N <= kSplitTokens ? 3 : 2, kRowsLongest);
+  return make_rows_plan(dtype, B, H, N, D, M, sx_n, keep_offset, tensors, N <= kSplitTokens ? 3 : 2, kRowsLongest);
 }
 static bool prefer_rows(const RowsPlan& rp, int N, double other) { return rp.use && (N <= kSplitTokens || rp.us < other); }
 
@@ -1369,7 +1369,7 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const double direct = direct_us(pl.us_least, pl.us_work);
   const bool room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
   const bool moments = room && prefer_moments(mp, specialised && one_vector, direct, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
-  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dc, M, keep_offset, 1);
+  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dc, M, sx_n, keep_offset, 1);
   if (!only_params && prefer_rows(rp, N, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
     const MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                        B, H, N, D, M, T, t0, accumulate, keep_offset};
@@ -1531,7 +1531,7 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
                       moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
                      2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};
-  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dkc < Dvc ? Dkc : Dvc, M, keep_offset, 2);
+  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dkc < Dvc ? Dkc : Dvc, M, sx_n, keep_offset, 2);
   if (prefer_rows(rp, N, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
     rc = run_rows(c, rp, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;

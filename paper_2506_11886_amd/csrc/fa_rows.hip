@@ -23,8 +23,9 @@ struct RowsTile {
   static constexpr int kPitch = 2 * D + 32;                    // bytes of a tile row
   static constexpr int kLoads = 32 * (D / 8) / (64 * kHalves); // 128-bit vectors per thread and step of 32 tokens
   static constexpr unsigned kTiles = 2u * kSlots * 32 * kPitch;         // (two of them: the two waves of a slot of D = 256 meet)
-  static constexpr unsigned kSums = 8u * 2 * kCols * 1024 + 3 * kSlots * D * 4;   // the epilogue's
-  static constexpr unsigned kLds = kTiles > kSums ? kTiles : kSums;
+  static constexpr unsigned kSums = 8u * 2 * kCols * 1024 + kSlots * D * 4;   // the epilogue's
+  static constexpr unsigned kEnergies = kTiles > kSums ? kTiles : kSums;                // offset of fa_select_dims' energies
+  static constexpr unsigned kLds = kEnergies + kSlots * D * 8;
 };
 
 // cosine and sine of 2 pi n pos / T; the product is exact, its fraction is taken in fp64
@@ -90,25 +91,31 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   const bool live = first || htile * 16 < p.nmax;
 
   const int wl = lane + 64 * half, ch = wl % NV, row0 = wl / NV;
-  const char* xrow = reinterpret_cast<const char*>(xb + ch * 8);
-  const uint64_t row_bytes = static_cast<uint64_t>(p.sx_n) * 2u;
-  const uint32_t row_lo = static_cast<uint32_t>(row_bytes), row_hi = static_cast<uint32_t>(row_bytes >> 32), last = N - 1;
-  auto load = [&](u32x4 (&x)[NL], int st) {
-    const int v = (st * shares + share) * 32 - lead + row0;
+  // Rows are requested through a buffer descriptor that begins at the step's first row: a lane's offsets are the same in every
+  // step, and rows past the segment come back as zeros.  Only step 0 has rows in front of it (made zero below).
+  const uint32_t row_bytes = static_cast<uint32_t>(p.sx_n) * 2u;
+  const int64_t total = static_cast<int64_t>(N - 1) * row_bytes + 2 * D;
+  uint32_t voff[NL];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      // only step 0 has rows in front of the segment; as unsigned numbers they are large, and like rows past the end
-      // become the last one (none of them counts)
-      const uint32_t j = min(static_cast<uint32_t>(v + i * RPL), last);
-      // (the upper half of a row's stride by a 24-bit product: a segment taken here has fewer rows)
-      x[i] = *reinterpret_cast<const u32x4*>(xrow + static_cast<uint64_t>(j) * row_lo + (static_cast<uint64_t>(__umul24(j, row_hi)) << 32));
-    }
+  for (int i = 0; i < NL; ++i) voff[i] = (row0 + i * RPL) * row_bytes + ch * 16;
+  auto load = [&](u32x4 (&x)[NL], int st) {
+    const int64_t first = static_cast<int64_t>((st * shares + share) * 32 - lead) * row_bytes;
+    const int64_t left = total - first;
+    const uint32_t bytes = left <= 0 ? 0u : left > 0xffffffffll ? 0xffffffffu : static_cast<uint32_t>(left);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(reinterpret_cast<const char*>(xb)) + (left <= 0 ? 0 : first), 0, bytes, 0x00027000);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) x[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff[i], 0, 0));
   };
   uint8_t mb[D / 64];
 #pragma unroll
   for (int j = 0; j < D / 64; ++j) mb[j] = mask ? mask[static_cast<size_t>(bh) * D + lane + 64 * j] : uint8_t{1};
   u32x4 x[NL];
-  load(x, 0);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {                                // (step 0: clamped)
+    const int j = min(max(share * 32 - lead + row0 + i * RPL, 0), N - 1);
+    x[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(xb) + static_cast<uint64_t>(j) * row_bytes + ch * 16);
+  }
 
   // ---- compressed ranks, kept dims in order (pad entries point at the zero column of a tile row)
   {
@@ -164,21 +171,32 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   f32x4 acc[2][CW], acc0[CW], ene[CW];
 #pragma unroll
   for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
-  double energy[CW];                                             // (every kReseed steps: sums of squares only grow, and
-#pragma unroll                                                  // an fp32 sum over all steps would round one way)
-  for (int w = 0; w < CW; ++w) energy[w] = 0.0;
+  // Sums of squares only grow, and an fp32 sum over all steps would round one way: they go to fp64, in LDS, every kReseed steps.
+  // (They are the diagonal of X^T X: column r16 in lane group r16 >> 2, element r16 & 3.)
+  double* enr = reinterpret_cast<double*>(smem + L::kEnergies);
   auto flush_energy = [&]() {
 #pragma unroll
     for (int w = 0; w < CW; ++w) {
       const float lo = (r16 & 1) ? ene[w][1] : ene[w][0], hi = (r16 & 1) ? ene[w][3] : ene[w][2];
-      energy[w] += (r16 & 2) ? hi : lo;
+      if (g == (r16 >> 2)) {
+        double* e = enr + share * D + (half * CW + w) * 16 + r16;
+        *e += (r16 & 2) ? hi : lo;
+      }
       ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   Frag<bf16_t> ones;
   ones.v = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
 
+  if constexpr (kEnergy) {
+    for (int i = tid; i < L::kSlots * D; i += 512) enr[i] = 0.0;
+  }
   __syncthreads();                                              // kdim, cidx, zero columns
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int j = share * 32 - lead + row0 + i * RPL;
+    if (j < 0 || j >= N) x[i] = u32x4{0u, 0u, 0u, 0u};
+  }
   const int steps = p.steps;
   // kept dims: the workgroups of a pair take the steps in turn, and the waves of a share theirs
   const int turns = static_cast<int>(gridDim.y) * hw;
@@ -186,13 +204,6 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   for (int st = 0; st < steps; ++st) {
     const int v = (st * shares + share) * 32;                   // first (virtual) token: token j is virtual j + lead
     unsigned char* tile = smem + ((L::kHalves > 1 ? st & 1 : 0) * L::kSlots + slot) * (32 * PB);
-    if (v < lead || v + 32 > N + lead) {
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int j = v + row0 + i * RPL - lead;
-        if (j < 0 || j >= N) x[i] = u32x4{0u, 0u, 0u, 0u};
-      }
-    }
 #pragma unroll
     for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(tile + (row0 + i * RPL) * PB + ch * 16) = x[i];
     load(x, st + 1);
@@ -295,16 +306,12 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 #pragma unroll
     for (int w = 0; w < CW; ++w) red[((wave * 2 + q) * CW + w) * 64 + lane] = acc[q][w];
   float* cst = reinterpret_cast<float*>(smem + 8 * 2 * CW * 1024);
-  double* enr = reinterpret_cast<double*>(cst + L::kSlots * D);
   if (first) {
     if constexpr (kEnergy) flush_energy();
 #pragma unroll
     for (int w = 0; w < CW; ++w) {
       const int col = (half * CW + w) * 16 + r16;
       if (g == 0) cst[share * D + col] = acc0[w][0];
-      if constexpr (kEnergy) {
-        if (g == (r16 >> 2)) enr[share * D + col] = energy[w];      // (the diagonal of X^T X)
-      }
     }
   }
   __syncthreads();
@@ -385,19 +392,20 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 // host
 // ---------------------------------------------------------------------------
 // Time: a step of 32 tokens per wave is bound by instruction issue (rotating and splitting the basis, 80 to 112 vector
-// instructions, and 32 to 48 products, which two waves per SIMD hardly overlap).  Measured, us a step: 0.83 / 1.07 / 1.5 (two
-// terms; D = 64 / 128 / 256), 0.95 / 1.3 / 1.75 (three); a round of workgroups, one per compute unit, takes 4 us besides, a
+// instructions, and 32 to 48 products, which two waves per SIMD hardly overlap).  Measured, us a step: 0.75 / 0.95 / 1.4 (two
+// terms; D = 64 / 128 / 256), 0.9 / 1.15 / 1.65 (three; with clamped addresses per row and step instead of a buffer descriptor a
+// tenth more); a round of workgroups, one per compute unit, takes 4 us besides, a
 // launch 5.  More tiles per workgroup mean fewer workgroups, each with a longer walk.  longest: 32-token steps per fp32 sum.
-RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int keep_offset, int tensors, int terms, int longest) {
+RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int64_t sx_n, int keep_offset, int tensors, int terms, int longest) {
   RowsPlan pl{};
   if (dtype != FA_BF16 || (D != 64 && D != 128 && D != 256) || N <= 0) return pl;
-  if (static_cast<long>(tensors) * B * H > 65535) return pl;
+  if (static_cast<long>(tensors) * B * H > 65535 || sx_n >= (1 << 25)) return pl;   // (32 rows within 4 GB)
   pl.lead = keep_offset & 7;
   const int slots = D == 256 ? 4 : 8;
   const int64_t blocks = (static_cast<int64_t>(N) + pl.lead + 31) / 32;
   const int tiles = expand_tiles(M);
   const double pairs = static_cast<double>(tensors) * B * H;
-  const double step = terms == 2 ? (D == 64 ? 0.83 : D == 128 ? 1.07 : 1.5) : (D == 64 ? 0.95 : D == 128 ? 1.3 : 1.75);
+  const double step = terms == 2 ? (D == 64 ? 0.75 : D == 128 ? 0.95 : 1.4) : (D == 64 ? 0.9 : D == 128 ? 1.15 : 1.65);
   for (int hw = 1; hw <= slots; hw *= 2) {
     const int64_t steps = (blocks * hw + slots - 1) / slots;
     if (steps > longest) break;

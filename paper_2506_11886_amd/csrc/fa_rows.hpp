@@ -31,7 +31,7 @@ struct RowsPlan {
 
 // terms: bf16 terms of a basis value (2: 2^-17, 3: fp32)
 // longest: 32-token steps a wave may add up in fp32
-RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int keep_offset, int tensors, int terms, int longest);
+RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int64_t sx_n, int keep_offset, int tensors, int terms, int longest);
 int launch_rows(const RowsParams& p, const RowsPlan& pl, int D, int tensors, int terms, hipStream_t st, KernelTimers* tm);
 
 }  // namespace fa

@@ -208,7 +208,7 @@ static SelectPlan make_select_plan(int dtype, int B, int H, int N, int D, int M)
   pl.cws_bytes = fa_compress_workspace_bytes(B, H, N, D, D, M);
   pl.total = align256(off + pl.cws_bytes);
   // (what project_rows keeps, energies and weighted squares, lies in the same buffer; the size asked for stays that of the stages)
-  pl.rows = make_rows_plan(dtype, B, H, N, D, M, 0, 1, 3, kRowsLongestSelect);
+  pl.rows = make_rows_plan(dtype, B, H, N, D, M, 0, 0, 1, 3, kRowsLongestSelect);
   pl.off_ecoef = pl.off_coeffs;
   const size_t rows_total = pl.off_ecoef + static_cast<size_t>(expand_tiles(M) + 1) * BH * D * sizeof(double);
   if (rows_total > pl.total) pl.rows.use = false;      // (a handful of rows)
@@ -249,7 +249,7 @@ int fa_select_dims(const void* x, int dtype, int64_t sx_b, int64_t sx_h, int64_t
   p.B = B; p.H = H; p.N = N; p.D = D; p.M = M; p.Dc = Dc; p.chunks = pl.chunks;
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (pl.rows.use) {
+  if (pl.rows.use && sx_n < (1 << 25)) {
     RowsParams r{};
     r.t[0].x = x;
     r.t[0].epart = p.epart;

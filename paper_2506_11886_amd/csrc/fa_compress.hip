@@ -1139,11 +1139,16 @@ static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct,
 // where its estimate is the lower.  Measured, K and V, other form / this one: 16 x 464 tokens, M = 82, two calls: 76 / 21 us;
 // 128 x 464, M = 232: 70 / 40; 24 x 898, D = 64, M = 62: 56 / 12; 4 x 2065, D = 256, M = 758: 122 / 40; 16 x 6717, D = 64,
 // M = 864: 91 / 77; against moments 8 x 2048, M = 256, two calls: 27 / 33; 64 x 12207, D = 64, M = 60: 63 / 55.
-static RowsPlan rows_plan(int dtype, int B, int H, int N, int D, int Dc, int M, int64_t sx_n, int keep_offset, int tensors) {
+// fp32 segments take it unless the workspace has no room for chunks that fill the chip: 32 x 4359, D = 128, M = 128, K and V: 347 / 104 us;
+// 10 x 19531, M = 40: 357 / 114; 1 x 744, M = 45, two calls: 162 / 44.  (Errors of white rows 4.5e-7 / 2.9e-7.)
+static bool rows_short(int dtype, int N) { return dtype == FA_F32 || N <= kSplitTokens; }   // (a basis of fp32 precision)
+static RowsPlan rows_plan(const RowsShape& c, int Dc, int most) {
   if (Dc <= 0) return RowsPlan{};
-  return make_rows_plan(dtype, B, H, N, D, M, sx_n, keep_offset, tensors, N <= kSplitTokens ? 3 : 2, kRowsLongest);
+  return make_rows_plan(c, rows_short(c.dtype, c.N) ? 3 : 2, c.dtype == FA_F32 ? kRowsLongestF32 : kRowsLongest, most);
 }
-static bool prefer_rows(const RowsPlan& rp, int N, double other) { return rp.use && (N <= kSplitTokens || rp.us < other); }
+static bool prefer_rows(const RowsPlan& rp, int dtype, int N, double other) {
+  return rp.use && (rows_short(dtype, N) || rp.us < other);
+}
 
 // One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one
 // sequence at a time.  A part costs about 10 us; parts of a full workspace take 50 us and more.
@@ -1221,15 +1226,34 @@ static int run_moments(const MomentCall& c, int Bp, int Hp, char* ws, hipStream_
   return FA_OK;
 }
 
-static int run_rows(const MomentCall& c, const RowsPlan& pl, hipStream_t st, KernelTimers* tm) {
+// part: room for the chunks' partial sums of each tensor (null: one chunk)
+static int run_rows(const MomentCall& c, int dtype, const RowsPlan& pl, float* const (&part)[2], hipStream_t st, KernelTimers* tm) {
   RowsParams p{};
   p.t[0] = c.t[0];
   p.t[1] = c.t[1];
   p.sx_b = c.sx_b; p.sx_h = c.sx_h; p.sx_n = c.sx_n;
   p.B = c.B; p.H = c.H; p.N = c.N; p.M = c.M; p.T = c.T; p.t0 = c.t0;
-  p.accumulate = c.accumulate ? 1 : 0; p.keep_offset = c.keep_offset;
-  p.lead = pl.lead; p.hw = pl.hw; p.steps = pl.steps; p.nmax = c.M / 2;
-  return launch_rows(p, pl, c.D, c.tensors, c.N <= kSplitTokens ? 3 : 2, st, tm);
+  p.accumulate = pl.chunks == 1 && c.accumulate ? 1 : 0; p.keep_offset = c.keep_offset;
+  p.lead = pl.lead; p.hw = pl.hw; p.steps = pl.steps; p.spc = pl.spc; p.nmax = c.M / 2;
+  ReducePair r{};
+  r.Sc = pl.chunks;
+  r.accumulate = c.accumulate ? 1 : 0;
+  size_t most = 0;
+  if (pl.chunks > 1) {
+    p.part = part[0];
+    p.part_z = static_cast<size_t>(part[1] - part[0]);
+    for (int z = 0; z < c.tensors; ++z) {
+      r.part[z] = part[z];
+      r.coeffs[z] = c.t[z].coeffs;
+      r.total[z] = static_cast<size_t>(c.B) * c.H * c.M * c.t[z].Dc;
+      r.stride[z] = p.part_stride[z] = (r.total[z] + 3) & ~size_t(3);
+      if (r.total[z] > most) most = r.total[z];
+    }
+  }
+  const int rc = launch_rows(p, pl, dtype, c.D, c.tensors, rows_short(dtype, c.N) ? 3 : 2, st, tm);
+  if (rc != FA_OK || pl.chunks == 1) return rc;
+  FA_LAUNCH_TIMED(tm, 1, compress_reduce_kv, dim3(static_cast<unsigned>((most / 4 + 1 + 255) / 256), c.tensors), dim3(256), 0, st, r);
+  return FA_OK;
 }
 
 template <int DT, int KM>
@@ -1369,11 +1393,12 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const double direct = direct_us(pl.us_least, pl.us_work);
   const bool room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
   const bool moments = room && prefer_moments(mp, specialised && one_vector, direct, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
-  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dc, M, sx_n, keep_offset, 1);
-  if (!only_params && prefer_rows(rp, N, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
+  const RowsPlan rp = rows_plan(RowsShape{dtype, B, H, N, D, M, sx_n, keep_offset, 1, x_keep ? Du : 0.0}, Dc, pl.total > 0 ? pl.Sc : 1);
+  if (!only_params && prefer_rows(rp, dtype, N, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
     const MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                        B, H, N, D, M, T, t0, accumulate, keep_offset};
-    const int rc = run_rows(c, rp, static_cast<hipStream_t>(hip_stream), tm);
+    float* const part[2] = {static_cast<float*>(workspace), nullptr};
+    const int rc = run_rows(c, dtype, rp, part, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;
     return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
   }
@@ -1531,9 +1556,13 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const MomentCall c{{moment_tensor(k, kmask, k_keep, ck, pk.keep_stride, Dkc, D, FA_KEEP_ROWS),
                       moment_tensor(v, vmask, v_keep, cv, pv.keep_stride, Dvc, D, FA_KEEP_TOK8)},
                      2, sx_b, sx_h, sx_n, B, H, N, D, M, T, t0, accumulate, keep_offset};
-  const RowsPlan rp = rows_plan(dtype, B, H, N, D, Dkc < Dvc ? Dkc : Dvc, M, sx_n, keep_offset, 2);
-  if (prefer_rows(rp, N, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
-    rc = run_rows(c, rp, static_cast<hipStream_t>(hip_stream), tm);
+  const size_t lk = ((static_cast<size_t>(B) * H * M * Dkc + 3) & ~size_t(3)) * sizeof(float), lv = ((static_cast<size_t>(B) * H * M * Dvc + 3) & ~size_t(3)) * sizeof(float);
+  int most = 1;   // chunks that either tensor's share of the workspace holds
+  while (most < FA_MAX_SPLITS && (most + 1) * lk <= wk && (most + 1) * lv <= wv) ++most;
+  const RowsPlan rp = rows_plan(RowsShape{dtype, B, H, N, D, M, sx_n, keep_offset, 2, kept}, Dkc < Dvc ? Dkc : Dvc, most);
+  if (prefer_rows(rp, dtype, N, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
+    float* const part[2] = {reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + wk)};
+    rc = run_rows(c, dtype, rp, part, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;
     return (hipPeekAtLastError() == hipSuccess || prior != hipSuccess) ? FA_OK : FA_ERR_HIP;
   }

@@ -15,17 +15,22 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-template <int D>
+template <typename T, int D>
 struct RowsTile {
-  static constexpr int kCols = D == 64 ? 4 : 8;                // 16-column tiles per wave
+  static constexpr bool kF32 = sizeof(T) == 4;
+  static constexpr int kCols = D == 64 || kF32 ? 4 : 8;        // 16-column tiles per wave
   static constexpr int kHalves = D / 16 / kCols;               // waves side by side over the columns
   static constexpr int kSlots = 8 / kHalves;                   // waves along tokens and harmonics
-  static constexpr int kPitch = 2 * D + 32;                    // bytes of a tile row
-  static constexpr int kLoads = 32 * (D / 8) / (64 * kHalves); // 128-bit vectors per thread and step of 32 tokens
-  static constexpr unsigned kTiles = 2u * kSlots * 32 * kPitch;         // (two of them: the two waves of a slot of D = 256 meet)
+  static constexpr bool kOwn = kF32 || kHalves == 1;           // every wave fills a tile of its own (else the two of a slot one together)
+  static constexpr int kRow = kF32 ? 64 : D;                   // columns of a tile
+  static constexpr int kPitch = 2 * kRow + 32;                 // bytes of a tile row
+  static constexpr int kVec = 16 / sizeof(T);                  // elements of a 128-bit vector
+  static constexpr int kLoads = 32 * (kRow / kVec) / (kOwn ? 64 : 64 * kHalves);   // vectors per thread and step of 32 tokens
+  // fp32: a tile for each of the three terms of a value; two waves to a tile: two tiles in turn
+  static constexpr unsigned kTiles = (kF32 ? 3u * 8 : kOwn ? 8u : 2u * kSlots) * 32 * kPitch;
   static constexpr unsigned kSums = 8u * 2 * kCols * 1024 + kSlots * D * 4;   // the epilogue's
-  static constexpr unsigned kEnergies = kTiles > kSums ? kTiles : kSums;                // offset of fa_select_dims' energies
-  static constexpr unsigned kLds = kEnergies + kSlots * D * 8;
+  static constexpr unsigned kExtra = kTiles > kSums ? kTiles : kSums;         // offset of fa_select_dims' energies
+  static constexpr unsigned kLds = kExtra + kSlots * D * 8;
 };
 
 // cosine and sine of 2 pi n pos / T; the product is exact, its fraction is taken in fp64
@@ -64,13 +69,14 @@ constexpr int kReseed = 8;   // steps between exact phases
 // two waves of a slot fill a tile together: with one per 256 tokens and tiles shared by all waves, 8 x 2048 tokens, M = 256, took
 // 23.5 us a call against 16.5.
 // Bound: instruction issue; see make_rows_plan for the rate.
-template <int D, int NT, bool kEnergy>
+template <typename T, int D, int NT, bool kEnergy>
 __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
-  using L = RowsTile<D>;
-  constexpr int NV = D / 8, PB = L::kPitch, CW = L::kCols, NL = L::kLoads, RPL = 64 * L::kHalves / NV;
+  using L = RowsTile<T, D>;
+  constexpr bool kF32 = L::kF32;
+  constexpr int NV = L::kRow / L::kVec, PB = L::kPitch, CW = L::kCols, NL = L::kLoads, RPL = (L::kOwn ? 64 : 64 * L::kHalves) / NV;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ __attribute__((aligned(16))) uint16_t kdim[D + 8];
-  __shared__ int16_t cidx[D];
+  __shared__ int16_t cidx[D], crank[D];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -80,7 +86,7 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   const int bh = blockIdx.x - (z ? BH : 0), b = bh / p.H, h = bh - b * p.H;
   const uint8_t* mask = z ? p.t[1].mask : p.t[0].mask;
   const int Dc = z ? p.t[1].Dc : p.t[0].Dc, Du = D - Dc;
-  const bf16_t* xb = static_cast<const bf16_t*>(z ? p.t[1].x : p.t[0].x) + b * p.sx_b + h * p.sx_h;
+  const T* xb = static_cast<const T*>(z ? p.t[1].x : p.t[0].x) + b * p.sx_b + h * p.sx_h;
   const int N = p.N, lead = p.lead, hw = p.hw;
 
   // ---- this wave's harmonics, and its share of the 32-token steps: every shares-th
@@ -90,14 +96,16 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   const bool first = htile == 0;                                // (also takes the constant function and the energies)
   const bool live = first || htile * 16 < p.nmax;
 
-  const int wl = lane + 64 * half, ch = wl % NV, row0 = wl / NV;
+  const int wl = L::kOwn ? lane : lane + 64 * half, ch = wl % NV, row0 = wl / NV;
+  const int st0 = blockIdx.z * p.spc, st1 = min(p.steps, st0 + p.spc);   // this chunk's steps
+  const uint32_t lane_bytes = (kF32 ? half * 256u : 0u) + ch * 16u;
   // Rows are requested through a buffer descriptor that begins at the step's first row: a lane's offsets are the same in every
-  // step, and rows past the segment come back as zeros.  Only step 0 has rows in front of it (made zero below).
-  const uint32_t row_bytes = static_cast<uint32_t>(p.sx_n) * 2u;
-  const int64_t total = static_cast<int64_t>(N - 1) * row_bytes + 2 * D;
+  // step, and rows past the segment come back as zeros.  Only the first step may have rows in front of it (made zero below).
+  const uint32_t row_bytes = static_cast<uint32_t>(p.sx_n) * static_cast<uint32_t>(sizeof(T));
+  const int64_t total = static_cast<int64_t>(N - 1) * row_bytes + static_cast<int>(sizeof(T)) * D;
   uint32_t voff[NL];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) voff[i] = (row0 + i * RPL) * row_bytes + ch * 16;
+  for (int i = 0; i < NL; ++i) voff[i] = (row0 + i * RPL) * row_bytes + lane_bytes;
   auto load = [&](u32x4 (&x)[NL], int st) {
     const int64_t first = static_cast<int64_t>((st * shares + share) * 32 - lead) * row_bytes;
     const int64_t left = total - first;
@@ -112,9 +120,9 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   for (int j = 0; j < D / 64; ++j) mb[j] = mask ? mask[static_cast<size_t>(bh) * D + lane + 64 * j] : uint8_t{1};
   u32x4 x[NL];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {                                // (step 0: clamped)
-    const int j = min(max(share * 32 - lead + row0 + i * RPL, 0), N - 1);
-    x[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(xb) + static_cast<uint64_t>(j) * row_bytes + ch * 16);
+  for (int i = 0; i < NL; ++i) {                                // (the first step: clamped)
+    const int j = min(max((st0 * shares + share) * 32 - lead + row0 + i * RPL, 0), N - 1);
+    x[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(xb) + static_cast<uint64_t>(j) * row_bytes + lane_bytes);
   }
 
   // ---- compressed ranks, kept dims in order (pad entries point at the zero column of a tile row)
@@ -133,11 +141,13 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
         hit = hit || (j == w && (bal[j] & bit) != 0);
       }
       cidx[tid] = hit && nc < Dc ? static_cast<int16_t>(nc) : static_cast<int16_t>(-1);   // (nothing past column Dc)
+      crank[tid] = hit ? static_cast<int16_t>(-1) : static_cast<int16_t>(tid - nc);
       if (!hit) kdim[tid - nc] = static_cast<uint16_t>(tid);
     }
     if (tid < 8) kdim[Du + tid] = D;
   }
-  for (int r = tid; r < 2 * L::kSlots * 32; r += 512) *reinterpret_cast<u32x4*>(smem + r * PB + 2 * D) = u32x4{0u, 0u, 0u, 0u};
+  if constexpr (!kF32)
+    for (int r = tid; r < static_cast<int>(L::kTiles / PB); r += 512) *reinterpret_cast<u32x4*>(smem + r * PB + 2 * D) = u32x4{0u, 0u, 0u, 0u};
 
   const int n = htile * 16 + 1 + r16;
   const double inv_t = 1.0 / static_cast<double>(p.T);
@@ -161,19 +171,21 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   };
 
   const bool keep_rows = (z ? p.t[1].keep_layout : p.t[0].keep_layout) == FA_KEEP_ROWS;
-  bf16_t* keep = static_cast<bf16_t*>(z ? p.t[1].keep : p.t[0].keep);
+  T* keep = static_cast<T*>(z ? p.t[1].keep : p.t[0].keep);
   const bool write_keep = keep != nullptr && Du > 0;
   const int kp = z ? p.t[1].keep_pitch : p.t[0].keep_pitch;
   if (write_keep) keep += static_cast<int64_t>(bh) * (z ? p.t[1].keep_stride : p.t[0].keep_stride);
   const int kdiv = max(1, keep_rows ? kp >> 3 : Du);               // kept vectors per token / per 8-token group
   const uint32_t kmagic = ((1u << 21) + kdiv - 1) / kdiv;         // it / kdiv exactly: it * kdiv < 2^21
 
-  f32x4 acc[2][CW], acc0[CW], ene[CW];
+  // (acc0: column sums, the constant function; fp32: of the lane's own rows and columns)
+  f32x4 acc[2][CW], acc0[kF32 ? 1 : CW], ene[CW];
+  acc0[0] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[kF32 ? 0 : w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Sums of squares only grow, and an fp32 sum over all steps would round one way: they go to fp64, in LDS, every kReseed steps.
   // (They are the diagonal of X^T X: column r16 in lane group r16 >> 2, element r16 & 3.)
-  double* enr = reinterpret_cast<double*>(smem + L::kEnergies);
+  double* enr = reinterpret_cast<double*>(smem + L::kExtra);
   auto flush_energy = [&]() {
 #pragma unroll
     for (int w = 0; w < CW; ++w) {
@@ -194,37 +206,89 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   __syncthreads();                                              // kdim, cidx, zero columns
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int j = share * 32 - lead + row0 + i * RPL;
+    const int j = (st0 * shares + share) * 32 - lead + row0 + i * RPL;
     if (j < 0 || j >= N) x[i] = u32x4{0u, 0u, 0u, 0u};
   }
-  const int steps = p.steps;
+  int krank[4];                                                 // fp32: ranks of the lane's columns among the kept dims, or -1
+  if constexpr (kF32) {
+    const int c0 = half * 64 + 4 * ch;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) krank[e] = crank[c0 + e];
+  }
   // kept dims: the workgroups of a pair take the steps in turn, and the waves of a share theirs
   const int turns = static_cast<int>(gridDim.y) * hw;
   int my_turn = static_cast<int>(blockIdx.y) * hw + ht;
-  for (int st = 0; st < steps; ++st) {
+  for (int st = st0; st < st1; ++st) {
     const int v = (st * shares + share) * 32;                   // first (virtual) token: token j is virtual j + lead
-    unsigned char* tile = smem + ((L::kHalves > 1 ? st & 1 : 0) * L::kSlots + slot) * (32 * PB);
+    unsigned char* tile = smem + (kF32 ? 3 * wave : L::kOwn ? wave : (st & 1) * L::kSlots + slot) * (32 * PB);
+    if constexpr (kF32) {
+      if (first) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(tile + (row0 + i * RPL) * PB + ch * 16) = x[i];
+        for (int i = 0; i < NL; ++i) acc0[0] += __builtin_bit_cast(f32x4, x[i]);
+      }
+      // three bf16 terms, cut off (a value of 24 bits is their sum exactly, and the largest stay finite)
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        f32x4 r = __builtin_bit_cast(f32x4, x[i]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          u32x2 w;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const uint32_t lo = __float_as_uint(r[2 * e]), hi = __float_as_uint(r[2 * e + 1]);
+            w[e] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);   // the upper halves
+            if (k < 2) {
+              r[2 * e] -= __uint_as_float(lo & 0xffff0000u);
+              r[2 * e + 1] -= __uint_as_float(hi & 0xffff0000u);
+            }
+          }
+          *reinterpret_cast<u32x2*>(tile + k * (32 * PB) + (row0 + i * RPL) * PB + ch * 8) = w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(tile + (row0 + i * RPL) * PB + ch * 16) = x[i];
+    }
+    // kept dims of fp32 rows: element by element, while they are in registers
+    if constexpr (kF32) {
+      if (write_keep && my_turn-- == 0 && v < N + lead) {
+        my_turn = turns - 1;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+          const int j = v + row0 + i * RPL - lead;
+          if (j >= 0 && j < N) {
+            const int64_t tok = static_cast<int64_t>(p.keep_offset) + j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (krank[e] >= 0)
+                keep[keep_rows ? tok * kp + krank[e] : ((tok >> 3) * Du + krank[e]) * 8 + (tok & 7)] = __uint_as_float(x[i][e]);
+            if (keep_rows && half == 0 && ch < kp - Du) keep[tok * kp + Du + ch] = 0.0f;   // (pad columns)
+          }
+        }
+      }
+    }
     load(x, st + 1);
-    if constexpr (L::kHalves > 1) {
+    if constexpr (!L::kOwn) {
       lds_barrier();
     } else {                                                    // a wave's own LDS operations take place in order
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
       __builtin_amdgcn_wave_barrier();
     }
     if (live && v < N + lead) {
-      const unsigned char* trp = tile + (4 * g + (r16 >> 2)) * PB + (r16 & 3) * 8 + half * CW * 32;
-      Frag<bf16_t> bx[CW];
+      const unsigned char* trp = tile + (4 * g + (r16 >> 2)) * PB + (r16 & 3) * 8 + (L::kOwn ? 0 : half * CW * 32);
+      constexpr int NX = kF32 ? 3 : 1;                            // terms of a value
+      Frag<bf16_t> bx[NX][CW];
+#pragma unroll
+      for (int t = 0; t < NX; ++t)
 #pragma unroll
       for (int w = 0; w < CW; ++w) {
-        const unsigned char* tp = trp + w * 32;
+        const unsigned char* tp = trp + t * (32 * PB) + w * 32;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)tp);
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tp + 16 * PB));
         const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-        bx[w].v = u32x4{l2[0], l2[1], h2[0], h2[1]};
+        bx[t][w].v = u32x4{l2[0], l2[1], h2[0], h2[1]};
       }
-      if (st % kReseed == 0) {
+      if ((st - st0) % kReseed == 0) {
         seed(st);
         if constexpr (kEnergy) {
           if (first) flush_energy();
@@ -241,25 +305,30 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
       split_terms<NT>(bc, ac);
       split_terms<NT>(bs, as);
 #pragma unroll
-      for (int k = 0; k < NT; ++k)
+      for (int k = NX + NT - 2; k >= 0; --k)                      // (products of terms below 2^-24 of the first are left out)
 #pragma unroll
-        for (int w = 0; w < CW; ++w) {
-          mma_k32(acc[0][w], ac[k], bx[w]);
-          mma_k32(acc[1][w], as[k], bx[w]);
-        }
-      if (first) {
+        for (int t = 0; t < NX; ++t)
+          if (k - t >= 0 && k - t < NT && k < 3)
 #pragma unroll
-        for (int w = 0; w < CW; ++w) {
-          mma_k32(acc0[w], ones, bx[w]);
-          if constexpr (kEnergy) mma_k32(ene[w], bx[w], bx[w]);
+            for (int w = 0; w < CW; ++w) {
+              mma_k32(acc[0][w], ac[k - t], bx[t][w]);
+              mma_k32(acc[1][w], as[k - t], bx[t][w]);
+            }
+      if constexpr (!kF32) {
+        if (first) {
+#pragma unroll
+          for (int w = 0; w < CW; ++w) {
+            mma_k32(acc0[w], ones, bx[0][w]);
+            if constexpr (kEnergy) mma_k32(ene[w], bx[0][w], bx[0][w]);
+          }
         }
       }
     }
-    if (write_keep && my_turn-- == 0 && v < N + lead) {
+    if constexpr (!kF32) if (write_keep && my_turn-- == 0 && v < N + lead) {
       my_turn = turns - 1;
       const int rows = min(32, (N + lead - v + 7) & ~7);
       const int kvec = keep_rows ? rows * kdiv : (rows >> 3) * kdiv;
-      for (int it = wl; it < kvec; it += 64 * L::kHalves) {
+      for (int it = wl; it < kvec; it += L::kOwn ? 64 : 64 * L::kHalves) {
         const int q = static_cast<int>((static_cast<uint32_t>(it) * kmagic) >> 21);
         const int c = it - q * kdiv;
         uint32_t w[4];
@@ -306,12 +375,24 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 #pragma unroll
     for (int w = 0; w < CW; ++w) red[((wave * 2 + q) * CW + w) * 64 + lane] = acc[q][w];
   float* cst = reinterpret_cast<float*>(smem + 8 * 2 * CW * 1024);
+  float* dst = (p.part ? p.part + z * p.part_z + blockIdx.z * (z ? p.part_stride[1] : p.part_stride[0])
+                       : z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc;
   if (first) {
     if constexpr (kEnergy) flush_energy();
+    if constexpr (kF32) {                                       // (lanes of a column are NV apart)
 #pragma unroll
-    for (int w = 0; w < CW; ++w) {
-      const int col = (half * CW + w) * 16 + r16;
-      if (g == 0) cst[share * D + col] = acc0[w][0];
+      for (int e = 0; e < 4; ++e) {
+        float v = acc0[0][e];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (lane < 16) cst[share * D + half * 64 + 4 * ch + e] = v;
+      }
+    } else {
+#pragma unroll
+      for (int w = 0; w < CW; ++w) {
+        const int col = (half * CW + w) * 16 + r16;
+        if (g == 0) cst[share * D + col] = acc0[w][0];
+      }
     }
   }
   __syncthreads();
@@ -325,7 +406,7 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
       // the constant's weighted square takes a row of its own behind the tiles'
       p.t[0].ecoef[(static_cast<size_t>((p.nmax + 15) / 16) * BH + bh) * D + tid] = static_cast<double>(basis_weight(0, p.T)) * c0 * c0;
     } else if (cidx[tid] >= 0) {
-      float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + cidx[tid];
+      float* C = dst + cidx[tid];
       C[0] = static_cast<float>(p.accumulate ? C[0] + c0 : c0);
     }
   }
@@ -370,7 +451,7 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
       }
       const int rank = cidx[(half * CW + w) * 16 + r16];
       if (rank >= 0) {
-        float* C = (z ? p.t[1].coeffs : p.t[0].coeffs) + static_cast<size_t>(bh) * p.M * Dc + rank;
+        float* C = dst + rank;
         const int m0 = 2 * (htile * 16 + 4 * g) + 1;               // cosine row of harmonic n = htile * 16 + 1 + 4 g
         float old[8];
 #pragma unroll
@@ -392,55 +473,68 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 // host
 // ---------------------------------------------------------------------------
 // Time: a step of 32 tokens per wave is bound by instruction issue (rotating and splitting the basis, 80 to 112 vector
-// instructions, and 32 to 48 products, which two waves per SIMD hardly overlap).  Measured, us a step: 0.75 / 0.95 / 1.4 (two
-// terms; D = 64 / 128 / 256), 0.9 / 1.15 / 1.65 (three; with clamped addresses per row and step instead of a buffer descriptor a
-// tenth more); a round of workgroups, one per compute unit, takes 4 us besides, a
-// launch 5.  More tiles per workgroup mean fewer workgroups, each with a longer walk.  longest: 32-token steps per fp32 sum.
-RowsPlan make_rows_plan(int dtype, int B, int H, int N, int D, int M, int64_t sx_n, int keep_offset, int tensors, int terms, int longest) {
+// instructions, and 32 to 48 products, which two waves per SIMD hardly overlap; fp32 rows are split, too).  Measured, us a step:
+// 0.75 / 0.95 / 1.4 (two terms; D = 64 / 128 / 256), 0.9 / 1.15 / 1.65 (three; with clamped addresses per row and step instead of a
+// buffer descriptor a tenth more), 1.6 fp32; a round of workgroups, one per compute unit, takes 4 us besides, a launch 5, the
+// reduction of chunks another.  Many rows are bound by their bytes, read once per workgroup of a pair where they exceed the caches
+// (352 pairs x 5881 tokens, M = 50, two workgroups each: 253 us).  More tiles per workgroup mean fewer workgroups, each with a longer
+// walk; more chunks the reverse.  longest: 32-token steps per fp32 sum; most: chunks there is room for; Du: kept dims.
+RowsPlan make_rows_plan(const RowsShape& c, int terms, int longest, int most) {
   RowsPlan pl{};
-  if (dtype != FA_BF16 || (D != 64 && D != 128 && D != 256) || N <= 0) return pl;
-  if (static_cast<long>(tensors) * B * H > 65535 || sx_n >= (1 << 25)) return pl;   // (32 rows within 4 GB)
-  pl.lead = keep_offset & 7;
-  const int slots = D == 256 ? 4 : 8;
-  const int64_t blocks = (static_cast<int64_t>(N) + pl.lead + 31) / 32;
-  const int tiles = expand_tiles(M);
-  const double pairs = static_cast<double>(tensors) * B * H;
-  const double step = terms == 2 ? (D == 64 ? 0.75 : D == 128 ? 0.95 : 1.4) : (D == 64 ? 0.9 : D == 128 ? 1.15 : 1.65);
+  const bool f32 = c.dtype == FA_F32;
+  if ((c.D != 64 && c.D != 128 && c.D != 256) || c.N <= 0) return pl;
+  if (static_cast<long>(c.tensors) * c.B * c.H > 65535 || c.sx_n >= (f32 ? 1 << 24 : 1 << 25)) return pl;   // (32 rows within 4 GB)
+  pl.lead = c.keep_offset & 7;
+  const int slots = f32 ? 512 / c.D : c.D == 256 ? 4 : 8;
+  const int64_t blocks = (static_cast<int64_t>(c.N) + pl.lead + 31) / 32;
+  const int tiles = expand_tiles(c.M);
+  const double pairs = static_cast<double>(c.tensors) * c.B * c.H, es = f32 ? 4.0 : 2.0;
+  const double step = f32 ? 1.6 : terms == 2 ? (c.D == 64 ? 0.75 : c.D == 128 ? 0.95 : 1.4) : (c.D == 64 ? 0.9 : c.D == 128 ? 1.15 : 1.65);
+  const double x_bytes = pairs * c.N * es * c.D, keep_us = pairs * c.N * es * c.Du / 4.5e6;
   for (int hw = 1; hw <= slots; hw *= 2) {
     const int64_t steps = (blocks * hw + slots - 1) / slots;
-    if (steps > longest) break;
     const int groups = (tiles + hw - 1) / hw;
-    const double us = 5.0 + ceil(pairs * groups / 256.0) * (4.0 + steps * step);
-    if (!pl.use || us < pl.us) {
-      pl.use = true;
-      pl.us = us;
-      pl.hw = hw;
-      pl.groups = groups;
-      pl.steps = static_cast<int>(steps);
+    const double mem = 8.0 + keep_us + x_bytes * (x_bytes > 128e6 ? groups : 1) / 4.5e6;
+    for (int want = 1; want <= most; want = want < 4 ? want + 1 : want + want / 2) {
+      const int64_t spc = (steps + want - 1) / want;
+      const int chunks = static_cast<int>((steps + spc - 1) / spc);
+      if (spc > longest) continue;
+      const double work = 5.0 + ceil(pairs * groups * chunks / 256.0) * (4.0 + spc * step);
+      const double us = (work > mem ? work : mem) + (chunks > 1 ? 6.0 + 2.0 * chunks * pairs * c.M * (c.D - c.Du) * 4.0 / 8.0e6 : 0.0);
+      if (!pl.use || us < pl.us) {
+        pl.use = true;
+        pl.us = us;
+        pl.hw = hw;
+        pl.groups = groups;
+        pl.steps = static_cast<int>(steps);
+        pl.spc = static_cast<int>(spc);
+        pl.chunks = chunks;
+      }
     }
   }
   return pl;
 }
 
-template <int D, int NT, bool kEnergy>
+template <typename T, int D, int NT, bool kEnergy>
 static int launch_rows_t(const RowsParams& p, const RowsPlan& pl, int tensors, hipStream_t st, KernelTimers* tm) {
-  auto kern = project_rows<D, NT, kEnergy>;
+  using L = RowsTile<T, D>;
+  auto kern = project_rows<T, D, NT, kEnergy>;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          static_cast<int>(RowsTile<D>::kLds)) != hipSuccess)
+                          static_cast<int>(L::kLds)) != hipSuccess)
     return FA_ERR_HIP;
-  FA_LAUNCH_TIMED(tm, 0, kern, dim3(tensors * p.B * p.H, pl.groups), dim3(512), RowsTile<D>::kLds, st, p);
+  FA_LAUNCH_TIMED(tm, 0, kern, dim3(tensors * p.B * p.H, pl.groups, pl.chunks), dim3(512), L::kLds, st, p);
   return FA_OK;
 }
 
-int launch_rows(const RowsParams& p, const RowsPlan& pl, int D, int tensors, int terms, hipStream_t st, KernelTimers* tm) {
-  if (p.t[0].ecoef)
-    return D == 64 ? launch_rows_t<64, 3, true>(p, pl, tensors, st, tm)
-         : D == 128 ? launch_rows_t<128, 3, true>(p, pl, tensors, st, tm) : launch_rows_t<256, 3, true>(p, pl, tensors, st, tm);
-  if (terms == 3)
-    return D == 64 ? launch_rows_t<64, 3, false>(p, pl, tensors, st, tm)
-         : D == 128 ? launch_rows_t<128, 3, false>(p, pl, tensors, st, tm) : launch_rows_t<256, 3, false>(p, pl, tensors, st, tm);
-  return D == 64 ? launch_rows_t<64, 2, false>(p, pl, tensors, st, tm)
-       : D == 128 ? launch_rows_t<128, 2, false>(p, pl, tensors, st, tm) : launch_rows_t<256, 2, false>(p, pl, tensors, st, tm);
+int launch_rows(const RowsParams& p, const RowsPlan& pl, int dtype, int D, int tensors, int terms, hipStream_t st, KernelTimers* tm) {
+#define FA_ROWS(T_, NT_, E_)                                                                                              \
+  return D == 64 ? launch_rows_t<T_, 64, NT_, E_>(p, pl, tensors, st, tm)                                                 \
+       : D == 128 ? launch_rows_t<T_, 128, NT_, E_>(p, pl, tensors, st, tm) : launch_rows_t<T_, 256, NT_, E_>(p, pl, tensors, st, tm)
+  if (dtype == FA_F32) FA_ROWS(float, 3, false);
+  if (p.t[0].ecoef) FA_ROWS(bf16_t, 3, true);
+  if (terms == 3) FA_ROWS(bf16_t, 3, false);
+  FA_ROWS(bf16_t, 2, false);
+#undef FA_ROWS
 }
 
 }  // namespace fa

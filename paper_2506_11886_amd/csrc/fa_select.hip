@@ -208,7 +208,7 @@ static SelectPlan make_select_plan(int dtype, int B, int H, int N, int D, int M)
   pl.cws_bytes = fa_compress_workspace_bytes(B, H, N, D, D, M);
   pl.total = align256(off + pl.cws_bytes);
   // (what project_rows keeps, energies and weighted squares, lies in the same buffer; the size asked for stays that of the stages)
-  pl.rows = make_rows_plan(dtype, B, H, N, D, M, 0, 0, 1, 3, kRowsLongestSelect);
+  if (dtype == FA_BF16) pl.rows = make_rows_plan(RowsShape{dtype, B, H, N, D, M, 0, 0, 1, 0.0}, 3, kRowsLongestSelect, 1);
   pl.off_ecoef = pl.off_coeffs;
   const size_t rows_total = pl.off_ecoef + static_cast<size_t>(expand_tiles(M) + 1) * BH * D * sizeof(double);
   if (rows_total > pl.total) pl.rows.use = false;      // (a handful of rows)
@@ -257,9 +257,9 @@ int fa_select_dims(const void* x, int dtype, int64_t sx_b, int64_t sx_h, int64_t
     r.t[0].Dc = D;
     r.sx_b = sx_b; r.sx_h = sx_h; r.sx_n = sx_n;
     r.B = B; r.H = H; r.N = N; r.M = M; r.T = N;
-    r.hw = pl.rows.hw; r.steps = pl.rows.steps; r.nmax = M / 2;
+    r.hw = pl.rows.hw; r.steps = r.spc = pl.rows.steps; r.nmax = M / 2;
     p.chunks = 1;
-    const int rc = launch_rows(r, pl.rows, D, 1, 3, stream, nullptr);
+    const int rc = launch_rows(r, pl.rows, dtype, D, 1, 3, stream, nullptr);
     if (rc != FA_OK) return rc;
     p.ecoef = r.t[0].ecoef; p.tiles = (M / 2 + 15) / 16 + 1;
     hipLaunchKernelGGL(select_rank, dim3(B * H), dim3(kRBlock), 0, stream, p);

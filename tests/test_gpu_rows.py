@@ -35,21 +35,24 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("D,N,M,T,t0,off,Dc", CASES)
+@pytest.mark.parametrize("D,N,M,T,t0,off,Dc", CASES + [(128, 9000, 40, 9000, 0, 4, 90), (256, 3001, 70, 3500, 11, 1, 200)])
 @pytest.mark.parametrize("layout", [0, 1])
-def test_rows_projection_matches_oracle(D, N, M, T, t0, off, Dc, layout):
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+def test_rows_projection_matches_oracle(D, N, M, T, t0, off, Dc, layout, dt):
     import paper_2506_11886_amd as fa
-    print(f"[case] rows D{D} N{N} M{M} T{T} t0 {t0} off {off} Dc{Dc} layout {layout}", flush=True)
+    print(f"[case] rows {dt} D{D} N{N} M{M} T{T} t0 {t0} off {off} Dc{Dc} layout {layout}", flush=True)
     x, mask = _segment(D, N, Dc, 3, N + M)
+    if dt == torch.float32:      # (all 24 bits of a value)
+        x = x * np.float32(1.2345678)
     want, keep = fk.compress_batched(x, mask, M, T, t0)
-    Du, dt = D - Dc, torch.bfloat16
+    Du = D - Dc
     prev = torch.randn((1, 3, M, Dc), device="cuda")
     shape = (1, 3, off + N, fa.keep_rows_pitch(Du)) if layout == fa.FA_KEEP_ROWS else (1, 3, fa.tok8_numel(off + N, Du))
     slab = torch.full(shape, 7.0, dtype=dt, device="cuda")
     c, _ = fa.fa_compress(to_dev(x, dtype=dt), to_dev(mask), Dc, M, T, t0, True, prev.clone(), slab, layout, off)
     torch.cuda.synchronize()
     # 2^-17 of a basis value's size at two terms, fp32 at three; a state sums N values of size 1
-    tol = 2e-5 if N > 512 else 2e-6
+    tol = 2e-5 if N > 512 and dt == torch.bfloat16 else 2e-6
     assert rel_err(c.cpu().numpy(), want + prev.cpu().numpy().astype(np.float64), np.sqrt(N)) <= tol
     if Du:
         if layout == fa.FA_KEEP_ROWS:
@@ -61,19 +64,21 @@ def test_rows_projection_matches_oracle(D, N, M, T, t0, off, Dc, layout):
             assert np.array_equal(got[:, :, off:], keep.astype(np.float32)) and (got[:, :, :off] == 7.0).all()
 
 
-@pytest.mark.parametrize("D,B,N,M,Dkc,Dvc", [(128, 70, 290, 90, 96, 101), (64, 40, 300, 150, 40, 64), (256, 20, 300, 64, 200, 150)])
-def test_rows_projection_of_a_pair(D, B, N, M, Dkc, Dvc):
-    """Enough pairs that a workgroup takes several harmonic tiles; rows of a wider tensor."""
+@pytest.mark.parametrize("D,B,N,M,Dkc,Dvc", [(128, 70, 290, 90, 96, 101), (64, 40, 300, 150, 40, 64), (256, 20, 300, 64, 200, 150),
+                                             (128, 2, 6001, 40, 96, 101)])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+def test_rows_projection_of_a_pair(D, B, N, M, Dkc, Dvc, dt):
+    """Enough pairs that a workgroup takes several harmonic tiles, or few of them and fp32 tokens in chunks; rows of a wider tensor."""
     import paper_2506_11886_amd as fa
     print(f"[case] rows pair D{D} B{B} N{N} M{M} {Dkc}/{Dvc}", flush=True)
     k, kmask = _segment(D, N, Dkc, B, 1)
     v, vmask = _segment(D, N, Dvc, B, 2)
-    wide = lambda a: torch.nn.functional.pad(to_dev(a, dtype=torch.bfloat16), (0, 8))[..., :D]
+    wide = lambda a: torch.nn.functional.pad(to_dev(a, dtype=dt), (0, 8))[..., :D]
     ck, kk, cv, vk = fa.fa_compress_kv(wide(k), wide(v), to_dev(kmask), to_dev(vmask), Dkc, Dvc, M, N + 100, t0=50)
     torch.cuda.synchronize()
     for x, mask, c in ((k, kmask, ck), (v, vmask, cv)):
         want, keep = fk.compress_batched(x, mask, M, N + 100, 50)
-        assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= 2e-6
+        assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= (2e-5 if N > 512 and dt == torch.bfloat16 else 2e-6)
         if x is k:
             assert np.array_equal(kk[..., :D - Dkc].float().cpu().numpy(), keep.astype(np.float32))
         else:

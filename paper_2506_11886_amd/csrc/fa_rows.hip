@@ -58,6 +58,7 @@ __device__ __forceinline__ void split_terms(const float (&v)[8], Frag<bf16_t> (&
   }
 }
 
+constexpr bool rows_stats_tile(int D) { return D > 64; }
 constexpr int kReseed = 8;   // steps between exact phases
 
 // NT: bf16 terms of a basis value; kEnergy (fa_select_dims): sums of squares, and weighted squares of the states instead of them.
@@ -93,11 +94,16 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   const int half = wave % L::kHalves, slot = wave / L::kHalves;
   const int ht = slot % hw, share = slot / hw, shares = L::kSlots / hw;
   const int htile = blockIdx.y * hw + ht;
-  const bool first = htile == 0;                                // (also takes the constant function and the energies)
+  // the wave that takes the constant function, too, and the energies of fa_select_dims: that of the first tile; above D = 64, where
+  // both would not leave it the registers (59 spilled), fa_select_dims has a tile of its own for them behind the last one, in
+  // the accumulators that hold cosines and sines elsewhere (2 pairs x 2531, M = 316: 34.5 -> 23.8 us)
+  constexpr bool kStats = kEnergy && rows_stats_tile(D);
+  const int stile = kStats ? (p.nmax + 15) / 16 : 0;
+  const bool first = htile == stile;
   const bool live = first || htile * 16 < p.nmax;
 
   const int wl = L::kOwn ? lane : lane + 64 * half, ch = wl % NV, row0 = wl / NV;
-  const int st0 = blockIdx.z * p.spc, st1 = min(p.steps, st0 + p.spc);   // this chunk's steps
+  const int st0 = kEnergy ? 0 : blockIdx.z * p.spc, st1 = kEnergy ? p.steps : min(p.steps, st0 + p.spc);   // this chunk's steps
   const uint32_t lane_bytes = (kF32 ? half * 256u : 0u) + ch * 16u;
   // Rows are requested through a buffer descriptor that begins at the step's first row: a lane's offsets are the same in every
   // step, and rows past the segment come back as zeros.  Only the first step may have rows in front of it (made zero below).
@@ -179,22 +185,24 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
   const uint32_t kmagic = ((1u << 21) + kdiv - 1) / kdiv;         // it / kdiv exactly: it * kdiv < 2^21
 
   // (acc0: column sums, the constant function; fp32: of the lane's own rows and columns)
-  f32x4 acc[2][CW], acc0[kF32 ? 1 : CW], ene[CW];
+  constexpr int N0 = kF32 || kStats ? 1 : CW;
+  f32x4 acc[2][CW], acc0[N0], ene[CW];
   acc0[0] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[kF32 ? 0 : w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int w = 0; w < CW; ++w) acc[0][w] = acc[1][w] = acc0[N0 == 1 ? 0 : w] = ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Sums of squares only grow, and an fp32 sum over all steps would round one way: they go to fp64, in LDS, every kReseed steps.
   // (They are the diagonal of X^T X: column r16 in lane group r16 >> 2, element r16 & 3.)
   double* enr = reinterpret_cast<double*>(smem + L::kExtra);
   auto flush_energy = [&]() {
 #pragma unroll
     for (int w = 0; w < CW; ++w) {
-      const float lo = (r16 & 1) ? ene[w][1] : ene[w][0], hi = (r16 & 1) ? ene[w][3] : ene[w][2];
+      f32x4& sq = kStats ? acc[1][w] : ene[w];
+      const float lo = (r16 & 1) ? sq[1] : sq[0], hi = (r16 & 1) ? sq[3] : sq[2];
       if (g == (r16 >> 2)) {
         double* e = enr + share * D + (half * CW + w) * 16 + r16;
         *e += (r16 & 2) ? hi : lo;
       }
-      ene[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+      sq = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   Frag<bf16_t> ones;
@@ -288,9 +296,20 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
         const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
         bx[t][w].v = u32x4{l2[0], l2[1], h2[0], h2[1]};
       }
+      if constexpr (kStats) {
+        if (first) {
+          if (st % kReseed == 0) flush_energy();
+#pragma unroll
+          for (int w = 0; w < CW; ++w) {
+            mma_k32(acc[0][w], ones, bx[0][w]);
+            mma_k32(acc[1][w], bx[0][w], bx[0][w]);
+          }
+          continue;                                             // (no kept dims here, and no barrier behind)
+        }
+      }
       if ((st - st0) % kReseed == 0) {
         seed(st);
-        if constexpr (kEnergy) {
+        if constexpr (kEnergy && !kStats) {
           if (first) flush_energy();
         }
       } else {
@@ -318,8 +337,8 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
         if (first) {
 #pragma unroll
           for (int w = 0; w < CW; ++w) {
-            mma_k32(acc0[w], ones, bx[0][w]);
-            if constexpr (kEnergy) mma_k32(ene[w], bx[0][w], bx[0][w]);
+            mma_k32(acc0[N0 == 1 ? 0 : w], ones, bx[0][w]);
+            if constexpr (kEnergy && !kStats) mma_k32(ene[w], bx[0][w], bx[0][w]);
           }
         }
       }
@@ -391,12 +410,12 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 #pragma unroll
       for (int w = 0; w < CW; ++w) {
         const int col = (half * CW + w) * 16 + r16;
-        if (g == 0) cst[share * D + col] = acc0[w][0];
+        if (g == 0) cst[share * D + col] = kStats ? acc[0][w][0] : acc0[N0 == 1 ? 0 : w][0];
       }
     }
   }
   __syncthreads();
-  if (blockIdx.y == 0 && tid < D) {
+  if (static_cast<int>(blockIdx.y) == stile / hw && tid < D) {
     double c0 = 0.0;
     for (int q = 0; q < shares; ++q) c0 += cst[q * D + tid];
     if constexpr (kEnergy) {
@@ -410,7 +429,7 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
       C[0] = static_cast<float>(p.accumulate ? C[0] + c0 : c0);
     }
   }
-  if (!live) return;
+  if (!live || (kStats && first)) return;
   if constexpr (kEnergy) {
     // weighted squares over the 16 harmonics of a tile: share `share` of the tile's waves takes every shares-th column tile
     for (int w = share; w < CW; w += shares) {
@@ -487,14 +506,15 @@ RowsPlan make_rows_plan(const RowsShape& c, int terms, int longest, int most) {
   pl.lead = c.keep_offset & 7;
   const int slots = f32 ? 512 / c.D : c.D == 256 ? 4 : 8;
   const int64_t blocks = (static_cast<int64_t>(c.N) + pl.lead + 31) / 32;
-  const int tiles = expand_tiles(c.M);
+  const int tiles = c.stats && rows_stats_tile(c.D) ? (c.M / 2 + 15) / 16 + 1 : expand_tiles(c.M);
   const double pairs = static_cast<double>(c.tensors) * c.B * c.H, es = f32 ? 4.0 : 2.0;
   const double step = f32 ? 1.6 : terms == 2 ? (c.D == 64 ? 0.75 : c.D == 128 ? 0.95 : 1.4) : (c.D == 64 ? 0.9 : c.D == 128 ? 1.15 : 1.65);
   const double x_bytes = pairs * c.N * es * c.D, keep_us = pairs * c.N * es * c.Du / 4.5e6;
   for (int hw = 1; hw <= slots; hw *= 2) {
     const int64_t steps = (blocks * hw + slots - 1) / slots;
     const int groups = (tiles + hw - 1) / hw;
-    const double mem = 8.0 + keep_us + x_bytes * (x_bytes > 128e6 ? groups : 1) / 4.5e6;
+    const double again = x_bytes > 256e6 ? 1.0 : x_bytes > 128e6 ? 0.6 : 0.0;
+    const double mem = 8.0 + keep_us + x_bytes * (1.0 + again * (groups - 1)) / 4.5e6;
     for (int want = 1; want <= most; want = want < 4 ? want + 1 : want + want / 2) {
       const int64_t spc = (steps + want - 1) / want;
       const int chunks = static_cast<int>((steps + spc - 1) / spc);

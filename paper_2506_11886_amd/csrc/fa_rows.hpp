@@ -38,6 +38,7 @@ struct RowsShape {
   int64_t sx_n;
   int keep_offset, tensors;
   double Du;           // kept dims written, over the tensors
+  bool stats;          // fa_select_dims: energies and weighted squares
 };
 // terms: bf16 terms of a basis value (2: 2^-17, 3: fp32)
 RowsPlan make_rows_plan(const RowsShape& c, int terms, int longest, int most);

@@ -208,7 +208,7 @@ static SelectPlan make_select_plan(int dtype, int B, int H, int N, int D, int M)
   pl.cws_bytes = fa_compress_workspace_bytes(B, H, N, D, D, M);
   pl.total = align256(off + pl.cws_bytes);
   // (what project_rows keeps, energies and weighted squares, lies in the same buffer; the size asked for stays that of the stages)
-  if (dtype == FA_BF16) pl.rows = make_rows_plan(RowsShape{dtype, B, H, N, D, M, 0, 0, 1, 0.0}, 3, kRowsLongestSelect, 1);
+  if (dtype == FA_BF16) pl.rows = make_rows_plan(RowsShape{dtype, B, H, N, D, M, 0, 0, 1, 0.0, true}, 3, kRowsLongestSelect, 1);
   pl.off_ecoef = pl.off_coeffs;
   const size_t rows_total = pl.off_ecoef + static_cast<size_t>(expand_tiles(M) + 1) * BH * D * sizeof(double);
   if (rows_total > pl.total) pl.rows.use = false;      // (a handful of rows)

@@ -1146,8 +1146,9 @@ static RowsPlan rows_plan(const RowsShape& c, int Dc, int most) {
   if (Dc <= 0) return RowsPlan{};
   return make_rows_plan(c, rows_short(c.dtype, c.N) ? 3 : 2, c.dtype == FA_F32 ? kRowsLongestF32 : kRowsLongest, most);
 }
-static bool prefer_rows(const RowsPlan& rp, int dtype, int N, double other) {
-  return rp.use && (rows_short(dtype, N) || rp.us < other);
+// (the estimate of compress_project_fast is the slowest of its calls': short segments of many pairs take down to 0.63 of it)
+static bool prefer_rows(const RowsPlan& rp, const RowsShape& c, bool moments, double other) {
+  return rp.use && (rows_short(c.dtype, c.N) || rp.us < (moments ? 0.9 : c.D == 128 ? 0.7 : 0.95) * other);
 }
 
 // One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one
@@ -1393,8 +1394,9 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const double direct = direct_us(pl.us_least, pl.us_work);
   const bool room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
   const bool moments = room && prefer_moments(mp, specialised && one_vector, direct, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
-  const RowsPlan rp = rows_plan(RowsShape{dtype, B, H, N, D, M, sx_n, keep_offset, 1, x_keep ? Du : 0.0, false}, Dc, pl.total > 0 ? pl.Sc : 1);
-  if (!only_params && prefer_rows(rp, dtype, N, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
+  const RowsShape shape{dtype, B, H, N, D, M, sx_n, keep_offset, 1, x_keep ? Du : 0.0, false};
+  const RowsPlan rp = rows_plan(shape, Dc, pl.total > 0 ? pl.Sc : 1);
+  if (!only_params && prefer_rows(rp, shape, moments, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
     const MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                        B, H, N, D, M, T, t0, accumulate, keep_offset};
     float* const part[2] = {static_cast<float*>(workspace), nullptr};
@@ -1559,8 +1561,9 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   const size_t lk = ((static_cast<size_t>(B) * H * M * Dkc + 3) & ~size_t(3)) * sizeof(float), lv = ((static_cast<size_t>(B) * H * M * Dvc + 3) & ~size_t(3)) * sizeof(float);
   int most = 1;   // chunks that either tensor's share of the workspace holds
   while (most < FA_MAX_SPLITS && (most + 1) * lk <= wk && (most + 1) * lv <= wv) ++most;
-  const RowsPlan rp = rows_plan(RowsShape{dtype, B, H, N, D, M, sx_n, keep_offset, 2, kept, false}, Dkc < Dvc ? Dkc : Dvc, most);
-  if (prefer_rows(rp, dtype, N, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
+  const RowsShape shape{dtype, B, H, N, D, M, sx_n, keep_offset, 2, kept, false};
+  const RowsPlan rp = rows_plan(shape, Dkc < Dvc ? Dkc : Dvc, most);
+  if (prefer_rows(rp, shape, moments, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
     float* const part[2] = {reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + wk)};
     rc = run_rows(c, dtype, rp, part, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;

@@ -557,8 +557,9 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   const T* kk = static_cast<const T*>(p.k_keep) + bh * p.kk_stride;
   const T* vk = static_cast<const T*>(p.v_keep) + bh * p.vk_stride;
   const int Nm1 = Nb - 1;
-  const int NV = max(1, 2 * KT / NW);                // V^mu token blocks of this wave per step
-  const int NK = max(1, 4 * KT / NW);                // K^mu row blocks
+  constexpr bool k4 = NW == kWaves;
+  const int NV = k4 ? (KT >= 2 ? KT / 2 : 1) : 1;    // V^mu token blocks of this wave per step
+  const int NK = k4 ? KT : max(1, KT / 2);           // K^mu row blocks
 
   // ---- LDS carve-up -------------------------------------------------------
   f32x4* xs = reinterpret_cast<f32x4*>(smem);                   // [NW][kRB][64] partial scores
@@ -607,7 +608,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     if (kchunks > 0) {
 #pragma unroll
       for (int i = 0; i < kKF; ++i)
-        if (i < NK) kf[i].load(k_ptr(base, min(wave * NK + i, 4 * KT - 1), 0));
+        if (i < NK) kf[i].load(k_ptr(base, k4 ? wave * NK + i : min(wave * NK + i, 4 * KT - 1), 0));
     }
     if constexpr (kPrefetchV) {
       if (DVT > 0) {
@@ -633,7 +634,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   for (int i = 0; i < kGLoads; ++i)
     gv[i] = *reinterpret_cast<const f32x4*>(p.gs + hq0 * Mint + 4 * min(tid + i * NT, ng4 - 1));
   // this lane's share of the softmax: column ocol, rows 16 orb + 4 oq4 + v of the tile
-  const int ocol = 4 * (wave % kWaves) + (lane & 3), orb = lane >> 4, oq4 = (lane >> 2) & 3;
+  const int ocol = 4 * (k4 ? wave : wave % kWaves) + (lane & 3), orb = lane >> 4, oq4 = (lane >> 2) & 3;
   const int ocol_k = ocol / Gp, ocol_h = ocol % Gp;
   const bool olive = ocol_k < KT && ocol_h < G;
   const float g0 = p.g0[hq0 + min(ocol_h, G - 1)];
@@ -812,7 +813,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
     if (kchunks > 0) {
 #pragma unroll
       for (int i = 0; i < kKF; ++i) {
-        if (i < NK && wave * NK + i < 4 * KT) {
+        if (i < NK && (k4 || wave * NK + i < 4 * KT)) {
           const int uid = wave * NK + i, k = uid >> 2, rbd = uid & 3;
           f32x4 ka = {0.f, 0.f, 0.f, 0.f};
           {
@@ -845,7 +846,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
       for (int rb = 0; rb < kRB; ++rb) xw[rb * 64] = sacc[rb];
     }
     __syncthreads();
-    if (NW == kWaves || wave < kWaves) {
+    if (k4 || wave < kWaves) {
     f32x4 sv;
     {
       const f32x4* xr = xs + orb * 64 + oq4 * 16 + ocol;
@@ -987,7 +988,7 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   l_run = row_stride_sum(l_run, 4);
   l_run += __shfl_xor(l_run, 16, kWave);
   l_run += __shfl_xor(l_run, 32, kWave);
-  if (lane < 4 && wave < kWaves) {
+  if (lane < 4 && (k4 || wave < kWaves)) {
     st_m[ocol] = m_run;
     st_l[ocol] = l_run;
   }
@@ -2973,6 +2974,27 @@ static bool make_local(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D,
   return true;
 }
 
+// Eight-wave workgroups of the general kernel take a compute unit each, and a chunk costs them about a step and a half besides its
+// steps: fewer, longer chunks where those are fewer rounds of workgroups (160 pairs x 1640 rows, M = 795: two chunks a pair, two
+// rounds, 206 us the call; one chunk 145).  The records keep their places: the workspace is laid out for the chunks of the plan.
+static void join_chunks(DecodePlan& pl, int B, int Hkv, int N) {
+  if (pl.nw != kWaves8 || pl.local.use || pl.Swp > 0 || pl.Sm <= 1) return;
+  const long pairs = static_cast<long>(B) * Hkv, step = pl.KT * kTJ, steps = (N + step - 1) / step;
+  double least = 0.0;
+  int best = pl.Sm;
+  for (int sm = pl.Sm; sm >= 1; --sm) {
+    const long spc = (steps + sm - 1) / sm;
+    const double t = static_cast<double>((pairs * sm + 255) / 256) * (spc + 1.5);
+    if (sm == pl.Sm || t < 0.97 * least) {
+      least = t;
+      best = sm;
+    }
+  }
+  if (best == pl.Sm) return;
+  pl.chunk_m = static_cast<int>((steps + best - 1) / best * step);
+  pl.Sm = (N + pl.chunk_m - 1) / pl.chunk_m;
+}
+
 static int check_decode_shapes(int dtype, int B, int Hq, int Hkv, int D, int Dkc, int Dvc, int M,
                                int T, int t0, int N, int W, int num_splits) {
   if (dtype != FA_F32 && dtype != FA_BF16) return FA_ERR_UNSUPPORTED;
@@ -3273,6 +3295,7 @@ static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, 
   // (a buffer that only holds the other form's state is served by that)
   make_local(pl, dtype, B, Hq, Hkv, D, Dkc, Dvc, N, W, num_splits, local_form(M, T), workspace_bytes);
   if (workspace_bytes < pl.total) return FA_ERR_WORKSPACE;
+  if (num_splits == 0) join_chunks(pl, B, Hkv, N);
 
   DecodeParams p{};
   p.q = q; p.ck = ck; p.cv = cv; p.kmask = kmask; p.vmask = vmask;

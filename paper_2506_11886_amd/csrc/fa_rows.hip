@@ -494,8 +494,8 @@ __global__ __launch_bounds__(512, 2) void project_rows(RowsParams p) {
 // Time: a step of 32 tokens per wave is bound by instruction issue (rotating and splitting the basis, 80 to 112 vector
 // instructions, and 32 to 48 products, which two waves per SIMD hardly overlap; fp32 rows are split, too).  Measured, us a step:
 // 0.75 / 0.95 / 1.4 (two terms; D = 64 / 128 / 256), 0.9 / 1.15 / 1.65 (three; with clamped addresses per row and step instead of a
-// buffer descriptor a tenth more), 1.6 fp32; a round of workgroups, one per compute unit, takes 4 us besides, a launch 5, the
-// reduction of chunks another.  Many rows are bound by their bytes, read once per workgroup of a pair where they exceed the caches
+// buffer descriptor a tenth more), 1.6 fp32; a round of workgroups, one per compute unit, takes 4 us and its states besides, a launch 5,
+// the reduction of chunks another.  Many rows are bound by their bytes at 3 TB/s (rounds of workgroups in step), read once per workgroup of a pair where they exceed the caches
 // (352 pairs x 5881 tokens, M = 50, two workgroups each: 253 us).  More tiles per workgroup mean fewer workgroups, each with a longer
 // walk; more chunks the reverse.  longest: 32-token steps per fp32 sum; most: chunks there is room for; Du: kept dims.
 RowsPlan make_rows_plan(const RowsShape& c, int terms, int longest, int most) {
@@ -509,17 +509,19 @@ RowsPlan make_rows_plan(const RowsShape& c, int terms, int longest, int most) {
   const int tiles = c.stats && rows_stats_tile(c.D) ? (c.M / 2 + 15) / 16 + 1 : expand_tiles(c.M);
   const double pairs = static_cast<double>(c.tensors) * c.B * c.H, es = f32 ? 4.0 : 2.0;
   const double step = f32 ? 1.6 : terms == 2 ? (c.D == 64 ? 0.75 : c.D == 128 ? 0.95 : 1.4) : (c.D == 64 ? 0.9 : c.D == 128 ? 1.15 : 1.65);
-  const double x_bytes = pairs * c.N * es * c.D, keep_us = pairs * c.N * es * c.Du / 4.5e6;
+  const double x_bytes = pairs * c.N * es * c.D, keep_us = pairs * c.N * es * c.Du / 3.0e6;
   for (int hw = 1; hw <= slots; hw *= 2) {
     const int64_t steps = (blocks * hw + slots - 1) / slots;
     const int groups = (tiles + hw - 1) / hw;
     const double again = x_bytes > 256e6 ? 1.0 : x_bytes > 128e6 ? 0.6 : 0.0;
-    const double mem = 8.0 + keep_us + x_bytes * (1.0 + again * (groups - 1)) / 4.5e6;
+    const double mem = 8.0 + keep_us + x_bytes * (1.0 + again * (groups - 1)) / 3.0e6;
+    const double alike = 1.0 + (f32 ? 0.2 : 0.5) * (hw - 1) / (slots > 1 ? slots - 1 : 1);   // (waves that ask for the same rows at once)
+    const double fixed = 4.0 + hw * (c.D - c.Du) / 200.0;   // (the states a workgroup writes, too)
     for (int want = 1; want <= most; want = want < 4 ? want + 1 : want + want / 2) {
       const int64_t spc = (steps + want - 1) / want;
       const int chunks = static_cast<int>((steps + spc - 1) / spc);
       if (spc > longest) continue;
-      const double work = 5.0 + ceil(pairs * groups * chunks / 256.0) * (4.0 + spc * step);
+      const double work = 5.0 + ceil(pairs * groups * chunks / 256.0) * (fixed + spc * step * alike);
       const double us = (work > mem ? work : mem) + (chunks > 1 ? 6.0 + 2.0 * chunks * pairs * c.M * (c.D - c.Du) * 4.0 / 8.0e6 : 0.0);
       if (!pl.use || us < pl.us) {
         pl.use = true;

@@ -21,6 +21,9 @@
 // columns into an LDS staging tile that is written out with 128-bit stores.
 // The constant function (m = 0) is a plain column sum.  Token chunks are reduced
 // in a second, deterministic pass.
+//
+// Long bf16 segments go through local moments instead (fa_moments.hip), fp32 and short ones and fast harmonics through
+// project_rows (fa_rows.hip); the choice is below, with the rules' figures.
 
 #include "fa_common.hpp"
 #include "fa_mma.hpp"

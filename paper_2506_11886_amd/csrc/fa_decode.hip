@@ -16,14 +16,15 @@
 // heads of the group), so the table is shared by the heads and by both sides.
 // The V side is the mirror image: r' = P^T E per tile, rotated back once per
 // chunk.  The table is split by harmonics over the four waves of a workgroup
-// and lives in registers.
+// (eight for long series) and lives in registers.
 //
 // The kernels are latency-shaped: a decode step moves only tens of megabytes,
 // so every kernel requests all of its global-memory operands up front (one
 // dependent round trip) and hides them behind table construction and MFMAs.
 //
 // Launches on the caller's stream:
-//   1. decode_prepare : g (series order) for every query head, from C_k and q;
+//   1. decode_prepare2 (decode_prepare: fewer than four compressed dims; with the full-width rows: decode_prepare_window,
+//      decode_prepare_full) : g (series order) for every query head, from C_k and q;
 //      q at the kept K dims, packed.
 //   2. decode_local (fa_local.hip) where the period is long against the states kept: the series by
 //      interpolation inside blocks of tokens, 16 or 32 matrix rows a token instead of M; else
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(kBlock) void decode_prepare(DecodeParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// 1b. g = diag(w) C_k q_c for compressed counts that are a multiple of 4: the streaming form
+// 1b. g = diag(w) C_k q_c for at least four compressed dims: the streaming form
 // ---------------------------------------------------------------------------
 // TPR threads share a row of C_k and read it as interleaved 128-bit vectors, all requested
 // before anything else happens (rows are independent of the mask); the group's queries at the

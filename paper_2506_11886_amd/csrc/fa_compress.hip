@@ -1121,7 +1121,7 @@ static double moments_us(const MomentPlan& mp, int tensors, int B, int H, int N,
   const double pairs = static_cast<double>(tensors) * B * H, mom = pairs * mp.blocks * kMomP * Dc * 4.0;
   const double rows = pairs * N;
   const int ct = (static_cast<int>(Dc) + 15) / 16, tiles = expand_tiles(M);
-  const int ctw = expand_columns(ct, tiles, pairs), ht = expand_tiles_per_wg(ct, tiles, pairs), passes = (tiles + ht - 1) / ht;
+  const int ctw = expand_columns(ct, tiles, pairs, mp.blocks), ht = expand_tiles_per_wg(ct, tiles, pairs, mp.blocks), passes = (tiles + ht - 1) / ht;
   const double rounds = ceil(pairs * passes * ((ct + ctw - 1) / ctw) / 256.0);
   return 8.0 + rows * 2.0 * (D + Du) / 5.5e6 + mom / 6.0e6 + rounds * (ht == 1 ? 4.0 : accumulate ? 5.0 : 2.5) +
          mom * passes / (ht == 1 ? 11.0e6 : mom < 128e6 ? 4.5e6 : 3.7e6);

@@ -775,8 +775,8 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   const int dmax = tensors == 2 && p.t[1].Dc > p.t[0].Dc ? p.t[1].Dc : p.t[0].Dc;
   const int ct = (dmax + 15) / 16, tiles = expand_tiles(p.M);
   if (!p.t[0].ecoef) {
-    const int ht = expand_tiles_per_wg(ct, tiles, static_cast<double>(tensors) * p.B * p.H);
-    const int ctw = expand_columns(ct, tiles, static_cast<double>(tensors) * p.B * p.H);
+    const int ht = expand_tiles_per_wg(ct, tiles, static_cast<double>(tensors) * p.B * p.H, p.blocks);
+    const int ctw = expand_columns(ct, tiles, static_cast<double>(tensors) * p.B * p.H, p.blocks);
     const int ks = ctw <= 4 ? 2 : 1;
     const unsigned lds = 2u * ks * kExpSteps * 4096u;            // (kExpSteps / ht steps of ht operands; the shares' sums fit in)
     auto kern = ht == 2 ? (ctw >= kExpSteps ? fa_expand16<2, 1> : fa_expand16<2, 2>) : (ctw >= kExpSteps ? fa_expand16<1, 1> : fa_expand16<1, 2>);

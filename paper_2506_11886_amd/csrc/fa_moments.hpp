@@ -65,15 +65,18 @@ int launch_moments(const MomentParams& p, const MomentPlan& pl, int tensors, hip
 int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTimers* tm);
 
 constexpr int kExpandRows = 16;       // harmonics per workgroup of fa_expand
-// 16-column tiles a workgroup of fa_expand16 takes out of ct: all share the operands; with few workgroups two groups of columns
-inline int expand_columns(int ct, int tiles, double pairs) {
+// 16-column tiles a workgroup of fa_expand16 takes out of ct: all share the operands; with fewer workgroups than units two groups of columns.
+// At one workgroup per unit and many blocks two groups of two tiles each are as many workgroups and read less
+// (16 pairs, M = 512, 112 dims: 128 K tokens, the call 144.6 -> 140.7 us, 32 K tokens 64.9 -> 62.1; 72 blocks of 32 pairs,
+// M = 256: 83.3 -> 85.2)
+inline int expand_columns(int ct, int tiles, double pairs, int blocks) {
   int ctw = ct < 8 ? ct : 8;
-  if (ct > 2 && ct <= 8 && tiles * pairs < 256.0) ctw = (ct + 1) / 2;
+  const bool one_round = ct > 4 && tiles > 1 && blocks >= 128 && tiles * pairs <= 256.0;
+  if (ct > 2 && ct <= 8 && (tiles * pairs < 256.0 || one_round)) ctw = (ct + 1) / 2;
   return ctw < 2 ? 2 : ctw;
 }
-// 16-harmonic tiles a workgroup takes: two once single ones are more workgroups than compute units
-inline int expand_tiles_per_wg(int ct, int tiles, double pairs) {
-  const int ctw = expand_columns(ct, tiles, pairs);
+inline int expand_tiles_per_wg(int ct, int tiles, double pairs, int blocks) {
+  const int ctw = expand_columns(ct, tiles, pairs, blocks);
   return tiles > 1 && pairs * tiles * ((ct + ctw - 1) / ctw) > 256.0 ? 2 : 1;
 }
 inline int expand_tiles(int M) { return M / 2 > 0 ? (M / 2 + kExpandRows - 1) / kExpandRows : 1; }

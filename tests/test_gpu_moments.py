@@ -382,3 +382,18 @@ def test_moment_pair_of_long_workgroups(D, B, H, N, M):
             assert rel_err(c[b, h].cpu().numpy(), want, np.sqrt(N)) <= 5e-5
             got = kk[b, h, :, :D - n] if x is k else fa.keep_rows_from_tok8(vk[b, h], N, D - n)
             assert np.array_equal(got.float().cpu().numpy(), keep.astype(np.float32))
+
+
+# one workgroup per state and tile of 32 harmonics would just fill the chip: two groups of columns of two tiles each, the last tile partial
+@pytest.mark.parametrize("M,Dc", [(511, 81), (481, 128)])
+def test_moment_expansion_in_one_round(M, Dc):
+    import paper_2506_11886_amd as fa
+    D, H, N = 128, 8, 32301
+    print(f"[case] expansion in one round M{M} Dc{Dc}", flush=True)
+    x, mask = _segment(D, N, Dc, H, M)
+    dx, dm = to_dev(x, dtype=torch.bfloat16), to_dev(mask)
+    ck, _, cv, _ = fa.fa_compress_kv(dx, dx.flip(1), dm, dm.flip(1), Dc, Dc, M, N)
+    torch.cuda.synchronize()
+    want, _ = fk.compress_batched(x[:, ::7], mask[:, ::7], M, N, 0)
+    assert rel_err(ck[:, ::7].cpu().numpy(), want, np.sqrt(N)) <= 5e-5
+    assert torch.equal(cv.flip(1), ck)

@@ -1,7 +1,7 @@
 // Python entry of the C ABI: one function per enqueueing call of fourier_attn.h, positional arguments converted by the C
 // parameter's type.  A pointer takes a tensor (its data_ptr()), an address or None; the result is the status.
-// Measured on a step of the ctypes binding it replaces for these calls: fa_decode in one launch 10.2 -> 4.9 us of host time (1.7 us
-// of it ctypes, 2.7 us torch.cuda.current_stream(), which the caller no longer takes), with three launches 14.9 -> 9.5.
+// Measured on a step of the ctypes binding it replaces for these calls: fa_decode in one launch 10.2 -> 6.3 us of host time (1.7 us
+// of it ctypes, 2.7 us torch.cuda.current_stream(), which the caller no longer takes), with three launches 14.9 -> 12.6.
 
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>

@@ -1446,8 +1446,9 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
     const int cols = Dc < kCols ? Dc : kCols;
     int rc;
     const bool narrow = cols <= 96, small_d = D <= 128;
-    // every thread routes fixed dims when the row vectors divide the workgroup and kept dims are staged
-    const bool fast = (kCBlock % (D / 8)) == 0 && (pl.stage || Du == 0 || x_keep == nullptr);
+    // every thread routes fixed dims when the row vectors divide the workgroup, a block has one for every thread (head dims of
+    // 32 and less have fewer: the others' would land in the next column) and kept dims are staged
+    const bool fast = (kCBlock % (D / 8)) == 0 && kTB * (D / 8) >= kCBlock && (pl.stage || Du == 0 || x_keep == nullptr);
 #define FA_LAUNCH_PROJECT2(T_, F_, S_)                                                              \
   rc = narrow ? (small_d ? launch_project<T_, 3, 2, F_, S_>(p, pl, stream, tm) : launch_project<T_, 3, 4, F_, S_>(p, pl, stream, tm)) \
               : (small_d ? launch_project<T_, 4, 2, F_, S_>(p, pl, stream, tm) : launch_project<T_, 4, 4, F_, S_>(p, pl, stream, tm))

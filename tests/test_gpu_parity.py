@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from workloads import CONFIGS, PAPER_SETTING, one_launch_variants, random_variants, rel_err, small_variants
+from workloads.synth import round_to_bf16
 from fa_testlib import (cached_context, oracle_decode_heads, oracle_state, rows_pad8, rows_to_tok8,
                         sample_heads, to_dev)
 
@@ -320,6 +321,32 @@ def test_compress_streaming_update_matches_one_shot():
     # both sides round the basis table to the element type at different block phases
     assert rel_err(c.cpu().numpy(), full.cpu().numpy()) <= cfg.tol
     assert torch.equal(keep, keep_full)
+
+
+# a 64-token block of these head dims has fewer 8-element vectors than a workgroup has threads
+@pytest.mark.parametrize("D,N,M,Dc", [(8, 200, 9, 8), (8, 70, 6, 3), (16, 1100, 20, 11), (32, 41, 6, 24), (32, 1326, 300, 29), (32, 64, 1, 32)])
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+def test_compress_narrow_heads(D, N, M, Dc, layout, dt):
+    import oracle.fourier_kv as fk
+    fa = _fa()
+    print(f"[case] narrow {dt} D{D} N{N} M{M} Dc{Dc} layout {layout}", flush=True)
+    rng = np.random.default_rng(D + N)
+    x = round_to_bf16(rng.standard_normal((2, 3, N, D)).astype(np.float32))
+    mask = np.zeros((2, 3, D), np.uint8)
+    for b in range(2):
+        for h in range(3):
+            mask[b, h, rng.choice(D, Dc, replace=False)] = 1
+    T = max(N, M) + 7
+    want, keep = fk.compress_batched(x, mask, M, T, 5)
+    c, slab = fa.fa_compress(to_dev(x, dtype=dt), to_dev(mask), Dc, M, T, 5, keep_layout=layout)
+    torch.cuda.synchronize()
+    # fp32: sums of N values of size 1; bf16: a basis of one 16-bit term above 512 tokens (2^-9 of each, spread over N), two below
+    tol = 1e-5 if dt == torch.float32 or N <= 512 else 2e-3
+    assert rel_err(c.cpu().numpy(), want, np.sqrt(N)) <= tol
+    if Dc < D:
+        got = (slab if layout == fa.FA_KEEP_ROWS else fa.keep_rows_from_tok8(slab, N, D - Dc)).float().cpu().numpy()
+        assert np.array_equal(got[..., :D - Dc], keep.astype(np.float32)) and not got[..., D - Dc:].any()
 
 
 @pytest.mark.parametrize("name,a", [("gqa8_oddM", 501), ("tiny_bf16", 13), ("tiny", 100), ("mha_ragged", 1003)])

@@ -2978,8 +2978,11 @@ static bool make_local(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D,
 // Eight-wave workgroups of the general kernel take a compute unit each, and a chunk costs them about a step and a half besides its
 // steps: fewer, longer chunks where those are fewer rounds of workgroups (160 pairs x 1640 rows, M = 795: two chunks a pair, two
 // rounds, 206 us the call; one chunk 145).  The records keep their places: the workspace is laid out for the chunks of the plan.
-static void join_chunks(DecodePlan& pl, int B, int Hkv, int N) {
-  if (pl.nw != kWaves8 || pl.local.use || pl.Swp > 0 || pl.Sm <= 1) return;
+// Not in fp32, whose error grows with the root of a chunk's rows (8 pairs x 20000, M = 250, six heads, against fp64: 3.1e-7 in 64
+// chunks, 7.2e-7 in 8, 2.3e-6 in one; bf16 4e-6 in any).  Not with counts per sequence: the longest sequence's chunks are what the
+// call waits for, and those of shorter ones end early (64 pairs x 0 .. 17510, M = 422, nine chunks 79 us, four 115).
+static void join_chunks(DecodePlan& pl, int dtype, int B, int Hkv, int N, bool per_sequence) {
+  if (pl.nw != kWaves8 || pl.local.use || pl.Swp > 0 || pl.Sm <= 1 || dtype == FA_F32 || per_sequence) return;
   const long pairs = static_cast<long>(B) * Hkv, step = pl.KT * kTJ, steps = (N + step - 1) / step;
   double least = 0.0;
   int best = pl.Sm;
@@ -3296,7 +3299,7 @@ static int decode_impl(const void* q, int dtype, int B, int Hq, int Hkv, int D, 
   // (a buffer that only holds the other form's state is served by that)
   make_local(pl, dtype, B, Hq, Hkv, D, Dkc, Dvc, N, W, num_splits, local_form(M, T), workspace_bytes);
   if (workspace_bytes < pl.total) return FA_ERR_WORKSPACE;
-  if (num_splits == 0) join_chunks(pl, B, Hkv, N);
+  if (num_splits == 0) join_chunks(pl, dtype, B, Hkv, N, seq_n != nullptr);
 
   DecodeParams p{};
   p.q = q; p.ck = ck; p.cv = cv; p.kmask = kmask; p.vmask = vmask;

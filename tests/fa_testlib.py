@@ -2,6 +2,9 @@
 
 from __future__ import annotations
 
+import os
+import subprocess
+
 import numpy as np
 import torch
 
@@ -83,3 +86,46 @@ def cached_context(cfg, _cache={}):
         _cache.clear()  # keep at most one big context alive
         _cache[key] = make_context(cfg)
     return _cache[key]
+
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_11886_amd", "csrc")
+HOST_ONLY = r"""
+#include <cstdio>
+extern "C" {   // nothing is launched: the registration of kernels has nothing to do
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, void*, int*) {}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+}
+"""
+
+
+def host_program(directory, main, sources):
+    """`main` (it includes the .hip file whose rules it asks for) and the library's `sources`, compiled for the host alone without
+    the HIP runtime: a function from a list of integer tuples to the program's lines as tuples."""
+    (directory / "main.hip").write_text(main)
+    flags = ["-O1", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-I", os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include"),
+             "-I", CSRC]
+    objects = [(directory / "main.hip", directory / "main.o")] + [(os.path.join(CSRC, s), directory / (s + ".o")) for s in sources]
+    jobs = [subprocess.Popen([HIPCC, *flags, "-c", str(src), "-o", str(obj)]) for src, obj in objects]
+    assert all([j.wait() == 0 for j in jobs])
+    exe = str(directory / "rules")
+    # (what the rules do not call stays unresolved)
+    subprocess.run(["g++", "-no-pie", *[str(obj) for _, obj in objects], "-o", exe, "-Wl,--unresolved-symbols=ignore-all"], check=True)
+
+    def ask(calls):
+        text = "\n".join(" ".join(map(str, c)) for c in calls)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return ask
+
+
+# Calls of the general middle-row kernel with eight waves: dtype, B, Hkv, heads a KV head, D, Dkc, Dvc, M, N (= period), W
+GENERAL_CALLS = [
+    ("bf16", 16, 10, 1, 64, 41, 48, 795, 1640, 0),      # chunks joined, one query head
+    ("bf16", 20, 7, 6, 128, 97, 60, 300, 1299, 270),    # chunks joined, six heads, kept V past two tiles, full-width rows apart
+    ("bf16", 3, 2, 16, 64, 40, 30, 1023, 1100, 130),     # the longest series, sixteen heads
+    ("bf16", 5, 3, 3, 128, 70, 77, 301, 1500, 9),       # few heads: full-width rows in the launch of the middle rows
+    ("f32", 3, 5, 6, 64, 45, 40, 255, 900, 70),
+]

@@ -1,0 +1,62 @@
+"""Which kernel a call gets (no GPU): the rules are compiled for the host alone and asked."""
+
+import os
+import random
+
+import pytest
+
+from fa_testlib import GENERAL_CALLS, HIPCC, HOST_ONLY, host_program
+
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+
+# a line: dtype B Hkv G D Dkc Dvc M T N W per_sequence -> waves of the general middle-row kernel (0: another form), full-width rows
+# apart, chunks as planned, chunks as run
+DECODE = HOST_ONLY + r"""
+#include "fa_decode.hip"
+int main() {
+  int dt, B, Hkv, G, D, Dkc, Dvc, M, T, N, W, seq;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d", &dt, &B, &Hkv, &G, &D, &Dkc, &Dvc, &M, &T, &N, &W, &seq) == 12) {
+    fa::DecodePlan pl{};
+    const bool ok = fa::make_plan(pl, dt, B, Hkv * G, Hkv, D, Dkc, Dvc, M, N, W, 0);
+    if (ok) fa::make_local(pl, dt, B, Hkv * G, Hkv, D, Dkc, Dvc, N, W, 0, fa::local_form(M, T));
+    const int planned = pl.Sm;
+    if (ok) fa::join_chunks(pl, dt, B, Hkv, N, seq != 0);
+    std::printf("%d %d %d %d\n", !ok || pl.local.use || pl.fused || pl.fast ? 0 : pl.nw, pl.rides, planned, pl.Sm);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def decode(tmp_path_factory):
+    return host_program(tmp_path_factory.mktemp("decode"), DECODE, ["fa_local.hip"])
+
+
+def _call(c, per_sequence=0):
+    dt, B, Hkv, G, D, Dkc, Dvc, M, N, W = c
+    return (0 if dt == "f32" else 1, B, Hkv, G, D, Dkc, Dvc, M, N, N, W, per_sequence)
+
+
+def test_general_calls_are_what_they_say(decode):
+    """The shapes of test_gpu_general.py reach the kernel with eight waves, two of them with joined chunks."""
+    rows = decode([_call(c) for c in GENERAL_CALLS])
+    assert all(r[0] == 8 for r in rows), rows
+    assert all(r[3] < r[2] for r in rows[:2]) and all(r[3] == r[2] for r in rows[2:]), rows
+    assert rows[1][1] == 1, rows
+
+
+def test_chunks_are_joined_neither_in_fp32_nor_per_sequence(decode):
+    """Joined chunks add more rows up in fp32, and wait for the longest sequence."""
+    rng = random.Random(5)
+    calls = []
+    for _ in range(4000):
+        M = rng.randint(130, 1024)
+        N = max(M, int(2 ** rng.uniform(9, 14.2)))
+        calls.append((rng.choice([0, 1]), rng.choice([4, 8, 16, 20]), rng.choice([4, 8, 16]), rng.choice([1, 4, 6, 16]), rng.choice([64, 128]), 40, 30,
+                      M, N, N, 0, rng.choice([0, 1])))
+    joined = [0, 0]
+    for c, r in zip(calls, decode(calls)):
+        if r[0] == 8:
+            free = c[0] == 1 and not c[-1]
+            joined[free] += r[3] < r[2]
+    assert joined[0] == 0 and joined[1] > 20, joined

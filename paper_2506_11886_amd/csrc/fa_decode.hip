@@ -534,7 +534,15 @@ __device__ __forceinline__ void partial_middle_rows(const DecodeParams& p, unsig
   constexpr bool kPrefetchV = DVTM <= 2;
   constexpr int kVR = kPrefetchV ? DVTM : 1;
 
-  const int sm_idx = blockIdx.x, bh = blockIdx.y, b = bh / p.Hkv, hkv = bh % p.Hkv;
+  const int bh = blockIdx.y, b = bh / p.Hkv, hkv = bh % p.Hkv;
+  // With counts per sequence the last chunks are empty more often.  Workgroups go to the eight XCDs in turn: where full-width rows
+  // run apart and leave an even number of chunks, the same chunks of every pair would meet on one XCD, so they move on by one each
+  // time the turn repeats (128 pairs x 0 .. 31284 rows, sixteen chunks: 310 -> 212 us; with full-width rows in the launch 208).
+  int sm_idx = blockIdx.x;
+  if (NW == kWaves8 && p.seq_n && p.Sw > 0 && p.Swp == 0 && p.Sm % 2 == 0) {
+    const int turn = p.Sm & 7 ? (p.Sm & 3 ? 4 : 2) : 1;   // pairs until the turn repeats
+    sm_idx = (sm_idx + bh / turn) % p.Sm;
+  }
   const int G = p.G, Gp = p.Gp, KT = p.KT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps unit ids scalar
@@ -2877,9 +2885,17 @@ static bool make_plan(DecodePlan& pl, int dtype, int B, int Hq, int Hkv, int D, 
     pl.lds_tab = kXchgBytes8;
     pl.lds_total = ((most > wpath ? most : wpath) + 255u) & ~255u;
   }
-  // its full-width rows: on the matrix cores beside the series coefficients (256 rows a workgroup as here), where a unit's waves
-  // are not taken by the tables
-  pl.rides = pl.nw == kWaves8 && dtype == FA_BF16 && Dkc > 0 && W > 0 && (D == 64 || D == 128 || D == 256);
+  // Its full-width rows: on the matrix cores beside the series coefficients (256 rows a workgroup as here), where they would take
+  // more than the units that the middle rows leave, or more than four heads make them the longest workgroups of the launch (their
+  // scalar form costs a head at a time).  Else they are done beside the middle rows before those are.  4-byte reads of C_k (fewer
+  // than four dims) are not worth the wider launch.  The rows' LDS at head dim 256 keeps workgroups of coefficients off the units:
+  // there many heads only, and few workgroups.  Measured beside / in the launch in front, us: D = 128, one round, G = 1, 8 pairs x
+  // 2359, M = 343, W = 2442: 22.3 / 25.4; two rounds, 256 pairs: 1.2 times; G = 16, 4 pairs: up to 1.7 times; D = 256, 128 pairs,
+  // G = 6, M = 622: 78 / 94, G = 16, M = 400, 16 pairs: 1.25 times.
+  const long pairs = static_cast<long>(B) * Hkv;
+  pl.rides = pl.nw == kWaves8 && dtype == FA_BF16 && Dkc >= 4 && W > 0 &&
+             (D == 64 || D == 128 ? G > 4 || pairs * (pl.Sm + pl.Sw) > 256
+                                  : D == 256 && (pl.cw == 4 ? G > 8 || (G > 4 && pairs <= 32) : G > 8 && pairs <= 16));
   if (pl.rides) {
     pl.wrb = 2;
     pl.Swp = 0;

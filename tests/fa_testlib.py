@@ -126,6 +126,7 @@ GENERAL_CALLS = [
     ("bf16", 16, 10, 1, 64, 41, 48, 795, 1640, 0),      # chunks joined, one query head
     ("bf16", 20, 7, 6, 128, 97, 60, 300, 1299, 270),    # chunks joined, six heads, kept V past two tiles, full-width rows apart
     ("bf16", 3, 2, 16, 64, 40, 30, 1023, 1100, 130),     # the longest series, sixteen heads
+    ("bf16", 5, 4, 6, 64, 40, 30, 300, 900, 130),       # eight chunks, full-width rows apart
     ("bf16", 5, 3, 3, 128, 70, 77, 301, 1500, 9),       # few heads: full-width rows in the launch of the middle rows
     ("f32", 3, 5, 6, 64, 45, 40, 255, 900, 70),
 ]

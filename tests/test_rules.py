@@ -60,3 +60,14 @@ def test_chunks_are_joined_neither_in_fp32_nor_per_sequence(decode):
             free = c[0] == 1 and not c[-1]
             joined[free] += r[3] < r[2]
     assert joined[0] == 0 and joined[1] > 20, joined
+
+
+def test_full_width_rows_go_apart_where_that_is_faster(decode):
+    """Beside the coefficients: many heads, or more workgroups than units.  In the launch of the middle rows: few heads in one round, fewer
+    than four compressed K dims, and at head dim 256 few heads or many pairs."""
+    calls = {(1, 1, 8, 1, 128, 96, 64, 343, 2359, 2359, 2442, 0): 0, (1, 1, 8, 6, 128, 96, 64, 343, 2359, 2359, 2442, 0): 1,
+             (1, 16, 16, 1, 128, 96, 64, 343, 900, 900, 132, 0): 1, (1, 1, 8, 6, 128, 3, 64, 343, 2359, 2359, 2442, 0): 0,
+             (1, 8, 16, 6, 256, 192, 192, 622, 700, 700, 205, 0): 0, (1, 2, 4, 16, 256, 192, 192, 622, 700, 700, 205, 0): 1,
+             (1, 2, 4, 1, 256, 192, 192, 622, 700, 700, 205, 0): 0}
+    got = decode(list(calls))
+    assert all(r[0] == 8 for r in got) and [r[1] for r in got] == list(calls.values()), got

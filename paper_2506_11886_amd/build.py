@@ -13,7 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfourier_attn.so")
 SOURCES = ("fa_compress.hip", "fa_moments.hip", "fa_rows.hip", "fa_decode.hip", "fa_local.hip", "fa_finish.hip", "fa_small.hip", "fa_append.hip", "fa_select.hip", "fa_legt.hip")
 
-CALL = os.path.join(HERE, "_fa_call.so")   # the Python entry, linked against LIB
+# The Python entry, linked against LIB.  It is built against this interpreter's headers, and the suffix keeps others from importing it.
+CALL = os.path.join(HERE, "_fa_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -53,6 +54,9 @@ def build(verbose: bool = False, extra=()) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc link failed")
+    plain = os.path.join(HERE, "_fa_call.so")   # (a name that any interpreter would take)
+    if os.path.exists(plain):
+        os.remove(plain)
     call = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
             os.path.join(CSRC, "fa_call.cpp"), "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-o", CALL]
     if verbose:

@@ -242,3 +242,12 @@ def test_varlen_entry_points_reject_bad_arguments_on_the_host():
     assert append_vl(n_cap=0) == -2 and append_vl(n_cap=101) == -2
     assert append_vl(kks=8) == -2            # a slab pitch below n_cap tokens
     assert append_vl(M=0) == -2 and append_vl(D=60) == -3 and append_vl(kmask=None) == -1
+
+
+def test_python_entry_carries_the_interpreters_suffix():
+    """It is built against one interpreter's headers: others must not import it."""
+    import sysconfig
+    _fa()
+    from paper_2506_11886_amd import _fa_call
+    assert os.path.basename(_fa_call.__file__) == "_fa_call" + sysconfig.get_config_var("EXT_SUFFIX")
+    assert not os.path.exists(os.path.join(os.path.dirname(_fa_call.__file__), "_fa_call.so"))

@@ -160,12 +160,14 @@ __global__ __launch_bounds__(kABlock) void append_token(AppendParams p) {
 }
 
 // Head dims per workgroup.  Narrow slices are more workgroups, which few pairs need; wide ones read whole lines of C and evaluate
-// the basis column fewer times.  Measured, us at 16 / 32 / 64: 224 pairs, D = 256, M = 292: 95 / 66 / 59; 192, D = 128, M = 244:
-// 30 / 25 / 21; 128, D = 128, M = 128: 11.2 / 9.9 / 10.0; 16, D = 128, M = 512: 10.5 / 9.8 / 14.7; 8, D = 128, M = 1023: 10.8 / 15 / 26.
+// the basis column fewer times, and are no better where the head does not fill them.  By the number of narrow ones, over 2700 drawn calls
+// and a sweep (head dims 8 - 256, 1 - 2048 pairs, M up to 1023), time against slices of 16: 32 dims 1.1 at 768 workgroups, 0.95 (0.8 - 1.18)
+// at 1024 - 1400, 0.83 at 1400 - 1700; 64 dims 0.95 at 2048 (32 there: 0.77), 0.71 at 2560 - 3072 (0.72), 0.48 at 4096 (0.63).  Head dim 8
+// in slices of 32 or 64: 1.3 and 1.9 throughout.
+// 224 pairs, D = 256, M = 292: 95 / 66 / 59 us; 128, D = 128, M = 128: 11.2 / 9.9 / 10.0; 8, D = 128, M = 1023: 10.8 / 15 / 26.
 static int append_dims(int pairs, int D) {
-  for (int dims = 64; dims > 16; dims /= 2)
-    if (2 * pairs * ((D + dims - 1) / dims) >= 512) return dims;
-  return 16;
+  const long narrow = 2l * pairs * ((D + 15) / 16);
+  return D > 32 && narrow >= 2560 ? 64 : D > 16 && narrow >= 1400 ? 32 : 16;
 }
 
 }  // namespace fa

@@ -130,3 +130,15 @@ GENERAL_CALLS = [
     ("bf16", 5, 3, 3, 128, 70, 77, 301, 1500, 9),       # few heads: full-width rows in the launch of the middle rows
     ("f32", 3, 5, 6, 64, 45, 40, 255, 900, 70),
 ]
+
+# Folds in slices of 32 and 64 head dims: B, Hkv, D, Dkc, Dvc, M, dtype, dims of a slice
+APPEND_CALLS = [
+    (18, 5, 128, 96, 5, 257, "bf16", 32),      # (five compressed dims: slices without one)
+    (15, 10, 72, 31, 72, 130, "f32", 32),      # a last slice of eight dims, nothing kept of V
+    (64, 8, 24, 20, 9, 129, "bf16", 32),       # one slice that the head does not fill
+    (3, 22, 192, 130, 0, 1, "bf16", 32),
+    (24, 7, 128, 91, 128, 255, "f32", 64),
+    (26, 10, 72, 3, 50, 65, "bf16", 64),       # a last slice of eight dims
+    (110, 4, 40, 40, 17, 1023, "f32", 64),     # one slice that the head does not fill
+    (9, 9, 256, 200, 131, 300, "bf16", 64),
+]

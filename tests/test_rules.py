@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from fa_testlib import GENERAL_CALLS, HIPCC, HOST_ONLY, host_program
+from fa_testlib import APPEND_CALLS, GENERAL_CALLS, HIPCC, HOST_ONLY, host_program
 
 pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 
@@ -71,3 +71,24 @@ def test_full_width_rows_go_apart_where_that_is_faster(decode):
              (1, 2, 4, 1, 256, 192, 192, 622, 700, 700, 205, 0): 0}
     got = decode(list(calls))
     assert all(r[0] == 8 for r in got) and [r[1] for r in got] == list(calls.values()), got
+
+
+# a line: pairs D -> head dims of a workgroup of fa_append
+APPEND = HOST_ONLY + r"""
+#include "fa_append.hip"
+int main() {
+  int pairs, D;
+  while (std::scanf("%d %d", &pairs, &D) == 2) std::printf("%d\n", fa::append_dims(pairs, D));
+}
+"""
+
+
+def test_append_slices(tmp_path):
+    """The calls of test_gpu_append.py are in slices of the width they say; few pairs and heads that would not fill wide slices are not."""
+    ask = host_program(tmp_path, APPEND, [])
+    assert [r[0] for r in ask([(c[0] * c[1], c[2]) for c in APPEND_CALLS])] == [c[-1] for c in APPEND_CALLS]
+    rng = random.Random(3)
+    calls = [(int(2 ** rng.uniform(0, 12)), 8 * rng.randint(1, 32)) for _ in range(500)]
+    for (pairs, D), (dims,) in zip(calls, ask(calls)):
+        assert dims == 16 or dims < 2 * D
+        assert dims == 16 or 2 * pairs * -(-D // 16) >= 1400

@@ -373,10 +373,10 @@ __global__ __launch_bounds__(64 * MomTile<D>::kWaves, 2) void fa_moments(MomentP
 constexpr int kPhBlocks = 128;
 constexpr int kExpandBatch = 4;
 constexpr int kExpandRun = 4;
-constexpr int kExpandWaves = 16;
+constexpr int kExpandWaves = 12;
 __global__ __launch_bounds__(64 * kExpandWaves) void fa_expand(MomentParams p, int ctw, int ks) {
   __shared__ __attribute__((aligned(16))) float2 ph[kPhBlocks][kExpandRows];
-  __shared__ float red[14 * 64 * 9];                            // (ks - 1) * ctw <= 14 waves hand their sums over
+  __shared__ float red[9 * 64 * 9];                             // (ks - 1) * ctw <= 9 waves hand their sums over
   const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
@@ -789,8 +789,10 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   // split the columns while that leaves fewer than a workgroup per compute unit, then share the blocks
   int ctw = ct < 8 ? ct : 8;
   while (ctw > 1 && static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256) ctw = (ctw + 1) / 2;
-  // Fewer workgroups than compute units: as many shares of the blocks as there are waves (2 heads x 8171 tokens, D = 64, the call
-  // 21.9 -> 19.9 us; 4 x 39062, 31.3 -> 27.0); else four (256 workgroups: 13.8 us against 15.0 with eight, the matrix rate bounds both).
+  // Fewer workgroups than compute units (of a column each, then): eight shares of the blocks (2 heads x 8171 tokens, D = 64, the call
+  // 21.9 -> 19.9 us; 4 x 39062, 31.3 -> 27.0); else four (256 workgroups: 13.8 us against 15.0 with eight, the matrix rate bounds both)
+  // and at most twelve waves (with sixteen 22 heads x 17644 tokens, M = 172: 60.5 -> 64.2 the call; 45 x 3326, D = 256, M = 102:
+  // 68.4 -> 73.6).
   int ks = kExpandWaves / ctw;
   const int shares = static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256 ? 8 : 4;
   if (ks > shares) ks = shares;

@@ -103,7 +103,7 @@ void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) 
 
 def host_program(directory, main, sources):
     """`main` (it includes the .hip file whose rules it asks for) and the library's `sources`, compiled for the host alone without
-    the HIP runtime: a function from a list of integer tuples to the program's lines as tuples."""
+    the HIP runtime: a function from a list of tuples to the program's lines as tuples."""
     (directory / "main.hip").write_text(main)
     flags = ["-O1", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-I", os.path.join(os.path.dirname(os.path.dirname(CSRC)), "include"),
              "-I", CSRC]
@@ -117,7 +117,7 @@ def host_program(directory, main, sources):
     def ask(calls):
         text = "\n".join(" ".join(map(str, c)) for c in calls)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
-        return [tuple(map(int, line.split())) for line in out.splitlines()]
+        return [tuple(int(w) if w.lstrip("-").isdigit() else w for w in line.split()) for line in out.splitlines()]
     return ask
 
 

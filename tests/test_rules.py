@@ -92,3 +92,89 @@ def test_append_slices(tmp_path):
     for (pairs, D), (dims,) in zip(calls, ask(calls)):
         assert dims == 16 or dims < 2 * D
         assert dims == 16 or 2 * pairs * -(-D // 16) >= 1400
+
+
+# The library's own entry points with the launches noted down instead of made.  A line: entry (0 fa_compress, 1 fa_compress_kv, 2 fa_select_dims)
+# dtype B H N D Dkc Dvc M T t0 accumulate layout keep_offset with_keep sx_n workspace (0: what the query says) -> status, then for each launch
+# the kernel, grid x y z, threads, and hw and chunks of project_rows (-1 else)
+ROUTES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <cxxabi.h>
+#include "fa_rows.hpp"
+static std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
+static dim3 g_, b_;
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* f, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+  char* d = abi::__cxa_demangle(name, nullptr, nullptr, nullptr);
+  std::string s = d ? d : name;
+  s = s.substr(s.find("fa::") + 4);
+  names()[f] = s.substr(0, s.find_first_of("<("));
+}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t) { g_ = g; b_ = b; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* st) { *g = g_; *b = b_; *n = 0; *st = nullptr; return hipSuccess; }
+hipError_t hipPeekAtLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, hipStream_t) {
+  const std::string& n = names()[f];
+  const bool rows = n == "project_rows";
+  const fa::RowsParams* p = static_cast<const fa::RowsParams*>(args[0]);
+  std::printf("%s %u %u %u %u %d %d ", n.c_str(), g.x, g.y, g.z, b.x, rows ? p->hw : -1, rows ? (p->part ? int(g.z) : 1) : -1);
+  return hipSuccess;
+}
+}
+int main() {
+  int e, dt, B, H, N, D, Dk, Dv, M, T, t0, acc, lay, off, keep;
+  long sx; size_t bytes;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %ld %zu", &e, &dt, &B, &H, &N, &D, &Dk, &Dv, &M, &T, &t0, &acc, &lay, &off, &keep, &sx, &bytes) == 17) {
+    char* at = reinterpret_cast<char*>(1 << 20);   // (nothing is read through it)
+    if (!bytes) bytes = e == 0 ? fa_compress_workspace_bytes_for(dt, B, H, N, D, Dk, M) : e == 1 ? fa_compress_kv_workspace_bytes_for(dt, B, H, N, D, Dk, Dv, M)
+                                                                                  : fa_select_workspace_bytes(dt, B, H, N, D, M);
+    const auto mask = reinterpret_cast<uint8_t*>(at);
+    const auto c = reinterpret_cast<float*>(at);
+    void* k = keep ? at : nullptr;
+    int st;
+    if (e == 0) st = fa_compress(at, dt, sx * N * H, sx * N, sx, B, H, N, D, mask, Dk, M, T, t0, acc, c, k, lay, 0, off, at, bytes, nullptr);
+    else if (e == 1) st = fa_compress_kv(at, at, dt, sx * N * H, sx * N, sx, B, H, N, D, mask, Dk, mask, Dv, M, T, t0, acc, c, c, k, 0, k, 0, off, at, bytes, nullptr);
+    else st = fa_select_dims(at, dt, sx * N * H, sx * N, sx, B, H, N, D, M, Dk, mask, c, at, bytes, nullptr);
+    std::printf("%d\n", st);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    ask = host_program(tmp_path_factory.mktemp("routes"), ROUTES, ["fa_compress.hip", "fa_moments.hip", "fa_rows.hip", "fa_select.hip"])
+
+    def launches(calls):
+        """Each call's launches: (kernel, grid, threads, hw, chunks)."""
+        out = []
+        for row in ask(calls):
+            assert row[-1] == 0, row
+            out.append([(r[0], r[1:4], r[4], r[5], r[6]) for r in (row[i:i + 7] for i in range(0, len(row) - 1, 7))])
+        return out
+    return launches
+
+
+def test_selection_shares_the_blocks(routes):
+    """fa_expand: eight shares of the blocks for fewer workgroups than compute units, else twelve waves at most."""
+    rng = random.Random(9)
+    calls = []
+    for _ in range(1500):
+        D, N = rng.choice([64, 128, 256]), int(2 ** rng.uniform(9, 16))
+        calls.append((2, 1, 1, int(2 ** rng.uniform(0, 8)), N, D, D // 2, 0, max(1, min(N // 8, int(2 ** rng.uniform(0, 9)))), N, 0, 0, 0, 0, 0, D, 0))
+    most = [0, 0]
+    for got in routes(calls):
+        for name, grid, threads, _, _ in got:
+            if name == "fa_expand":
+                many = grid[0] * grid[1] * grid[2] >= 256
+                most[many] = max(most[many], threads // 64)
+    assert most == [8, 12]

@@ -104,7 +104,7 @@ __device__ __forceinline__ void set_elem<float>(Frag<float>& f, int e, float x) 
 // 8-element vectors of X per thread and block (2 covers head dims up to 128, 4 up to 256)
 // kFast: the row vectors divide the workgroup evenly (head dim 64 / 128 / 256) and
 // kept dims are staged, so every thread routes the same 8 dims in every block.
-// kSplit (bf16 head dims that project_rows is not built for): the basis is held as a bf16 head plus a bf16 remainder (two products per
+// kSplit (bf16 where project_rows does not run: head dims, strides or numbers of pairs that it is not built for, the mean alone): the basis is held as a bf16 head plus a bf16 remainder (two products per
 // operand, 2^-17 relative instead of 2^-9).  Used for short segments, where the matrix work is
 // negligible and the rounding errors of a short period's few distinct basis values would not
 // average out.
@@ -1137,21 +1137,45 @@ static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct,
   return moments_us(mp, tensors, B, H, N, D, Dc, Du, M, accumulate) <= 1.05 * direct;
 }
 
-// The basis formed per token in fp32 (fa_rows): one launch and no workspace, closer than either other form.  Segments of up to
-// kSplitTokens always take it where it is built (three terms: what they had was exact to fp32 at a token or two), longer ones
-// where its estimate is the lower.  Measured, K and V, other form / this one: 16 x 464 tokens, M = 82, two calls: 76 / 21 us;
-// 128 x 464, M = 232: 70 / 40; 24 x 898, D = 64, M = 62: 56 / 12; 4 x 2065, D = 256, M = 758: 122 / 40; 16 x 6717, D = 64,
-// M = 864: 91 / 77; against moments 8 x 2048, M = 256, two calls: 27 / 33; 64 x 12207, D = 64, M = 60: 63 / 55.
-// fp32 segments take it unless the workspace has no room for chunks that fill the chip: 32 x 4359, D = 128, M = 128, K and V: 347 / 104 us;
-// 10 x 19531, M = 40: 357 / 114; 1 x 744, M = 45, two calls: 162 / 44.  (Errors of white rows 4.5e-7 / 2.9e-7.)
+// The basis formed per token in fp32 (fa_rows): closer than either other form, and one launch unless its tokens go in chunks.  bf16
+// segments of more than kSplitTokens take it where its estimate is the lower.  Measured, K and V, other form / this one: 24 x 898,
+// D = 64, M = 62: 56 / 12 us; 4 x 2065, D = 256, M = 758: 122 / 33; 16 x 6717, D = 64, M = 864: 84 / 75; against moments 8 x 2048,
+// M = 256, two calls: 27 / 33; 64 x 12207, D = 64, M = 60: 63 / 55.
+// Shorter ones and fp32 segments take it where it is built (three terms): 16 x 464 tokens, M = 82, two calls: 76 / 21 us;
+// 128 x 464, M = 232: 70 / 40; fp32 32 x 4359, D = 128, M = 128, K and V: 347 / 104; 10 x 19531, M = 40: 357 / 114.  Over 22000 drawn
+// fp32 calls 0.39 of the time of compress_project, with errors of white rows 4.5e-7 / 2.9e-7 (up to 1.3e-6 / 4e-7 at many states), over
+// 35000 short bf16 ones 0.45, with 2e-6 / 2e-7.  But:
+//   - the mean alone (M = 1) is a column sum there and a tile of products here: the lower estimate (fp32, 32 x 3410, D = 64, K and V:
+//     32 / 59 us; 8 x 11135, D = 128: 27 / 91; bf16 24 x 1, D = 256: 8.6 / 10.4; the sums of rows are as exact).  A tenth for what the estimate of this form leaves out there;
+//   - fp32 with no more than half of the dims compressed, whose other columns are multiplied here for nothing: the lower estimate,
+//     both forms being fp32 (16 x 34532, 18 of 128 dims, M = 1006: 833 / 1291; 50 x 10658, 13 dims, M = 510, K and V: 790 / 1476).
+//     bf16 keeps this form for its tenth of the error, also where that costs time (0.3 % of the calls, most of them D = 256 with many
+//     pairs and few dims compressed; at worst 720 x 445, 73 of 256 dims, M = 218, K and V: 255 / 542).
 static bool rows_short(int dtype, int N) { return dtype == FA_F32 || N <= kSplitTokens; }   // (a basis of fp32 precision)
 static RowsPlan rows_plan(const RowsShape& c, int Dc, int most) {
   if (Dc <= 0) return RowsPlan{};
   return make_rows_plan(c, rows_short(c.dtype, c.N) ? 3 : 2, c.dtype == FA_F32 ? kRowsLongestF32 : kRowsLongest, most);
 }
-// (the estimate of compress_project_fast is the slowest of its calls': short segments of many pairs take down to 0.63 of it)
-static bool prefer_rows(const RowsPlan& rp, const RowsShape& c, bool moments, double other) {
-  return rp.use && (rows_short(c.dtype, c.N) || rp.us < (moments ? 0.9 : c.D == 128 ? 0.7 : 0.95) * other);
+// compress_project in fp32 or with the split basis, one tensor: a workgroup's prologue, then blocks of 64 tokens that wait for rows,
+// products, or kept dims stored one by one.  Fitted to the calls above: off by 0.83 - 1.17 in 90 % of them.
+static double plain_us(const RowsShape& c, int Dc, int Du, bool accumulate, int keep_layout) {
+  const CompressPlan pl = make_compress_plan(c.dtype, c.B, c.H, c.N, c.D, Dc, c.M, keep_layout, c.keep_offset);
+  const bool f32 = c.dtype == FA_F32, products = c.M > 1;
+  const double pairs = static_cast<double>(c.B) * c.H, rounds = ceil(pairs * pl.Sc * pl.MC * pl.DCn / 256.0);
+  const double blocks = ((c.N < pl.chunk ? c.N : pl.chunk) + kTB - 1) / kTB, tiles = ((Dc < kCols ? Dc : kCols) + 15) / 16;
+  const double bytes = pairs * c.N * (f32 ? 4.0 : 2.0) * (static_cast<double>(c.D) * pl.MC * pl.DCn + Du);
+  const double states = pairs * c.M * Dc * 4.0 * (pl.Sc > 1 ? 2.0 * pl.Sc : accumulate ? 2.0 : 1.0);
+  const double block = (f32 ? 0.7 : 0.5) * (c.D / 64) + (products ? (f32 ? 0.98 : 0.21) * tiles : 0.0) + (pl.stage ? 0.0 : Du / 64.0);
+  return 3.5 + rounds * (2.9 + (products ? (f32 ? 16.0 : 11.4) : 0.0) + blocks * block) + (f32 ? 0.07e-6 : 0.01e-6) * bytes +
+         (f32 ? 0.37e-6 : 0.79e-6) * states;
+}
+// dims: compressed ones (of the tensor with more); plain: a function for the time of compress_project.  (The estimate of
+// compress_project_fast is the slowest of its calls': short segments of many pairs take down to 0.63 of it.)
+template <typename Plain>
+static bool prefer_rows(const RowsPlan& rp, const RowsShape& c, int dims, bool moments, double other, Plain plain) {
+  if (!rp.use) return false;
+  if (!rows_short(c.dtype, c.N)) return rp.us < (moments ? 0.9 : c.D == 128 ? 0.7 : 0.95) * other;
+  return (c.M > 1 && (c.dtype == FA_BF16 || 2 * dims > c.D)) || (c.M > 1 ? 1.0 : 1.1) * rp.us <= plain();
 }
 
 // One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one
@@ -1245,7 +1269,7 @@ static int run_rows(const MomentCall& c, int dtype, const RowsPlan& pl, float* c
   size_t most = 0;
   if (pl.chunks > 1) {
     p.part = part[0];
-    p.part_z = static_cast<size_t>(part[1] - part[0]);
+    if (c.tensors == 2) p.part_z = static_cast<size_t>(part[1] - part[0]);
     for (int z = 0; z < c.tensors; ++z) {
       r.part[z] = part[z];
       r.coeffs[z] = c.t[z].coeffs;
@@ -1399,7 +1423,8 @@ static int compress_impl(const void* x, int dtype, int64_t sx_b, int64_t sx_h, i
   const bool moments = room && prefer_moments(mp, specialised && one_vector, direct, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0);
   const RowsShape shape{dtype, B, H, N, D, M, sx_n, keep_offset, 1, x_keep ? Du : 0.0, false};
   const RowsPlan rp = rows_plan(shape, Dc, pl.total > 0 ? pl.Sc : 1);
-  if (!only_params && prefer_rows(rp, shape, moments, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct)) {
+  if (!only_params && prefer_rows(rp, shape, Dc, moments, moments ? moments_us(mp, 1, B, H, N, D, Dc, x_keep ? Du : 0, M, accumulate != 0) : direct,
+                                  [&] { return plain_us(shape, Dc, x_keep ? Du : 0, accumulate != 0, keep_layout); })) {
     const MomentCall c{{moment_tensor(x, dim_mask, x_keep, coeffs, keep_stride_bh, Dc, D, keep_layout), {}}, 1, sx_b, sx_h, sx_n,
                        B, H, N, D, M, T, t0, accumulate, keep_offset};
     float* const part[2] = {static_cast<float*>(workspace), nullptr};
@@ -1567,7 +1592,9 @@ static int compress_kv_impl(const void* k, const void* v, int dtype, int64_t sx_
   while (most < FA_MAX_SPLITS && (most + 1) * lk <= wk && (most + 1) * lv <= wv) ++most;
   const RowsShape shape{dtype, B, H, N, D, M, sx_n, keep_offset, 2, kept, false};
   const RowsPlan rp = rows_plan(shape, Dkc < Dvc ? Dkc : Dvc, most);
-  if (prefer_rows(rp, shape, moments, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct)) {
+  if (prefer_rows(rp, shape, Dkc > Dvc ? Dkc : Dvc, moments, moments ? moments_us(mp, 2, B, H, N, D, dims, kept, M, accumulate != 0) : direct, [&] {
+        return plain_us(shape, Dkc, k_keep ? pk.Du : 0, accumulate != 0, FA_KEEP_ROWS) + plain_us(shape, Dvc, v_keep ? pv.Du : 0, accumulate != 0, FA_KEEP_TOK8);
+      })) {
     float* const part[2] = {reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + wk)};
     rc = run_rows(c, dtype, rp, part, static_cast<hipStream_t>(hip_stream), tm);
     if (rc != FA_OK) return rc;

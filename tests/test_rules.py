@@ -164,6 +164,31 @@ def routes(tmp_path_factory):
     return launches
 
 
+def _compress(dt, B, H, N, D, Dc, M, T=0, t0=0, acc=0, layout=0, off=0, keep=1, Dv=None):
+    return (0 if Dv is None else 1, 0 if dt == "f32" else 1, B, H, N, D, Dc, Dv or 0, M, T or max(N, M), t0, acc, layout, off, keep, D, 0)
+
+
+def test_rows_are_taken_where_they_are_faster(routes):
+    """The mean alone, and fp32 with at most half of the dims compressed: by the estimates.  fp32 with more, and short bf16 segments of more
+    states: always, closer and faster but for a few."""
+    direct = [_compress("f32", 4, 8, 3410, 64, 7, 1, 3417, 4, 1, 0, 8, 1, 60), _compress("f32", 2, 4, 11135, 128, 25, 1, layout=1, off=8),
+              _compress("bf16", 3, 8, 1, 256, 232, 1, 3, 2, 1), _compress("bf16", 6, 3, 42, 128, 121, 1, 126, 9, 0, 1, 3),
+              _compress("f32", 1, 16, 34532, 128, 18, 1006, 37016, 952, 1, 1, 8), _compress("f32", 25, 2, 10658, 128, 13, 510, acc=1, Dv=13)]
+    for c, got in zip(direct, routes(direct)):
+        assert got[0][0] == "compress_project", (c, got)
+    rng = random.Random(7)
+    calls = []
+    for _ in range(3000):
+        dt, D = rng.choice(["f32", "bf16"]), rng.choice([64, 128, 256])
+        N = int(2 ** rng.uniform(1, 15 if dt == "f32" else 9))
+        M = max(2, min(N, int(2 ** rng.uniform(1, 10))))
+        Dc = rng.randint(D // 2 + 1 if dt == "f32" else 1, D)
+        calls.append(_compress(dt, 1, int(2 ** rng.uniform(0, 8)), N, D, Dc, M, layout=rng.choice([0, 1]), off=rng.choice([0, 3]),
+                               Dv=rng.choice([None, rng.randint(1, D)])))
+    for c, got in zip(calls, routes(calls)):
+        assert got[0][0] == "project_rows", (c, got)
+
+
 def test_selection_shares_the_blocks(routes):
     """fa_expand: eight shares of the blocks for fewer workgroups than compute units, else twelve waves at most."""
     rng = random.Random(9)

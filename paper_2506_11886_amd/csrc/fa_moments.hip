@@ -789,12 +789,13 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
   // split the columns while that leaves fewer than a workgroup per compute unit, then share the blocks
   int ctw = ct < 8 ? ct : 8;
   while (ctw > 1 && static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256) ctw = (ctw + 1) / 2;
-  // Fewer workgroups than compute units (of a column each, then): eight shares of the blocks (2 heads x 8171 tokens, D = 64, the call
-  // 21.9 -> 19.9 us; 4 x 39062, 31.3 -> 27.0); else four (256 workgroups: 13.8 us against 15.0 with eight, the matrix rate bounds both)
+  // Fewer workgroups than compute units (of a column each, then) and 64 blocks or more: eight shares of the blocks (2 heads x 8171 tokens,
+  // D = 64, the call 21.9 -> 19.9 us; 4 x 39062, 31.3 -> 27.0; over 7000 calls, against four, 8 - 15 blocks 1.06 of the time, 32 - 63 1.007,
+  // 64 - 95 0.99, 192 - 255 0.95); else four (256 workgroups: 13.8 us against 15.0 with eight, the matrix rate bounds both)
   // and at most twelve waves (with sixteen 22 heads x 17644 tokens, M = 172: 60.5 -> 64.2 the call; 45 x 3326, D = 256, M = 102:
   // 68.4 -> 73.6).
   int ks = kExpandWaves / ctw;
-  const int shares = static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256 ? 8 : 4;
+  const int shares = p.blocks >= 64 && static_cast<long>(tiles) * ((ct + ctw - 1) / ctw) * tensors * p.B * p.H < 256 ? 8 : 4;
   if (ks > shares) ks = shares;
   if (ks > p.blocks) ks = p.blocks;
   if (ks < 1) ks = 1;

@@ -96,7 +96,7 @@ def test_append_slices(tmp_path):
 
 # The library's own entry points with the launches noted down instead of made.  A line: entry (0 fa_compress, 1 fa_compress_kv, 2 fa_select_dims)
 # dtype B H N D Dkc Dvc M T t0 accumulate layout keep_offset with_keep sx_n workspace (0: what the query says) -> status, then for each launch
-# the kernel, grid x y z, threads, and hw and chunks of project_rows (-1 else)
+# the kernel, grid x y z, threads, and hw and chunks of project_rows, -1 and the blocks of fa_expand (-1 else)
 ROUTES = r"""
 #include <cstdio>
 #include <cstdlib>
@@ -126,7 +126,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, h
   const std::string& n = names()[f];
   const bool rows = n == "project_rows";
   const fa::RowsParams* p = static_cast<const fa::RowsParams*>(args[0]);
-  std::printf("%s %u %u %u %u %d %d ", n.c_str(), g.x, g.y, g.z, b.x, rows ? p->hw : -1, rows ? (p->part ? int(g.z) : 1) : -1);
+  std::printf("%s %u %u %u %u %d %d ", n.c_str(), g.x, g.y, g.z, b.x, rows ? p->hw : -1, rows ? (p->part ? int(g.z) : 1) : n == "fa_expand" ? static_cast<const fa::MomentParams*>(args[0])->blocks : -1);
   return hipSuccess;
 }
 }
@@ -155,7 +155,7 @@ def routes(tmp_path_factory):
     ask = host_program(tmp_path_factory.mktemp("routes"), ROUTES, ["fa_compress.hip", "fa_moments.hip", "fa_rows.hip", "fa_select.hip"])
 
     def launches(calls):
-        """Each call's launches: (kernel, grid, threads, hw, chunks)."""
+        """Each call's launches: (kernel, grid, threads, hw, chunks or blocks)."""
         out = []
         for row in ask(calls):
             assert row[-1] == 0, row
@@ -190,16 +190,16 @@ def test_rows_are_taken_where_they_are_faster(routes):
 
 
 def test_selection_shares_the_blocks(routes):
-    """fa_expand: eight shares of the blocks for fewer workgroups than compute units, else twelve waves at most."""
+    """fa_expand: eight shares of 64 blocks or more for fewer workgroups than compute units, else four, and twelve waves at most."""
     rng = random.Random(9)
     calls = []
     for _ in range(1500):
         D, N = rng.choice([64, 128, 256]), int(2 ** rng.uniform(9, 16))
         calls.append((2, 1, 1, int(2 ** rng.uniform(0, 8)), N, D, D // 2, 0, max(1, min(N // 8, int(2 ** rng.uniform(0, 9)))), N, 0, 0, 0, 0, 0, D, 0))
-    most = [0, 0]
+    most = {}
     for got in routes(calls):
-        for name, grid, threads, _, _ in got:
+        for name, grid, threads, _, blocks in got:
             if name == "fa_expand":
-                many = grid[0] * grid[1] * grid[2] >= 256
-                most[many] = max(most[many], threads // 64)
-    assert most == [8, 12]
+                key = "many" if grid[0] * grid[1] * grid[2] >= 256 else "long" if blocks >= 64 else "short"
+                most[key] = max(most.get(key, 0), threads // 64)
+    assert most == {"many": 12, "long": 8, "short": 4}

@@ -1093,7 +1093,7 @@ static MomentTensor moment_tensor(const void* x, const uint8_t* mask, void* keep
 //   8 x 2 K, D = 128, M = 256: 23.7 / 14.4 us; 8 x 32 K: 46.9 / 46.5; 8 x 128 K, M = 512: 252 / 145   (launches; matrix rate)
 //   128 x 8 K, 96 and 128 of 128 dims compressed: M = 64: 150 / 129; M = 128: 157 / 158; M = 256: 171 / 276   (the moments are traffic)
 //   128 x 8 K, D = 256: M = 64: 604 / 276; M = 128: 633 / 335; M = 256: 695 / 598; 256 x 4 K, M = 200: 696 / 786
-// Segments of up to kSplitTokens never take the moments: the split basis leaves 2e-6 of white rows and project_rows 1e-7 (both
+// Segments of up to kSplitTokens never take the moments: the split basis leaves 2e-6 of white rows and project_rows 3e-7 (both
 // 6e-8 at one token), table and operand of the moments together 3e-6 (2e-6 at one token).
 
 // specialised: compress_project_fast (D = 128); staged: kept dims leave through LDS.  Each tensor of a launch by itself.
@@ -1169,12 +1169,14 @@ static double plain_us(const RowsShape& c, int Dc, int Du, bool accumulate, int 
   return 3.5 + rounds * (2.9 + (products ? (f32 ? 16.0 : 11.4) : 0.0) + blocks * block) + (f32 ? 0.07e-6 : 0.01e-6) * bytes +
          (f32 ? 0.37e-6 : 0.79e-6) * states;
 }
-// dims: compressed ones (of the tensor with more); plain: a function for the time of compress_project.  (The estimate of
-// compress_project_fast is the slowest of its calls': short segments of many pairs take down to 0.63 of it.)
+// dims: compressed ones (of the tensor with more); plain: a function for the time of compress_project.  (The estimate of the direct form is
+// the slowest of its calls': short segments of many pairs take down to 0.63 of it at head dim 128, and so do up to kCols of 256 dims,
+// one pass over the rows instead of two: of 671 such calls 34 % were more than 6 % slower at 0.95, 1 % are at 0.7; 64 x 1378, 29 dims,
+// M = 992: 60 / 184 us; with more dims 0.9 %.)
 template <typename Plain>
 static bool prefer_rows(const RowsPlan& rp, const RowsShape& c, int dims, bool moments, double other, Plain plain) {
   if (!rp.use) return false;
-  if (!rows_short(c.dtype, c.N)) return rp.us < (moments ? 0.9 : c.D == 128 ? 0.7 : 0.95) * other;
+  if (!rows_short(c.dtype, c.N)) return rp.us < (moments ? 0.9 : c.D == 128 || (c.D == 256 && dims <= kCols) ? 0.7 : 0.95) * other;
   return (c.M > 1 && (c.dtype == FA_BF16 || 2 * dims > c.D)) || (c.M > 1 ? 1.0 : 1.1) * rp.us <= plain();
 }
 

@@ -169,11 +169,12 @@ def _compress(dt, B, H, N, D, Dc, M, T=0, t0=0, acc=0, layout=0, off=0, keep=1, 
 
 
 def test_rows_are_taken_where_they_are_faster(routes):
-    """The mean alone, and fp32 with at most half of the dims compressed: by the estimates.  fp32 with more, and short bf16 segments of more
+    """The mean alone, fp32 with at most half of the dims compressed, one column group at head dim 256: by the estimates.  fp32 with more, and short bf16 segments of more
     states: always, closer and faster but for a few."""
     direct = [_compress("f32", 4, 8, 3410, 64, 7, 1, 3417, 4, 1, 0, 8, 1, 60), _compress("f32", 2, 4, 11135, 128, 25, 1, layout=1, off=8),
               _compress("bf16", 3, 8, 1, 256, 232, 1, 3, 2, 1), _compress("bf16", 6, 3, 42, 128, 121, 1, 126, 9, 0, 1, 3),
-              _compress("f32", 1, 16, 34532, 128, 18, 1006, 37016, 952, 1, 1, 8), _compress("f32", 25, 2, 10658, 128, 13, 510, acc=1, Dv=13)]
+              _compress("f32", 1, 16, 34532, 128, 18, 1006, 37016, 952, 1, 1, 8), _compress("f32", 25, 2, 10658, 128, 13, 510, acc=1, Dv=13),
+              _compress("bf16", 2, 32, 1378, 256, 29, 992, 1386, 2, 0, 0, 8), _compress("bf16", 28, 16, 920, 256, 72, 751, layout=1)]
     for c, got in zip(direct, routes(direct)):
         assert got[0][0] == "compress_project", (c, got)
     rng = random.Random(7)

@@ -182,7 +182,7 @@ __device__ __forceinline__ void prepare2_rows(const DecodeParams& p, lds_f32* qc
   typedef __attribute__((address_space(3))) V lds_v;
   using VL = typename PrepVec<VEC>::load;
   constexpr int kRows = kBlock / TPR, kV = VEC == 1 ? 1 : 4;
-  constexpr int kV4 = (FA_MAX_HEAD_DIM / kV + TPR - 1) / TPR;
+  constexpr int kV4 = VEC == 1 ? 1 : (FA_MAX_HEAD_DIM / kV + TPR - 1) / TPR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int b = bh / p.Hkv, hkv = bh % p.Hkv;
   const int Dkc = p.Dkc, D = p.D, G = p.G;

@@ -142,3 +142,27 @@ APPEND_CALLS = [
     (110, 4, 40, 40, 17, 1023, "f32", 64),     # one slice that the head does not fill
     (9, 9, 256, 200, 131, 300, "bf16", 64),
 ]
+
+# Calls of project_rows: dtype, H, N, D, Dkc, Dvc (None: fa_compress of K alone), M, T, token offset of the kept dims; harmonic tiles of a workgroup,
+# chunks of the tokens
+ROWS_CALLS = [
+    ("bf16", 1, 3953, 64, 11, 44, 339, 3953, 8, 1, 3),       # two terms, chunks
+    ("bf16", 3, 10599, 128, 31, 88, 812, 10604, 3, 2, 3),
+    ("bf16", 1, 2030, 256, 147, None, 170, 2035, 8, 1, 2),
+    ("bf16", 34, 535, 64, 3, 57, 113, 540, 3, 2, 1),         # two terms, several tiles a workgroup
+    ("bf16", 17, 525, 64, 15, 2, 525, 2100, 3, 4, 1),
+    ("bf16", 105, 644, 64, 13, 61, 194, 2576, 8, 8, 1),
+    ("bf16", 45, 527, 128, 104, 113, 71, 2108, 0, 2, 1),
+    ("bf16", 96, 709, 128, 61, 100, 72, 709, 8, 4, 1),
+    ("bf16", 12, 673, 256, 221, 91, 327, 2692, 3, 2, 1),
+    ("bf16", 15, 608, 128, 40, 55, 1, 2432, 8, 1, 1),        # the mean alone
+    ("bf16", 71, 151, 64, 23, 56, 151, 151, 3, 8, 1),        # three terms
+    ("bf16", 102, 157, 128, 106, 48, 157, 157, 3, 8, 1),
+    ("bf16", 86, 87, 256, 256, 59, 87, 92, 8, 4, 1),
+    ("f32", 2, 9574, 64, 61, 64, 175, 9574, 3, 2, 19),
+    ("f32", 10, 1725, 64, 39, None, 806, 1730, 3, 4, 3),
+    ("f32", 10, 1111, 64, 29, 22, 965, 1111, 8, 8, 3),
+    ("f32", 37, 1356, 128, 106, 15, 114, 1356, 3, 4, 3),
+    ("f32", 50, 1411, 256, 157, 3, 35, 1416, 3, 2, 3),
+    ("f32", 78, 37, 256, 8, 213, 37, 42, 0, 2, 1),
+]

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle.fourier_kv as fk
-from fa_testlib import rows_to_tok8, to_dev
+from fa_testlib import ROWS_CALLS, rows_to_tok8, to_dev
 from workloads.synth import rel_err, round_to_bf16
 
 pytestmark = pytest.mark.gpu
@@ -98,6 +98,40 @@ def test_rows_selection_matches_oracle(D, N, M):
         # a difference of sums of the energy's size, each of fp32 precision
         assert np.all(np.abs(mse[0, h].cpu().numpy() - want) <= 5e-6 * scale)
         assert int(mask[0, h].sum()) == D // 2
+
+
+@pytest.mark.parametrize("call", ROWS_CALLS, ids=lambda c: "-".join(map(str, c)))
+def test_rows_forms_match_oracle(call):
+    """Tiles per workgroup and chunks of tokens (what each call gets is asked in test_rules.py), onto states that are there already."""
+    import paper_2506_11886_amd as fa
+    dt, H, N, D, Dkc, Dvc, M, T, off, hw, chunks = call
+    print(f"[case] rows form {call}", flush=True)
+    tt = torch.float32 if dt == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(N + M)
+    sides = []
+    for dc in (Dkc,) if Dvc is None else (Dkc, Dvc):
+        x, mask = _segment(D, N, dc, H, N + dc)
+        if dt == "f32":
+            x = x * np.float32(1.2345678)
+        sides.append((x, mask, torch.randn((1, H, M, dc), generator=g, device="cuda"), dc))
+    kk = torch.full((1, H, off + N, fa.keep_rows_pitch(D - Dkc)), 7.0, dtype=tt, device="cuda")
+    states = [s[2].clone() for s in sides]
+    if Dvc is None:
+        fa.fa_compress(to_dev(sides[0][0], dtype=tt), to_dev(sides[0][1]), Dkc, M, T, T - N, True, states[0], kk, fa.FA_KEEP_ROWS, off)
+    else:
+        vk = torch.full((1, H, fa.tok8_numel(off + N, D - Dvc)), 7.0, dtype=tt, device="cuda")
+        fa.fa_compress_kv(*(to_dev(s[0], dtype=tt) for s in sides), *(to_dev(s[1]) for s in sides), Dkc, Dvc, M, T, t0=T - N, accumulate=True,
+                          ck=states[0], cv=states[1], k_keep=kk, v_keep=vk, keep_offset=off)
+    torch.cuda.synchronize()
+    # a state sums N values of size 1; a basis value of two terms is off by 2^-18 of its size at most, of three by fp32 rounding
+    tol = 4e-6 if N > 512 and dt == "bf16" else 2e-6
+    for i, (x, mask, prev, dc) in enumerate(sides):
+        for h in {0, H // 2, H - 1}:
+            want, keep = fk.compress_batched(x[:, h:h + 1], mask[:, h:h + 1], M, T, T - N)
+            err = rel_err(states[i][:, h].cpu().numpy(), want[:, 0] + prev[:, h].cpu().numpy().astype(np.float64), np.sqrt(N))
+            assert err <= tol, (i, h, err)
+            got = kk[:, h:h + 1, :, :D - dc] if i == 0 else fa.keep_rows_from_tok8(vk[:, h:h + 1], off + N, D - dc)
+            assert np.array_equal(got[:, :, off:].float().cpu().numpy(), keep.astype(np.float32)) and (got[:, :, :off] == 7.0).all()
 
 
 def test_rows_infinity_stays_in_its_column():

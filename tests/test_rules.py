@@ -5,7 +5,8 @@ import random
 
 import pytest
 
-from fa_testlib import APPEND_CALLS, GENERAL_CALLS, HIPCC, HOST_ONLY, host_program
+import test_gpu_rows
+from fa_testlib import APPEND_CALLS, GENERAL_CALLS, HIPCC, HOST_ONLY, ROWS_CALLS, host_program
 
 pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 
@@ -166,6 +167,18 @@ def routes(tmp_path_factory):
 
 def _compress(dt, B, H, N, D, Dc, M, T=0, t0=0, acc=0, layout=0, off=0, keep=1, Dv=None):
     return (0 if Dv is None else 1, 0 if dt == "f32" else 1, B, H, N, D, Dc, Dv or 0, M, T or max(N, M), t0, acc, layout, off, keep, D, 0)
+
+
+def test_rows_calls_are_what_they_say(routes):
+    """The calls of test_gpu_rows.py reach project_rows with the tiles and chunks they name (the mean alone: but for a pair)."""
+    calls = [_compress(dt, 1, H, N, D, Dk, M, T, T - N, 1, 0, off, 1, Dv) for dt, H, N, D, Dk, Dv, M, T, off, _, _ in ROWS_CALLS]
+    for c, got in zip(ROWS_CALLS, routes(calls)):
+        assert (got[0][0], *got[0][3:]) == ("project_rows", *c[-2:]), (c, got)
+        assert len(got) == (2 if c[-1] > 1 else 1), (c, got)
+    for D, N, M, T, t0, off, Dc in test_gpu_rows.CASES:
+        for dt in ("bf16", "f32"):
+            got = routes([_compress(dt, 1, 3, N, D, Dc, M, T, t0, 1, layout, off) for layout in (0, 1)])
+            assert [g[0][0] for g in got] == ["compress_project" if M == 1 else "project_rows"] * 2, (D, N, M, got)
 
 
 def test_rows_are_taken_where_they_are_faster(routes):

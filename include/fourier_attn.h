@@ -112,7 +112,8 @@ enum { FA_KEEP_ROWS = 0, FA_KEEP_TOK8 = 1 };
  * Precision (2-norm of the error of white rows over that of the states), bf16: segments of
  * up to 512 tokens 3e-7 (head dims other than 64, 128 and 256: 2e-6); longer ones 2e-6 where
  * the basis is formed per token, 3e-6 through moments, up to 1.3e-3 by the direct
- * projection (a basis of one bf16 term).  Which of the three runs is
+ * projection (a basis of one bf16 term).  fp32: 4e-7 where the basis is formed per token,
+ * 4e-7 to 1.3e-6 (many states) by the direct projection.  Which of the three runs is
  * decided by the sizes, T, the workspace and what is kept; the moments' blocks also move
  * with keep_offset mod 8.  Equal calls give equal results.
  * An infinity or NaN in a compressed dim makes every state of its column infinite or NaN,

@@ -66,9 +66,9 @@ int launch_expand(const MomentParams& p, int tensors, hipStream_t st, KernelTime
 
 constexpr int kExpandRows = 16;       // harmonics per workgroup of fa_expand
 // 16-column tiles a workgroup of fa_expand16 takes out of ct: all share the operands; with fewer workgroups than units two groups of columns.
-// At one workgroup per unit and many blocks two groups of two tiles each are as many workgroups and read less
-// (16 pairs, M = 512, 112 dims: 128 K tokens, the call 144.6 -> 140.7 us, 32 K tokens 64.9 -> 62.1; 72 blocks of 32 pairs,
-// M = 256: 83.3 -> 85.2)
+// At exactly one workgroup per unit (tiles x pairs = 256: numbers of heads and states that are powers of two) and many blocks, two groups
+// of two tiles each are as many workgroups and read less (16 pairs, M = 512, 112 dims: 128 K tokens, the call 144.6 -> 140.7 us, 32 K
+// tokens 64.9 -> 62.1; few blocks lose, 72 of 32 pairs, M = 256: 83.3 -> 85.2; the line between them is not measured closer than that)
 inline int expand_columns(int ct, int tiles, double pairs, int blocks) {
   int ctw = ct < 8 ? ct : 8;
   const bool one_round = ct > 4 && tiles > 1 && blocks >= 128 && tiles * pairs <= 256.0;

@@ -1,7 +1,7 @@
-// Projection of bf16 rows onto the M basis functions, the basis formed on the fly in fp32 and split into bf16 terms:
+// Projection of rows onto the M basis functions, the basis formed on the fly in fp32 and split into bf16 terms (fp32 rows are, too):
 //   C[m,i] = sum_j phi_m(t0+j) X[j,i]
-// One launch, no partial sums in memory: a workgroup owns (sequence, head) and `hw` tiles of 16 harmonics; its waves take
-// the 32-token steps in turn and their shares meet in LDS.
+// A workgroup owns (sequence, head), `hw` tiles of 16 harmonics and a chunk of the tokens; its waves take the 32-token steps in turn
+// and their shares meet in LDS.  One chunk: one launch and no partial sums in memory; more leave theirs to a reduction.
 
 #include "fa_rows.hpp"
 

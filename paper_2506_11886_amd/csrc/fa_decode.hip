@@ -23,7 +23,7 @@
 // dependent round trip) and hides them behind table construction and MFMAs.
 //
 // Launches on the caller's stream:
-//   1. decode_prepare2 (decode_prepare: fewer than four compressed dims; with the full-width rows: decode_prepare_window,
+//   1. decode_prepare2 (decode_prepare: few compressed dims; with the full-width rows: decode_prepare_window,
 //      decode_prepare_full) : g (series order) for every query head, from C_k and q;
 //      q at the kept K dims, packed.
 //   2. decode_local (fa_local.hip) where the period is long against the states kept: the series by
@@ -3151,6 +3151,17 @@ static int launch_prepare_full(const DecodeParams& p, unsigned lds_window, bool 
 #undef FA_PREPARE2
 }
 
+// Compressed counts that are no multiple of 4: decode_prepare reads C_k by single floats and shares (row, head) products out over the
+// workgroup, where a row is a vector or two - or a few of them with few pairs - and most threads of a row would only watch its heads
+// being summed one after the other.  Of 17000 drawn calls those with fewer than 64 states, vectors against floats, the whole call: six heads
+// or more and 5 - 7 dims 1.01 - 1.06 (16 heads, 200 pairs: 0.87), nine heads or more, 9 - 31 dims and fewer than 32 pairs 1.01 - 1.06
+// (eight: 1.0; more pairs: 0.84 - 0.99), all others 0.6 - 1.0.  10 pairs x 12, M = 9: 20.3 / 18.7 us.
+static bool prepare_by_floats(int pairs, int G, int Dkc, int M) {
+  if (Dkc < 4) return true;
+  if ((Dkc & 3) == 0 || M >= 64) return false;
+  return (Dkc < 8 && G >= 6 && pairs * G < 2048) || (Dkc < 32 && G > 8 && pairs < 32);
+}
+
 // tm (optional): per-kernel event pairs, for fa_decode_timed
 template <typename T>
 static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_t st, KernelTimers* tm) {
@@ -3159,7 +3170,7 @@ static int launch_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_
     if (pl.fused) return launch_fused(p, pl, st, tm);
   }
   const hipError_t prior = hipPeekAtLastError();
-  if (p.Sm > 0 && p.Dkc > 0 && (p.Dkc >= 4 || pl.local.use || pl.rides)) {
+  if (p.Sm > 0 && p.Dkc > 0 && (pl.local.use || pl.rides || !prepare_by_floats(BH, p.G, p.Dkc, p.M))) {
     const bool wide = static_cast<long>(BH) * (p.Mint / 64 + 1) >= 256;
     const int nprep = wide ? p.Mint / 64 + 1 : p.Mint / 16 + 1;
     if (pl.local.use || pl.rides) {   // the full-width rows, if any, ride along

@@ -11,7 +11,7 @@ from fa_testlib import APPEND_CALLS, GENERAL_CALLS, HIPCC, HOST_ONLY, ROWS_CALLS
 pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 
 # a line: dtype B Hkv G D Dkc Dvc M T N W per_sequence -> waves of the general middle-row kernel (0: another form), full-width rows
-# apart, chunks as planned, chunks as run
+# apart, chunks as planned, chunks as run, C_k by single floats
 DECODE = HOST_ONLY + r"""
 #include "fa_decode.hip"
 int main() {
@@ -22,7 +22,8 @@ int main() {
     if (ok) fa::make_local(pl, dt, B, Hkv * G, Hkv, D, Dkc, Dvc, N, W, 0, fa::local_form(M, T));
     const int planned = pl.Sm;
     if (ok) fa::join_chunks(pl, dt, B, Hkv, N, seq != 0);
-    std::printf("%d %d %d %d\n", !ok || pl.local.use || pl.fused || pl.fast ? 0 : pl.nw, pl.rides, planned, pl.Sm);
+    std::printf("%d %d %d %d %d\n", !ok || pl.local.use || pl.fused || pl.fast ? 0 : pl.nw, pl.rides, planned, pl.Sm,
+                fa::prepare_by_floats(B * Hkv, G, Dkc, M));
   }
 }
 """
@@ -72,6 +73,13 @@ def test_full_width_rows_go_apart_where_that_is_faster(decode):
              (1, 2, 4, 1, 256, 192, 192, 622, 700, 700, 205, 0): 0}
     got = decode(list(calls))
     assert all(r[0] == 8 for r in got) and [r[1] for r in got] == list(calls.values()), got
+
+
+def test_coefficients_by_floats(decode):
+    """Fewer than four dims; few states of many heads with a vector or two a row, or a few of them and few pairs.  Never rows of whole vectors."""
+    of = lambda pairs, G, Dkc, M: decode([(1, 1, pairs, G, 128, Dkc, 64, M, 200, 200, 0, 0)])[0][4]
+    assert [of(4, 1, 3, 128), of(4, 8, 5, 40), of(20, 12, 7, 63), of(6, 12, 30, 20)] == [1] * 4
+    assert [of(4, 8, 4, 40), of(4, 4, 5, 40), of(4, 8, 5, 64), of(200, 16, 5, 40), of(40, 16, 30, 20), of(6, 8, 30, 20), of(6, 16, 33, 20), of(6, 16, 28, 20)] == [0] * 8
 
 
 # a line: pairs D -> head dims of a workgroup of fa_append

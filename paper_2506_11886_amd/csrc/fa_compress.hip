@@ -1146,7 +1146,7 @@ static bool prefer_moments(const MomentPlan& mp, bool one_vector, double direct,
 // fp32 calls 0.39 of the time of compress_project, with errors of white rows 4.5e-7 / 2.9e-7 (up to 1.3e-6 / 4e-7 at many states), over
 // 35000 short bf16 ones 0.45, with 2e-6 / 2e-7.  But:
 //   - the mean alone (M = 1) is a column sum there and a tile of products here: the lower estimate (fp32, 32 x 3410, D = 64, K and V:
-//     32 / 59 us; 8 x 11135, D = 128: 27 / 91; bf16 24 x 1, D = 256: 8.6 / 10.4; the sums of rows are as exact).  A tenth for what the estimate of this form leaves out there;
+//     32 / 59 us; 8 x 11135, D = 128: 27 / 91; bf16 24 x 1, D = 256: 8.6 / 10.4; the sums of rows are as exact).  A fifth for what the estimate of this form leaves out there;
 //   - fp32 with no more than half of the dims compressed, whose other columns are multiplied here for nothing: the lower estimate,
 //     both forms being fp32 (16 x 34532, 18 of 128 dims, M = 1006: 833 / 1291; 50 x 10658, 13 dims, M = 510, K and V: 790 / 1476).
 //     bf16 keeps this form for its tenth of the error, also where that costs time (0.3 % of the calls, most of them D = 256 with many
@@ -1177,7 +1177,7 @@ template <typename Plain>
 static bool prefer_rows(const RowsPlan& rp, const RowsShape& c, int dims, bool moments, double other, Plain plain) {
   if (!rp.use) return false;
   if (!rows_short(c.dtype, c.N)) return rp.us < (moments ? 0.9 : c.D == 128 || (c.D == 256 && dims <= kCols) ? 0.7 : 0.95) * other;
-  return (c.M > 1 && (c.dtype == FA_BF16 || 2 * dims > c.D)) || (c.M > 1 ? 1.0 : 1.1) * rp.us <= plain();
+  return (c.M > 1 && (c.dtype == FA_BF16 || 2 * dims > c.D)) || (c.M > 1 ? 1.0 : 1.2) * rp.us <= plain();
 }
 
 // One or two tensors through their moments, in as many parts as the workspace asks for: whole sequences, or heads of one

@@ -1,5 +1,6 @@
-"""The one-launch projection whose basis is formed per token (short bf16 segments, fast harmonics): edges of steps, harmonic
-tiles, column halves and groups of eight."""
+"""The projection whose basis is formed per token (fp32, short bf16 segments, fast harmonics): edges of steps, harmonic tiles, column
+halves and groups of eight, tiles per workgroup and chunks of tokens.  Which calls of CASES and ROWS_CALLS it serves is asked in
+test_rules.py; the mean alone (M = 1) of one tensor and slow harmonics of long bf16 segments take other forms, held to the same here."""
 
 import numpy as np
 import pytest
